@@ -17,10 +17,8 @@ struct P_ {
 
 static inline unsigned nblocks(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
 
-// A = [-dt/2 W | -sqrt(dt) F], zero padded to P rows and 2P columns; in the
-// split form 6P columns [Wh | Wh | Wl | Fh | Fh | Fl] against operand columns
-// (sh, sl, sh, zh, zl, zh); stored stage-blocked (a_index) with kt columns
-// per block
+// A = [-dt/2 W | -sqrt(dt) F], zero padded to P rows and 2P columns, stored
+// stage-blocked (a_index) with kt columns per block
 template <int PREC>
 __global__ void build_A_kernel(const double* W, const double* F, int64_t N, int64_t P, int64_t kt, double cw,
                                double cf, typename Prec<PREC>::G* A) {
@@ -32,16 +30,7 @@ __global__ void build_A_kernel(const double* W, const double* F, int64_t N, int6
         if (j < N) v = cw * W[i * N + j];
         else if (j >= P && j - P < N) v = cf * F[i * N + (j - P)];
     }
-    if constexpr (Prec<PREC>::SPLIT == 3) {
-        uint16_t hi, lo;
-        bf16_split((float)v, hi, lo);
-        const int64_t c = j < P ? j : 3 * P + (j - P);
-        A[a_index(i, c, P, kt)].v = hi;
-        A[a_index(i, c + P, P, kt)].v = hi;
-        A[a_index(i, c + 2 * P, P, kt)].v = lo;
-    } else {
-        A[a_index(i, j, P, kt)] = Prec<PREC>::to_g((typename Prec<PREC>::S)v);
-    }
+    put_a<PREC>(A, i, j, P, kt, (typename Prec<PREC>::S)v);
 }
 
 template <int PREC>
@@ -87,14 +76,14 @@ __global__ void build_A_coh_kernel(const double* W, const double* F, const doubl
         const double m = blk == 0 ? W[i * N + jj] : blk == 1 ? F[i * N + jj] : Om[i * N + jj];
         v = (blk == 0 ? cw : blk == 1 ? cf : co) * m;
     }
-    A[a_index(i, j, P, kt)] = Prec<PREC>::to_g((S)v);
-    if (blk != 1) A2[a_index(i, blk == 0 ? jj : P + jj, P, kt)] = Prec<PREC>::to_g((S)v);
+    put_a<PREC>(A, i, j, P, kt, (S)v);
+    if (blk != 1) put_a<PREC>(A2, i, blk == 0 ? jj : P + jj, P, kt, (S)v);
 }
 
 template <int PREC>
 static int build_A_coh_t(const Geometry& g, const double* W, const double* F, const double* Om, double dt, void* A,
                          void* A2, hipStream_t st) {
-    if constexpr (Prec<PREC>::SPLIT != 1) {
+    if constexpr (PREC == TWA_PREC_BF16X3) {
         set_error("coherent exchange: not with the split precision");
         return TWA_EINVAL;
     } else {
@@ -117,7 +106,7 @@ int launch_build_A_coh(const Geometry& g, const double* W, const double* F, cons
 template <int PREC>
 __global__ void init_kernel(int64_t N, int64_t B, int64_t P, int64_t Bp, double s0z, uint32_t k0, uint32_t k1,
                             uint32_t point, const double* init, typename Prec<PREC>::S* s,
-                            typename Prec<PREC>::S* norm0, typename Prec<PREC>::G* Xop, int coh) {
+                            typename Prec<PREC>::S* norm0, typename Prec<PREC>::G* Xop, int64_t kt, int coh) {
     typedef typename Prec<PREC>::S S;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= Bp * P) return;
@@ -143,13 +132,12 @@ __global__ void init_kernel(int64_t N, int64_t B, int64_t P, int64_t Bp, double 
     s[SP + t] = y;
     s[2 * SP + t] = z;
     norm0[t] = x * x + y * y + z * z;
-    constexpr int SPL = Prec<PREC>::SPLIT;
-    const int64_t ld = (2 + coh) * P * SPL;   // operand column length
-    put_op<PREC>(Xop + opcol(k, 0) * ld + i, P, x);
-    put_op<PREC>(Xop + opcol(k, 1) * ld + i, P, y);
+    const int64_t C2 = 2 * Bp;
+    put_x<PREC>(Xop, opcol(k, 0), i, C2, kt, x);
+    put_x<PREC>(Xop, opcol(k, 1), i, C2, kt, y);
     if (coh) {   // s_perp block: (s^y, -s^x)
-        Xop[opcol(k, 0) * ld + 2 * P + i] = Prec<PREC>::to_g(y);
-        Xop[opcol(k, 1) * ld + 2 * P + i] = Prec<PREC>::to_g(-x);
+        put_x<PREC>(Xop, opcol(k, 0), 2 * P + i, C2, kt, y);
+        put_x<PREC>(Xop, opcol(k, 1), 2 * P + i, C2, kt, -x);
     }
 }
 
@@ -161,7 +149,7 @@ static int init_t(const Geometry& g, const EnsembleBuffers& b, const StepConsts&
     const int64_t n = g.Bp * g.P;
     hipLaunchKernelGGL(init_kernel<PREC>, dim3(nblocks(n, 256)), dim3(256), 0, st, g.N, g.B, g.P, g.Bp, c.s0z,
                        c.key0, c.key1, (uint32_t)c.point, init, static_cast<S*>(b.s[0]), static_cast<S*>(b.norm0),
-                       static_cast<G*>(b.Xop), g.coh);
+                       static_cast<G*>(b.Xop), g.kt, g.coh);
     TWA_HIP_CHECK(hipGetLastError());
     return TWA_OK;
 }
@@ -202,7 +190,7 @@ int launch_reduce_state(const Geometry& g, const void* s, void* part, hipStream_
 template <int PREC>
 __global__ void noise_kernel(int64_t N, int64_t B, int64_t P, int64_t Bp, uint32_t k0, uint32_t k1,
                              uint32_t point, const int64_t* step, typename Prec<PREC>::G* Xop,
-                             typename Prec<PREC>::S* g, int64_t ldop) {
+                             typename Prec<PREC>::S* g, int64_t kt) {
     typedef typename Prec<PREC>::S S;
     // grid: x over Philox slots (pairs of spins), y over trajectories (strided)
     const int64_t nslot = (N + 1) / 2;
@@ -215,14 +203,12 @@ __global__ void noise_kernel(int64_t N, int64_t B, int64_t P, int64_t Bp, uint32
         box_muller(w.x, w.y, z0, z1);
         box_muller(w.z, w.w, z2, z3);
         const int64_t i = 2 * m;
-        constexpr int SPL = Prec<PREC>::SPLIT;
-        typename Prec<PREC>::G* cx = Xop + opcol(k, 0) * ldop + P * SPL;
-        typename Prec<PREC>::G* cy = Xop + opcol(k, 1) * ldop + P * SPL;
-        put_op<PREC>(cx + i, P, z0);
-        put_op<PREC>(cy + i, P, z1);
+        const int64_t C2 = 2 * Bp, cx = opcol(k, 0), cy = opcol(k, 1);
+        put_x<PREC>(Xop, cx, P + i, C2, kt, z0);
+        put_x<PREC>(Xop, cy, P + i, C2, kt, z1);
         if (i + 1 < N) {
-            put_op<PREC>(cx + i + 1, P, z2);
-            put_op<PREC>(cy + i + 1, P, z3);
+            put_x<PREC>(Xop, cx, P + i + 1, C2, kt, z2);
+            put_x<PREC>(Xop, cy, P + i + 1, C2, kt, z3);
         }
         if (m == 0) {
             const U4 v = philox4x32_10(U4{0u, (uint32_t)k, n, TAG_COLLECTIVE | (point << 8)}, k0, k1);
@@ -242,7 +228,7 @@ static int noise_t(const Geometry& g, const EnsembleBuffers& b, const StepConsts
                        g.Bp, c.key0,
                        c.key1, (uint32_t)c.point, (const int64_t*)b.step,
                        static_cast<typename Prec<PREC>::G*>(b.Xop), static_cast<typename Prec<PREC>::S*>(b.g),
-                       (int64_t)(2 + g.coh) * g.P * Prec<PREC>::SPLIT);
+                       g.kt);
     TWA_HIP_CHECK(hipGetLastError());
     return TWA_OK;
 }
@@ -254,7 +240,8 @@ int launch_noise(const Geometry& g, const EnsembleBuffers& b, const StepConsts& 
 // ---------------------------------------------------------------------------
 // response copies at the origin: ds = x^ (copy 0) and ds = y^ (copy 1)
 template <int PREC>
-__global__ void seed_kernel(int64_t N, int64_t B, int64_t P, int64_t Bp, int64_t C2, typename Prec<PREC>::S* ts,
+__global__ void seed_kernel(int64_t N, int64_t B, int64_t P, int64_t Bp, int64_t C2, int64_t kt,
+                            typename Prec<PREC>::S* ts,
                             typename Prec<PREC>::G* tXop) {
     typedef typename Prec<PREC>::S S;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -267,11 +254,9 @@ __global__ void seed_kernel(int64_t N, int64_t B, int64_t P, int64_t Bp, int64_t
         base[t] = cp == 0 ? one : S(0);
         base[SP + t] = cp == 1 ? one : S(0);
         base[2 * SP + t] = S(0);
-        // operand columns of pitch P (split form: hi, lo, hi blocks of P)
-        constexpr int SPL = Prec<PREC>::SPLIT;
-        typename Prec<PREC>::G* op = tXop + cp * C2 * P * SPL;
-        put_op<PREC>(op + opcol(k, 0) * P * SPL + i, P, cp == 0 ? one : S(0));
-        put_op<PREC>(op + opcol(k, 1) * P * SPL + i, P, cp == 1 ? one : S(0));
+        typename Prec<PREC>::G* op = tXop + cp * C2 * P * Prec<PREC>::NP;
+        put_x<PREC>(op, opcol(k, 0), i, C2, kt, cp == 0 ? one : S(0));
+        put_x<PREC>(op, opcol(k, 1), i, C2, kt, cp == 1 ? one : S(0));
     }
 }
 
@@ -279,7 +264,7 @@ template <int PREC>
 static int seed_t(const Geometry& g, const EnsembleBuffers& b, int cur, hipStream_t st) {
     typedef typename Prec<PREC>::S S;
     const int64_t n = g.Bp * g.P;
-    hipLaunchKernelGGL(seed_kernel<PREC>, dim3(nblocks(n, 256)), dim3(256), 0, st, g.N, g.B, g.P, g.Bp, g.C2,
+    hipLaunchKernelGGL(seed_kernel<PREC>, dim3(nblocks(n, 256)), dim3(256), 0, st, g.N, g.B, g.P, g.Bp, g.C2, g.kt,
                        static_cast<S*>(b.ts[cur]), static_cast<typename Prec<PREC>::G*>(b.tXop));
     TWA_HIP_CHECK(hipGetLastError());
     for (int cp = 0; cp < 2; ++cp) {

@@ -32,7 +32,7 @@ inline unsigned nblk(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
 
 // per-point description used by the grouped noise and observation kernels
 struct PointDesc {
-    int64_t N, B, P, Bp, nmt, burnin, L, stride;
+    int64_t N, B, P, Bp, nmt, burnin, L, stride, kt;
     uint32_t key0, key1, point;
     int32_t pad_;
     void* Xop;
@@ -69,16 +69,14 @@ __global__ void noise_grouped_kernel(const PointDesc* __restrict__ pd, const int
     box_muller(w.x, w.y, z0, z1);
     box_muller(w.z, w.w, z2, z3);
     const int64_t i = 2 * m;
-    // operand column: [s ; zeta], each block P long, or in the split form
-    // (hi, lo, hi) blocks of P each for s and then for zeta
-    constexpr int SPL = Prec<PREC>::SPLIT;
-    G* cx = static_cast<G*>(d.Xop) + opcol(k, 0) * 2 * d.P * SPL + d.P * SPL;
-    G* cy = static_cast<G*>(d.Xop) + opcol(k, 1) * 2 * d.P * SPL + d.P * SPL;
-    put_op<PREC>(cx + i, d.P, z0);
-    put_op<PREC>(cy + i, d.P, z1);
+    // operand column: [s ; zeta]
+    G* X = static_cast<G*>(d.Xop);
+    const int64_t C2 = 2 * d.Bp, cx = opcol(k, 0), cy = opcol(k, 1);
+    put_x<PREC>(X, cx, d.P + i, C2, d.kt, z0);
+    put_x<PREC>(X, cy, d.P + i, C2, d.kt, z1);
     if (i + 1 < d.N) {
-        put_op<PREC>(cx + i + 1, d.P, z2);
-        put_op<PREC>(cy + i + 1, d.P, z3);
+        put_x<PREC>(X, cx, d.P + i + 1, C2, d.kt, z2);
+        put_x<PREC>(X, cy, d.P + i + 1, C2, d.kt, z3);
     }
     if (m == 0) {
         const U4 v = philox4x32_10(U4{0u, (uint32_t)k, n, TAG_COLLECTIVE | (d.point << 8)}, d.key0, d.key1);
@@ -279,6 +277,7 @@ int build_bucket(const BatchSpec& sp, const std::vector<int>& idx, int cfg, Buck
         d.burnin = sp.burnin;
         d.L = sp.L;
         d.stride = sp.stride;
+        d.kt = g.kt;
         d.key0 = c.key0;
         d.key1 = c.key1;
         d.point = (uint32_t)p;
@@ -438,12 +437,10 @@ int run_steps(std::vector<Bucket>& bks, const Plan& plan, int64_t n0, int64_t n1
 int bucket_of(int64_t N) { return N <= 128 ? 0 : N <= 1024 ? 1 : 2; }
 
 std::vector<int> bucket_candidates(int bucket, int precision) {
-    std::vector<int> c;
-    if (bucket == 0) c = {0, 1};
-    else if (bucket == 1) c = {1, 2, 3, 7};
-    else c = {2, 3, 7};
-    if (precision == TWA_PREC_FP64) c.erase(std::remove(c.begin(), c.end(), 7), c.end());
-    return c;
+    if (bucket == 0) return {0, 1};
+    if (precision == TWA_PREC_FP64) return {0, 1};
+    if (bucket == 2 && operand_split(precision) == 2) return {2, 3, 7};
+    return {1, 3, 7};
 }
 
 std::string tune_key(const BatchSpec& sp, const std::vector<int>& idx) {

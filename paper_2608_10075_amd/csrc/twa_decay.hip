@@ -32,8 +32,8 @@ __global__ void decay_ops_kernel(const double* G, int64_t N, int64_t P, int64_t 
     if (t >= P * P) return;
     const int64_t i = t / P, j = t % P;
     const double v = (i < N && j < N) ? G[i * N + j] : 0.0;
-    AG[a_index(i, j, P, kt)] = Prec<PREC>::to_g((S)v);
-    AGG[a_index(i, j, P, kt)] = Prec<PREC>::to_g((S)(v * v));
+    put_a<PREC>(AG, i, j, P, kt, (S)v);
+    put_a<PREC>(AGG, i, j, P, kt, (S)(v * v));
     if (i == j) dg[i] = (S)v;
 }
 
@@ -42,11 +42,12 @@ __global__ void decay_ops_kernel(const double* G, int64_t N, int64_t P, int64_t 
 // store kind writes (G o G) z_k to plane k div Bp/2, row k mod Bp/2 of an
 // output with Bp/2 rows per plane, i.e. to k * P in a plain [Bp][P] layout
 template <int PREC>
-__global__ void pack_z_kernel(const typename Prec<PREC>::S* s, int64_t Bp, int64_t P, typename Prec<PREC>::G* Zop) {
+__global__ void pack_z_kernel(const typename Prec<PREC>::S* s, int64_t Bp, int64_t P, int64_t kt,
+                              typename Prec<PREC>::G* Zop) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= Bp * P) return;
     const int64_t k = t / P, i = t % P, half = Bp / 2;
-    Zop[opcol(k % half, (int)(k / half)) * P + i] = Prec<PREC>::to_g(s[2 * Bp * P + t]);
+    put_x<PREC>(Zop, opcol(k % half, (int)(k / half)), i, Bp, kt, s[2 * Bp * P + t]);
 }
 
 __device__ __forceinline__ void kahan_add(double& sum, double& comp, double v) {
@@ -122,14 +123,13 @@ int observe_t(const Geometry& g, const EnsembleBuffers& b, int cur, hipStream_t 
     c.stage = 1;
     c.A = b.AG;
     c.X = b.Xop;
-    c.ldx = (2 + g.coh) * g.P;   // the state block leads every operand column
-    c.K = g.P;
+    c.K = g.P * Prec<PREC>::NP;   // the state block leads every operand column
     c.Sout = b.GX;
     c.store_sign = 1.0;
     if ((rc = launch_gemm_call(g, c, st))) return rc;
     // (G o G) s^z over Bp / 2 column pairs
     hipLaunchKernelGGL(pack_z_kernel<PREC>, dim3(nblk(g.Bp * g.P, 256)), dim3(256), 0, st,
-                       static_cast<const S*>(b.s[cur]), g.Bp, g.P, static_cast<GT*>(b.Zop));
+                       static_cast<const S*>(b.s[cur]), g.Bp, g.P, g.kt, static_cast<GT*>(b.Zop));
     TWA_HIP_CHECK(hipGetLastError());
     Geometry gz = g;
     gz.Bp = g.Bp / 2;
@@ -139,8 +139,7 @@ int observe_t(const Geometry& g, const EnsembleBuffers& b, int cur, hipStream_t 
     u.stage = 1;
     u.A = b.AGG;
     u.X = b.Zop;
-    u.ldx = g.P;
-    u.K = g.P;
+    u.K = g.P * Prec<PREC>::NP;
     u.Sout = b.UZ;
     u.store_sign = 1.0;
     if ((rc = launch_gemm_call(gz, u, st))) return rc;
@@ -154,7 +153,7 @@ int observe_t(const Geometry& g, const EnsembleBuffers& b, int cur, hipStream_t 
 }  // namespace
 
 int decay_geometry_ok(const Geometry& g) {
-    const TileCfg& tc = tile_cfg(g.cfg);
+    const TileCfg& tc = tile_cfg(g.precision, g.cfg);
     if (g.Bp % tc.nt != 0) {
         set_error("correlated decay: trajectory padding must be a multiple of the column tile");
         return TWA_EINVAL;

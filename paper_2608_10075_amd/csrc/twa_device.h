@@ -15,8 +15,11 @@ namespace twa {
 // is then a single contiguous run of MT * kt elements (whole cache lines),
 // where a row-major matrix would give MT runs of kt elements one row pitch
 // apart.  kt = K elements per LDS stage of the tile configuration.
-__host__ __device__ __forceinline__ int64_t a_index(int64_t i, int64_t j, int64_t P, int64_t kt) {
-    return (j / kt) * P * kt + i * kt + (j % kt);
+// In the split forms (Prec::NP parts per value) a stage holds the kt columns
+// of all P rows of part 0, then those of part 1, ...: element (i, j) of part p.
+__host__ __device__ __forceinline__ int64_t a_index(int64_t i, int64_t j, int64_t P, int64_t kt, int np = 1,
+                                                    int p = 0) {
+    return ((j / kt) * np + p) * P * kt + i * kt + (j % kt);
 }
 
 // ---------------------------------------------------------------------------
@@ -74,6 +77,17 @@ __device__ __forceinline__ int64_t opcol(int64_t k, int a) {
     return 32 * (k >> 4) + 16 * a + (k & 15);
 }
 
+// The column operand X of a contraction (C2 columns) is stage-blocked the same
+// way: element i of column c, part p, with the kt elements of one K stage of
+// all columns contiguous.  A stage's columns of a tile are then one contiguous
+// run (a row-major operand gave runs of one stage's 64 or 128 bytes, half a
+// cache line at 64), and 16 neighbouring columns written by one epilogue block
+// share cache lines.
+__host__ __device__ __forceinline__ int64_t x_index(int64_t c, int64_t i, int64_t C2, int64_t kt, int np = 1,
+                                                    int p = 0) {
+    return ((i / kt) * np + p) * C2 * kt + c * kt + i % kt;
+}
+
 // ---------------------------------------------------------------------------
 // number formats
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -85,11 +99,8 @@ struct bf16s {
     uint16_t v;
 };
 
-__device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
-    uint32_t u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
+// round to nearest even (v_cvt_pk_bf16_f32)
+__device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
 typedef double f64x2 __attribute__((ext_vector_type(2)));
@@ -100,7 +111,7 @@ struct Prec;
 
 template <>
 struct Prec<TWA_PREC_FP64> {
-    static constexpr int SPLIT = 1;   // operand blocks per value (3: bf16 hi, lo, hi)
+    static constexpr int NP = 1;      // bf16 parts per operand value (split forms: 2 or 3)
     typedef double G;   // contraction operand
     typedef double S;   // state / accumulator
     typedef f64x4 AV;
@@ -117,26 +128,8 @@ struct Prec<TWA_PREC_FP64> {
 };
 
 template <>
-struct Prec<TWA_PREC_FP32> {
-    static constexpr int SPLIT = 1;
-    // 16x16 MFMA output: register r of lane l holds row 4 (l/16) + r
-    __device__ static __forceinline__ int arow(int m) { return m; }
-    typedef float G;
-    typedef float S;
-    typedef f32x4 AV;
-    __device__ static __forceinline__ G to_g(S v) { return v; }
-    __device__ static __forceinline__ void mma(AV& c, const uint4& a, const uint4& b) {
-        const f32x4 fa = __builtin_bit_cast(f32x4, a), fb = __builtin_bit_cast(f32x4, b);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[0], fb[0], c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[1], fb[1], c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[2], fb[2], c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[3], fb[3], c, 0, 0, 0);
-    }
-};
-
-template <>
 struct Prec<TWA_PREC_BF16> {
-    static constexpr int SPLIT = 1;
+    static constexpr int NP = 1;
     // 16x16 MFMA output: register r of lane l holds row 4 (l/16) + r
     __device__ static __forceinline__ int arow(int m) { return m; }
     typedef bf16s G;
@@ -151,7 +144,7 @@ struct Prec<TWA_PREC_BF16> {
 
 template <>
 struct Prec<TWA_PREC_FP16> {
-    static constexpr int SPLIT = 1;
+    static constexpr int NP = 1;
     // 16x16 MFMA output: register r of lane l holds row 4 (l/16) + r
     __device__ static __forceinline__ int arow(int m) { return m; }
     typedef _Float16 G;
@@ -164,33 +157,80 @@ struct Prec<TWA_PREC_FP16> {
     }
 };
 
-// Split BF16: every operand value x is stored as three K blocks (hi, lo, hi)
-// with hi = bf16(x), lo = bf16(x - hi), and the pump matrix as (hi, hi, lo),
-// so that one BF16 contraction over the tripled K sums Ahi Xhi + Ahi Xlo +
-// Alo Xhi; the dropped Alo Xlo and the rounding of lo are O(2^-17) relative.
+// Split forms: every operand value x is stored as NP bf16 parts, each the
+// rounded remainder of the parts before it (hi = bf16(x), then bf16(x - hi),
+// ...; Henry, Tang and Heinecke 2019), each part in a K block of its own, and
+// a contraction sums the products of parts pa and px with pa + px < NP on
+// BF16 MFMA with FP32 accumulation.
+// NP = 2 (TWA_PREC_BF16X3): hi hi + lo hi + hi lo; the dropped lo lo and the
+// rounding of lo are O(2^-17) relative.
 template <>
 struct Prec<TWA_PREC_BF16X3> : Prec<TWA_PREC_BF16> {
-    static constexpr int SPLIT = 3;
+    static constexpr int NP = 2;
+};
+// NP = 3 (TWA_PREC_FP32): the three parts hold all 24 bits of a binary32
+// value and the six products kept leave out less than 2^-25 of one.  The BF16
+// MFMA is 16 times the FP32 one, so six products take 0.375 of its time.
+// Rounding of the BF16 MFMA, measured on gfx950: unbiased where products are
+// within 2^-8 of C, but smaller ones are added 6 bits below C's last place and
+// cut towards minus infinity there, a bias of -0.0088 of C's last place per
+// MFMA (the FP32 MFMA has none).  The products of lower parts, 5 of the 6, all
+// fall below: in one sum with the first they made the error of N = 201 over
+// 800 steps 2.0e-5 (5.6e-6 with the FP32 MFMA) - one sign on every spin of a
+// trajectory is the uniform field that collective decay amplifies.  So they
+// are summed apart, where C is 2^-8 smaller, and what is left of the bias (far
+// elements of a row) alternates in sign along the chain: the rows of odd spins
+// are stored and contracted with the opposite sign (row_flipped).
+template <>
+struct Prec<TWA_PREC_FP32> : Prec<TWA_PREC_BF16> {
+    static constexpr int NP = 3;
 };
 
-// operand hi / lo parts of a value (for the split form)
-__device__ __forceinline__ void bf16_split(float v, uint16_t& hi, uint16_t& lo) {
-    hi = f32_to_bf16_rne(v);
-    lo = f32_to_bf16_rne(v - bf16_to_f32(hi));
+// sign of spin i's row in the constant operands of a precision
+template <int PREC>
+__host__ __device__ constexpr bool row_flipped(int64_t i) {
+    return Prec<PREC>::NP > 1 && (i & 1);
 }
 
-// one operand value: p[0], or for the split form (hi, lo, hi) blk elements apart
+// the bf16 parts of a value
+template <int NP>
+__device__ __forceinline__ void bf16_parts(float v, uint16_t (&h)[NP]) {
+    h[0] = f32_to_bf16_rne(v);
+#pragma unroll
+    for (int p = 1; p < NP; ++p) {
+        v -= bf16_to_f32(h[p - 1]);
+        h[p] = f32_to_bf16_rne(v);
+    }
+}
+
+// one operand value: p[0], or in the split forms its parts blk elements apart
 template <int PREC>
 __device__ __forceinline__ void put_op(typename Prec<PREC>::G* p, int64_t blk, typename Prec<PREC>::S v) {
-    if constexpr (Prec<PREC>::SPLIT == 3) {
-        uint16_t hi, lo;
-        bf16_split(v, hi, lo);
-        p[0].v = hi;
-        p[blk].v = lo;
-        p[2 * blk].v = hi;
+    constexpr int NP = Prec<PREC>::NP;
+    if constexpr (NP > 1) {
+        uint16_t h[NP];
+        bf16_parts<NP>(v, h);
+#pragma unroll
+        for (int q = 0; q < NP; ++q) p[q * blk].v = h[q];
     } else {
         p[0] = Prec<PREC>::to_g(v);
     }
+}
+
+// element (i, j) of a stage-blocked constant operand, all its parts, with its
+// row's sign
+template <int PREC>
+__device__ __forceinline__ void put_a(typename Prec<PREC>::G* A, int64_t i, int64_t j, int64_t P, int64_t kt,
+                                      typename Prec<PREC>::S v) {
+    constexpr int NP = Prec<PREC>::NP;
+    put_op<PREC>(A + a_index(i, j, P, kt, NP, 0), P * kt, row_flipped<PREC>(i) ? -v : v);
+}
+
+// element i of column c of a column operand, all its parts
+template <int PREC>
+__device__ __forceinline__ void put_x(typename Prec<PREC>::G* X, int64_t c, int64_t i, int64_t C2, int64_t kt,
+                                      typename Prec<PREC>::S v) {
+    put_op<PREC>(X + x_index(c, i, C2, kt, Prec<PREC>::NP, 0), C2 * kt, v);
 }
 
 }  // namespace twa

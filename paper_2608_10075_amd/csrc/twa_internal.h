@@ -43,19 +43,34 @@ struct Status {
 // tile configurations of the channel-mixing contraction.  A configuration is
 // (MT rows of spins, NT operand columns = NT/2 trajectories x 2 components,
 // K bytes per LDS stage, waves along M, waves along N).
+// The shapes depend on the parts per operand value (operand_split).  nstage
+// counts ring units, one part of one K stage each.
 struct TileCfg {
-    int id;
     int mt, nt, kbytes, waves_m, waves_n, nstage;
-    const char* name;
 };
-int n_tile_cfgs();
-const TileCfg& tile_cfg(int id);
+constexpr int kTileCfgs = 9;
+constexpr TileCfg kTiles[3][kTileCfgs] = {
+    // one part (FP64, BF16, FP16)
+    {{16, 32, 64, 1, 1, 2}, {64, 64, 64, 2, 2, 4}, {128, 128, 128, 2, 2, 4}, {128, 128, 64, 2, 2, 8},
+     {256, 128, 64, 4, 1, 6}, {128, 256, 64, 2, 2, 6}, {256, 128, 64, 4, 2, 4}, {320, 256, 128, 4, 2, 2},
+     {320, 256, 64, 4, 2, 4}},
+    // two parts (split BF16)
+    {{16, 32, 64, 1, 1, 8}, {64, 64, 64, 2, 2, 6}, {128, 128, 64, 4, 2, 8}, {128, 64, 64, 2, 2, 6},
+     {256, 128, 64, 4, 2, 6}, {128, 256, 64, 2, 4, 6}, {256, 256, 64, 4, 2, 4}, {320, 256, 64, 4, 2, 4},
+     {192, 192, 64, 4, 2, 6}},
+    // three parts (FP32)
+    {{16, 32, 64, 1, 1, 6}, {64, 64, 64, 2, 2, 6}, {128, 128, 64, 4, 2, 6}, {128, 64, 64, 2, 2, 6},
+     {256, 64, 64, 4, 2, 6}, {64, 128, 64, 2, 2, 6}, {128, 256, 64, 2, 4, 6}, {256, 128, 64, 4, 2, 6},
+     {192, 192, 64, 4, 2, 6}},
+};
+inline int n_tile_cfgs() { return kTileCfgs; }
+const TileCfg& tile_cfg(int precision, int id);
 int pick_tile_cfg(int precision, int64_t N, int64_t n_traj);
 
 inline int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
 int gemm_elt_bytes(int precision);
 int state_elt_bytes(int precision);
-int operand_split(int precision);   // K blocks per operand value (3 for TWA_PREC_BF16X3)
+int operand_split(int precision);   // bf16 parts per operand value (FP32 3, split BF16 2, else 1)
 
 // ---------------------------------------------------------------------------
 // device buffers and launch geometry of one trajectory ensemble
@@ -126,12 +141,11 @@ constexpr int KIND_PRIMAL_WITH_Q = 0x100;
 struct GemmCall {
     int kind = 0, stage = 1, ncopy = 1;
     const void* A = nullptr;        // P rows, stage-blocked (a_index, the geometry's kt)
-    const void* X = nullptr;
-    int64_t ldx = 0, x_copy = 0, K = 0;
+    const void* X = nullptr;        // columns, stage-blocked (x_index)
+    int64_t x_copy = 0, K = 0;      // K: operand elements of one row along the contraction (all parts)
     double c1 = 0, c2 = 0;
     const void* s_cur = nullptr;
     void *s_next = nullptr, *dlt = nullptr, *Y = nullptr, *Y2out = nullptr, *Dop = nullptr, *Xnext = nullptr;
-    int64_t ldxn = 0;
     const void* part_prim = nullptr;
     void* part_out = nullptr;
     const void* g = nullptr;

@@ -26,7 +26,11 @@ namespace twa {
 
 namespace {
 
-__device__ __align__(256) unsigned char scratch[TWA_NOALLOC_SCRATCH_BYTES];
+// The split forms lay their operands out in bf16 parts (six bytes a value in
+// FP32) and in tiles of their own, so a run of TWA_NOALLOC_SCRATCH_BYTES as
+// documented_bytes counts them takes up to twice that.
+constexpr size_t kScratchBytes = 2 * (size_t)TWA_NOALLOC_SCRATCH_BYTES;
+__device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -64,6 +68,59 @@ struct Carver {
         return p;
     }
 };
+
+// the buffers twa_run allocates for a run without lags, op_bytes a
+// contraction operand value
+double* carve(Carver& cv, const Geometry& g, size_t op_bytes, EnsembleBuffers& b) {
+    const size_t se = (size_t)state_elt_bytes(g.precision);
+    const size_t P = (size_t)g.P, Bp = (size_t)g.Bp, C2 = (size_t)g.C2, nmt = (size_t)g.nmt;
+    b.A = cv.take(P * 2 * P * op_bytes);
+    b.Xop = cv.take(C2 * 2 * P * op_bytes);
+    b.Dop = cv.take(C2 * P * op_bytes);
+    b.s[0] = cv.take(3 * Bp * P * se);
+    b.s[1] = cv.take(3 * Bp * P * se);
+    b.Sn = cv.take(2 * Bp * se);
+    b.Y = cv.take(2 * Bp * P * se);
+    b.part[0] = cv.take(3 * nmt * Bp * se);
+    b.part[1] = cv.take(3 * nmt * Bp * se);
+    b.g = cv.take(2 * Bp * se);
+    b.norm0 = cv.take(Bp * P * se);
+    b.mom = cv.take(10 * Bp * se);
+    b.step = static_cast<int64_t*>(cv.take(sizeof(int64_t)));
+    b.diag = static_cast<float*>(cv.take(2 * 1024 * sizeof(float)));
+    return static_cast<double*>(cv.take((32 * 5 + 3) * sizeof(double)));
+}
+
+// The bytes a run counts against TWA_NOALLOC_SCRATCH_BYTES: its buffers
+// padded to fixed tiles (16x32 to N = 48, 64x64 to 768, then 128x128, or
+// 320x256 where that is fewer rounds of 256 tiles at 1.64 times the rate), an
+// operand value at 8 (FP64), 4 (FP32), 6 (split BF16) or 2 bytes.  What a run
+// takes in fact follows its own tiles and parts; which runs are accepted does
+// not change with them.
+size_t documented_bytes(const twa_params* p, int64_t N, int64_t B) {
+    int id = p->tile_config;
+    if (id < 0) {
+        auto est = [&](const TileCfg& t, double rate) {
+            const int64_t tiles = (round_up(N, t.mt) / t.mt) * (2 * round_up(B, t.nt / 2) / t.nt);
+            return (double)((tiles + 255) / 256) * (double)(t.mt * t.nt) / rate;
+        };
+        id = N <= 48 ? 0 : N <= 768 ? 1
+             : p->precision != TWA_PREC_FP64 && est(kTiles[0][7], 1.64) < est(kTiles[0][2], 1.0) ? 7 : 2;
+    }
+    const TileCfg& tc = kTiles[0][id];
+    const size_t op = p->precision == TWA_PREC_FP64 ? 8 : p->precision == TWA_PREC_FP32 ? 4
+                      : p->precision == TWA_PREC_BF16X3 ? 6 : 2;
+    Geometry g;
+    g.precision = p->precision;
+    g.P = round_up(N, std::max<int64_t>(tc.mt, tc.kbytes / (op == 6 ? 2 : (int)op)));
+    g.Bp = round_up(B, tc.nt / 2);
+    g.nmt = g.P / tc.mt;
+    g.C2 = 2 * g.Bp;
+    Carver cv{nullptr};
+    EnsembleBuffers b;
+    carve(cv, g, op, b);
+    return cv.used;
+}
 
 __global__ void zero_kernel(uint4* p, size_t n16) {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += (size_t)gridDim.x * blockDim.x)
@@ -145,33 +202,16 @@ int run_noalloc(const twa_params* p, int64_t n_traj, double dt, int64_t n_steps,
     const int nblk = (int)std::min<int64_t>(1024, std::max<int64_t>(1, (B * N + 255) / 256));
     hipStream_t st = (hipStream_t)p->stream;
 
-    // the buffers twa_run allocates for a run without lags, in the scratch array
-    const size_t ge = (size_t)gemm_elt_bytes(g.precision), se = (size_t)state_elt_bytes(g.precision);
-    const size_t P = (size_t)g.P, Bp = (size_t)g.Bp, C2 = (size_t)g.C2, nmt = (size_t)g.nmt;
-    const size_t spl = (size_t)operand_split(g.precision);
+    const size_t need = documented_bytes(p, N, B);
     void* base = nullptr;
     int rc = scratch_address(&base);
     if (rc) return rc;
     Carver cv{static_cast<char*>(base)};
     EnsembleBuffers b;
-    b.A = cv.take(P * 2 * P * ge * spl);
-    b.Xop = cv.take(C2 * 2 * P * ge * spl);
-    b.Dop = cv.take(C2 * P * ge * spl);
-    b.s[0] = cv.take(3 * Bp * P * se);
-    b.s[1] = cv.take(3 * Bp * P * se);
-    b.Sn = cv.take(2 * Bp * se);
-    b.Y = cv.take(2 * Bp * P * se);
-    b.part[0] = cv.take(3 * nmt * Bp * se);
-    b.part[1] = cv.take(3 * nmt * Bp * se);
-    b.g = cv.take(2 * Bp * se);
-    b.norm0 = cv.take(Bp * P * se);
-    b.mom = cv.take(10 * Bp * se);
-    b.step = static_cast<int64_t*>(cv.take(sizeof(int64_t)));
-    b.diag = static_cast<float*>(cv.take(2 * 1024 * sizeof(float)));
-    double* res = static_cast<double*>(cv.take((32 * 5 + 3) * sizeof(double)));
-    if (cv.used > (size_t)TWA_NOALLOC_SCRATCH_BYTES) {
+    double* res = carve(cv, g, (size_t)gemm_elt_bytes(g.precision) * operand_split(g.precision), b);
+    if (need > (size_t)TWA_NOALLOC_SCRATCH_BYTES || cv.used > kScratchBytes) {
         set_error("twa_run_noalloc: N = " + std::to_string(N) + ", n_traj = " + std::to_string(B) + " needs " +
-                  std::to_string(cv.used) + " bytes of device scratch; the limit is " +
+                  std::to_string(need) + " bytes of device scratch; the limit is " +
                   std::to_string((size_t)TWA_NOALLOC_SCRATCH_BYTES) + " (use twa_run)");
         return TWA_ENOMEM;
     }

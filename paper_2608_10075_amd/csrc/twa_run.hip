@@ -25,22 +25,13 @@ void set_error(const std::string& msg) { g_err = msg; }
 int gemm_elt_bytes(int precision) {
     switch (precision) {
         case TWA_PREC_FP64: return 8;
-        case TWA_PREC_FP32: return 4;
         default: return 2;
     }
 }
 int state_elt_bytes(int precision) { return precision == TWA_PREC_FP64 ? 8 : 4; }
-int operand_split(int precision) { return precision == TWA_PREC_BF16X3 ? 3 : 1; }
+int operand_split(int precision) { return precision == TWA_PREC_FP32 ? 3 : precision == TWA_PREC_BF16X3 ? 2 : 1; }
 
-int pick_tile_cfg(int precision, int64_t N, int64_t n_traj) {
-    if (N <= 48) return 0;
-    if (N <= 768) return 1;
-    if (precision == TWA_PREC_FP64) return 2;
-    // Large N: 128x128 tiles (4 waves) or 320x256 tiles (8 waves), whichever
-    // gives the shorter estimated contraction time = rounds of resident tiles
-    // x work per tile / per-tile rate.  The larger tile moves 45 % fewer bytes
-    // per flop through the vector-memory path (the bound of the smaller one)
-    // and runs 1.64x faster per tile, but needs enough tiles to fill the device.
+static int n_compute_units() {
     static int ncu = 0;
     if (ncu <= 0) {
         int dev = 0;
@@ -48,14 +39,53 @@ int pick_tile_cfg(int precision, int64_t N, int64_t n_traj) {
             hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu <= 0)
             ncu = 256;
     }
-    auto est = [&](int cfg, double rate) {
-        const TileCfg& t = tile_cfg(cfg);
-        const int64_t P = round_up(N, t.mt), Bp = round_up(n_traj, t.nt / 2);
-        const int64_t tiles = (P / t.mt) * (2 * Bp / t.nt);
-        const int64_t rounds = (tiles + ncu - 1) / ncu;
-        return (double)rounds * (double)(t.mt * t.nt) / rate;
+    return ncu;
+}
+
+// Tile shape of a contraction: the shortest estimate, in us per step and 1000
+// spins, of rounds of tiles over the compute units x the cost of a round.  A
+// larger tile loads fewer bytes per product but leaves compute units idle
+// where there are few tiles; a round that is the only one costs more (nothing
+// runs beside its epilogue).  Costs measured per step of N x B = 700 x 512 to
+// 10^4 x 1024, e.g. at 1000 x 4096 in FP32 424 us with 64x64 tiles, 333 with
+// 128x64, 340 with 128x128 and 307 with 256x128; at 4096 x 512 in split BF16
+// 377, 312, 289 and (320x256) 1003; at 10^4 x 1024 in BF16 3211 (64x64), 1752
+// (128x128) and 991 (320x256).  FP64 is bound by its MFMA: 64x64 takes 1765 us
+// at 3000 x 1024, 128x128 2607.
+// Where 64x64 tiles are too few to fill the device, 16x32 ones are shorter:
+// FP32 201 x 500 (64 tiles) 29 against 31 us, 700 x 512 (176) 58 against 56;
+// FP64 600 x 400 (130) 89 against 101, 2000 x 512 (512) 531 against 433.
+int pick_tile_cfg(int precision, int64_t N, int64_t n_traj) {
+    struct Cost {
+        int cfg;
+        double single, round;
     };
-    return est(7, 1.64) < est(2, 1.0) ? 7 : 2;
+    static const Cost one[] = {{1, 30, 15}, {3, 42, 36}, {7, 105, 105}};
+    static const Cost two[] = {{1, 45, 26}, {3, 70, 39}, {2, 72, 66}, {7, 250, 250}};
+    static const Cost three[] = {{1, 70, 48}, {3, 100, 75}, {2, 140, 140}, {7, 215, 215}};
+    static const Cost fp64[] = {{1, 149, 105}};
+    const int np = operand_split(precision);
+    const bool f64 = precision == TWA_PREC_FP64;
+    const Cost* c = f64 ? fp64 : np == 1 ? one : np == 2 ? two : three;
+    const int n = f64 ? 1 : np == 1 ? 3 : 4;
+    const int64_t ncu = n_compute_units();
+    auto tiles = [&](int cfg) {
+        const TileCfg& t = tile_cfg(precision, cfg);
+        return (round_up(N, t.mt) / t.mt) * (2 * round_up(n_traj, t.nt / 2) / t.nt);
+    };
+    if (N <= 48) return 0;
+    if ((f64 && 5 * tiles(1) < 4 * ncu) || (np == 3 && 5 * tiles(1) < 2 * ncu)) return 0;
+    int best = 1;
+    double tb = 1e300;
+    for (int q = 0; q < n; ++q) {
+        const int64_t rounds = (tiles(c[q].cfg) + ncu - 1) / ncu;
+        const double t = rounds == 1 ? c[q].single : (double)rounds * c[q].round;
+        if (t < tb) {
+            tb = t;
+            best = c[q].cfg;
+        }
+    }
+    return best;
 }
 
 // ---------------------------------------------------------------------------
@@ -315,13 +345,13 @@ int alloc_buffers(const Geometry& g, bool tangents, int64_t L, int J, EnsembleBu
     int rc;
 #define TWA_A(ptr, bytes) \
     if ((rc = dalloc((void**)&(ptr), (bytes), st)) != TWA_OK) return rc;
-    const size_t spl = (size_t)operand_split(g.precision);   // split form: hi, lo, hi blocks
+    const size_t spl = (size_t)operand_split(g.precision);   // parts per operand value
     const size_t ck = g.coh ? 1 : 0;                          // coherent exchange: one more K block
     TWA_A(b.A, P * (2 + ck) * P * ge * spl)
     TWA_A(b.Xop, C2 * (2 + ck) * P * ge * spl)
     TWA_A(b.Dop, C2 * (1 + ck) * P * ge * spl)
     if (ck) {
-        TWA_A(b.A2, P * 2 * P * ge)
+        TWA_A(b.A2, P * 2 * P * ge * spl)
     }
     TWA_A(b.s[0], 3 * Bp * P * se)
     TWA_A(b.s[1], 3 * Bp * P * se)
@@ -355,10 +385,10 @@ int alloc_buffers(const Geometry& g, bool tangents, int64_t L, int J, EnsembleBu
 
 int alloc_decay_buffers(const Geometry& g, EnsembleBuffers& b, hipStream_t st) {
     const size_t ge = (size_t)gemm_elt_bytes(g.precision), se = (size_t)state_elt_bytes(g.precision);
-    const size_t P = (size_t)g.P, Bp = (size_t)g.Bp;
+    const size_t P = (size_t)g.P, Bp = (size_t)g.Bp, gp = ge * (size_t)operand_split(g.precision);
     int rc;
-    if ((rc = dalloc(&b.AG, P * P * ge, st)) || (rc = dalloc(&b.AGG, P * P * ge, st)) ||
-        (rc = dalloc(&b.Zop, Bp * P * ge, st)) || (rc = dalloc(&b.GX, 2 * Bp * P * se, st)) ||
+    if ((rc = dalloc(&b.AG, P * P * gp, st)) || (rc = dalloc(&b.AGG, P * P * gp, st)) ||
+        (rc = dalloc(&b.Zop, Bp * P * gp, st)) || (rc = dalloc(&b.GX, 2 * Bp * P * se, st)) ||
         (rc = dalloc(&b.UZ, Bp * P * se, st)) || (rc = dalloc(&b.dg, P * se, st)) ||
         (rc = dalloc((void**)&b.gmom, 18 * Bp * sizeof(double), st)))
         return rc;
@@ -369,7 +399,7 @@ Geometry make_geometry(int precision, int cfg, int64_t N, int64_t B) {
     Geometry g;
     g.precision = precision;
     g.cfg = cfg;
-    const TileCfg& tc = tile_cfg(cfg);
+    const TileCfg& tc = tile_cfg(precision, cfg);
     g.kt = tc.kbytes / gemm_elt_bytes(precision);
     g.N = N;
     g.B = B;

@@ -137,7 +137,7 @@ int run_single(const twa_params* p, int64_t n_traj, double dt, int64_t n_steps, 
     g.coh = pump->Om ? 1 : 0;
     if (decay) {
         // the packed s^z contraction covers Bp / 2 column pairs
-        g.Bp = round_up(B, tile_cfg(cfg).nt);
+        g.Bp = round_up(B, tile_cfg(p->precision, cfg).nt);
         g.C2 = 2 * g.Bp;
     }
     const bool fused = p->tile_config < 0 && !decay && !toep && small_path_applies(p->precision, N, L);

@@ -9,21 +9,7 @@
 
 namespace twa {
 
-// ---------------------------------------------------------------------------
-// tile configurations
-static const TileCfg kCfgs[] = {
-    {0, 16, 32, 64, 1, 1, 2, "16x32 K64B 1w 2st"},
-    {1, 64, 64, 64, 2, 2, 4, "64x64 K64B 4w 4st"},
-    {2, 128, 128, 128, 2, 2, 4, "128x128 K128B 4w 4st"},
-    {3, 128, 128, 64, 2, 2, 8, "128x128 K64B 4w 8st"},
-    {4, 256, 128, 64, 4, 1, 6, "256x128 K64B 4w 6st"},
-    {5, 128, 256, 64, 2, 2, 6, "128x256 K64B 4w 6st"},
-    {6, 256, 128, 64, 4, 2, 4, "256x128 K64B 8w 4st"},
-    {7, 320, 256, 128, 4, 2, 2, "320x256 K128B 8w 2st"},
-    {8, 320, 256, 64, 4, 2, 4, "320x256 K64B 8w 4st"},
-};
-int n_tile_cfgs() { return (int)(sizeof(kCfgs) / sizeof(kCfgs[0])); }
-const TileCfg& tile_cfg(int id) { return kCfgs[id]; }
+const TileCfg& tile_cfg(int precision, int id) { return kTiles[operand_split(precision) - 1][id]; }
 
 int launch_gemm(const Geometry& g, const EnsembleBuffers& b, const StepConsts& c, int stage, bool tangent,
                 int cur, bool store_y2, bool keep_dlt, hipStream_t st) {

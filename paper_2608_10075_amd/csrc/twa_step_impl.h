@@ -26,6 +26,8 @@
 #pragma once
 
 #include <algorithm>
+#include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "twa_internal.h"
@@ -38,10 +40,9 @@ struct GemmArgs {
     typedef typename Prec<PREC>::G G;
     typedef typename Prec<PREC>::S S;
     const G* A;         // P rows, stage-blocked with KB bytes per row and stage (a_index)
-    const G* X;         // operand of copy 0
-    int64_t ldx;
+    const G* X;         // column operand of copy 0, stage-blocked (x_index)
     int64_t x_copy;     // element offset between copies
-    int64_t K;          // contraction length
+    int64_t K;          // operand elements of one row along the contraction (all parts)
     int64_t P, Bp, nmt;
     int nnt;            // column tiles
     S c1, c2;
@@ -51,10 +52,8 @@ struct GemmArgs {
     S* dlt;
     S* Y;
     G* Dop;             // stage 1 writes
-    int64_t ldd;        // Dop column length (P; SPLIT P in the split form; 2P with coherent exchange)
     int coh;            // coherent exchange: also write the perpendicular blocks (s^y, -s^x) / (D^y, -D^x)
-    G* Xnext;           // stage 2 writes (s-part, ld 2P for primal, P for tangents)
-    int64_t ldxn;
+    G* Xnext;           // stage 2 writes (s-part)
     const S* part_prim; // primal partial sums read by the epilogue
     S* part_out;        // partial sums written
     const S* g;
@@ -151,23 +150,6 @@ __device__ __forceinline__ void st4(S* p, const S (&v)[4]) {
         *reinterpret_cast<double2*>(p + 2) = make_double2(v[2], v[3]);
     }
 }
-template <int PREC>
-__device__ __forceinline__ void stg4(typename Prec<PREC>::G* p, const typename Prec<PREC>::S (&v)[4]) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) p[r] = Prec<PREC>::to_g(v[r]);
-}
-// coherent exchange: the perpendicular block at row offset off of the x and y
-// columns holds (v^y, -v^x)
-template <int PREC>
-__device__ __forceinline__ void stg4perp(typename Prec<PREC>::G* cx, typename Prec<PREC>::G* cy,
-                                         const typename Prec<PREC>::S (&vx)[4], const typename Prec<PREC>::S (&vy)[4]) {
-    typename Prec<PREC>::S m[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) m[r] = -vx[r];
-    stg4<PREC>(cx, vy);
-    stg4<PREC>(cy, m);
-}
-
 // Epilogue streams as raw buffers: the descriptor's base is the wave's first
 // element of an array (wave-uniform, scalar registers), the lane adds one
 // 32-bit byte offset (voff) and the block one uniform byte offset, so every
@@ -227,19 +209,21 @@ __device__ __forceinline__ void bstg4(Rsrc r, uint32_t voff, const typename Prec
         bst4(r, voff, g);
     }
 }
-// operand store of a state-like value: one block, or for the split form the
-// (hi, lo, hi) blocks blk bytes apart
+// operand store of a state-like value: one block, or in the split forms its
+// parts blk bytes apart
 template <int PREC>
 __device__ __forceinline__ void bstg4s(Rsrc r, uint32_t voff, uint32_t blk, const typename Prec<PREC>::S (&v)[4]) {
-    if constexpr (Prec<PREC>::SPLIT == 3) {
-        uint16_t hi[4], lo[4];
+    constexpr int NP = Prec<PREC>::NP;
+    if constexpr (NP > 1) {
+        uint16_t h[4][NP];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) bf16_split(v[q], hi[q], lo[q]);
-        const u32x2 th = {(uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16)};
-        const u32x2 tl = {(uint32_t)lo[0] | ((uint32_t)lo[1] << 16), (uint32_t)lo[2] | ((uint32_t)lo[3] << 16)};
-        __builtin_amdgcn_raw_buffer_store_b64(th, r, voff, 0, 0);
-        __builtin_amdgcn_raw_buffer_store_b64(tl, r, voff + blk, 0, 0);
-        __builtin_amdgcn_raw_buffer_store_b64(th, r, voff + 2 * blk, 0, 0);
+        for (int q = 0; q < 4; ++q) bf16_parts<NP>(v[q], h[q]);
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const u32x2 t = {(uint32_t)h[0][p] | ((uint32_t)h[1][p] << 16),
+                             (uint32_t)h[2][p] | ((uint32_t)h[3][p] << 16)};
+            __builtin_amdgcn_raw_buffer_store_b64(t, r, voff + p * blk, 0, 0);
+        }
     } else {
         bstg4<PREC>(r, voff, v);
     }
@@ -247,32 +231,35 @@ __device__ __forceinline__ void bstg4s(Rsrc r, uint32_t voff, uint32_t blk, cons
 // coherent exchange: (v^y, -v^x) into the perpendicular blocks of the x and y
 // columns (byte offsets vx_off, vy_off)
 template <int PREC>
-__device__ __forceinline__ void bstg4perp(Rsrc r, uint32_t vx_off, uint32_t vy_off,
+__device__ __forceinline__ void bstg4perp(Rsrc r, uint32_t vx_off, uint32_t vy_off, uint32_t blk,
                                           const typename Prec<PREC>::S (&vx)[4],
                                           const typename Prec<PREC>::S (&vy)[4]) {
     typename Prec<PREC>::S m[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) m[q] = -vx[q];
-    bstg4<PREC>(r, vx_off, vy);
-    bstg4<PREC>(r, vy_off, m);
+    bstg4s<PREC>(r, vx_off, blk, vy);
+    bstg4s<PREC>(r, vy_off, blk, m);
 }
 
-// operand store of a state-like value: one block, or for the split form the
-// (hi, lo, hi) blocks blk elements apart
+// operand store of four consecutive spins of a column (they share a K stage)
 template <int PREC>
-__device__ __forceinline__ void stg4s(typename Prec<PREC>::G* p, int64_t blk, const typename Prec<PREC>::S (&v)[4]) {
-    if constexpr (Prec<PREC>::SPLIT == 3) {
+__device__ __forceinline__ void stg4x(typename Prec<PREC>::G* X, int64_t c, int64_t i, int64_t C2, int64_t kt,
+                                      const typename Prec<PREC>::S (&v)[4]) {
+    constexpr int NP = Prec<PREC>::NP;
+    typename Prec<PREC>::G* p = X + x_index(c, i, C2, kt, NP);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            uint16_t hi, lo;
-            bf16_split(v[r], hi, lo);
-            p[r].v = hi;
-            p[blk + r].v = lo;
-            p[2 * blk + r].v = hi;
-        }
-    } else {
-        stg4<PREC>(p, v);
-    }
+    for (int r = 0; r < 4; ++r) put_op<PREC>(p + r, C2 * kt, v[r]);
+}
+
+// f(u0 + V, V) for every V of a sequence, V a compile-time constant; the second
+// form leaves out those with u0 + V >= n
+template <typename F, int... V>
+__device__ __forceinline__ void unroll_all(F& f, const int u0, std::integer_sequence<int, V...>) {
+    (f(u0 + V, std::integral_constant<int, V>{}), ...);
+}
+template <typename F, int... V>
+__device__ __forceinline__ void unroll_units(F& f, const int u0, const int n, std::integer_sequence<int, V...>) {
+    ((u0 + V < n ? f(u0 + V, std::integral_constant<int, V>{}) : void()), ...);
 }
 
 // ---------------------------------------------------------------------------
@@ -297,19 +284,22 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     constexpr int WM = MT / WMW, WN = NT / WNW;
     constexpr int BI = WM / 16, BJ = WN / 16;
     constexpr int PCS = KB / 16;             // 16-byte pieces per row
-    constexpr int PA = MT * PCS, PX = NT * PCS;
     constexpr int KT = KB / (int)sizeof(G);
+    constexpr int NP = Prec<PREC>::NP;       // parts per operand value
     constexpr int NTRJ = NT / 2;             // trajectories per tile
     static_assert(WM % 16 == 0 && WN % 32 == 0, "wave tile");
     static_assert(KB % 64 == 0, "K stage");
 
-    // NST LDS stages (a ring), each rows [0, MT) of A then [MT, MT + NT) of X,
-    // KB bytes per row; inside every 16-row block the 16-byte piece c of row r
-    // is stored at piece position c ^ swz(r), which makes the 16-lane fragment
-    // reads of one MFMA operand hit distinct LDS banks.  The stages are
-    // distinct LDS objects so that the compiler can tell the loads in flight
-    // into one stage from the reads of another.
-    static_assert(NST >= 2 && NST <= 8, "LDS ring depth");
+    // NST LDS units (a ring).  A unit holds one part of one K stage of the
+    // operands: rows [0, MT) of A then [MT, MT + NT) of X, KB bytes per row.
+    // The split forms load each part once and form all its products from
+    // registers and LDS, so NP parts cost NP times the load traffic of one
+    // for NP (NP + 1) / 2 times the MFMA work.  Inside every 16-row block the
+    // 16-byte piece c of row r is stored at piece position c ^ swz(r), which
+    // makes the 16-lane fragment reads of one MFMA operand hit distinct LDS
+    // banks.  The units are distinct LDS objects so that the compiler can tell
+    // the loads in flight into one from the reads of another.
+    static_assert(NST >= 2 && NST <= 12, "LDS ring depth");
     constexpr int SB = (MT + NT) * KB;
     __shared__ __attribute__((aligned(1024))) char L0[SB];
     __shared__ __attribute__((aligned(1024))) char L1[SB];
@@ -319,13 +309,17 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     __shared__ __attribute__((aligned(1024))) char L5[NST > 5 ? SB : 16];
     __shared__ __attribute__((aligned(1024))) char L6[NST > 6 ? SB : 16];
     __shared__ __attribute__((aligned(1024))) char L7[NST > 7 ? SB : 16];
+    __shared__ __attribute__((aligned(1024))) char L8[NST > 8 ? SB : 16];
+    __shared__ __attribute__((aligned(1024))) char L9[NST > 9 ? SB : 16];
+    __shared__ __attribute__((aligned(1024))) char L10[NST > 10 ? SB : 16];
+    __shared__ __attribute__((aligned(1024))) char L11[NST > 11 ? SB : 16];
     __shared__ S sS[NTRJ][2];      // primal collective sums of the trajectories of the tile
     __shared__ S sT[NTRJ][2];      // tangent collective sums
     __shared__ S sG[NTRJ][2];      // collective normals
     // cross-wave partial sums: [wave row][trajectory][4 channels] in the
     // epilogue, [thread group][trajectory][5 channels] for the collective sums
     constexpr int NG = NTHR / NTRJ;            // thread groups of the collective sums
-    static_assert(NTHR % NTRJ == 0, "thread groups");
+    static_assert(NG >= 1, "thread groups");
     __shared__ S red[WMW > NG ? WMW : NG][NTRJ][5];
     __shared__ S sSrc[NTRJ][3];    // adjoint: observation source of each trajectory
 
@@ -339,32 +333,38 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     // ---- main loop: acc[i][col] = sum_k A[m0+i][k] X[n0+col][k]
     AV acc[BI][BJ];
     AV accW[QSNAP ? BI : 1][QSNAP ? BJ : 1];   // accumulator at K stage kq (snapshot kind)
+    // three parts: the products of lower parts have a sum of their own (see
+    // Prec<TWA_PREC_FP32>)
+    constexpr bool LOW = NP == 3;
+    AV accL[LOW ? BI : 1][LOW ? BJ : 1];
 #pragma unroll
     for (int i = 0; i < BI; ++i)
 #pragma unroll
-        for (int j = 0; j < BJ; ++j) acc[i][j] = AV{0, 0, 0, 0};
+        for (int j = 0; j < BJ; ++j) {
+            acc[i][j] = AV{0, 0, 0, 0};
+            if constexpr (LOW) accL[i][j] = AV{0, 0, 0, 0};
+        }
 
-    // A is stage-blocked: row r of K stage q at byte (q P + r) KB; X columns
-    // are row-major with a pitch of ldx elements
+    // Both operands are stage-blocked: unit u (part u % NP of K stage u / NP)
+    // holds the tile's rows of A as one contiguous run of MT KB bytes and its
+    // columns of X as one of NT KB bytes.
     const char* Ag = reinterpret_cast<const char*>(a.A) + m0 * KB;
-    const char* Xg = reinterpret_cast<const char*>(a.X + cp * a.x_copy + n0 * a.ldx);
-    const int64_t ldx_b = a.ldx * (int64_t)sizeof(G);
-    const int nk = (int)(a.K / KT);
+    const char* Xg = reinterpret_cast<const char*>(a.X + cp * a.x_copy) + n0 * KB;
+    const int nu = (int)(a.K / KT);                // units
+    const int64_t a_unit = P * KB, x_unit = 2 * Bp * KB;
     // Direct memory -> LDS loads (buffer_load_dwordx4 ... lds): one wave
     // instruction moves 64 x 16 bytes into 1 KB of LDS, lane i to offset 16 i,
     // so each lane fetches the piece that belongs at its slot.  The buffer
     // form, not global_load_lds: the compiler takes a FLAT-encoded load into
     // LDS for a possible out-of-order LDS access and then waits for every
-    // fragment read before the first MFMA of a stage (lgkmcnt(0)); with the
+    // fragment read before the first MFMA of a unit (lgkmcnt(0)); with the
     // buffer form it waits for each read only where its MFMA needs it.  A
-    // stage's descriptors span exactly this tile's rows of that stage (A:
-    // MT rows of KB bytes; X: NT rows at a pitch of ldx elements), so no
-    // load can leave them; the offsets fit 32 bits for any A that fits in
-    // device memory.
+    // unit's descriptors span exactly this tile's rows, so no load can leave
+    // them.
     constexpr int RPC = 1024 / KB;                 // rows per 1 KB chunk
-    constexpr int NCH = (MT + NT) / RPC;           // chunks per stage
+    constexpr int NCH = (MT + NT) / RPC;           // chunks per unit
     constexpr int NWV = NTHR / 64;
-    constexpr int CPW = (NCH + NWV - 1) / NWV;     // chunks per wave per stage (at most)
+    constexpr int CPW = (NCH + NWV - 1) / NWV;     // chunks per wave per unit (at most)
     constexpr int CPWMIN = NCH / NWV;              // (at least)
     static_assert(MT % RPC == 0 && (MT + NT) % RPC == 0, "chunking");
     // (gfx950 serves a 16-byte LDS read in four passes of 16 lanes over 64
@@ -374,7 +374,7 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
         return PREC == TWA_PREC_FP64 ? (r16 ^ (r16 >> 2)) % PCS : (PCS >= 16 ? r16 : r16 >> 1) % PCS;
     };
     const int wv = __builtin_amdgcn_readfirstlane(wave);
-    uint32_t voff[CPW];           // lane's byte offset in its chunk's operand rows of one stage
+    uint32_t voff[CPW];           // lane's byte offset in its chunk's operand rows of one unit
     bool srcA[CPW];               // chunk j holds rows of A (else of X); wave-uniform
 #pragma unroll
     for (int j = 0; j < CPW; ++j) {
@@ -382,15 +382,12 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
         const int row = q * RPC + lane / PCS;
         const int pc = (lane % PCS) ^ swz(row & 15);
         srcA[j] = q * RPC < MT;
-        voff[j] = row < MT ? (uint32_t)(row * KB + pc * 16) : (uint32_t)((row - MT) * ldx_b + pc * 16);
+        voff[j] = (uint32_t)((row < MT ? row : row - MT) * KB + pc * 16);
     }
-    const int64_t astage_b = P * KB;   // bytes between K stages of A
-    const int64_t a_stage_bytes = (int64_t)MT * KB;               // this tile's A rows of one stage
-    const int64_t x_stage_bytes = (int64_t)(NT - 1) * ldx_b + KB; // its X rows of one stage
-#define TWA_DMA(KT_, BUF_)                                                                              \
+#define TWA_DMA(U_, BUF_)                                                                               \
     do {                                                                                                \
-        const Rsrc ra_ = wave_rsrc(Ag + (int64_t)(KT_) * astage_b, a_stage_bytes);                      \
-        const Rsrc rx_ = wave_rsrc(Xg + (int64_t)(KT_) * KB, x_stage_bytes);                            \
+        const Rsrc ra_ = wave_rsrc(Ag + (int64_t)(U_) * a_unit, (int64_t)MT * KB);                      \
+        const Rsrc rx_ = wave_rsrc(Xg + (int64_t)(U_) * x_unit, (int64_t)NT * KB);                      \
         _Pragma("unroll") for (int j = 0; j < CPW; ++j) if (CPW == CPWMIN || wv + j * NWV < NCH)        \
             buffer_dma16(srcA[j] ? ra_ : rx_, (BUF_) + (wv + j * NWV) * 1024, voff[j]);                  \
     } while (0)
@@ -400,28 +397,29 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     const int offA = (wm0 + ra) * KB, offX = (MT + wn0 + rx) * KB;
     const int swA = swz(ra), swX = swz(rx), grp = lane >> 4;
 #define TWA_BUF(I_) ((I_) == 0 ? L0 : (I_) == 1 ? L1 : (I_) == 2 ? L2 : (I_) == 3 ? L3 : \
-                     (I_) == 4 ? L4 : (I_) == 5 ? L5 : (I_) == 6 ? L6 : L7)
-    // vmcnt-only wait (expcnt and lgkmcnt left at their maxima), gfx9 encoding
-#define TWA_WAIT_VM(N_) __builtin_amdgcn_s_waitcnt(((N_) & 15) | (((N_) >> 4) << 14) | (7 << 4) | (15 << 8))
-
-#define TWA_COMPUTE(BUF_)                                                                               \
-    do {                                                                                                \
-        _Pragma("unroll") for (int seg = 0; seg < KB / 64; ++seg) {                                     \
-            uint4 af[BI], xf[BJ];                                                                       \
-            const int c_ = seg * 4 + grp;                                                               \
-            _Pragma("unroll") for (int i = 0; i < BI; ++i) af[i] = *reinterpret_cast<const uint4*>(     \
-                (BUF_) + offA + 16 * i * KB + ((c_ ^ swA) << 4));                                       \
-            _Pragma("unroll") for (int j = 0; j < BJ; ++j) xf[j] = *reinterpret_cast<const uint4*>(     \
-                (BUF_) + offX + 16 * j * KB + ((c_ ^ swX) << 4));                                       \
-            _Pragma("unroll") for (int i = 0; i < BI; ++i)                                              \
-                _Pragma("unroll") for (int j = 0; j < BJ; ++j) Prec<PREC>::mma(acc[i][j], af[i], xf[j]); \
-        }                                                                                               \
-    } while (0)
-#define TWA_BUF(I_) ((I_) == 0 ? L0 : (I_) == 1 ? L1 : (I_) == 2 ? L2 : (I_) == 3 ? L3 : \
-                     (I_) == 4 ? L4 : (I_) == 5 ? L5 : (I_) == 6 ? L6 : L7)
-    // vmcnt-only wait (expcnt and lgkmcnt left at their maxima), gfx9 encoding
-#define TWA_WAIT_VM(N_) __builtin_amdgcn_s_waitcnt(((N_) & 15) | (((N_) >> 4) << 14) | (7 << 4) | (15 << 8))
-
+                     (I_) == 4 ? L4 : (I_) == 5 ? L5 : (I_) == 6 ? L6 : (I_) == 7 ? L7 : \
+                     (I_) == 8 ? L8 : (I_) == 9 ? L9 : (I_) == 10 ? L10 : L11)
+    // wait until at most N_ direct loads and no LDS read are pending (expcnt left at its maximum), gfx9 encoding
+#define TWA_WAIT_VM(N_) __builtin_amdgcn_s_waitcnt(((N_) & 15) | (((N_) >> 4) << 14) | (7 << 4) | (0 << 8))
+    // fragments of one 64-byte segment of a unit
+#define TWA_FRAG_A(DST_, BUF_, SEG_)                                                                    \
+    _Pragma("unroll") for (int i = 0; i < BI; ++i) DST_[i] = *reinterpret_cast<const uint4*>(           \
+        (BUF_) + offA + 16 * i * KB + ((((SEG_) * 4 + grp) ^ swA) << 4))
+#define TWA_FRAG_X(DST_, BUF_, SEG_)                                                                    \
+    _Pragma("unroll") for (int j = 0; j < BJ; ++j) DST_[j] = *reinterpret_cast<const uint4*>(           \
+        (BUF_) + offX + 16 * j * KB + ((((SEG_) * 4 + grp) ^ swX) << 4))
+#define TWA_MMA(A_, X_)                                                                                 \
+    _Pragma("unroll") for (int i = 0; i < BI; ++i)                                                      \
+        _Pragma("unroll") for (int j = 0; j < BJ; ++j) {                                                \
+            if constexpr (LOW && p > 0) Prec<PREC>::mma(accL[i][j], A_[i], X_[j]);                      \
+            else Prec<PREC>::mma(acc[i][j], A_[i], X_[j]);                                              \
+        }
+    // Registers allow it: the fragments of the next unit are read while this
+    // unit's products run, so no MFMA waits for an LDS read and a unit's LDS is
+    // free as soon as its turn comes (LOOK units of the ring are then in
+    // registers, not in LDS).
+    constexpr bool AHEAD = KB == 64 && 4 * (BI * BJ * ((QSNAP ? 2 : 1) + (LOW ? 1 : 0)) + NP * (BI + BJ)) + (LOW ? 32 : 48) <= 256;
+    constexpr int LOOK = AHEAD ? 1 : 0;
 
     // ---- collective sums of this tile's trajectories: thread group g of
     // trajectory kl adds the partial sums of the M tiles
@@ -433,7 +431,7 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
         {
             const int kl = tid % NTRJ, gq = tid / NTRJ;
             const int64_t k = k0t + kl;
-            const int64_t q0 = nmt * gq / NG, q1 = nmt * (gq + 1) / NG;
+            const int64_t q0 = nmt * gq / NG, q1 = gq < NG ? nmt * (gq + 1) / NG : q0;
             const S* pp = a.part_prim;
             const S* tp = TCOPY ? a.tpart_in + cp * a.t_part_copy : nullptr;
             S v[5] = {0, 0, 0, 0, 0};
@@ -447,8 +445,9 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                 }
                 if constexpr (KD == KIND_ADJ1) v[4] += pp[(2 * nmt + q) * Bp + k];
             }
+            if (gq < NG)
 #pragma unroll
-            for (int c = 0; c < NCHAN; ++c) red[gq][kl][c] = v[c];
+                for (int c = 0; c < NCHAN; ++c) red[gq][kl][c] = v[c];
         }
         __syncthreads();
         for (int t = tid; t < NTRJ; t += NTHR) {
@@ -502,46 +501,110 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
         }
         __syncthreads();   // the sums are visible to every wave; red is free again
     }
-    // prologue: stages 0 .. NST-2 in flight
+    // prologue: units 0 .. NST - 2 + LOOK in flight
+    constexpr int UN = NST % NP == 0 ? NST : NST * NP;   // unroll: ring slot and part are compile-time
+    uint4 fa[NP][BI], fx[NP][BJ];
 #pragma unroll
-    for (int u = 0; u < NST - 1; ++u)
-        if (u < nk) TWA_DMA(u, TWA_BUF(u));
-    for (int kt0 = 0; kt0 < nk; kt0 += NST) {
+    for (int u = 0; u < NST - 1 + LOOK; ++u)
+        if (u < nu) TWA_DMA(u, TWA_BUF(u % NST));
+    if constexpr (AHEAD) {
+        if (nu >= NST) TWA_WAIT_VM((NST - 1) * CPWMIN);
+        else TWA_WAIT_VM(0);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        TWA_FRAG_A(fa[0], TWA_BUF(0), 0);
+        TWA_FRAG_X(fx[0], TWA_BUF(0), 0);
+    }
+    // one unit: its part is v % NP, its ring slot v % NST
+    auto unit = [&](const int u, auto vc) __attribute__((always_inline)) {
+        constexpr int v = decltype(vc)::value, p = v % NP, pn = (p + 1) % NP;
+        // unit u (u + 1 with LOOK) has landed once at most the later units are
+        // pending (waves that load fewer chunks per unit wait conservatively)
+        __builtin_amdgcn_sched_barrier(0);
+        if (nu - 1 - u >= NST - 2 + LOOK) TWA_WAIT_VM((NST - 2) * CPWMIN);
+        else TWA_WAIT_VM(0);
+        // Barrier without a memory fence: a fence would wait for every load
+        // still in flight into the later units.  What it has to order is
+        // covered explicitly: this wave's loads into the unit completed (vmcnt
+        // above), and its reads of the LDS that the next load overwrites are in
+        // registers (lgkmcnt above).
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        if (u + NST - 1 + LOOK < nu) TWA_DMA(u + NST - 1 + LOOK, TWA_BUF((v + NST - 1 + LOOK) % NST));
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (QSNAP && p == 0) {
+            if (u == a.kq * NP) {
 #pragma unroll
-        for (int u = 0; u < NST; ++u) {
-            const int kt = kt0 + u;
-            if (kt < nk) {
-                // stage kt has landed once at most the later stages are pending
-                // (waves that load fewer chunks per stage wait conservatively)
-                if (nk - 1 - kt >= NST - 2) TWA_WAIT_VM((NST - 2) * CPWMIN);
-                else TWA_WAIT_VM(0);
-                // Barrier without a memory fence: a fence would wait for every
-                // load still in flight into the later stages.  What it has to
-                // order is covered explicitly: this wave's loads into stage kt
-                // completed (vmcnt above), and its reads of the stage the next
-                // load overwrites were consumed by MFMAs before this point.
-                __builtin_amdgcn_s_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-                if (kt + NST - 1 < nk) TWA_DMA(kt + NST - 1, TWA_BUF((u + NST - 1) % NST));
-                __builtin_amdgcn_sched_barrier(0);
-                if constexpr (QSNAP) {
-                    if (kt == a.kq) {
+                for (int i = 0; i < BI; ++i)
 #pragma unroll
-                        for (int i = 0; i < BI; ++i)
-#pragma unroll
-                            for (int j = 0; j < BJ; ++j) accW[i][j] = acc[i][j];
+                    for (int j = 0; j < BJ; ++j) {
+                        if constexpr (LOW) accW[i][j] = acc[i][j] + accL[i][j];
+                        else accW[i][j] = acc[i][j];
                     }
-                }
-                TWA_COMPUTE(TWA_BUF(u));
             }
         }
+        if constexpr (AHEAD) {
+            // (after the last unit these reads return stale LDS, never used)
+            uint4 na[BI], nx[BJ];
+            TWA_FRAG_A(na, TWA_BUF((v + 1) % NST), 0);
+            TWA_FRAG_X(nx, TWA_BUF((v + 1) % NST), 0);
+            // the products of part p with the parts up to it that are kept
+            // (those with pa + px < NP)
+#pragma unroll
+            for (int q = 0; q <= p; ++q) {
+                if (p + q < NP) TWA_MMA(fa[p], fx[q]);
+                if (q < p && p + q < NP) TWA_MMA(fa[q], fx[p]);
+            }
+#pragma unroll
+            for (int i = 0; i < BI; ++i) fa[pn][i] = na[i];
+#pragma unroll
+            for (int j = 0; j < BJ; ++j) fx[pn][j] = nx[j];
+        } else if constexpr (NP == 1) {
+#pragma unroll
+            for (int seg = 0; seg < KB / 64; ++seg) {
+                TWA_FRAG_A(fa[0], TWA_BUF(v % NST), seg);
+                TWA_FRAG_X(fx[0], TWA_BUF(v % NST), seg);
+                TWA_MMA(fa[0], fx[0]);
+            }
+        } else {
+            static_assert(KB == 64, "one segment per unit in the split forms");
+            TWA_FRAG_A(fa[p], TWA_BUF(v % NST), 0);
+#pragma unroll
+            for (int q = 0; q < p; ++q)
+                if (p + q < NP) TWA_MMA(fa[p], fx[q]);
+            TWA_FRAG_X(fx[p], TWA_BUF(v % NST), 0);
+#pragma unroll
+            for (int q = 0; q <= p; ++q)
+                if (p + q < NP) TWA_MMA(fa[q], fx[p]);
+        }
+    };
+    if constexpr (AHEAD) {
+        // whole rounds of the ring without a branch around the products (the
+        // fragments keep their registers from unit to unit), then the rest
+        const int full = nu / UN * UN;
+        for (int u0 = 0; u0 < full; u0 += UN) unroll_all(unit, u0, std::make_integer_sequence<int, UN>{});
+        unroll_units(unit, full, nu, std::make_integer_sequence<int, UN>{});
+    } else {
+        for (int u0 = 0; u0 < nu; u0 += UN) unroll_units(unit, u0, nu, std::make_integer_sequence<int, UN>{});
+    }
+    if constexpr (LOW) {
+#pragma unroll
+        for (int i = 0; i < BI; ++i)
+#pragma unroll
+            for (int j = 0; j < BJ; ++j) acc[i][j] = acc[i][j] + accL[i][j];
     }
 #undef TWA_DMA
-#undef TWA_COMPUTE
+#undef TWA_FRAG_A
+#undef TWA_FRAG_X
+#undef TWA_MMA
 #undef TWA_BUF
 #undef TWA_WAIT_VM
 
     // ---- epilogue: fused Heun stage on (spin i, trajectory k)
+    // (register r of an accumulator is spin i0 + r with i0 a multiple of 4, so
+    // the sign of its row is known at compile time)
+    auto sgn = [](const S v, const int r) { return row_flipped<PREC>(r) ? -v : v; };
+    auto av = [&](const int bi, const int c, const int r) { return sgn(acc[bi][c][r], r); };
     const S c1 = a.c1, c2 = a.c2;
     const int64_t SP = Bp * P;   // plane size
     // The primal kinds load the state (and, in the corrector, the predictor
@@ -562,32 +625,39 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     const uint32_t lane_s = (uint32_t)(((lane & 15) * P + 4 * (lane >> 4)) * (int64_t)sizeof(S));
     auto so_s = [&](const int p, const int bi) { return (uint32_t)((16 * p * P + 16 * bi) * (int64_t)sizeof(S)); };
     auto plane = [&](const S* arr, const int c) { return wave_rsrc(arr + c * SP + eb_s, rem_s); };
-    // operand columns: trajectory kw0 + 16 p + (lane & 15) has columns
-    // opcol(k, c) = 32 (kw0 / 16 + p) + 16 c + (lane & 15), rows m0 + wm0u + ...
-    auto op_rsrc = [&](const G* arr, const int64_t ld) {
-        const int64_t eb = 32 * (kw0 >> 4) * ld + m0 + wm0u;
-        return wave_rsrc(arr + eb, (2 * Bp * ld - eb) * (int64_t)sizeof(G));
+    // operand columns (stage-blocked): trajectory kw0 + 16 p + (lane & 15) has
+    // columns opcol(k, c) = 32 (kw0 / 16 + p) + 16 c + (lane & 15), rows
+    // m0 + wm0u + 16 bi + 4 (lane / 16) + ..; the base is the K stage and the
+    // column block of the wave's first element
+    const int64_t C2 = 2 * Bp;
+    const int64_t r0 = m0 + wm0u;
+    auto op_rsrc = [&](const G* arr, const int64_t row0, const int64_t rows) {
+        const int64_t eb = ((row0 + r0) / KT * (NP * C2) + 32 * (kw0 >> 4)) * KT;
+        return wave_rsrc(arr + eb, (rows * NP * C2 - eb) * (int64_t)sizeof(G));
     };
-    auto op_lane = [&](const int64_t ld) {
-        return (uint32_t)(((lane & 15) * ld + 4 * (lane >> 4)) * (int64_t)sizeof(G));
+    const int r4 = 4 * (lane >> 4);
+    const uint32_t op_lane = KT >= 16 ? (uint32_t)(((lane & 15) * KT + r4) * sizeof(G))
+                                      : (uint32_t)(((int64_t)(r4 / KT) * C2 * KT + (lane & 15) * KT + r4 % KT) *
+                                                   (int64_t)sizeof(G));
+    const int rin = (int)(r0 % KT);
+    auto so_op = [&](const int p, const int c, const int bi) {
+        const int rr = rin + 16 * bi;
+        return (uint32_t)(((int64_t)(rr / KT) * NP * C2 + 32 * p + 16 * c) * (KT * (int64_t)sizeof(G)) +
+                          (rr % KT) * (int64_t)sizeof(G));
     };
-    auto so_op = [&](const int64_t ld, const int p, const int c, const int bi, const int64_t row) {
-        return (uint32_t)(((32 * p + 16 * c) * ld + row + 16 * bi) * (int64_t)sizeof(G));
-    };
-    const uint32_t blk_b = (uint32_t)(P * (int64_t)sizeof(G));   // split (hi, lo, hi) block stride
-    Rsrc rs[3], ry[2], rop;
-    uint32_t ld_d = 0, ld_x = 0;
+    const uint32_t blk_b = (uint32_t)(C2 * (KT * (int64_t)sizeof(G)));   // stride of the parts
+    Rsrc rs[3], ry[2], rop, rperp;
     if constexpr (PF) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) rs[c] = plane(a.s_cur, c);
 #pragma unroll
         for (int c = 0; c < 2; ++c) ry[c] = plane(a.Y, c);
         if constexpr (STAGE == 1) {
-            rop = op_rsrc(a.Dop, a.ldd);
-            ld_d = op_lane(a.ldd);
+            rop = op_rsrc(a.Dop, 0, (1 + a.coh) * P);
+            rperp = op_rsrc(a.Dop, a.coh * P, (1 + a.coh) * P);
         } else {
-            rop = op_rsrc(a.Xnext, a.ldxn);
-            ld_x = op_lane(a.ldxn);
+            rop = op_rsrc(a.Xnext, 0, (2 + a.coh) * P);
+            rperp = op_rsrc(a.Xnext, a.coh * 2 * P, (2 + a.coh) * P);
         }
     }
     S pfn[NPF][4];
@@ -646,7 +716,7 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                 S dx[4], dy[4], dz[4], yx[4], yy[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const S ax = acc[bi][2 * p][r], ay = acc[bi][2 * p + 1][r];
+                    const S ax = av(bi, 2 * p, r), ay = av(bi, 2 * p + 1, r);
                     const S Hx = ax + hx0, Hy = ay + hy0;
                     dx[r] = z[r] * Hx;
                     dy[r] = z[r] * Hy;
@@ -664,16 +734,16 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                 }
                 bst4(ry[0], lane_s + so_s(p, bi), yx);
                 bst4(ry[1], lane_s + so_s(p, bi), yy);
-                bstg4s<PREC>(rop, ld_d + so_op(a.ldd, p, 0, bi, 0), blk_b, dx);
-                bstg4s<PREC>(rop, ld_d + so_op(a.ldd, p, 1, bi, 0), blk_b, dy);
+                bstg4s<PREC>(rop, op_lane + so_op(p, 0, bi), blk_b, dx);
+                bstg4s<PREC>(rop, op_lane + so_op(p, 1, bi), blk_b, dy);
                 if (a.coh)
-                    bstg4perp<PREC>(rop, ld_d + so_op(a.ldd, p, 0, bi, P), ld_d + so_op(a.ldd, p, 1, bi, P), dx, dy);
+                    bstg4perp<PREC>(rperp, op_lane + so_op(p, 0, bi), op_lane + so_op(p, 1, bi), blk_b, dx, dy);
                 if constexpr (QSNAP) {
                     S qx[4], qy[4];
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        qx[r] = acc[bi][2 * p][r] - accW[bi][2 * p][r];
-                        qy[r] = acc[bi][2 * p + 1][r] - accW[bi][2 * p + 1][r];
+                        qx[r] = av(bi, 2 * p, r) - sgn(accW[bi][2 * p][r], r);
+                        qy[r] = av(bi, 2 * p + 1, r) - sgn(accW[bi][2 * p + 1][r], r);
                     }
                     bst4(plane(a.Sout, 0), lane_s + so_s(p, bi), qx);
                     bst4(plane(a.Sout, 1), lane_s + so_s(p, bi), qy);
@@ -684,7 +754,7 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                 S dx[4], dy[4], yx[4], yy[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const S ax = acc[bi][2 * p][r], ay = acc[bi][2 * p + 1][r];
+                    const S ax = av(bi, 2 * p, r), ay = av(bi, 2 * p + 1, r);
                     S dz;
                     midpoint_increment(x[r], y[r], z[r], ax + hx0, ay + hy0, dx[r], dy[r], dz);
                     yx[r] = ax;
@@ -695,10 +765,10 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                 }
                 bst4(ry[0], lane_s + so_s(p, bi), yx);
                 bst4(ry[1], lane_s + so_s(p, bi), yy);
-                bstg4s<PREC>(rop, ld_d + so_op(a.ldd, p, 0, bi, 0), blk_b, dx);
-                bstg4s<PREC>(rop, ld_d + so_op(a.ldd, p, 1, bi, 0), blk_b, dy);
+                bstg4s<PREC>(rop, op_lane + so_op(p, 0, bi), blk_b, dx);
+                bstg4s<PREC>(rop, op_lane + so_op(p, 1, bi), blk_b, dy);
                 if (a.coh)
-                    bstg4perp<PREC>(rop, ld_d + so_op(a.ldd, p, 0, bi, P), ld_d + so_op(a.ldd, p, 1, bi, P), dx, dy);
+                    bstg4perp<PREC>(rperp, op_lane + so_op(p, 0, bi), op_lane + so_op(p, 1, bi), blk_b, dx, dy);
             } else if constexpr (KD == KIND_SIB && STAGE == 2) {
                 // corrector: the midpoint rule from s_n with the field at the
                 // midpoint m = s_n + D/2: contraction Y1 + A_left D / 2, sums (S_n + S~)/2
@@ -709,8 +779,8 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                 const S hym = c1 * (S(0.5) * (sT[kl][1] + Sy)) + c2 * sG[kl][1];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const S Hx = (yx[r] + S(0.5) * acc[bi][2 * p][r]) + hxm;
-                    const S Hy = (yy[r] + S(0.5) * acc[bi][2 * p + 1][r]) + hym;
+                    const S Hx = (yx[r] + S(0.5) * av(bi, 2 * p, r)) + hxm;
+                    const S Hy = (yy[r] + S(0.5) * av(bi, 2 * p + 1, r)) + hym;
                     midpoint_rotate(x[r], y[r], z[r], Hx, Hy, nx[r], ny[r], nz[r]);
                     ps0 += nx[r];
                     ps1 += ny[r];
@@ -719,11 +789,10 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                 bst4(plane(a.s_next, 0), lane_s + so_s(p, bi), nx);
                 bst4(plane(a.s_next, 1), lane_s + so_s(p, bi), ny);
                 bst4(plane(a.s_next, 2), lane_s + so_s(p, bi), nz);
-                bstg4s<PREC>(rop, ld_x + so_op(a.ldxn, p, 0, bi, 0), blk_b, nx);
-                bstg4s<PREC>(rop, ld_x + so_op(a.ldxn, p, 1, bi, 0), blk_b, ny);
+                bstg4s<PREC>(rop, op_lane + so_op(p, 0, bi), blk_b, nx);
+                bstg4s<PREC>(rop, op_lane + so_op(p, 1, bi), blk_b, ny);
                 if (a.coh)
-                    bstg4perp<PREC>(rop, ld_x + so_op(a.ldxn, p, 0, bi, 2 * P), ld_x + so_op(a.ldxn, p, 1, bi, 2 * P),
-                                    nx, ny);
+                    bstg4perp<PREC>(rperp, op_lane + so_op(p, 0, bi), op_lane + so_op(p, 1, bi), blk_b, nx, ny);
             } else if constexpr (KD == KIND_PRIMAL && STAGE == 2) {
                 S dx[4], dy[4], dz[4], yx[4], yy[4], nx[4], ny[4], nz[4];
 #pragma unroll
@@ -753,7 +822,7 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                 }
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const S ax = yx[r] + acc[bi][2 * p][r], ay = yy[r] + acc[bi][2 * p + 1][r];
+                    const S ax = yx[r] + av(bi, 2 * p, r), ay = yy[r] + av(bi, 2 * p + 1, r);
                     const S Hx = ax + hx0, Hy = ay + hy0;
                     const S px = x[r] + dx[r], py = y[r] + dy[r], pz = z[r] + dz[r];
                     const S ex = pz * Hx, ey = pz * Hy, ez = -(px * Hx + py * Hy);
@@ -774,11 +843,10 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                     bst4(plane(yo, 0), lane_s + so_s(p, bi), yx);
                     bst4(plane(yo, 1), lane_s + so_s(p, bi), yy);
                 }
-                bstg4s<PREC>(rop, ld_x + so_op(a.ldxn, p, 0, bi, 0), blk_b, nx);
-                bstg4s<PREC>(rop, ld_x + so_op(a.ldxn, p, 1, bi, 0), blk_b, ny);
+                bstg4s<PREC>(rop, op_lane + so_op(p, 0, bi), blk_b, nx);
+                bstg4s<PREC>(rop, op_lane + so_op(p, 1, bi), blk_b, ny);
                 if (a.coh)
-                    bstg4perp<PREC>(rop, ld_x + so_op(a.ldxn, p, 0, bi, 2 * P), ld_x + so_op(a.ldxn, p, 1, bi, 2 * P),
-                                    nx, ny);
+                    bstg4perp<PREC>(rperp, op_lane + so_op(p, 0, bi), op_lane + so_op(p, 1, bi), blk_b, nx, ny);
             } else if constexpr (KD == KIND_TANGENT && STAGE == 1) {
                 const S tSx = sT[kl][0], tSy = sT[kl][1];
                 const S* tc = a.t_cur + cp * a.t_state_copy;
@@ -804,7 +872,7 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const S Hx = yx[r] + hx0, Hy = yy[r] + hy0;
-                    const S ax = acc[bi][2 * p][r], ay = acc[bi][2 * p + 1][r];
+                    const S ax = av(bi, 2 * p, r), ay = av(bi, 2 * p + 1, r);
                     const S dHx = ax + c1 * tSx + sx[r], dHy = ay + c1 * tSy + sy[r];
                     ex[r] = w[r] * Hx + z[r] * dHx;
                     ey[r] = w[r] * Hy + z[r] * dHy;
@@ -823,9 +891,8 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                 st4(ty + off, ax4);
                 st4(ty + SP + off, ay4);
                 G* tdo = a.tDop + cp * a.t_op_copy;
-                constexpr int SPLT = Prec<PREC>::SPLIT;
-                stg4s<PREC>(tdo + opcol(k, 0) * P * SPLT + i0, P, ex);
-                stg4s<PREC>(tdo + opcol(k, 1) * P * SPLT + i0, P, ey);
+                stg4x<PREC>(tdo, opcol(k, 0), i0, 2 * Bp, KT, ex);
+                stg4x<PREC>(tdo, opcol(k, 1), i0, 2 * Bp, KT, ey);
             } else if constexpr (KD == KIND_STORE) {
                 S ox[4], oy[4];
                 if (a.Sin) {
@@ -837,8 +904,8 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                 }
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    ox[r] += a.store_sign * acc[bi][2 * p][r];
-                    oy[r] += a.store_sign * acc[bi][2 * p + 1][r];
+                    ox[r] += a.store_sign * av(bi, 2 * p, r);
+                    oy[r] += a.store_sign * av(bi, 2 * p + 1, r);
                 }
                 st4(a.Sout + off, ox);
                 st4(a.Sout + SP + off, oy);
@@ -866,8 +933,8 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                     const S Hx = y2x[r] + hx0, Hy = y2y[r] + hy0;
                     const S ux = S(0.5) * lx[r], uy = S(0.5) * ly[r], uz = S(0.5) * lz[r];
                     const S n2x = ux * pz - uz * px, n2y = uy * pz - uz * py;
-                    const S tx = -uz * Hx + c1 * tSx + acc[bi][2 * p][r];
-                    const S ty = -uz * Hy + c1 * tSy + acc[bi][2 * p + 1][r];
+                    const S tx = -uz * Hx + c1 * tSx + av(bi, 2 * p, r);
+                    const S ty = -uz * Hy + c1 * tSy + av(bi, 2 * p + 1, r);
                     const S tz = ux * Hx + uy * Hy;
                     m1x[r] = ux + tx;
                     m1y[r] = uy + ty;
@@ -890,8 +957,8 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                 st4(a.Rb + co + SP + off, ry);
                 st4(a.Rb + co + 2 * SP + off, rz);
                 G* no = a.Xnext + cp * a.t_op_copy;
-                stg4s<PREC>(no + opcol(k, 0) * a.ldxn + i0, P, n1x);
-                stg4s<PREC>(no + opcol(k, 1) * a.ldxn + i0, P, n1y);
+                stg4x<PREC>(no, opcol(k, 0), i0, 2 * Bp, KT, n1x);
+                stg4x<PREC>(no, opcol(k, 1), i0, 2 * Bp, KT, n1y);
             } else if constexpr (KD == KIND_ADJ1) {
                 // reverse of the predictor: (mu1, R) -> lam of the step's input state
                 const int64_t co = cp * a.t_state_copy;
@@ -915,8 +982,8 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                 for (int r = 0; r < 4; ++r) {
                     const S Hx = y1x[r] + hx0, Hy = y1y[r] + hy0;
                     const S msk = (i0 + r < a.N) ? S(1) : S(0);
-                    nlx[r] = rx[r] - mz[r] * Hx + c1 * tSx + acc[bi][2 * p][r] + msk * ox;
-                    nly[r] = ry[r] - mz[r] * Hy + c1 * tSy + acc[bi][2 * p + 1][r] + msk * oy;
+                    nlx[r] = rx[r] - mz[r] * Hx + c1 * tSx + av(bi, 2 * p, r) + msk * ox;
+                    nly[r] = ry[r] - mz[r] * Hy + c1 * tSy + av(bi, 2 * p + 1, r) + msk * oy;
                     nlz[r] = rz[r] + mx[r] * Hx + my[r] * Hy + msk * oz;
                     const S n1x = mx[r] * z[r] - mz[r] * x[r], n1y = my[r] * z[r] - mz[r] * y[r];
                     ps2 += n1x * (y1x[r] * a.inv_w - S(0.5) * a.inv_w * qx[r]) +
@@ -963,8 +1030,8 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                     const S px = x[r] + dx[r], py = y[r] + dy[r], pz = z[r] + dz[r];
                     const S Hx = yx[r] + hx0, Hy = yy[r] + hy0;
                     const S pu = u[r] + du[r], pv = v[r] + dv[r], pw = w[r] + dw[r];
-                    const S dHx = tyx[r] + acc[bi][2 * p][r] + c1 * tSx + sx[r];
-                    const S dHy = tyy[r] + acc[bi][2 * p + 1][r] + c1 * tSy + sy[r];
+                    const S dHx = tyx[r] + av(bi, 2 * p, r) + c1 * tSx + sx[r];
+                    const S dHy = tyy[r] + av(bi, 2 * p + 1, r) + c1 * tSy + sy[r];
                     const S ex = pw * Hx + pz * dHx;
                     const S ey = pw * Hy + pz * dHy;
                     const S ez = -(pu * Hx + px * dHx + pv * Hy + py * dHy);
@@ -980,8 +1047,8 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                 st4(tn + SP + off, nv);
                 st4(tn + 2 * SP + off, nw);
                 G* txo = a.Xnext + cp * a.t_op_copy;
-                stg4s<PREC>(txo + opcol(k, 0) * a.ldxn + i0, P, nu);
-                stg4s<PREC>(txo + opcol(k, 1) * a.ldxn + i0, P, nv);
+                stg4x<PREC>(txo, opcol(k, 0), i0, 2 * Bp, KT, nu);
+                stg4x<PREC>(txo, opcol(k, 1), i0, 2 * Bp, KT, nv);
             }
             // the partial sums are formed inside their block (an empty asm pins
             // each sum in a register here): sunk to the end of the group, they
@@ -1075,37 +1142,14 @@ __global__ __launch_bounds__(64 * WMW * WNW) void heun_stage_grouped(const GemmA
 }
 
 template <int PREC, int CFG>
-struct CfgT;
-#define TWA_CFG(ID, MT_, NT_, KB_, WM_, WN_, NST_)  \
-    template <int PREC>                             \
-    struct CfgT<PREC, ID> {                         \
-        static constexpr int MT = MT_, NT = NT_, KB = KB_, WMW = WM_, WNW = WN_, NST = NST_; \
-    };
-TWA_CFG(0, 16, 32, 64, 1, 1, 2)
-TWA_CFG(1, 64, 64, 64, 2, 2, 4)
-TWA_CFG(2, 128, 128, 128, 2, 2, 4)
-TWA_CFG(3, 128, 128, 64, 2, 2, 8)
-TWA_CFG(4, 256, 128, 64, 4, 1, 6)
-TWA_CFG(5, 128, 256, 64, 2, 2, 6)
-TWA_CFG(6, 256, 128, 64, 4, 2, 4)
-TWA_CFG(7, 320, 256, 128, 4, 2, 2)
-TWA_CFG(8, 320, 256, 64, 4, 2, 4)
-
-// The contraction loop reaches a stage's X rows by 32-bit byte offsets from
-// the stage's base: NT - 1 rows at a pitch of ldx elements plus one K stage
-// must stay within 4 GiB (beyond it the buffer loads would return zeros).
-template <int PREC>
-static bool x_offsets_fit(int64_t ldx, int nt, int kbytes) {
-    return (int64_t)(nt - 1) * ldx * (int64_t)sizeof(typename Prec<PREC>::G) + kbytes <= (int64_t)0xFFFFFFFF;
-}
+struct CfgT {
+    static constexpr TileCfg C = kTiles[Prec<PREC>::NP - 1][CFG];
+    static constexpr int MT = C.mt, NT = C.nt, KB = C.kbytes, WMW = C.waves_m, WNW = C.waves_n, NST = C.nstage;
+};
 
 template <int PREC, int CFG, int STAGE, int KIND>
 static int launch_kernel(const GemmArgs<PREC>& a, int64_t P, int64_t C2, int ncopy, hipStream_t st) {
     typedef CfgT<PREC, CFG> C;
-    if (!x_offsets_fit<PREC>(a.ldx, C::NT, C::KB)) {
-        set_error("operand pitch too large for the contraction's 32-bit offsets");
-        return TWA_EINVAL;
-    }
     GemmArgs<PREC> aa = a;
     aa.nnt = (int)(C2 / C::NT);
     dim3 grid((unsigned)((P / C::MT) * (C2 / C::NT)), 1u, (unsigned)ncopy);
@@ -1119,7 +1163,7 @@ static int launch_kernel(const GemmArgs<PREC>& a, int64_t P, int64_t C2, int nco
 template <int PREC, int CFG>
 static int dispatch_kind(const GemmArgs<PREC>& a, int stage, int kind, int64_t P, int64_t C2, int ncopy,
                          hipStream_t st) {
-    if constexpr (Prec<PREC>::SPLIT == 3) {
+    if constexpr (PREC == TWA_PREC_BF16X3) {
         // the split form runs the forward step and the forward-mode tangent
         // (with the predictor that keeps its noise part)
         if (kind == KIND_PRIMAL)
@@ -1192,10 +1236,9 @@ static GemmArgs<PREC> make_args(const Geometry& g, const EnsembleBuffers& b, con
     typedef typename Prec<PREC>::S S;
     GemmArgs<PREC> a{};
     const int64_t P = g.P, Bp = g.Bp;
-    constexpr int SPL = Prec<PREC>::SPLIT;   // K blocks per value (split form: hi, lo, hi)
+    constexpr int SPL = Prec<PREC>::NP;   // parts per operand value
     const int64_t CK = g.coh ? 1 : 0;         // coherent exchange: one more K block (s_perp, D_perp)
     a.A = static_cast<const G*>(b.A);
-    a.ldd = (1 + CK) * P * SPL;
     a.coh = g.coh;
     a.P = P;
     a.Bp = Bp;
@@ -1220,19 +1263,16 @@ static GemmArgs<PREC> make_args(const Geometry& g, const EnsembleBuffers& b, con
     if (!tangent) {
         if (stage == 1) {
             a.X = static_cast<const G*>(b.Xop);
-            a.ldx = (2 + CK) * P * SPL;
             a.K = (2 + CK) * P * SPL;
             a.part_prim = static_cast<const S*>(b.part[0]);
             a.part_out = static_cast<S*>(b.part[1]);
         } else {
             if (CK) a.A = static_cast<const G*>(b.A2);   // corrector: [-dt/2 W | dt Omega] against (D, D_perp)
             a.X = static_cast<const G*>(b.Dop);
-            a.ldx = (1 + CK) * P * SPL;
             a.K = (1 + CK) * P * SPL;
             a.part_prim = static_cast<const S*>(b.part[1]);
             a.part_out = static_cast<S*>(b.part[0]);
             a.Xnext = static_cast<G*>(b.Xop);
-            a.ldxn = (2 + CK) * P * SPL;
         }
     } else {
         a.t_cur = static_cast<const S*>(b.ts[cur]);
@@ -1242,7 +1282,6 @@ static GemmArgs<PREC> make_args(const Geometry& g, const EnsembleBuffers& b, con
         a.tDop = static_cast<G*>(b.tDop);
         a.x_copy = g.C2 * P * SPL;
         a.K = P * SPL;
-        a.ldx = P * SPL;
         if (stage == 1) {
             a.X = static_cast<const G*>(b.tXop);
             a.part_prim = static_cast<const S*>(b.part[0]);
@@ -1254,7 +1293,6 @@ static GemmArgs<PREC> make_args(const Geometry& g, const EnsembleBuffers& b, con
             a.tpart_in = static_cast<const S*>(b.tpart[1]);
             a.part_out = static_cast<S*>(b.tpart[0]);
             a.Xnext = static_cast<G*>(b.tXop);
-            a.ldxn = P * SPL;
         }
     }
     return a;
@@ -1277,7 +1315,6 @@ int launch_call_p(const Geometry& g, const GemmCall& c, hipStream_t st) {
     GemmArgs<PREC> a{};
     a.A = static_cast<const G*>(c.A);
     a.X = static_cast<const G*>(c.X);
-    a.ldx = c.ldx;
     a.x_copy = c.x_copy;
     a.K = c.K;
     a.P = g.P;
@@ -1293,10 +1330,8 @@ int launch_call_p(const Geometry& g, const GemmCall& c, hipStream_t st) {
     a.Y = static_cast<S*>(c.Y);
     a.Y2out = static_cast<S*>(c.Y2out);
     a.Dop = static_cast<G*>(c.Dop);
-    a.ldd = g.P * Prec<PREC>::SPLIT;
     a.coh = 0;
     a.Xnext = static_cast<G*>(c.Xnext);
-    a.ldxn = c.ldxn;
     a.part_prim = static_cast<const S*>(c.part_prim);
     a.part_out = static_cast<S*>(c.part_out);
     a.g = static_cast<const S*>(c.g);
@@ -1310,12 +1345,12 @@ int launch_call_p(const Geometry& g, const GemmCall& c, hipStream_t st) {
     a.t_state_copy = 3 * g.Bp * g.P;
     a.t_y_copy = 2 * g.Bp * g.P;
     a.t_part_copy = 3 * g.nmt * g.Bp;
-    a.t_op_copy = g.C2 * g.P * Prec<PREC>::SPLIT;
+    a.t_op_copy = g.C2 * g.P * Prec<PREC>::NP;
     a.step = c.step;
     a.Sin = static_cast<const S*>(c.Sin);
     a.Sout = static_cast<S*>(c.Sout);
     a.store_sign = (S)c.store_sign;
-    a.kq = (int)(g.P * Prec<PREC>::SPLIT / g.kt);   // K stage where the noise columns start
+    a.kq = (int)(g.P / g.kt);   // K stage where the noise columns start
     a.Y2in = static_cast<const S*>(c.Y2in);
     a.Qin = static_cast<const S*>(c.Qin);
     a.YA = static_cast<const S*>(c.YA);
@@ -1386,7 +1421,7 @@ int grouped_prepare_p(const std::vector<Geometry>& gs, const std::vector<Ensembl
                              hipStream_t st) {
     const int np = (int)gs.size();
     const int cfg = gs[0].cfg;
-    const TileCfg& tc = tile_cfg(cfg);
+    const TileCfg& tc = tile_cfg(PREC, cfg);
     for (int v = 0; v < (tangents ? GV_COUNT : 1); ++v)
         for (int stage = 1; stage <= 2; ++stage)
             for (int cur = 0; cur < 2; ++cur) {
@@ -1398,10 +1433,6 @@ int grouped_prepare_p(const std::vector<Geometry>& gs, const std::vector<Ensembl
                     h[(size_t)p] = make_args<PREC>(gs[(size_t)p], bs[(size_t)p], cs[(size_t)p], stage, tan, cur,
                                                    win && stage == 2, win || tan);
                     h[(size_t)p].nnt = (int)(gs[(size_t)p].C2 / tc.nt);
-                    if (!x_offsets_fit<PREC>(h[(size_t)p].ldx, tc.nt, tc.kbytes)) {
-                        set_error("operand pitch too large for the contraction's 32-bit offsets");
-                        return TWA_EINVAL;
-                    }
                 }
                 TWA_HIP_CHECK(hipMalloc(&pl.d_args[v][stage - 1][cur], h.size() * sizeof(GemmArgs<PREC>)));
                 TWA_HIP_CHECK(hipMemcpyAsync(pl.d_args[v][stage - 1][cur], h.data(), h.size() * sizeof(GemmArgs<PREC>),
