@@ -140,7 +140,9 @@ int run_single(const twa_params* p, int64_t n_traj, double dt, int64_t n_steps, 
         g.Bp = round_up(B, tile_cfg(p->precision, cfg).nt);
         g.C2 = 2 * g.Bp;
     }
-    const bool fused = p->tile_config < 0 && !decay && !toep && small_path_applies(p->precision, N, L);
+    // (a timed run above 64 atoms keeps the contraction launches it times)
+    const bool fused = p->tile_config < 0 && !decay && !toep && small_path_applies(p->precision, N, L) &&
+                       !(p->timing && N > 64);
     const int J = (int)std::min<int64_t>(32, B);
     const bool tangents = L > 0;
 

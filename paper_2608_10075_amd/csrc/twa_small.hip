@@ -1,15 +1,22 @@
 // Fused small-N path of the TWA trajectories (Eq. (S1), SM Sec. S1): for
-// short chains the per-step work is a few N x N matrix-vector products per
-// trajectory, far too little to fill the device per launch, so the run is
-// bound by per-step latency.  One launch integrates every step: a trajectory
-// occupies NL = 2^k >= N lanes of one wave (lane i holds spin i), the scaled
-// operand rows [-dt/2 W | -sqrt(dt) F] live in LDS, the spin vectors of each
-// trajectory are exchanged through LDS, every step's noise is drawn in
-// registers from the same Philox counters as the multi-kernel path, and the
-// window moments are Kahan-summed in registers.  Heun and the semi-implicit
-// midpoint scheme; FP64 or FP32 arithmetic.
+// short chains the per-step work is a few N x N products per trajectory, far
+// too little to fill the device per launch, so the multi-kernel step is bound
+// by its launches.  One launch integrates every step: a workgroup owns T = 8 CB
+// trajectories for the whole run, with
+//   * NB = ceil(N / 16) compute waves, wave w holding the 16 rows of spins
+//     16 w .. 16 w + 15 of A' = -dt/2 W + Gamma dt/2 (the collective term of
+//     Eq. (S1) is a constant added to the matrix) and of -sqrt(dt) F in
+//     registers and the spins themselves in the MFMA output layout; the spin
+//     vectors are exchanged through LDS;
+//   * four producer waves that draw the next steps' noise into LDS and form
+//     the window moments of the steps before, off the compute waves' path.
+// Bound by the per-step chain exchange -> MFMA -> update -> exchange ->
+// MFMA -> update of the compute waves (MFMA issue from N of about 50 on).
+// Heun and the semi-implicit midpoint scheme; FP64 or FP32 state, operands and
+// MFMA.  Noise from the same Philox counters as the multi-kernel path.
 #include <algorithm>
 #include <cmath>
+
 
 #include "twa_device.h"
 #include "twa_internal.h"
@@ -17,8 +24,32 @@
 namespace twa {
 namespace {
 
-constexpr int SMALL_NMAX = 64;
-constexpr int SMALL_THREADS = 256;
+constexpr int PRODUCERS = 4;   // producer waves per workgroup
+
+template <typename S>
+struct Small;
+template <>
+struct Small<float> {
+    static constexpr int MAX_NB = 8;    // rows of A' and F: 8 NB registers per lane
+    static constexpr int PAD = 4;       // spins of padding per LDS vector: 16 bytes, so columns start on other banks
+    typedef f32x4 V;
+    __device__ static __forceinline__ int arow(int m) { return m; }
+    __device__ static __forceinline__ V mfma(float a, float b, V c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+};
+template <>
+struct Small<double> {
+    static constexpr int MAX_NB = 4;    // 16 NB registers per lane
+    static constexpr int PAD = 2;
+    typedef f64x4 V;
+    // operand row m feeds spin 4 (m % 4) + m / 4, so that output register r of
+    // lane l is spin 4 (l / 16) + r as in binary32
+    __device__ static __forceinline__ int arow(int m) { return 4 * (m & 3) + (m >> 2); }
+    __device__ static __forceinline__ V mfma(double a, double b, V c) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+};
 
 template <typename S>
 __device__ __forceinline__ void kahan(S& sum, S& comp, S v) {
@@ -28,191 +59,416 @@ __device__ __forceinline__ void kahan(S& sum, S& comp, S v) {
     sum = t;
 }
 
-// midpoint rotation of the semi-implicit scheme (same closed form as the step kernels)
+// the value of the lane 8 columns away within a row of 16 lanes
+__device__ __forceinline__ float ror8(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x128, 0xf, 0xf, true));
+}
+__device__ __forceinline__ double ror8(double v) {
+    const int2 h = __builtin_bit_cast(int2, v);
+    return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_mov_dpp(h.x, 0x128, 0xf, 0xf, true),
+                                                __builtin_amdgcn_mov_dpp(h.y, 0x128, 0xf, 0xf, true)));
+}
+
+// orders a wave's own LDS accesses (which the hardware executes in order) for
+// the compiler
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 template <typename S>
-__device__ __forceinline__ void rotate(S x, S y, S z, S Hx, S Hy, S& ox, S& oy, S& oz) {
-    const S bx = S(0.5) * Hy, by = S(-0.5) * Hx;
-    const S ax = x - by * z, ay = y + bx * z, az = z - (bx * y - by * x);
-    const S bd = bx * ax + by * ay;
-    const S inv = S(1) / (S(1) + bx * bx + by * by);
-    ox = (ax - by * az + bx * bd) * inv;
-    oy = (ay + bx * az + by * bd) * inv;
-    oz = (az - (bx * ay - by * ax)) * inv;
-}
+struct SmallArgs {
+    int n;                    // atoms
+    int64_t B, P, Bp;
+    const double *W, *F;
+    double cw, cf, c1;        // -dt/2, -sqrt(dt), Gamma dt / 2
+    S c2;                     // sqrt(Gamma dt)
+    uint32_t k0, k1, point;
+    int64_t n_steps, burnin;
+    int sib;
+    const S* s_in;
+    S *s_out, *mom;
+};
 
-template <typename S, int NL>
-__global__ __launch_bounds__(SMALL_THREADS) void small_run_kernel(
-    int64_t N, int64_t B, int64_t P, int64_t Bp, const double* __restrict__ W, const double* __restrict__ F,
-    double cw, double cf, S c1, S c2, uint32_t k0, uint32_t k1, uint32_t point, int64_t n_steps, int64_t burnin,
-    int sib, const S* __restrict__ s_in, S* __restrict__ s_out, S* __restrict__ mom) {
-    constexpr int TPW = 64 / NL;                       // trajectories per wave
-    constexpr int TPB = TPW * (SMALL_THREADS / 64);    // trajectories per block
-    __shared__ S Aw[SMALL_NMAX * SMALL_NMAX];          // -dt/2 W, row-major N x N
-    __shared__ S Af[SMALL_NMAX * SMALL_NMAX];          // -sqrt(dt) F
-    __shared__ S vx[TPB][NL], vy[TPB][NL], ux[TPB][NL], uy[TPB][NL];
-    const int n = (int)N;
-    for (int t = threadIdx.x; t < n * n; t += SMALL_THREADS) {
-        Aw[t] = (S)(cw * W[t]);
-        Af[t] = (S)(cf * F[t]);
+// CB column blocks of 16: CB = 2 holds the x and y components of 16
+// trajectories in one block each; CB = 1 those of 8 in the two halves of one
+// block (the lanes of a pair exchange their fields and both carry the spin).
+// U steps per batch of noise: with one compute wave nothing but the noise
+// crosses waves, so waves meet once per batch of 8 steps; else every step.
+template <typename S, int NB, int CB>
+__global__ __launch_bounds__(64 * (NB + PRODUCERS)) void small_run_kernel(SmallArgs<S> a) {
+    typedef Small<S> K;
+    typedef typename K::V V;
+    constexpr int T = 8 * CB, COLS = 16 * CB, XP = 16 * NB + K::PAD, U = NB == 1 ? 8 : 1;
+    constexpr int ZB = NB == 1 ? PRODUCERS : 2;
+    __shared__ __attribute__((aligned(16))) S Xs[COLS][XP];     // state, x and y columns
+    __shared__ __attribute__((aligned(16))) S Xd[COLS][XP];     // predictor increment
+    __shared__ __attribute__((aligned(16))) S Z[ZB][COLS][XP];  // pump normals (NB = 1: one per producer)
+    __shared__ S Gn[NB == 1 ? PRODUCERS : 2][T][2];             // collective normals
+    __shared__ __attribute__((aligned(16))) S Q[NB == 1 ? 2 * U : 1][NB == 1 ? COLS : 1][XP];   // noise fields (NB = 1)
+    __shared__ S R[2][U][NB][4][3][T];                          // partial spin sums of the steps of a batch
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int c = lane & 15, g = lane >> 4, n = a.n;
+    const int64_t kb = (int64_t)blockIdx.x * T;      // first trajectory
+    const int64_t SP = a.Bp * a.P;
+    const bool compute = wave < NB;
+    const int w = compute ? wave : 0;
+
+    for (int t = tid; t < ZB * COLS * XP; t += 64 * (NB + PRODUCERS)) (&Z[0][0][0])[t] = S(0);
+
+    // rows of the operands (lane: row c, columns 16 q + 4 g + s)
+    V aw[NB], af[NB];
+    const bool has_f = NB == 1 ? !compute : compute;
+    {
+        const int i = 16 * w + K::arow(c);
+#pragma unroll
+        for (int q = 0; q < NB; ++q)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int j = 16 * q + 4 * g + s;
+                const bool in = i < n && j < n;
+                aw[q][s] = compute && in ? (S)(a.cw * a.W[i * n + j] + a.c1) : S(0);
+                af[q][s] = has_f && in ? (S)(a.cf * a.F[i * n + j]) : S(0);
+            }
     }
-    const int tl = threadIdx.x / NL, i = threadIdx.x % NL;   // trajectory in block, spin
-    const int64_t k = (int64_t)blockIdx.x * TPB + tl;
-    const bool live = k < B && i < n;
-    const int64_t SP = Bp * P;
-    S x = 0, y = 0, z = 0;
-    if (live) {
-        x = s_in[k * P + i];
-        y = s_in[SP + k * P + i];
-        z = s_in[2 * SP + k * P + i];
-    }
+    auto contract = [&](const V (&m)[NB], const S (&X)[COLS][XP], V (&acc)[CB]) {
+#pragma unroll
+        for (int q = 0; q < NB; ++q)
+#pragma unroll
+            for (int b = 0; b < CB; ++b) {
+                const V v = *reinterpret_cast<const V*>(&X[16 * b + c][16 * q + 4 * g]);
+#pragma unroll
+                for (int s = 0; s < 4; ++s) acc[b] = K::mfma(m[q][s], v[s], acc[b]);
+            }
+    };
+
+    // ---- compute waves: spins of rows i0 .. i0 + 3 of trajectory tl
+    const int tl = CB == 1 ? (c & 7) : c, i0 = 16 * w + 4 * g;
+    const bool isy = CB == 1 && c >= 8;
+    const int64_t k = kb + tl;
+    S x[4] = {0, 0, 0, 0}, y[4] = {0, 0, 0, 0}, z[4] = {0, 0, 0, 0};
+    auto put = [&](S (&X)[COLS][XP], const S (&vx)[4], const S (&vy)[4]) {
+        if constexpr (CB == 2) {
+            *reinterpret_cast<V*>(&X[c][i0]) = V{vx[0], vx[1], vx[2], vx[3]};
+            *reinterpret_cast<V*>(&X[16 + c][i0]) = V{vy[0], vy[1], vy[2], vy[3]};
+        } else {
+            V v;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = isy ? vy[r] : vx[r];
+            *reinterpret_cast<V*>(&X[c][i0]) = v;
+        }
+    };
+    auto fields = [&](const V (&acc)[CB], S (&fx)[4], S (&fy)[4]) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if constexpr (CB == 2) {
+                fx[r] = acc[0][r];
+                fy[r] = acc[1][r];
+            } else {
+                const S o = ror8(acc[0][r]);
+                fx[r] = isy ? o : acc[0][r];
+                fy[r] = isy ? acc[0][r] : o;
+            }
+        }
+    };
+    S hx[4], hy[4], dx[4], dy[4], dz[4];
+    // predictor: the fields at s_n (their noise part in acc already), its increment
+    auto predictor = [&](V (&acc)[CB], const S gx, const S gy) {
+        contract(aw, Xs, acc);
+        fields(acc, hx, hy);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            hx[r] += gx;
+            hy[r] += gy;
+            if (a.sib) {
+                const S bx = S(0.5) * hy[r], by = S(-0.5) * hx[r];
+                const S cx = by * z[r], cy = -(bx * z[r]), cz = bx * y[r] - by * x[r];
+                const S f = S(-2) / (S(1) + bx * bx + by * by);
+                dx[r] = f * (cx - by * cz);
+                dy[r] = f * (cy + bx * cz);
+                dz[r] = f * (cz - (bx * cy - by * cx));
+            } else {
+                dx[r] = z[r] * hx[r];
+                dy[r] = z[r] * hy[r];
+                dz[r] = -(x[r] * hx[r] + y[r] * hy[r]);
+            }
+        }
+        put(Xd, dx, dy);
+    };
+    // corrector: the field moves by A' D (Heun) or A' D / 2 (midpoint)
+    auto corrector = [&](S* red) {
+        V acc[CB] = {};
+        contract(aw, Xd, acc);
+        S fx[4], fy[4], sx = 0, sy = 0, sz = 0;
+        fields(acc, fx, fy);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if (a.sib) {
+                const S Hx = hx[r] + S(0.5) * fx[r], Hy = hy[r] + S(0.5) * fy[r];
+                const S bx = S(0.5) * Hy, by = S(-0.5) * Hx;
+                const S ax = x[r] - by * z[r], ay = y[r] + bx * z[r], az = z[r] - (bx * y[r] - by * x[r]);
+                const S bd = bx * ax + by * ay;
+                const S inv = S(1) / (S(1) + bx * bx + by * by);
+                x[r] = (ax - by * az + bx * bd) * inv;
+                y[r] = (ay + bx * az + by * bd) * inv;
+                z[r] = (az - (bx * ay - by * ax)) * inv;
+            } else {
+                const S Hx = hx[r] + fx[r], Hy = hy[r] + fy[r];
+                const S px = x[r] + dx[r], py = y[r] + dy[r], pz = z[r] + dz[r];
+                const S ex = pz * Hx, ey = pz * Hy, ez = -(px * Hx + py * Hy);
+                x[r] = x[r] + S(0.5) * (dx[r] + ex);
+                y[r] = y[r] + S(0.5) * (dy[r] + ey);
+                z[r] = z[r] + S(0.5) * (dz[r] + ez);
+            }
+            sx += x[r];
+            sy += y[r];
+            sz += z[r];
+        }
+        put(Xs, x, y);
+        if (!isy) {   // red: [4 (g)][3][T]
+            red[(g * 3 + 0) * T + tl] = sx;
+            red[(g * 3 + 1) * T + tl] = sy;
+            red[(g * 3 + 2) * T + tl] = sz;
+        }
+    };
+
+    // ---- producer waves
+    const int pw = wave - NB, pl = pw * 64 + lane;
+    const int ns = (n + 1) / 2;
+    // item it of a step's noise: one Philox call of a (trajectory, slot), both
+    // pairs in FP32, one pair per item in FP64 (half as long a chain)
+    constexpr int HALVES = sizeof(S) == 8 ? 2 : 1;
+    const int items = T * ns * HALVES;
+    auto pump_item = [&](const int it, const int64_t st, S (&zb)[COLS][XP]) {
+        const int q = it / HALVES, h = it % HALVES, t = q / ns, m = q - t * ns;
+        const U4 wd = philox4x32_10(U4{(uint32_t)m, (uint32_t)(kb + t), (uint32_t)st, TAG_PUMP | (a.point << 8)}, a.k0,
+                                    a.k1);
+        const int cx = t, cy = (CB == 1 ? 8 : 16) + t;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            if (HALVES == 2 && e == 1) break;
+            const bool second = HALVES == 2 ? h == 1 : e == 1;
+            S za, zc;
+            box_muller(second ? wd.z : wd.x, second ? wd.w : wd.y, za, zc);
+            const int i = 2 * m + (second ? 1 : 0);
+            if (i < n) {
+                zb[cx][i] = za;
+                zb[cy][i] = zc;
+            }
+        }
+    };
+    auto collective_item = [&](const int t, const int64_t st, S (&gb)[T][2]) {
+        const U4 wd = philox4x32_10(U4{0u, (uint32_t)(kb + t), (uint32_t)st, TAG_COLLECTIVE | (a.point << 8)}, a.k0,
+                                    a.k1);
+        S g0, g1;
+        box_muller(wd.x, wd.y, g0, g1);
+        gb[t][0] = g0;
+        gb[t][1] = g1;
+    };
+    // window moments of the steps st .. st + nst - 1 of a batch (first
+    // producer wave): lane l < 3 T adds the partial sums of component l / T of
+    // trajectory l % T, lanes t < T keep the Kahan sums of trajectory t
     S msum[5] = {0, 0, 0, 0, 0}, mcmp[5] = {0, 0, 0, 0, 0};
-    const S* aw = Aw + i * n;
-    const S* af = Af + i * n;
-    __syncthreads();
+    auto observe = [&](const int64_t st, const int nst, const S (&rb)[U][NB][4][3][T]) {
+        for (int u = 0; u < nst; ++u) {
+            if (st + u + 1 <= a.burnin) continue;
+            const int l = lane < 3 * T ? lane : 0, cc = l / T, t = l % T;
+            S v = 0;
+#pragma unroll
+            for (int q = 0; q < NB; ++q)
+#pragma unroll
+                for (int gg = 0; gg < 4; ++gg) v += rb[u][q][gg][cc][t];
+            const S Sx = v, Sy = __shfl(v, T + (lane % T)), Sz = __shfl(v, 2 * T + (lane % T));
+            const S T2 = S(0.25) * (Sx * Sx + Sy * Sy);
+            const S mv[5] = {T2, T2 * Sz, T2 * T2, Sz, Sz * Sz};
+#pragma unroll
+            for (int m = 0; m < 5; ++m) kahan(msum[m], mcmp[m], mv[m]);
+        }
+    };
 
-    for (int64_t st = 0; st < n_steps; ++st) {
-        // noise of the step (counters of the multi-kernel path)
-        S zx = 0, zy = 0, g0 = 0, g1 = 0;
-        {
-            const uint32_t ks = (uint32_t)k, ns = (uint32_t)st;
-            const U4 w = philox4x32_10(U4{(uint32_t)(i >> 1), ks, ns, TAG_PUMP | (point << 8)}, k0, k1);
-            S a0, a1, a2, a3;
-            box_muller(w.x, w.y, a0, a1);
-            box_muller(w.z, w.w, a2, a3);
-            if (live) {
-                zx = (i & 1) ? a2 : a0;
-                zy = (i & 1) ? a3 : a1;
-            }
-            const U4 v = philox4x32_10(U4{0u, ks, ns, TAG_COLLECTIVE | (point << 8)}, k0, k1);
-            box_muller(v.x, v.y, g0, g1);
-        }
-        // stage 1: fields at s_n
-        vx[tl][i] = x;
-        vy[tl][i] = y;
-        ux[tl][i] = zx;
-        uy[tl][i] = zy;
-        __syncthreads();
-        S Yx = 0, Yy = 0, Qx = 0, Qy = 0, Sx = 0, Sy = 0;
-        for (int j = 0; j < n; ++j) {
-            Yx += aw[j] * vx[tl][j];
-            Yy += aw[j] * vy[tl][j];
-            Qx += af[j] * ux[tl][j];
-            Qy += af[j] * uy[tl][j];
-            Sx += vx[tl][j];
-            Sy += vy[tl][j];
-        }
-        const S Hx = (Yx + Qx) + (c1 * Sx + c2 * g0), Hy = (Yy + Qy) + (c1 * Sy + c2 * g1);
-        S px, py, pz, dx = 0, dy = 0, dz = 0;
-        if (sib) {
-            rotate(x, y, z, Hx, Hy, px, py, pz);
-        } else {
-            dx = z * Hx;
-            dy = z * Hy;
-            dz = -(x * Hx + y * Hy);
-            px = x + dx;
-            py = y + dy;
-            pz = z + dz;
-        }
-        if (!live) px = py = pz = 0;
-        // stage 2: fields at the predictor (Heun) or the midpoint (semi-implicit)
-        const S mx = sib ? S(0.5) * (x + px) : px, my = sib ? S(0.5) * (y + py) : py;
-        __syncthreads();   // stage-1 reads done
-        vx[tl][i] = mx;
-        vy[tl][i] = my;
-        __syncthreads();
-        S Y2x = 0, Y2y = 0, S2x = 0, S2y = 0;
-        for (int j = 0; j < n; ++j) {
-            Y2x += aw[j] * vx[tl][j];
-            Y2y += aw[j] * vy[tl][j];
-            S2x += vx[tl][j];
-            S2y += vy[tl][j];
-        }
-        const S H2x = (Y2x + Qx) + (c1 * S2x + c2 * g0), H2y = (Y2y + Qy) + (c1 * S2y + c2 * g1);
-        if (sib) {
-            rotate(x, y, z, H2x, H2y, x, y, z);
-        } else {
-            const S ex = pz * H2x, ey = pz * H2y, ez = -(px * H2x + py * H2y);
-            x = x + S(0.5) * (dx + ex);
-            y = y + S(0.5) * (dy + ey);
-            z = z + S(0.5) * (dz + ez);
-        }
-        if (!live) x = y = z = 0;
-        // window moments of the new state
-        if (st + 1 > burnin) {
-            __syncthreads();   // stage-2 reads done
-            vx[tl][i] = x;
-            vy[tl][i] = y;
-            ux[tl][i] = z;
-            __syncthreads();
-            if (i == 0) {
-                S Tx = 0, Ty = 0, Tz = 0;
-                for (int j = 0; j < n; ++j) {
-                    Tx += vx[tl][j];
-                    Ty += vy[tl][j];
-                    Tz += ux[tl][j];
+    if (compute) {
+        if (k < a.B)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (i0 + r < n) {
+                    x[r] = a.s_in[k * a.P + i0 + r];
+                    y[r] = a.s_in[SP + k * a.P + i0 + r];
+                    z[r] = a.s_in[2 * SP + k * a.P + i0 + r];
                 }
-                const S T2 = S(0.25) * (Tx * Tx + Ty * Ty);
-                const S v[5] = {T2, T2 * Tz, T2 * T2, Tz, Tz * Tz};
-#pragma unroll
-                for (int m = 0; m < 5; ++m) kahan(msum[m], mcmp[m], v[m]);
-            }
-        }
-        __syncthreads();   // all reads of this step done before the next step's writes
+        put(Xs, x, y);
     }
-    if (k < B) {
-        if (i < n) {
-            s_out[k * P + i] = x;
-            s_out[SP + k * P + i] = y;
-            s_out[2 * SP + k * P + i] = z;
-        }
-        if (i == 0)
+    __syncthreads();   // Z cleared, Xs written
+
+    const S c2 = a.c2;
+    if constexpr (NB == 1) {
+        // noise fields of the steps st .. st + nst - 1, one producer wave per step
+        auto produce = [&](const int64_t st, const int nst, const int buf) {
+            for (int u = pw; u < nst; u += PRODUCERS) {
+                for (int it = lane; it < items; it += 64) pump_item(it, st + u, Z[pw]);
+                if (lane < T) collective_item(lane, st + u, Gn[pw]);
+                wave_lds_fence();
+                V acc[CB] = {};
+                contract(af, Z[pw], acc);
+                S fx[4], fy[4];
+                fields(acc, fx, fy);
+                const S gx = c2 * Gn[pw][tl][0], gy = c2 * Gn[pw][tl][1];
 #pragma unroll
-            for (int m = 0; m < 5; ++m) {
-                mom[(2 * m) * Bp + k] = msum[m];
-                mom[(2 * m + 1) * Bp + k] = mcmp[m];
+                for (int r = 0; r < 4; ++r) {
+                    fx[r] += gx;
+                    fy[r] += gy;
+                }
+                if constexpr (CB == 2) {
+                    *reinterpret_cast<V*>(&Q[buf * U + u][c][4 * g]) = V{fx[0], fx[1], fx[2], fx[3]};
+                    *reinterpret_cast<V*>(&Q[buf * U + u][16 + c][4 * g]) = V{fy[0], fy[1], fy[2], fy[3]};
+                } else {
+                    V v;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) v[r] = isy ? fy[r] : fx[r];
+                    *reinterpret_cast<V*>(&Q[buf * U + u][c][4 * g]) = v;
+                }
+                wave_lds_fence();
             }
+        };
+        auto len = [&](const int64_t st) { return (int)(a.n_steps - st < U ? a.n_steps - st : U); };
+        if (!compute && a.n_steps > 0) produce(0, len(0), 0);
+        __syncthreads();
+        int buf = 0;
+        for (int64_t st = 0; st < a.n_steps; st += U, buf ^= 1) {
+            const int nst = len(st);
+            if (compute) {
+                for (int u = 0; u < nst; ++u) {
+                    V acc[CB];
+#pragma unroll
+                    for (int b = 0; b < CB; ++b)
+                        acc[b] = *reinterpret_cast<const V*>(&Q[buf * U + u][16 * b + c][4 * g]);
+                    predictor(acc, S(0), S(0));
+                    wave_lds_fence();
+                    corrector(&R[buf][u][0][0][0][0]);
+                    wave_lds_fence();
+                }
+            } else {
+                if (st + nst < a.n_steps) produce(st + nst, len(st + nst), buf ^ 1);
+                if (pw == 0 && st > 0) observe(st - U, U, R[buf ^ 1]);
+            }
+            __syncthreads();
+        }
+        if (!compute && pw == 0 && a.n_steps > 0) {
+            const int64_t last = (a.n_steps - 1) / U * U;
+            observe(last, len(last), R[buf ^ 1]);
+        }
+    } else {
+        // items [0, cut) of a step are drawn while the predictor runs (two
+        // thirds of its time), the rest while the corrector does
+        const int all = items + T, cut = (2 * all / 3 + 255) / 256 * 256;
+        auto produce = [&](const int from, const int to, const int64_t st, const int buf) {
+            for (int it = from + pl; it < to; it += 64 * PRODUCERS) {
+                if (it < items) pump_item(it, st, Z[buf]);
+                else collective_item(it - items, st, Gn[buf]);
+            }
+        };
+        if (!compute && a.n_steps > 0) produce(0, all, 0, 0);
+        __syncthreads();
+        int buf = 0;
+        for (int64_t st = 0; st < a.n_steps; ++st, buf ^= 1) {
+            if (compute) {
+                V acc[CB] = {};
+                contract(af, Z[buf], acc);
+                predictor(acc, c2 * Gn[buf][tl][0], c2 * Gn[buf][tl][1]);
+            } else {
+                if (pw == 0 && st > 0) observe(st - 1, 1, R[buf ^ 1]);
+                if (st + 1 < a.n_steps) produce(0, min(cut, all), st + 1, buf ^ 1);
+            }
+            __syncthreads();
+            if (compute) corrector(&R[buf][0][w][0][0][0]);
+            else if (st + 1 < a.n_steps) produce(min(cut, all), all, st + 1, buf ^ 1);
+            __syncthreads();
+        }
+        if (!compute && pw == 0 && a.n_steps > 0) observe(a.n_steps - 1, 1, R[buf ^ 1]);
+    }
+
+    if (compute) {
+        if (k < a.B && !isy)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (i0 + r < n) {
+                    a.s_out[k * a.P + i0 + r] = x[r];
+                    a.s_out[SP + k * a.P + i0 + r] = y[r];
+                    a.s_out[2 * SP + k * a.P + i0 + r] = z[r];
+                }
+    } else if (pw == 0 && lane < T && kb + lane < a.B) {
+#pragma unroll
+        for (int m = 0; m < 5; ++m) {
+            a.mom[(2 * m) * a.Bp + kb + lane] = msum[m];
+            a.mom[(2 * m + 1) * a.Bp + kb + lane] = mcmp[m];
+        }
     }
 }
 
-template <typename S, int NL>
-int launch_small_t(const Geometry& g, const EnsembleBuffers& b, const StepConsts& c, const twa_pump* pump, double dt,
-                   int64_t n_steps, int sib, int out_cur, hipStream_t st) {
-    constexpr int TPB = (64 / NL) * (SMALL_THREADS / 64);
-    const unsigned grid = (unsigned)((g.B + TPB - 1) / TPB);
-    hipLaunchKernelGGL((small_run_kernel<S, NL>), dim3(grid), dim3(SMALL_THREADS), 0, st, g.N, g.B, g.P, g.Bp, pump->W,
-                       pump->F, -0.5 * dt, -std::sqrt(dt), (S)c.c1, (S)c.c2, c.key0, c.key1, (uint32_t)c.point,
-                       n_steps, c.burnin, sib, static_cast<const S*>(b.s[0]), static_cast<S*>(b.s[out_cur]),
-                       static_cast<S*>(b.mom));
+template <typename S, int NB, int CB>
+int launch_small_t(const SmallArgs<S>& a, hipStream_t st) {
+    constexpr int T = 8 * CB;
+    hipLaunchKernelGGL((small_run_kernel<S, NB, CB>), dim3((unsigned)((a.B + T - 1) / T)),
+                       dim3(64 * (NB + PRODUCERS)), 0, st, a);
     TWA_HIP_CHECK(hipGetLastError());
     return TWA_OK;
 }
 
+template <typename S, int NB>
+int launch_small_nb(const SmallArgs<S>& a, int nb, int cb, hipStream_t st) {
+    if constexpr (NB > Small<S>::MAX_NB) {
+        set_error("fused small-N path: too many atoms");
+        return TWA_EINVAL;
+    } else {
+        if (nb > NB) return launch_small_nb<S, NB + 1>(a, nb, cb, st);
+        return cb == 1 ? launch_small_t<S, NB, 1>(a, st) : launch_small_t<S, NB, 2>(a, st);
+    }
+}
+
 template <typename S>
 int launch_small_s(const Geometry& g, const EnsembleBuffers& b, const StepConsts& c, const twa_pump* pump, double dt,
-                   int64_t n_steps, int sib, int out_cur, hipStream_t st) {
-    if (g.N <= 8) return launch_small_t<S, 8>(g, b, c, pump, dt, n_steps, sib, out_cur, st);
-    if (g.N <= 16) return launch_small_t<S, 16>(g, b, c, pump, dt, n_steps, sib, out_cur, st);
-    if (g.N <= 32) return launch_small_t<S, 32>(g, b, c, pump, dt, n_steps, sib, out_cur, st);
-    return launch_small_t<S, 64>(g, b, c, pump, dt, n_steps, sib, out_cur, st);
+                   int64_t n_steps, int out_cur, hipStream_t st) {
+    SmallArgs<S> a{};
+    a.n = (int)g.N;
+    a.B = g.B;
+    a.P = g.P;
+    a.Bp = g.Bp;
+    a.W = pump->W;
+    a.F = pump->F;
+    a.cw = -0.5 * dt;
+    a.cf = -std::sqrt(dt);
+    a.c1 = c.c1;
+    a.c2 = (S)c.c2;
+    a.k0 = c.key0;
+    a.k1 = c.key1;
+    a.point = (uint32_t)c.point;
+    a.n_steps = n_steps;
+    a.burnin = c.burnin;
+    a.sib = g.integrator == TWA_INT_SIB ? 1 : 0;
+    a.s_in = static_cast<const S*>(b.s[0]);
+    a.s_out = static_cast<S*>(b.s[out_cur]);
+    a.mom = static_cast<S*>(b.mom);
+    // 8 trajectories per workgroup up to one workgroup per compute unit (FP64 N = 50 x 512: 3.7 us per step
+    // against 6.1 with 16; FP32 N = 100 x 2000: 4.1 against 6.4), then 16 (FP32 N = 128 x 4096: 8.1 against 9.3)
+    const int cb = g.B <= 8 * 256 ? 1 : 2;
+    return launch_small_nb<S, 1>(a, (int)((g.N + 15) / 16), cb, st);
 }
 
 }  // namespace
 
 bool small_path_applies(int precision, int64_t N, int64_t n_lags) {
-    return N <= SMALL_NMAX && n_lags == 0 && (precision == TWA_PREC_FP64 || precision == TWA_PREC_FP32);
+    if (n_lags != 0) return false;
+    if (precision == TWA_PREC_FP64) return N <= 16 * Small<double>::MAX_NB;
+    return precision == TWA_PREC_FP32 && N <= 16 * Small<float>::MAX_NB;
 }
 
 int launch_small_run(const Geometry& g, const EnsembleBuffers& b, const StepConsts& c, const twa_pump* pump,
                      double dt, int64_t n_steps, int out_cur, hipStream_t st) {
-    if (g.N > SMALL_NMAX) {
-        set_error("fused small-N path: N > 64");
+    if (!small_path_applies(g.precision, g.N, 0)) {
+        set_error("fused small-N path: FP64 with N <= 64 or FP32 with N <= 128 only");
         return TWA_EINVAL;
     }
-    const int sib = g.integrator == TWA_INT_SIB ? 1 : 0;
-    if (g.precision == TWA_PREC_FP64) return launch_small_s<double>(g, b, c, pump, dt, n_steps, sib, out_cur, st);
-    if (g.precision == TWA_PREC_FP32) return launch_small_s<float>(g, b, c, pump, dt, n_steps, sib, out_cur, st);
-    set_error("fused small-N path: FP64 or FP32 only");
-    return TWA_EINVAL;
+    if (g.precision == TWA_PREC_FP64) return launch_small_s<double>(g, b, c, pump, dt, n_steps, out_cur, st);
+    return launch_small_s<float>(g, b, c, pump, dt, n_steps, out_cur, st);
 }
 
 }  // namespace twa
