@@ -373,7 +373,6 @@ cleanup:
     hipFree(init_dev);
     hipFree(export_dev);
     hipFree(toep_tw);
-    hipFree(toep_spec);
     free_buffers(b);
     if (own) hipStreamDestroy(own);
 #undef TWA_TRY

@@ -22,7 +22,6 @@
 // per-spin epilogues need no extra exchange.
 #include <algorithm>
 #include <cmath>
-#include <complex>
 #include <utility>
 #include <vector>
 
@@ -99,44 +98,80 @@ constexpr double reduce(double x) {
 constexpr double ksin(int m, int n) { return taylor_sin(reduce(2.0 * kPi * m / n)); }
 constexpr double kcos(int m, int n) { return taylor_sin(reduce(2.0 * kPi * m / n + 0.5 * kPi)); }
 
-// butterflies of twiddle index MM in the stage of half-size H:
-// (a, b) <- (a + w b, a - w b), w = exp(-+2 pi i MM / (2H))
-template <typename S, int RAD, int H, int MM, bool INV>
-__device__ __forceinline__ void butterflies(S* re, S* im) {
-    constexpr S wx = (S)kcos(MM, 2 * H);
-    constexpr S wy = (S)(INV ? ksin(MM, 2 * H) : -ksin(MM, 2 * H));
+// One radix-2 butterfly (a, b) <- (a + w b, a - w b) in six multiply-adds (the
+// difference as 2 a - sum).  KEEP_B = false leaves out the difference.
+template <typename S, bool KEEP_B>
+__device__ __forceinline__ void butterfly(S& ar, S& ai, S& br, S& bi, const S wx, const S wy) {
+    const S sr = ar + wx * br - wy * bi, si = ai + wx * bi + wy * br;
+    if constexpr (KEEP_B) {
+        br = S(2) * ar - sr;
+        bi = S(2) * ai - si;
+    }
+    ar = sr;
+    ai = si;
+}
+
+// The twiddles of a pass are folded into its butterflies: a RAD-point DFT of
+// x_r t^r by decimation in time has the stage of half-size H combine its two
+// halves with t^(RAD / 2H) W_{2H}^m, m = 0 .. H - 1, so no value is multiplied
+// by its own twiddle first.  tx, ty: t^(RAD / 2H) of the stage (null for
+// t = 1, whose factors are constants: 1 and -+i cost no multiplication).
+// ZERO_B: the second halves are zero (their butterflies are copies).
+template <typename S, int RAD, int H, int MM, bool INV, bool TW, bool ZERO_B, bool KEEP_B>
+__device__ __forceinline__ void butterflies(S* re, S* im, const S tx, const S ty) {
+    // the factor of index MM; MM and MM + H / 2 differ by -+i and share a product
+    constexpr int MB = (H > 1 && MM >= H / 2) ? MM - H / 2 : MM;
+    constexpr bool ROT = MB != MM;
+    constexpr S kx = (S)kcos(MB, 2 * H), ky = (S)(INV ? ksin(MB, 2 * H) : -ksin(MB, 2 * H));
+    S wx = kx, wy = ky;
+    if constexpr (TW) {
+        wx = MB ? tx * kx - ty * ky : tx;
+        wy = MB ? tx * ky + ty * kx : ty;
+    }
 #pragma unroll
     for (int i = 0; i < RAD; i += 2 * H) {
         const int a = i + MM, b = a + H;
-        S tr = re[b], ti = im[b];
-        if constexpr (MM != 0) {
-            tr = re[b] * wx - im[b] * wy;
-            ti = re[b] * wy + im[b] * wx;
+        if constexpr (ZERO_B) {
+            re[b] = re[a];
+            im[b] = im[a];
+        } else if constexpr (!TW && MB == 0) {
+            // w = 1 or -+i
+            const S tr = !ROT ? re[b] : INV ? -im[b] : im[b], ti = !ROT ? im[b] : INV ? re[b] : -re[b];
+            if constexpr (KEEP_B) {
+                re[b] = re[a] - tr;
+                im[b] = im[a] - ti;
+            }
+            re[a] = re[a] + tr;
+            im[a] = im[a] + ti;
+        } else if constexpr (!ROT) {
+            butterfly<S, KEEP_B>(re[a], im[a], re[b], im[b], wx, wy);
+        } else {
+            butterfly<S, KEEP_B>(re[a], im[a], re[b], im[b], INV ? -wy : wy, INV ? wx : -wx);
         }
-        re[b] = re[a] - tr;
-        im[b] = im[a] - ti;
-        re[a] = re[a] + tr;
-        im[a] = im[a] + ti;
     }
 }
 
-template <typename S, int RAD, int H, bool INV, int... MS>
-__device__ __forceinline__ void stage(S* re, S* im, std::integer_sequence<int, MS...>) {
-    (butterflies<S, RAD, H, MS, INV>(re, im), ...);
+template <typename S, int RAD, int H, bool INV, bool TW, bool ZERO_B, bool KEEP_B, int... MS>
+__device__ __forceinline__ void stage(S* re, S* im, const S tx, const S ty, std::integer_sequence<int, MS...>) {
+    (butterflies<S, RAD, H, MS, INV, TW, ZERO_B, KEEP_B>(re, im, tx, ty), ...);
 }
 
-template <typename S, int RAD, int H, bool INV>
-__device__ __forceinline__ void stages(S* re, S* im) {
+// the stages of half-size H and up; t[s]: t^(RAD / 2H) of the stage H = 2^s
+template <typename S, int RAD, int H, bool INV, bool TW, bool HALF_IN, bool HALF_OUT>
+__device__ __forceinline__ void stages(S* re, S* im, const S* tx, const S* ty) {
     if constexpr (H < RAD) {
-        stage<S, RAD, H, INV>(re, im, std::make_integer_sequence<int, H>{});
-        stages<S, RAD, 2 * H, INV>(re, im);
+        constexpr int s = ilog2(H);
+        stage<S, RAD, H, INV, TW, HALF_IN && H == 1, !(HALF_OUT && 2 * H == RAD)>(
+            re, im, TW ? tx[s] : S(0), TW ? ty[s] : S(0), std::make_integer_sequence<int, H>{});
+        stages<S, RAD, 2 * H, INV, TW, HALF_IN, HALF_OUT>(re, im, tx, ty);
     }
 }
 
-// in-register RAD-point DFT of re/im[0 .. RAD) in natural order (radix-2
-// decimation in time)
-template <typename S, int RAD, bool INV>
-__device__ __forceinline__ void dft(S* re, S* im) {
+// in-register RAD-point DFT of x_r t^r, r = 0 .. RAD - 1, in natural order
+// (radix-2 decimation in time).  HALF_IN: x_r = 0 for r >= RAD / 2; HALF_OUT:
+// only the first half of the result is formed.
+template <typename S, int RAD, bool INV, bool TW, bool HALF_IN, bool HALF_OUT>
+__device__ __forceinline__ void dft(S* re, S* im, const S* tx, const S* ty) {
     constexpr int LB = ilog2(RAD);
 #pragma unroll
     for (int i = 0; i < RAD; ++i) {
@@ -149,19 +184,21 @@ __device__ __forceinline__ void dft(S* re, S* im) {
             im[j] = b;
         }
     }
-    stages<S, RAD, 1, INV>(re, im);
+    stages<S, RAD, 1, INV, TW, HALF_IN, HALF_OUT>(re, im, tx, ty);
 }
 
 // one Stockham pass: positions j = t + g T (g < R / RAD) each take RAD values
-// at stride M / RAD (already in registers), twiddle, RAD-point DFT.  The
-// twiddle w_M^q is the product of two LDS table entries, w_M^(64 (q >> 6)) and
-// w_M^(q & 63).  The thread index is made opaque at the start of the pass (it
-// depends on the values just read), so the twiddle addresses are formed here
-// and not shared with, or hoisted from, the other passes and transforms.
-template <typename S, int M, int T, int R, int RAD, int NS, bool INV>
+// at stride M / RAD (already in registers), twiddle t = w_M^q, RAD-point DFT.
+// The powers t^(RAD / 2H) the stages need are products of two LDS table
+// entries, w_M^(64 (q >> 6)) and w_M^(q & 63).  The thread index is made
+// opaque at the start of the pass (it depends on the values just read), so the
+// twiddle addresses are formed here and not shared with, or hoisted from, the
+// other passes and transforms.
+template <typename S, int M, int T, int R, int RAD, int NS, bool INV, bool HALF_IN, bool HALF_OUT>
 __device__ __forceinline__ void pass(S (&re)[R], S (&im)[R], int t, const typename V2<S>::T* twh,
                                      const typename V2<S>::T* twl) {
-    constexpr int G = R / RAD;
+    constexpr int G = R / RAD, LB = ilog2(RAD);
+    static_assert(G == 1 || !(HALF_IN || HALF_OUT), "half transforms are the radix-R passes");
     if constexpr (NS > 1) {
         int tq = t;
         asm volatile("" : "+v"(tq) : "v"(re[0]), "v"(im[0]));
@@ -169,36 +206,22 @@ __device__ __forceinline__ void pass(S (&re)[R], S (&im)[R], int t, const typena
         for (int g = 0; g < G; ++g) {
             const int j = tq + g * T;
             const int qs = (j & (NS - 1)) * (M / (NS * RAD));
-            // w^r for r = 1 .. RAD-1: a table product at r = 1 and at every
-            // fourth r, the others by one more factor w (at most three
-            // roundings from a table value), a quarter of the LDS reads
-            S w1x = 0, w1y = 0, wx = 0, wy = 0;
+            S tx[LB], ty[LB];
 #pragma unroll
-            for (int r = 1; r < RAD; ++r) {
-                if (r == 1 || (r & 3) == 0) {
-                    const int q = r * qs;
-                    const typename V2<S>::T a = twh[q >> 6], b = twl[q & 63];
-                    wx = a.x * b.x - a.y * b.y;
-                    wy = a.x * b.y + a.y * b.x;
-                    if (r == 1) {
-                        w1x = wx;
-                        w1y = wy;
-                    }
-                } else {
-                    const S nx = wx * w1x - wy * w1y;
-                    wy = wx * w1y + wy * w1x;
-                    wx = nx;
-                }
-                const S vy = INV ? -wy : wy;
-                const S xr = re[g * RAD + r], xi = im[g * RAD + r];
-                re[g * RAD + r] = xr * wx - xi * vy;
-                im[g * RAD + r] = xr * vy + xi * wx;
-                if ((r & 3) == 3) SCHED_FENCE();
+            for (int s = 0; s < LB; ++s) {
+                const int q = (RAD >> (s + 1)) * qs;   // < M
+                const typename V2<S>::T a = twh[q >> 6], b = twl[q & 63];
+                tx[s] = a.x * b.x - a.y * b.y;
+                const S y = a.x * b.y + a.y * b.x;
+                ty[s] = INV ? -y : y;
             }
+            dft<S, RAD, INV, true, HALF_IN, HALF_OUT>(&re[g * RAD], &im[g * RAD], tx, ty);
+            SCHED_FENCE();
         }
-    }
+    } else {
 #pragma unroll
-    for (int g = 0; g < G; ++g) dft<S, RAD, INV>(&re[g * RAD], &im[g * RAD]);
+        for (int g = 0; g < G; ++g) dft<S, RAD, INV, false, HALF_IN, HALF_OUT>(&re[g * RAD], &im[g * RAD], nullptr, nullptr);
+    }
 }
 
 __device__ __forceinline__ int lpad(int i) { return i + (i >> 5); }
@@ -239,23 +262,26 @@ __device__ __forceinline__ void exchange(S (&re)[R], S (&im)[R], int t, S* lds) 
     exchange_half<S, M, T, R, RAD_A, NS_A, RAD_B>(im, t, lds);
 }
 
-template <typename S, int LOGM, int LOGR, bool INV, int P>
+// HALF: the input (INV = false) is zero, or the output (INV = true) not needed,
+// from element M / 2 on: the halves of the first and last radix-R pass
+template <typename S, int LOGM, int LOGR, bool INV, bool HALF, int P>
 __device__ __forceinline__ void passes(S (&re)[1 << LOGR], S (&im)[1 << LOGR], int t,
                                        const typename V2<S>::T* twh, const typename V2<S>::T* twl, S* lds) {
     typedef Plan<LOGM, LOGR> PL;
-    pass<S, PL::M, PL::T, PL::R, PL::rad(P), PL::ns(P), INV>(re, im, t, twh, twl);
+    pass<S, PL::M, PL::T, PL::R, PL::rad(P), PL::ns(P), INV, HALF && !INV && P == 0, HALF && INV && P + 1 == PL::NP>(
+        re, im, t, twh, twl);
     if constexpr (P + 1 < PL::NP) {
         exchange<S, PL::M, PL::T, PL::R, PL::rad(P), PL::ns(P), PL::rad(P + 1)>(re, im, t, lds);
-        passes<S, LOGM, LOGR, INV, P + 1>(re, im, t, twh, twl, lds);
+        passes<S, LOGM, LOGR, INV, HALF, P + 1>(re, im, t, twh, twl, lds);
     }
 }
 
 // unnormalised DFT (INV = false: exponent -, INV = true: exponent +) of the M
 // values held as element t + r T in slot r; the result is held the same way
-template <typename S, int LOGM, int LOGR, bool INV>
+template <typename S, int LOGM, int LOGR, bool INV, bool HALF>
 __device__ __forceinline__ void transform(S (&re)[1 << LOGR], S (&im)[1 << LOGR], int t,
                                           const typename V2<S>::T* twh, const typename V2<S>::T* twl, S* lds) {
-    passes<S, LOGM, LOGR, INV, 0>(re, im, t, twh, twl, lds);
+    passes<S, LOGM, LOGR, INV, HALF, 0>(re, im, t, twh, twl, lds);
 }
 
 // the thread index made opaque after a transform: addresses and counters
@@ -264,7 +290,7 @@ __device__ __forceinline__ void transform(S (&re)[1 << LOGR], S (&im)[1 << LOGR]
 template <typename S, int R>
 __device__ __forceinline__ int after(int t, const S (&re)[R], const S (&im)[R]) {
     int q = t;
-    asm volatile("" : "+v"(q) : "v"(re[0]), "v"(im[0]), "v"(re[R - 1]), "v"(im[R - 1]));
+    asm volatile("" : "+v"(q) : "v"(re[0]), "v"(im[0]), "v"(re[R / 2 - 1]), "v"(im[R / 2 - 1]));
     return q;
 }
 
@@ -347,13 +373,17 @@ __device__ __forceinline__ void kahan(S& sum, S& comp, S v) {
     sum = t;
 }
 
-template <typename S, int LOGM, int LOGR>
+// HALF: N <= M / 2, so slots r >= R / 2 of the spin vectors are padding: they
+// are zero in the forward transforms and not formed by the inverse ones (the
+// largest N of an embedding, M / 2 + 1, takes the general form).
+template <typename S, int LOGM, int LOGR, bool HALF>
 __global__ __launch_bounds__((1 << LOGM) >> LOGR) void toeplitz_run_kernel(
     int64_t N, int64_t P, int64_t Bp, const typename V2<S>::T* __restrict__ tw,
     const typename V2<S>::T* __restrict__ spec, S c1, S c2, uint32_t k0, uint32_t k1, uint32_t point, int64_t step0,
     int64_t n_steps, int64_t burnin, S* __restrict__ s, S* __restrict__ H, S* __restrict__ mom) {
     typedef Plan<LOGM, LOGR> PL;
     constexpr int M = PL::M, T = PL::T, R = PL::R;
+    constexpr int RS = HALF ? R / 2 : R;   // slots that hold spins
     __shared__ S lds[M + M / 32];
     __shared__ S red[(T / 64) * 3];
     __shared__ typename V2<S>::T twh[M / 64 > 0 ? M / 64 : 1], twl[64];
@@ -371,7 +401,7 @@ __global__ __launch_bounds__((1 << LOGM) >> LOGR) void toeplitz_run_kernel(
     {
         S acc[2] = {0, 0};
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
+        for (int r = 0; r < RS; ++r) {
             re[r] = bld(bx, t + r * T, S(0));
             im[r] = bld(by, t + r * T, S(0));
             acc[0] += re[r];
@@ -401,7 +431,7 @@ __global__ __launch_bounds__((1 << LOGM) >> LOGR) void toeplitz_run_kernel(
             box_muller(v.x, v.y, g0, g1);
         }
         // stage 1: -dt/2 W s - sqrt(dt) eta, through the embedding
-        transform<S, LOGM, LOGR, false>(re, im, tt, twh, twl, lds);
+        transform<S, LOGM, LOGR, false, HALF>(re, im, tt, twh, twl, lds);
         const int t1 = after(tt, re, im);
 #pragma unroll
         for (int r = 0; r < R / 2; ++r) {
@@ -417,11 +447,11 @@ __global__ __launch_bounds__((1 << LOGM) >> LOGR) void toeplitz_run_kernel(
             im[r + R / 2] = p1.x * im[r + R / 2] + p1.y * b1;
             SCHED_FENCE();
         }
-        transform<S, LOGM, LOGR, true>(re, im, tt, twh, twl, lds);
+        transform<S, LOGM, LOGR, true, HALF>(re, im, tt, twh, twl, lds);
         const int t2 = after(tt, re, im);
         S sd[2] = {0, 0};
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
+        for (int r = 0; r < RS; ++r) {
             // padding slots: z = 0 gives a zero increment, the field store is dropped
             const int n = t2 + r * T;
             const S z = bld(bz, n, S(0));
@@ -437,7 +467,7 @@ __global__ __launch_bounds__((1 << LOGM) >> LOGR) void toeplitz_run_kernel(
         }
         block_sum<S, T, 2>(sd, red);
         // stage 2: field at the predictor = H + (-dt/2 W Delta) + Gamma dt/2 sum(Delta)
-        transform<S, LOGM, LOGR, false>(re, im, tt, twh, twl, lds);
+        transform<S, LOGM, LOGR, false, HALF>(re, im, tt, twh, twl, lds);
         const int t3 = after(tt, re, im);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -446,11 +476,11 @@ __global__ __launch_bounds__((1 << LOGM) >> LOGR) void toeplitz_run_kernel(
             im[r] *= a;
             SCHED_FENCE();
         }
-        transform<S, LOGM, LOGR, true>(re, im, tt, twh, twl, lds);
+        transform<S, LOGM, LOGR, true, HALF>(re, im, tt, twh, twl, lds);
         const int t4 = after(tt, re, im);
         S acc[3] = {0, 0, 0};
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
+        for (int r = 0; r < RS; ++r) {
             // padding slots load zeros and produce zeros (the next transform's padding)
             const int n = t4 + r * T;
             const S x = bld(bx, n, S(0)), y = bld(by, n, S(0)), z = bld(bz, n, S(0));
@@ -485,37 +515,76 @@ __global__ __launch_bounds__((1 << LOGM) >> LOGR) void toeplitz_run_kernel(
         for (int m = 0; m < 10; ++m) mom[m * Bp + k] = kmom[m];
 }
 
-// host FFT (FP64, radix 2) of the circulant's first column: its eigenvalues
-void host_dft(std::vector<std::complex<double>>& a) {
-    const size_t n = a.size();
-    for (size_t i = 1, j = 0; i < n; ++i) {
-        size_t bit = n >> 1;
-        for (; j & bit; bit >>= 1) j ^= bit;
-        j ^= bit;
-        if (i < j) std::swap(a[i], a[j]);
-    }
-    for (size_t len = 2; len <= n; len <<= 1) {
-        const double ang = -2.0 * M_PI / (double)len;
-        for (size_t i = 0; i < n; i += len)
-            for (size_t m = 0; m < len / 2; ++m) {
-                const std::complex<double> w(std::cos(ang * (double)m), std::sin(ang * (double)m));
-                const std::complex<double> u = a[i + m], v = a[i + m + len / 2] * w;
-                a[i + m] = u + v;
-                a[i + m + len / 2] = u - v;
-            }
-    }
+// ---- tables of one run, formed on the device in FP64
+// first column of the circulant
+__global__ void column_kernel(int64_t M, double w, double alpha, double2* c) {
+    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j < M) c[j] = make_double2(w / pow(1.0 + (double)(j < M - j ? j : M - j), alpha), 0.0);
 }
 
-template <typename S, int LOGM, int LOGR>
-int launch_t(const Geometry& g, const EnsembleBuffers& b, const StepConsts& c, const void* tw, const void* spec,
+// one radix-2 Stockham pass of a DFT of M points (sub-transforms of NS points)
+__global__ void dft_pass_kernel(int64_t M, int64_t NS, const double2* in, double2* out) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= M / 2) return;
+    const int64_t k = t & (NS - 1), d = (t - k) * 2 + k;
+    double sn, cs;
+    sincospi((double)k / (double)NS, &sn, &cs);
+    const double2 u = in[t], v = in[t + M / 2];
+    const double vx = v.x * cs + v.y * sn, vy = v.y * cs - v.x * sn;
+    out[d] = make_double2(u.x + vx, u.y + vy);
+    out[d + NS] = make_double2(u.x - vx, u.y - vy);
+}
+
+// twiddles w_M^q and spectral coefficients (lam (-dt / 2M), sqrt(lam+)
+// (-sqrt(dt / M))) in the state precision.  The column is positive, so its
+// largest eigenvalue is the one at k = 0.
+template <typename S>
+__global__ void tables_kernel(int64_t M, const double2* lam, double dt, typename V2<S>::T* tw,
+                              typename V2<S>::T* spec) {
+    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= M) return;
+    double sn, cs;
+    sincospi(2.0 * (double)q / (double)M, &sn, &cs);
+    tw[q].x = (S)cs;
+    tw[q].y = (S)(-sn);
+    const double l = lam[q].x, tol = 8.0 * (double)M * 2.220446049250313e-16 * lam[0].x;
+    spec[q].x = (S)(l * (-dt / (2.0 * (double)M)));
+    spec[q].y = (S)((l > tol ? sqrt(l) : 0.0) * (-sqrt(dt / (double)M)));
+}
+
+template <typename S>
+int build_tables(int64_t M, double w, double alpha, double dt, void* tw, void* spec, double2* work, hipStream_t st) {
+    typedef typename V2<S>::T S2;
+    const unsigned nb = (unsigned)((M + 255) / 256);
+    hipLaunchKernelGGL(column_kernel, dim3(nb), dim3(256), 0, st, M, w, alpha, work);
+    double2 *a = work, *b = work + M;
+    for (int64_t ns = 1; ns < M; ns *= 2) {
+        hipLaunchKernelGGL(dft_pass_kernel, dim3((nb + 1) / 2), dim3(256), 0, st, M, ns, (const double2*)a, b);
+        std::swap(a, b);
+    }
+    hipLaunchKernelGGL(tables_kernel<S>, dim3(nb), dim3(256), 0, st, M, (const double2*)a, dt, static_cast<S2*>(tw),
+                       static_cast<S2*>(spec));
+    TWA_HIP_CHECK(hipGetLastError());
+    return TWA_OK;
+}
+
+template <typename S, int LOGM, int LOGR, bool HALF>
+int launch_h(const Geometry& g, const EnsembleBuffers& b, const StepConsts& c, const void* tw, const void* spec,
              int64_t step0, int64_t n, int cur, hipStream_t st) {
     typedef typename V2<S>::T S2;
-    hipLaunchKernelGGL((toeplitz_run_kernel<S, LOGM, LOGR>), dim3((unsigned)g.B), dim3((1 << LOGM) >> LOGR), 0, st,
+    hipLaunchKernelGGL((toeplitz_run_kernel<S, LOGM, LOGR, HALF>), dim3((unsigned)g.B), dim3((1 << LOGM) >> LOGR), 0, st,
                        g.N, g.P, g.Bp, static_cast<const S2*>(tw), static_cast<const S2*>(spec), (S)c.c1, (S)c.c2,
                        c.key0, c.key1, (uint32_t)c.point, step0, n, c.burnin, static_cast<S*>(b.s[cur]),
                        static_cast<S*>(b.Y), static_cast<S*>(b.mom));
     TWA_HIP_CHECK(hipGetLastError());
     return TWA_OK;
+}
+
+template <typename S, int LOGM, int LOGR>
+int launch_t(const Geometry& g, const EnsembleBuffers& b, const StepConsts& c, const void* tw, const void* spec,
+             int64_t step0, int64_t n, int cur, hipStream_t st) {
+    return 2 * g.N <= (int64_t(1) << LOGM) ? launch_h<S, LOGM, LOGR, true>(g, b, c, tw, spec, step0, n, cur, st)
+                                           : launch_h<S, LOGM, LOGR, false>(g, b, c, tw, spec, step0, n, cur, st);
 }
 
 // (LOGM, LOGR): FP32 keeps R = 32 values per thread (T = M / 32 >= 64),
@@ -553,15 +622,18 @@ int launch_s(int logm, const Geometry& g, const EnsembleBuffers& b, const StepCo
 
 }  // namespace
 
+// largest eigenvalue of the embedding: its column is positive, so the one at
+// k = 0, the sum of the column (Kahan)
 double toeplitz_spectrum_max(int64_t N, double w, double alpha) {
     const int64_t M = int64_t(1) << toeplitz_embedding_log2(N);
-    std::vector<std::complex<double>> a((size_t)M);
-    for (int64_t j = 0; j < M; ++j)
-        a[(size_t)j] = std::complex<double>(w / std::pow(1.0 + (double)std::min(j, M - j), alpha), 0.0);
-    host_dft(a);
-    double m = 0;
-    for (const auto& v : a) m = std::max(m, v.real());
-    return m;
+    double sum = 0, comp = 0;
+    for (int64_t j = 0; j < M; ++j) {
+        const double y = w / std::pow(1.0 + (double)std::min(j, M - j), alpha) - comp;
+        const double t = sum + y;
+        comp = (t - sum) - y;
+        sum = t;
+    }
+    return sum;
 }
 
 int toeplitz_embedding_log2(int64_t N) {
@@ -572,52 +644,21 @@ int toeplitz_embedding_log2(int64_t N) {
 
 int64_t toeplitz_max_n(int precision) { return precision == TWA_PREC_FP64 ? 8193 : 16385; }
 
-// tables of one run: twiddles w_M^q and the spectral coefficients
-// (lam (-dt / 2M), sqrt(lam+) (-sqrt(dt / M))) in the state precision
+// tables of one run in one allocation: *tw holds twiddles, coefficients and
+// the transform's FP64 work space.  On the host the transform took 7 ms at
+// M = 32768, a fifth of a run of 64 steps; here 0.1 ms.
 int toeplitz_tables(const Geometry& g, double w, double alpha, double dt, void** tw, void** spec, hipStream_t st) {
-    const int logm = toeplitz_embedding_log2(g.N);
-    const int64_t M = int64_t(1) << logm;
-    std::vector<std::complex<double>> a((size_t)M);
-    for (int64_t j = 0; j < M; ++j) {
-        const double d = (double)std::min(j, M - j);
-        a[(size_t)j] = std::complex<double>(w / std::pow(1.0 + d, alpha), 0.0);
-    }
-    host_dft(a);
-    double lmax = 0;
-    for (int64_t j = 0; j < M; ++j) lmax = std::max(lmax, a[(size_t)j].real());
-    const double tol = 8.0 * (double)M * 2.220446049250313e-16 * lmax;
-    const bool f64 = g.precision == TWA_PREC_FP64;
-    const size_t es = f64 ? 16 : 8;
-    std::vector<double> twd((size_t)2 * M), spd((size_t)2 * M);
-    for (int64_t q = 0; q < M; ++q) {
-        const double ang = 2.0 * M_PI * (double)q / (double)M;
-        twd[(size_t)2 * q] = std::cos(ang);
-        twd[(size_t)2 * q + 1] = -std::sin(ang);
-        const double lam = a[(size_t)q].real();
-        spd[(size_t)2 * q] = lam * (-dt / (2.0 * (double)M));
-        spd[(size_t)2 * q + 1] = (lam > tol ? std::sqrt(lam) : 0.0) * (-std::sqrt(dt / (double)M));
-    }
-    if (hipMalloc(tw, (size_t)M * es) != hipSuccess || hipMalloc(spec, (size_t)M * es) != hipSuccess) {
+    const int64_t M = int64_t(1) << toeplitz_embedding_log2(g.N);
+    const size_t es = g.precision == TWA_PREC_FP64 ? 16 : 8;
+    if (hipMalloc(tw, (size_t)M * (2 * es + 2 * sizeof(double2))) != hipSuccess) {
+        *tw = nullptr;
         set_error("Toeplitz path: device allocation failed");
         return TWA_ENOMEM;
     }
-    if (f64) {
-        if (hipMemcpyAsync(*tw, twd.data(), (size_t)M * es, hipMemcpyHostToDevice, st) != hipSuccess ||
-            hipMemcpyAsync(*spec, spd.data(), (size_t)M * es, hipMemcpyHostToDevice, st) != hipSuccess ||
-            hipStreamSynchronize(st) != hipSuccess) {
-            set_error("Toeplitz path: hipMemcpy failed");
-            return TWA_EHIP;
-        }
-    } else {
-        std::vector<float> t32(twd.begin(), twd.end()), s32(spd.begin(), spd.end());
-        if (hipMemcpyAsync(*tw, t32.data(), (size_t)M * es, hipMemcpyHostToDevice, st) != hipSuccess ||
-            hipMemcpyAsync(*spec, s32.data(), (size_t)M * es, hipMemcpyHostToDevice, st) != hipSuccess ||
-            hipStreamSynchronize(st) != hipSuccess) {
-            set_error("Toeplitz path: hipMemcpy failed");
-            return TWA_EHIP;
-        }
-    }
-    return TWA_OK;
+    *spec = static_cast<char*>(*tw) + (size_t)M * es;
+    double2* work = reinterpret_cast<double2*>(static_cast<char*>(*tw) + 2 * (size_t)M * es);
+    return es == 16 ? build_tables<double>(M, w, alpha, dt, *tw, *spec, work, st)
+                    : build_tables<float>(M, w, alpha, dt, *tw, *spec, work, st);
 }
 
 int launch_toeplitz_run(const Geometry& g, const EnsembleBuffers& b, const StepConsts& c, const void* tw,
