@@ -262,25 +262,7 @@ struct SegStore {
     void* nu2p = nullptr;   // [2][3][nmt][Bp]
     void* nu1p = nullptr;
     double* gacc = nullptr; // [2][2][nmt][Bp]
-    void release() {
-        void* ptrs[] = {s,    d,  y1,  y2, q,   ya1, ya2,  partS, partP, g,   ckpt,
-                        ckpt_part, Aa, lam, M1, Rb, nu2, nu1, nu2p, nu1p, gacc};
-        for (void* p : ptrs) hipFree(p);
-    }
 };
-
-int dalloc0(void** p, size_t bytes, hipStream_t st) {
-    if (hipMalloc(p, bytes ? bytes : 16) != hipSuccess) {
-        *p = nullptr;
-        set_error("twa_adjoint: device allocation of " + std::to_string(bytes) + " bytes failed");
-        return TWA_ENOMEM;
-    }
-    if (hipMemsetAsync(*p, 0, bytes ? bytes : 16, st) != hipSuccess) {
-        set_error("twa_adjoint: hipMemsetAsync failed");
-        return TWA_EHIP;
-    }
-    return TWA_OK;
-}
 
 template <int PREC>
 int adjoint_impl(const twa_params* p, int64_t n_traj, double dt, int64_t n_steps, uint64_t seed, int K,
@@ -315,6 +297,7 @@ int adjoint_impl(const twa_params* p, int64_t n_traj, double dt, int64_t n_steps
     }
     EnsembleBuffers b;
     SegStore m;
+    Arena ar;
     double *Wa = nullptr, *Fa = nullptr;
     int rc = TWA_OK;
     int cur = 0;
@@ -360,43 +343,43 @@ int adjoint_impl(const twa_params* p, int64_t n_traj, double dt, int64_t n_steps
         const double need = (double)plane * (3.0 * (K + 1) + 13.0 * K + 3.0 * nseg + 18.0) +
                             (double)partsz * (2.0 * K + 5 + nseg) + (double)g.C2 * KP * ge * 7.0 +
                             (double)g.P * 2 * KP * ge * 2.0;
-        if (need > 0.9 * (double)freeb) {
+        if (need > 0.9 * (double)(freeb + kept_block_bytes())) {
             set_error("twa_adjoint: the checkpoint segment needs " + std::to_string(need / 1e9) +
                       " GB of device memory; reduce ckpt_every");
             rc = TWA_ENOMEM;
             goto cleanup;
         }
     }
-    TWA_TRY(alloc_buffers(g, false, 0, J, b, st));
-    TWA_TRY(dalloc0(&m.s, plane * 3 * (K + 1), st));
-    TWA_TRY(dalloc0(&m.d, plane * 3 * K, st));
-    TWA_TRY(dalloc0(&m.y1, plane * 2 * K, st));
-    TWA_TRY(dalloc0(&m.y2, plane * 2 * K, st));
-    TWA_TRY(dalloc0(&m.q, plane * 2 * K, st));
-    TWA_TRY(dalloc0(&m.ya1, plane * 2 * K, st));
-    TWA_TRY(dalloc0(&m.ya2, plane * 2 * K, st));
-    TWA_TRY(dalloc0(&m.partS, partsz * (K + 1), st));
-    TWA_TRY(dalloc0(&m.partP, partsz * K, st));
-    TWA_TRY(dalloc0(&m.g, (size_t)2 * g.Bp * se * K, st));
-    TWA_TRY(dalloc0(&m.ckpt, plane * 3 * nseg, st));
-    TWA_TRY(dalloc0(&m.ckpt_part, partsz * nseg, st));
-    TWA_TRY(dalloc0(&m.Aa, (size_t)g.P * 2 * KP * ge, st));
-    TWA_TRY(dalloc0(&m.lam, plane * 6, st));
-    TWA_TRY(dalloc0(&m.M1, plane * 6, st));
-    TWA_TRY(dalloc0(&m.Rb, plane * 6, st));
-    TWA_TRY(dalloc0(&m.nu2, (size_t)2 * g.C2 * KP * ge, st));
-    TWA_TRY(dalloc0(&m.nu1, (size_t)2 * g.C2 * KP * ge, st));
-    TWA_TRY(dalloc0(&m.nu2p, partsz * 2, st));
-    TWA_TRY(dalloc0(&m.nu1p, partsz * 2, st));
-    TWA_TRY(dalloc0((void**)&m.gacc, (size_t)4 * g.nmt * g.Bp * sizeof(double), st));
-    TWA_HTRY(hipMalloc(&Wa, (size_t)N * N * sizeof(double)));
-    TWA_HTRY(hipMalloc(&Fa, (size_t)N * N * sizeof(double)));
+    add_buffers(g, false, 0, J, true, b, ar);
+    ar.add(m.s, plane * 3 * (K + 1), false);
+    ar.add(m.d, plane * 3 * K, false);
+    ar.add(m.y1, plane * 2 * K, false);
+    ar.add(m.y2, plane * 2 * K, false);
+    ar.add(m.q, plane * 2 * K, false);
+    ar.add(m.ya1, plane * 2 * K, false);
+    ar.add(m.ya2, plane * 2 * K, false);
+    ar.add(m.partS, partsz * (K + 1), false);
+    ar.add(m.partP, partsz * K, false);
+    ar.add(m.g, (size_t)2 * g.Bp * se * K, true);   // normals of padding trajectories stay zero
+    ar.add(m.ckpt, plane * 3 * nseg, false);
+    ar.add(m.ckpt_part, partsz * nseg, false);
+    ar.add(m.Aa, (size_t)g.P * 2 * KP * ge, false);
+    ar.add(m.lam, plane * 6, false);
+    ar.add(m.M1, plane * 6, false);
+    ar.add(m.Rb, plane * 6, false);
+    ar.add(m.nu2, (size_t)2 * g.C2 * KP * ge, false);
+    ar.add(m.nu1, (size_t)2 * g.C2 * KP * ge, false);
+    ar.add(m.nu2p, partsz * 2, false);
+    ar.add(m.nu1p, partsz * 2, false);
+    ar.add(m.gacc, (size_t)4 * g.nmt * g.Bp * sizeof(double), true);
+    ar.add(Wa, (size_t)N * N * sizeof(double), false);
+    ar.add(Fa, (size_t)N * N * sizeof(double), false);
+    TWA_TRY(ar.commit(true, st));
     TWA_TRY(dfactor_dalpha(pump, Wa, Fa, st));
     TWA_TRY(launch_build_A(g, pump->W, pump->F, dt, b.A, st));
     TWA_TRY(launch_build_A(g, Wa, Fa, dt, m.Aa, st));
     TWA_TRY(launch_init_state(g, b, c, nullptr, st));
     TWA_TRY(launch_reduce_state(g, b.s[0], b.part[0], st));
-    TWA_HTRY(hipMemsetAsync(b.step, 0, sizeof(int64_t), st));
     TWA_HTRY(hipEventCreate(&e0));
     TWA_HTRY(hipEventCreate(&e1));
     TWA_HTRY(hipEventCreate(&e2));
@@ -574,10 +557,7 @@ cleanup:
     if (e0) hipEventDestroy(e0);
     if (e1) hipEventDestroy(e1);
     if (e2) hipEventDestroy(e2);
-    hipFree(Wa);
-    hipFree(Fa);
-    m.release();
-    free_buffers(b);
+    ar.release();
     if (own) hipStreamDestroy(own);
 #undef TWA_TRY
 #undef TWA_HTRY

@@ -132,6 +132,7 @@ __global__ void init_kernel(int64_t N, int64_t B, int64_t P, int64_t Bp, double 
     s[SP + t] = y;
     s[2 * SP + t] = z;
     norm0[t] = x * x + y * y + z * z;
+    if (!Xop) return;
     const int64_t C2 = 2 * Bp;
     put_x<PREC>(Xop, opcol(k, 0), i, C2, kt, x);
     put_x<PREC>(Xop, opcol(k, 1), i, C2, kt, y);

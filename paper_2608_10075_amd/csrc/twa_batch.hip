@@ -192,8 +192,8 @@ struct Bucket {
     hipStream_t stream = nullptr;    // the branch this bucket runs on (not owned)
     void release() {
         for (auto& b : bs) {
-            b.step = nullptr;   // shared counter, freed once below
-            free_buffers(b);
+            hipFree(b.block);
+            b = EnsembleBuffers();
         }
         bs.clear();
         hipFree(d_pd);
@@ -236,7 +236,7 @@ int build_bucket(const BatchSpec& sp, const std::vector<int>& idx, int cfg, Buck
     bk.cs.resize((size_t)np);
     bk.J = (int)std::min<int64_t>(32, o->n_traj);
     const bool tangents = sp.L > 0;
-    if (hipMalloc(&bk.step, sizeof(int64_t)) != hipSuccess) {
+    if (device_malloc(&bk.step, sizeof(int64_t)) != hipSuccess) {
         set_error("twa_run_batch: allocation failed");
         return TWA_ENOMEM;
     }
@@ -249,8 +249,10 @@ int build_bucket(const BatchSpec& sp, const std::vector<int>& idx, int cfg, Buck
         g = make_geometry(o->precision, cfg, pt.N, o->n_traj);
         g.integrator = o->integrator;
         EnsembleBuffers& b = bk.bs[(size_t)q];
-        if ((rc = alloc_buffers(g, tangents, sp.L, bk.J, b, st))) return rc;
-        hipFree(b.step);
+        Arena ar;
+        add_buffers(g, tangents, sp.L, bk.J, true, b, ar);
+        if ((rc = ar.commit(false, st))) return rc;
+        b.block = ar.detach();
         b.step = bk.step;   // one step counter for the bucket
         StepConsts& c = bk.cs[(size_t)q];
         c.c1 = 0.5 * o->gamma * pt.dt;

@@ -86,7 +86,54 @@ struct Geometry {
     int64_t kt;          // K elements per LDS stage
 };
 
+// Device buffers of one call, carved from one allocation: the pieces that
+// have to start at zero lie first and are cleared by one memset.  One
+// hipMalloc, memset and hipFree instead of twenty each (a call of 64 steps at
+// N = 10 took 480 us, most of it these).
+class Arena {
+  public:
+    Arena() = default;
+    Arena(const Arena&) = delete;
+    Arena& operator=(const Arena&) = delete;
+    ~Arena() { release(); }
+    template <typename T>
+    void add(T*& p, size_t bytes, bool zero) {
+        items_.push_back({reinterpret_cast<void**>(&p), bytes, zero});
+    }
+    // allocates, sets the pointers and clears on st.  keep: the block may be
+    // the one kept from an earlier call and is kept after this one (only for
+    // calls that wait for their stream before they release).
+    int commit(bool keep, hipStream_t st);
+    void release();
+    // the block without its owner: freed by free_buffers
+    void* detach();
+
+  private:
+    struct Item {
+        void** p;
+        size_t bytes;
+        bool zero;
+    };
+    std::vector<Item> items_;
+    void* block_ = nullptr;
+    size_t bytes_ = 0;
+    bool keep_ = false;
+};
+// hipMalloc that gives back the kept block and tries again if memory is short
+hipError_t device_malloc(void** p, size_t bytes);
+template <typename T>
+hipError_t device_malloc(T** p, size_t bytes) {
+    return device_malloc(reinterpret_cast<void**>(p), bytes);
+}
+// The kept block lives as long as any pump handle does, holds at most a 64th
+// of the device's memory and is only touched under the API lock.
+void kept_block_free();
+size_t kept_block_bytes();
+void pump_born();
+void pump_gone();
+
 struct EnsembleBuffers {
+    void* block = nullptr;      // the allocation of a batch point's buffers (single runs: the call's Arena)
     void* A = nullptr;          // GT [P][2P]  = [-dt/2 W | -sqrt(dt) F]
                                 //    coherent exchange: [P][3P] = [-dt/2 W | -sqrt(dt) F | dt Omega]
     void* A2 = nullptr;         // GT [P][2P]  coherent exchange only: [-dt/2 W | dt Omega] (corrector)
@@ -208,6 +255,7 @@ void grouped_free(GroupedPlan& pl);
 int launch_build_A(const Geometry& g, const double* W, const double* F, double dt, void* A, hipStream_t st);
 int launch_build_A_coh(const Geometry& g, const double* W, const double* F, const double* Om, double dt, void* A,
                        void* A2, hipStream_t st);
+// (Xop null: a path that contracts nothing)
 int launch_init_state(const Geometry& g, const EnsembleBuffers& b, const StepConsts& c,
                       const double* init_dev, hipStream_t st);
 int launch_reduce_state(const Geometry& g, const void* s, void* part, hipStream_t st);
@@ -233,7 +281,6 @@ int launch_small_run(const Geometry& g, const EnsembleBuffers& b, const StepCons
 // estimator of correlated emission; the geometry pads trajectories to a
 // multiple of the column tile
 int decay_geometry_ok(const Geometry& g);
-int alloc_decay_buffers(const Geometry& g, EnsembleBuffers& b, hipStream_t st);
 int launch_decay_ops(const Geometry& g, const double* G, const EnsembleBuffers& b, hipStream_t st);
 int launch_decay_observe(const Geometry& g, const EnsembleBuffers& b, int cur, hipStream_t st);
 
@@ -242,7 +289,8 @@ int launch_decay_observe(const Geometry& g, const EnsembleBuffers& b, int cur, h
 int toeplitz_embedding_log2(int64_t N);
 double toeplitz_spectrum_max(int64_t N, double w, double alpha);
 int64_t toeplitz_max_n(int precision);
-int toeplitz_tables(const Geometry& g, double w, double alpha, double dt, void** tw, void** spec, hipStream_t st);
+size_t toeplitz_table_bytes(const Geometry& g);
+int toeplitz_tables(const Geometry& g, double w, double alpha, double dt, void* tw, void** spec, hipStream_t st);
 int launch_toeplitz_run(const Geometry& g, const EnsembleBuffers& b, const StepConsts& c, const void* tw,
                         const void* spec, int64_t n_steps, int cur, hipStream_t st);
 
@@ -286,4 +334,7 @@ struct twa_pump {
                              // W holds the drift matrix W - G and F, V, lam belong to W + G
     double* Om = nullptr;    // device FP64 [N][N] coherent exchange Omega (model handles, optional)
     int device = 0;
+    twa_pump() { twa::pump_born(); }
+    twa_pump(const twa_pump&) = delete;
+    ~twa_pump() { twa::pump_gone(); }
 };

@@ -235,9 +235,9 @@ int run_noalloc(const twa_params* p, int64_t n_traj, double dt, int64_t n_steps,
                            static_cast<uint4*>(base), n16);
         TWA_HIP_CHECK(hipGetLastError());
     }
-    if ((rc = launch_build_A(g, pump->W, pump->F, dt, b.A, st))) return rc;
+    if (!fused && (rc = launch_build_A(g, pump->W, pump->F, dt, b.A, st))) return rc;
     if ((rc = launch_init_state(g, b, c, nullptr, st))) return rc;
-    if ((rc = launch_reduce_state(g, b.s[0], b.part[0], st))) return rc;
+    if (!fused && (rc = launch_reduce_state(g, b.s[0], b.part[0], st))) return rc;
     int cur = 0;
     if (fused) {
         cur = (int)(n_steps & 1);

@@ -76,10 +76,10 @@ static int factorise(twa_pump* p, hipStream_t st) {
         rc = code;
     };
     std::vector<double> lam((size_t)N), rr((size_t)N);
-    if (hipMalloc(&p->V, bytes) != hipSuccess || hipMalloc(&D, N * sizeof(double)) != hipSuccess ||
-        hipMalloc(&E, N * sizeof(double)) != hipSuccess || hipMalloc(&r, N * sizeof(double)) != hipSuccess ||
-        hipMalloc(&Vs, bytes) != hipSuccess || hipMalloc(&info, sizeof(rocblas_int)) != hipSuccess ||
-        hipMalloc(&p->F, bytes) != hipSuccess) {
+    if (device_malloc(&p->V, bytes) != hipSuccess || device_malloc(&D, N * sizeof(double)) != hipSuccess ||
+        device_malloc(&E, N * sizeof(double)) != hipSuccess || device_malloc(&r, N * sizeof(double)) != hipSuccess ||
+        device_malloc(&Vs, bytes) != hipSuccess || device_malloc(&info, sizeof(rocblas_int)) != hipSuccess ||
+        device_malloc(&p->F, bytes) != hipSuccess) {
         fail(TWA_ENOMEM, "device allocation for the pump factorisation failed");
         goto done;
     }
@@ -207,8 +207,8 @@ int pump_scaled(const twa_pump* b, double w, twa_pump** out) {
     p->lam_max = f * b->lam_max;
     p->device = b->device;
     const size_t bytes = (size_t)n2 * sizeof(double);
-    if (hipMalloc(&p->W, bytes) != hipSuccess || hipMalloc(&p->F, bytes) != hipSuccess ||
-        hipMalloc(&p->V, bytes) != hipSuccess) {
+    if (device_malloc(&p->W, bytes) != hipSuccess || device_malloc(&p->F, bytes) != hipSuccess ||
+        device_malloc(&p->V, bytes) != hipSuccess) {
         pump_release(p);
         set_error("pump_scaled: device allocation failed");
         return TWA_ENOMEM;
@@ -257,7 +257,7 @@ TWA_API int twa_build_pump(int64_t N, double w, double alpha, twa_pump** out) {
     p->w = w;
     p->alpha = alpha;
     hipGetDevice(&p->device);
-    if (hipMalloc(&p->W, (size_t)N * N * sizeof(double)) != hipSuccess) {
+    if (device_malloc(&p->W, (size_t)N * N * sizeof(double)) != hipSuccess) {
         delete p;
         set_error("twa_build_pump: device allocation failed");
         return TWA_ENOMEM;
@@ -305,7 +305,7 @@ TWA_API int twa_build_pump_dense(int64_t N, const double* W_host, twa_pump** out
     p->w = NAN;
     p->alpha = NAN;
     hipGetDevice(&p->device);
-    if (hipMalloc(&p->W, (size_t)N * N * sizeof(double)) != hipSuccess) {
+    if (device_malloc(&p->W, (size_t)N * N * sizeof(double)) != hipSuccess) {
         delete p;
         set_error("twa_build_pump_dense: device allocation failed");
         return TWA_ENOMEM;
@@ -361,7 +361,7 @@ TWA_API int twa_build_model_dense(int64_t N, const double* W_host, const double*
         twa_pump* q = new twa_pump();
         q->N = N;
         q->w = q->alpha = NAN;
-        if (hipMalloc(&q->W, bytes) != hipSuccess) {
+        if (device_malloc(&q->W, bytes) != hipSuccess) {
             delete q;
             set_error("twa_build_model_dense: device allocation failed");
             return TWA_ENOMEM;
@@ -383,8 +383,8 @@ TWA_API int twa_build_model_dense(int64_t N, const double* W_host, const double*
     p->alpha = NAN;
     hipGetDevice(&p->device);
     double* Wd = nullptr;
-    if (hipMalloc(&p->W, bytes) != hipSuccess || hipMalloc(&p->G, bytes) != hipSuccess ||
-        hipMalloc(&Wd, bytes) != hipSuccess) {
+    if (device_malloc(&p->W, bytes) != hipSuccess || device_malloc(&p->G, bytes) != hipSuccess ||
+        device_malloc(&Wd, bytes) != hipSuccess) {
         hipFree(Wd);
         pump_release(p);
         set_error("twa_build_model_dense: device allocation failed");
@@ -413,7 +413,7 @@ TWA_API int twa_build_model_dense(int64_t N, const double* W_host, const double*
     hipStreamSynchronize(bs.s);
     hipFree(Wd);
     if (rc == TWA_OK && Om_host) {
-        if (hipMalloc(&p->Om, bytes) != hipSuccess) {
+        if (device_malloc(&p->Om, bytes) != hipSuccess) {
             set_error("twa_build_model_dense: device allocation failed");
             rc = TWA_ENOMEM;
         } else if (hipMemcpyAsync(p->Om, Om_host, bytes, hipMemcpyHostToDevice, bs.s) != hipSuccess ||

@@ -55,8 +55,10 @@ struct StepTimer {
 inline double effective_norm_tol(double t) { return t == 0 ? 1e-2 : t; }
 int run_status(const char* who, bool nan, double max_norm_dev, double norm_tol);
 
-void free_buffers(EnsembleBuffers& b);
-int alloc_buffers(const Geometry& g, bool tangents, int64_t L, int J, EnsembleBuffers& b, hipStream_t st);
+// adds an ensemble's buffers to an arena; contraction = false leaves out the
+// operands and what only the stage kernels read
+void add_buffers(const Geometry& g, bool tangents, int64_t L, int J, bool contraction, EnsembleBuffers& b, Arena& ar);
+void add_decay_buffers(const Geometry& g, EnsembleBuffers& b, Arena& ar);
 Geometry make_geometry(int precision, int cfg, int64_t N, int64_t B);
 void finalize_moments(const std::vector<double>& traj, int64_t B, twa_observables* o);
 // the same from the jackknife block sums bsum [J][5] of the per-trajectory

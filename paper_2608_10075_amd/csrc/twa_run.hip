@@ -313,86 +313,152 @@ void finalize_lags(const std::vector<double>& hlag, int64_t L, int J, int64_t B,
 }
 
 // ---------------------------------------------------------------------------
-void free_buffers(EnsembleBuffers& b) {
-    void* ptrs[] = {b.A,      b.Xop,    b.Dop,  b.s[0], b.s[1],    b.dlt,     b.Y,      b.part[0],
-                    b.part[1], b.g,     b.norm0, b.mom, b.tXop,    b.tDop,    b.ts[0],  b.ts[1],
-                    b.tdlt,   b.tY,     b.tpart[0], b.tpart[1], b.sm0, b.lag, b.step, b.diag, b.Sn,
-                    b.AG,     b.AGG,    b.Zop,  b.GX,   b.UZ,      b.dg,      b.gmom,  b.A2};
-    for (void* q : ptrs) hipFree(q);
-    b = EnsembleBuffers();
+// the block kept between calls (see Arena)
+static struct {
+    void* p = nullptr;
+    size_t bytes = 0;
+    int device = -1;
+    bool lent = false;
+    int64_t pumps = 0;
+} g_kept;
+
+void kept_block_free() {
+    if (g_kept.p && !g_kept.lent) {
+        hipFree(g_kept.p);
+        g_kept.p = nullptr;
+        g_kept.bytes = 0;
+    }
+}
+size_t kept_block_bytes() { return g_kept.lent ? 0 : g_kept.bytes; }
+void pump_born() { ++g_kept.pumps; }
+void pump_gone() {
+    if (--g_kept.pumps == 0) kept_block_free();
 }
 
-// device allocation cleared on the run's stream (never the null stream: a
-// null-stream operation would synchronise with streams that other threads
-// may be capturing into graphs)
-static int dalloc(void** p, size_t bytes, hipStream_t st) {
-    if (bytes == 0) bytes = 16;
-    if (hipMalloc(p, bytes) != hipSuccess) {
-        *p = nullptr;
-        set_error("device allocation of " + std::to_string(bytes) + " bytes failed");
-        return TWA_ENOMEM;
+hipError_t device_malloc(void** p, size_t bytes) {
+    hipError_t e = hipMalloc(p, bytes);
+    if (e != hipSuccess && g_kept.p && !g_kept.lent) {
+        hipGetLastError();
+        kept_block_free();
+        e = hipMalloc(p, bytes);
     }
-    if (hipMemsetAsync(*p, 0, bytes, st) != hipSuccess) {
-        set_error("hipMemsetAsync failed");
-        return TWA_EHIP;
+    if (e != hipSuccess) *p = nullptr;
+    return e;
+}
+
+int Arena::commit(bool keep, hipStream_t st) {
+    auto padded = [](size_t n) { return (std::max<size_t>(n, 16) + 255) / 256 * 256; };
+    size_t zeroed = 0, total = 0;
+    for (const Item& it : items_) {
+        if (it.zero) zeroed += padded(it.bytes);
+        total += padded(it.bytes);
     }
+    int dev = 0;
+    TWA_HIP_CHECK(hipGetDevice(&dev));
+    if (keep && g_kept.p && !g_kept.lent && g_kept.device == dev && g_kept.bytes >= total) {
+        block_ = g_kept.p;
+        bytes_ = g_kept.bytes;
+        g_kept.lent = true;
+    } else {
+        if (keep) kept_block_free();
+        if (device_malloc(&block_, total) != hipSuccess) {
+            hipGetLastError();
+            set_error("device allocation of " + std::to_string(total) + " bytes failed");
+            return TWA_ENOMEM;
+        }
+        bytes_ = total;
+    }
+    keep_ = keep;
+    char* z = static_cast<char*>(block_);
+    char* q = z + zeroed;
+    for (const Item& it : items_) {
+        char*& at = it.zero ? z : q;
+        *it.p = at;
+        at += padded(it.bytes);
+    }
+    // cleared on the call's stream (never the null stream: a null-stream
+    // operation would synchronise with streams that other threads may be
+    // capturing into graphs)
+    if (zeroed) TWA_HIP_CHECK(hipMemsetAsync(block_, 0, zeroed, st));
     return TWA_OK;
 }
 
-int alloc_buffers(const Geometry& g, bool tangents, int64_t L, int J, EnsembleBuffers& b, hipStream_t st) {
+void Arena::release() {
+    if (!block_) return;
+    if (g_kept.p == block_) {
+        g_kept.lent = false;
+    } else if (keep_ && !g_kept.p && g_kept.pumps > 0) {
+        size_t freeb = 0, totb = 0;
+        int dev = 0;
+        if (hipMemGetInfo(&freeb, &totb) == hipSuccess && hipGetDevice(&dev) == hipSuccess && bytes_ <= totb / 64) {
+            g_kept.p = block_;
+            g_kept.bytes = bytes_;
+            g_kept.device = dev;
+            g_kept.lent = false;
+        } else {
+            hipFree(block_);
+        }
+    } else {
+        hipFree(block_);
+    }
+    block_ = nullptr;
+}
+
+void* Arena::detach() {
+    void* p = block_;
+    block_ = nullptr;
+    return p;
+}
+
+void add_buffers(const Geometry& g, bool tangents, int64_t L, int J, bool contraction, EnsembleBuffers& b, Arena& ar) {
     const size_t ge = (size_t)gemm_elt_bytes(g.precision), se = (size_t)state_elt_bytes(g.precision);
     const size_t P = (size_t)g.P, Bp = (size_t)g.Bp, C2 = (size_t)g.C2, nmt = (size_t)g.nmt;
-    int rc;
-#define TWA_A(ptr, bytes) \
-    if ((rc = dalloc((void**)&(ptr), (bytes), st)) != TWA_OK) return rc;
-    const size_t spl = (size_t)operand_split(g.precision);   // parts per operand value
-    const size_t ck = g.coh ? 1 : 0;                          // coherent exchange: one more K block
-    TWA_A(b.A, P * (2 + ck) * P * ge * spl)
-    TWA_A(b.Xop, C2 * (2 + ck) * P * ge * spl)
-    TWA_A(b.Dop, C2 * (1 + ck) * P * ge * spl)
-    if (ck) {
-        TWA_A(b.A2, P * 2 * P * ge * spl)
-    }
-    TWA_A(b.s[0], 3 * Bp * P * se)
-    TWA_A(b.s[1], 3 * Bp * P * se)
-    TWA_A(b.dlt, 3 * Bp * P * se)
-    TWA_A(b.Sn, 2 * Bp * se)
-    TWA_A(b.Y, 2 * Bp * P * se)
-    TWA_A(b.part[0], 3 * nmt * Bp * se)
-    TWA_A(b.part[1], 3 * nmt * Bp * se)
-    TWA_A(b.g, 2 * Bp * se)
-    TWA_A(b.norm0, Bp * P * se)
-    TWA_A(b.mom, 10 * Bp * se)
-    TWA_A(b.step, sizeof(int64_t))
-    TWA_A(b.diag, 2 * 1024 * sizeof(float))
-    TWA_A(b.sm0, 2 * Bp * se)
-    if (L > 0) {
-        TWA_A(b.lag, (size_t)L * J * 6 * sizeof(double))
+    const size_t op = ge * (size_t)operand_split(g.precision);   // bytes per operand value
+    const size_t ck = g.coh ? 1 : 0;                              // coherent exchange: one more K block
+    // zero at the start: what a run reads before it writes all of (padding of
+    // the noise columns, normals of padding trajectories, sums, counters)
+    ar.add(b.g, 2 * Bp * se, true);
+    ar.add(b.mom, 10 * Bp * se, true);
+    ar.add(b.step, sizeof(int64_t), true);
+    ar.add(b.diag, 2 * 1024 * sizeof(float), true);
+    ar.add(b.sm0, 2 * Bp * se, true);
+    if (L > 0) ar.add(b.lag, (size_t)L * J * 6 * sizeof(double), true);
+    ar.add(b.s[0], 3 * Bp * P * se, false);
+    ar.add(b.s[1], 3 * Bp * P * se, false);
+    ar.add(b.Y, 2 * Bp * P * se, false);
+    ar.add(b.norm0, Bp * P * se, false);
+    if (contraction) {
+        ar.add(b.Xop, C2 * (2 + ck) * P * op, true);
+        ar.add(b.Sn, 2 * Bp * se, true);
+        ar.add(b.part[0], 3 * nmt * Bp * se, true);
+        ar.add(b.part[1], 3 * nmt * Bp * se, true);
+        ar.add(b.A, P * (2 + ck) * P * op, false);
+        ar.add(b.Dop, C2 * (1 + ck) * P * op, false);
+        if (ck) ar.add(b.A2, P * 2 * P * op, false);
+        ar.add(b.dlt, 3 * Bp * P * se, false);
     }
     if (tangents) {
-        TWA_A(b.tXop, 2 * C2 * P * ge * spl)
-        TWA_A(b.tDop, 2 * C2 * P * ge * spl)
-        TWA_A(b.ts[0], 2 * 3 * Bp * P * se)
-        TWA_A(b.ts[1], 2 * 3 * Bp * P * se)
-        TWA_A(b.tdlt, 2 * 3 * Bp * P * se)
-        TWA_A(b.tY, 2 * 2 * Bp * P * se)
-        TWA_A(b.tpart[0], 2 * 3 * nmt * Bp * se)
-        TWA_A(b.tpart[1], 2 * 3 * nmt * Bp * se)
+        ar.add(b.tXop, 2 * C2 * P * op, true);
+        ar.add(b.ts[0], 2 * 3 * Bp * P * se, true);
+        ar.add(b.tpart[0], 2 * 3 * nmt * Bp * se, true);
+        ar.add(b.tpart[1], 2 * 3 * nmt * Bp * se, true);
+        ar.add(b.tDop, 2 * C2 * P * op, false);
+        ar.add(b.ts[1], 2 * 3 * Bp * P * se, false);
+        ar.add(b.tdlt, 2 * 3 * Bp * P * se, false);
+        ar.add(b.tY, 2 * 2 * Bp * P * se, false);
     }
-#undef TWA_A
-    return TWA_OK;
 }
 
-int alloc_decay_buffers(const Geometry& g, EnsembleBuffers& b, hipStream_t st) {
+void add_decay_buffers(const Geometry& g, EnsembleBuffers& b, Arena& ar) {
     const size_t ge = (size_t)gemm_elt_bytes(g.precision), se = (size_t)state_elt_bytes(g.precision);
-    const size_t P = (size_t)g.P, Bp = (size_t)g.Bp, gp = ge * (size_t)operand_split(g.precision);
-    int rc;
-    if ((rc = dalloc(&b.AG, P * P * gp, st)) || (rc = dalloc(&b.AGG, P * P * gp, st)) ||
-        (rc = dalloc(&b.Zop, Bp * P * gp, st)) || (rc = dalloc(&b.GX, 2 * Bp * P * se, st)) ||
-        (rc = dalloc(&b.UZ, Bp * P * se, st)) || (rc = dalloc(&b.dg, P * se, st)) ||
-        (rc = dalloc((void**)&b.gmom, 18 * Bp * sizeof(double), st)))
-        return rc;
-    return TWA_OK;
+    const size_t P = (size_t)g.P, Bp = (size_t)g.Bp, op = ge * (size_t)operand_split(g.precision);
+    ar.add(b.gmom, 18 * Bp * sizeof(double), true);
+    ar.add(b.AG, P * P * op, false);
+    ar.add(b.AGG, P * P * op, false);
+    ar.add(b.Zop, Bp * P * op, false);
+    ar.add(b.GX, 2 * Bp * P * se, false);
+    ar.add(b.UZ, Bp * P * se, false);
+    ar.add(b.dg, P * se, false);
 }
 
 Geometry make_geometry(int precision, int cfg, int64_t N, int64_t B) {

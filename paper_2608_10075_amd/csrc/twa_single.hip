@@ -156,6 +156,7 @@ int run_single(const twa_params* p, int64_t n_traj, double dt, int64_t n_steps, 
         st = own;
     }
     EnsembleBuffers b;
+    Arena ar;
     double* init_dev = nullptr;
     double* export_dev = nullptr;
     void *toep_tw = nullptr, *toep_spec = nullptr;
@@ -200,25 +201,28 @@ int run_single(const twa_params* p, int64_t n_traj, double dt, int64_t n_steps, 
         }                                                                \
     } while (0)
 
-    TWA_TRY(alloc_buffers(g, tangents, L, J, b, st));
+    // the fused and Toeplitz paths contract nothing through the stage kernels
+    add_buffers(g, tangents, L, J, !fused && !toep, b, ar);
+    if (decay) add_decay_buffers(g, b, ar);
+    if (p->init_state) ar.add(init_dev, (size_t)3 * B * N * sizeof(double), false);
+    if (outs && outs->final_state) ar.add(export_dev, (size_t)3 * B * N * sizeof(double), false);
+    if (toep) ar.add(toep_tw, toeplitz_table_bytes(g), false);
+    TWA_TRY(ar.commit(true, st));
     if (toep)
-        TWA_TRY(toeplitz_tables(g, pump->w, pump->alpha, dt, &toep_tw, &toep_spec, st));
+        TWA_TRY(toeplitz_tables(g, pump->w, pump->alpha, dt, toep_tw, &toep_spec, st));
     else if (g.coh)
         TWA_TRY(launch_build_A_coh(g, pump->W, pump->F, pump->Om, dt, b.A, b.A2, st));
-    else
+    else if (!fused)
         TWA_TRY(launch_build_A(g, pump->W, pump->F, dt, b.A, st));
     if (decay) {
         TWA_TRY(decay_geometry_ok(g));
-        TWA_TRY(alloc_decay_buffers(g, b, st));
         TWA_TRY(launch_decay_ops(g, pump->G, b, st));
     }
     if (p->init_state) {
-        TWA_HTRY(hipMalloc(&init_dev, (size_t)3 * B * N * sizeof(double)));
         TWA_HTRY(hipMemcpyAsync(init_dev, p->init_state, (size_t)3 * B * N * sizeof(double), hipMemcpyHostToDevice, st));
     }
     TWA_TRY(launch_init_state(g, b, c, init_dev, st));
-    TWA_TRY(launch_reduce_state(g, b.s[0], b.part[0], st));
-    TWA_HTRY(hipMemsetAsync(b.step, 0, sizeof(int64_t), st));
+    if (!fused && !toep) TWA_TRY(launch_reduce_state(g, b.s[0], b.part[0], st));
     if (L > 0 && burnin == 0) {
         TWA_TRY(launch_seed_tangents(g, b, cur, st));
         TWA_TRY(launch_observe(g, b, c, cur, true, st));
@@ -295,7 +299,6 @@ int run_single(const twa_params* p, int64_t n_traj, double dt, int64_t n_steps, 
         TWA_HTRY(hipMemcpyAsync(hlag.data(), b.lag, hlag.size() * sizeof(double), hipMemcpyDeviceToHost, st));
     }
     if (outs && outs->final_state) {
-        TWA_HTRY(hipMalloc(&export_dev, (size_t)3 * B * N * sizeof(double)));
         TWA_TRY(launch_export_state(g, b.s[cur], export_dev, st));
         TWA_HTRY(hipMemcpyAsync(outs->final_state, export_dev, (size_t)3 * B * N * sizeof(double),
                                 hipMemcpyDeviceToHost, st));
@@ -370,10 +373,7 @@ cleanup:
     delete tm;
     if (e0) hipEventDestroy(e0);
     if (e1) hipEventDestroy(e1);
-    hipFree(init_dev);
-    hipFree(export_dev);
-    hipFree(toep_tw);
-    free_buffers(b);
+    ar.release();
     if (own) hipStreamDestroy(own);
 #undef TWA_TRY
 #undef TWA_HTRY

@@ -299,7 +299,7 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     // makes the 16-lane fragment reads of one MFMA operand hit distinct LDS
     // banks.  The units are distinct LDS objects so that the compiler can tell
     // the loads in flight into one from the reads of another.
-    static_assert(NST >= 2 && NST <= 12, "LDS ring depth");
+    static_assert(NST >= 2 && NST <= 8, "LDS ring depth");
     constexpr int SB = (MT + NT) * KB;
     __shared__ __attribute__((aligned(1024))) char L0[SB];
     __shared__ __attribute__((aligned(1024))) char L1[SB];
@@ -309,10 +309,6 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     __shared__ __attribute__((aligned(1024))) char L5[NST > 5 ? SB : 16];
     __shared__ __attribute__((aligned(1024))) char L6[NST > 6 ? SB : 16];
     __shared__ __attribute__((aligned(1024))) char L7[NST > 7 ? SB : 16];
-    __shared__ __attribute__((aligned(1024))) char L8[NST > 8 ? SB : 16];
-    __shared__ __attribute__((aligned(1024))) char L9[NST > 9 ? SB : 16];
-    __shared__ __attribute__((aligned(1024))) char L10[NST > 10 ? SB : 16];
-    __shared__ __attribute__((aligned(1024))) char L11[NST > 11 ? SB : 16];
     __shared__ S sS[NTRJ][2];      // primal collective sums of the trajectories of the tile
     __shared__ S sT[NTRJ][2];      // tangent collective sums
     __shared__ S sG[NTRJ][2];      // collective normals
@@ -397,8 +393,7 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     const int offA = (wm0 + ra) * KB, offX = (MT + wn0 + rx) * KB;
     const int swA = swz(ra), swX = swz(rx), grp = lane >> 4;
 #define TWA_BUF(I_) ((I_) == 0 ? L0 : (I_) == 1 ? L1 : (I_) == 2 ? L2 : (I_) == 3 ? L3 : \
-                     (I_) == 4 ? L4 : (I_) == 5 ? L5 : (I_) == 6 ? L6 : (I_) == 7 ? L7 : \
-                     (I_) == 8 ? L8 : (I_) == 9 ? L9 : (I_) == 10 ? L10 : L11)
+                     (I_) == 4 ? L4 : (I_) == 5 ? L5 : (I_) == 6 ? L6 : L7)
     // wait until at most N_ direct loads and no LDS read are pending (expcnt left at its maximum), gfx9 encoding
 #define TWA_WAIT_VM(N_) __builtin_amdgcn_s_waitcnt(((N_) & 15) | (((N_) >> 4) << 14) | (7 << 4) | (0 << 8))
     // fragments of one 64-byte segment of a unit
@@ -418,7 +413,7 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     // unit's products run, so no MFMA waits for an LDS read and a unit's LDS is
     // free as soon as its turn comes (LOOK units of the ring are then in
     // registers, not in LDS).
-    constexpr bool AHEAD = KB == 64 && 4 * (BI * BJ * ((QSNAP ? 2 : 1) + (LOW ? 1 : 0)) + NP * (BI + BJ)) + (LOW ? 32 : 48) <= 256;
+    constexpr bool AHEAD = KB == 64 && 4 * (BI * BJ * ((QSNAP ? 2 : 1) + (LOW ? 1 : 0)) + NP * (BI + BJ)) + 32 <= 256;
     constexpr int LOOK = AHEAD ? 1 : 0;
 
     // ---- collective sums of this tile's trajectories: thread group g of

@@ -102,6 +102,7 @@ int run_tangent_w(const twa_params* p, int64_t n_traj, double dt, int64_t n_step
         st = own;
     }
     EnsembleBuffers b;
+    Arena ar;
     void* Q = nullptr;
     double* dacc = nullptr;
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -139,14 +140,13 @@ int run_tangent_w(const twa_params* p, int64_t n_traj, double dt, int64_t n_step
     } while (0)
 
     // the tangent starts at zero: the initial sampling does not depend on w
-    TWA_TRY(alloc_buffers(g, true, 0, J, b, st));
-    TWA_HTRY(hipMalloc(&Q, 2 * plane));
-    TWA_HTRY(hipMalloc((void**)&dacc, (size_t)5 * g.Bp * sizeof(double)));
-    TWA_HTRY(hipMemsetAsync(dacc, 0, (size_t)5 * g.Bp * sizeof(double), st));
+    add_buffers(g, true, 0, J, true, b, ar);
+    ar.add(Q, 2 * plane, false);
+    ar.add(dacc, (size_t)5 * g.Bp * sizeof(double), true);
+    TWA_TRY(ar.commit(true, st));
     TWA_TRY(launch_build_A(g, pump->W, pump->F, dt, b.A, st));
     TWA_TRY(launch_init_state(g, b, c, nullptr, st));
     TWA_TRY(launch_reduce_state(g, b.s[0], b.part[0], st));
-    TWA_HTRY(hipMemsetAsync(b.step, 0, sizeof(int64_t), st));
     TWA_HTRY(hipEventCreate(&e0));
     TWA_HTRY(hipEventCreate(&e1));
     TWA_HTRY(hipEventRecord(e0, st));
@@ -245,9 +245,7 @@ cleanup:
     if (rc != TWA_OK && rc != TWA_EUNSTABLE) hipStreamSynchronize(st);
     if (e0) hipEventDestroy(e0);
     if (e1) hipEventDestroy(e1);
-    hipFree(Q);
-    hipFree(dacc);
-    free_buffers(b);
+    ar.release();
     if (own) hipStreamDestroy(own);
 #undef TWA_TRY
 #undef TWA_HTRY

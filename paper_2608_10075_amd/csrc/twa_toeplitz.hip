@@ -644,21 +644,21 @@ int toeplitz_embedding_log2(int64_t N) {
 
 int64_t toeplitz_max_n(int precision) { return precision == TWA_PREC_FP64 ? 8193 : 16385; }
 
-// tables of one run in one allocation: *tw holds twiddles, coefficients and
-// the transform's FP64 work space.  On the host the transform took 7 ms at
+// tables of one run: tw (toeplitz_table_bytes) holds twiddles, coefficients
+// and the transform's FP64 work space.  On the host the transform took 7 ms at
 // M = 32768, a fifth of a run of 64 steps; here 0.1 ms.
-int toeplitz_tables(const Geometry& g, double w, double alpha, double dt, void** tw, void** spec, hipStream_t st) {
+size_t toeplitz_table_bytes(const Geometry& g) {
+    const size_t M = (size_t)1 << toeplitz_embedding_log2(g.N), es = g.precision == TWA_PREC_FP64 ? 16 : 8;
+    return M * (2 * es + 2 * sizeof(double2));
+}
+
+int toeplitz_tables(const Geometry& g, double w, double alpha, double dt, void* tw, void** spec, hipStream_t st) {
     const int64_t M = int64_t(1) << toeplitz_embedding_log2(g.N);
     const size_t es = g.precision == TWA_PREC_FP64 ? 16 : 8;
-    if (hipMalloc(tw, (size_t)M * (2 * es + 2 * sizeof(double2))) != hipSuccess) {
-        *tw = nullptr;
-        set_error("Toeplitz path: device allocation failed");
-        return TWA_ENOMEM;
-    }
-    *spec = static_cast<char*>(*tw) + (size_t)M * es;
-    double2* work = reinterpret_cast<double2*>(static_cast<char*>(*tw) + 2 * (size_t)M * es);
-    return es == 16 ? build_tables<double>(M, w, alpha, dt, *tw, *spec, work, st)
-                    : build_tables<float>(M, w, alpha, dt, *tw, *spec, work, st);
+    *spec = static_cast<char*>(tw) + (size_t)M * es;
+    double2* work = reinterpret_cast<double2*>(static_cast<char*>(tw) + 2 * (size_t)M * es);
+    return es == 16 ? build_tables<double>(M, w, alpha, dt, tw, *spec, work, st)
+                    : build_tables<float>(M, w, alpha, dt, tw, *spec, work, st);
 }
 
 int launch_toeplitz_run(const Geometry& g, const EnsembleBuffers& b, const StepConsts& c, const void* tw,
