@@ -439,8 +439,8 @@ int run_steps(std::vector<Bucket>& bks, const Plan& plan, int64_t n0, int64_t n1
 int bucket_of(int64_t N) { return N <= 128 ? 0 : N <= 1024 ? 1 : 2; }
 
 std::vector<int> bucket_candidates(int bucket, int precision) {
+    if (precision == TWA_PREC_FP64) return {0, 1, 2};
     if (bucket == 0) return {0, 1};
-    if (precision == TWA_PREC_FP64) return {0, 1};
     if (bucket == 2 && operand_split(precision) == 2) return {2, 3, 7};
     return {1, 3, 7};
 }

@@ -43,26 +43,35 @@ struct Status {
 // tile configurations of the channel-mixing contraction.  A configuration is
 // (MT rows of spins, NT operand columns = NT/2 trajectories x 2 components,
 // K bytes per LDS stage, waves along M, waves along N).
-// The shapes depend on the parts per operand value (operand_split).  nstage
-// counts ring units, one part of one K stage each.
+// The shapes depend on the parts per operand value (operand_split).  A ring
+// stage holds `group` units, one part of one K stage each: 1, all the parts of
+// a K stage, or with one part several K stages.
 struct TileCfg {
-    int mt, nt, kbytes, waves_m, waves_n, nstage;
+    int mt, nt, kbytes, waves_m, waves_n, nstage, group;
 };
 constexpr int kTileCfgs = 9;
-constexpr TileCfg kTiles[3][kTileCfgs] = {
-    // one part (FP64, BF16, FP16)
-    {{16, 32, 64, 1, 1, 2}, {64, 64, 64, 2, 2, 4}, {128, 128, 128, 2, 2, 4}, {128, 128, 64, 2, 2, 8},
-     {256, 128, 64, 4, 1, 6}, {128, 256, 64, 2, 2, 6}, {256, 128, 64, 4, 2, 4}, {320, 256, 128, 4, 2, 2},
-     {320, 256, 64, 4, 2, 4}},
-    // two parts (split BF16)
-    {{16, 32, 64, 1, 1, 8}, {64, 64, 64, 2, 2, 6}, {128, 128, 64, 4, 2, 8}, {128, 64, 64, 2, 2, 6},
-     {256, 128, 64, 4, 2, 6}, {128, 256, 64, 2, 4, 6}, {256, 256, 64, 4, 2, 4}, {320, 256, 64, 4, 2, 4},
-     {192, 192, 64, 4, 2, 6}},
-    // three parts (FP32)
-    {{16, 32, 64, 1, 1, 6}, {64, 64, 64, 2, 2, 6}, {128, 128, 64, 4, 2, 6}, {128, 64, 64, 2, 2, 6},
-     {256, 64, 64, 4, 2, 6}, {64, 128, 64, 2, 2, 6}, {128, 256, 64, 2, 4, 6}, {256, 128, 64, 4, 2, 6},
-     {192, 192, 64, 4, 2, 6}},
+constexpr TileCfg kTiles[4][kTileCfgs] = {
+    // one part: BF16, FP16
+    {{32, 32, 64, 2, 1, 6, 2}, {64, 64, 64, 2, 2, 4, 2}, {128, 128, 128, 2, 2, 4, 1}, {128, 128, 64, 2, 2, 8, 1},
+     {64, 64, 64, 2, 2, 4, 4}, {16, 32, 64, 1, 1, 4, 2}, {32, 32, 64, 2, 1, 4, 4}, {320, 256, 128, 4, 2, 2, 1},
+     {320, 256, 64, 4, 2, 4, 1}},
+    // two parts: split BF16
+    {{32, 32, 64, 2, 1, 6, 2}, {64, 64, 64, 2, 2, 3, 2}, {128, 128, 64, 4, 2, 8, 1}, {128, 64, 64, 2, 2, 3, 2},
+     {64, 64, 64, 2, 2, 6, 2}, {16, 32, 64, 1, 1, 6, 2}, {128, 64, 64, 2, 2, 6, 1}, {320, 256, 64, 4, 2, 4, 1},
+     {256, 128, 64, 4, 2, 6, 1}},
+    // three parts: FP32
+    {{32, 32, 64, 2, 1, 6, 3}, {64, 64, 64, 2, 2, 3, 3}, {128, 128, 64, 4, 2, 9, 1}, {128, 64, 64, 2, 2, 2, 3},
+     {64, 64, 64, 2, 2, 2, 3}, {16, 32, 64, 1, 1, 4, 3}, {128, 64, 64, 2, 2, 6, 1}, {256, 128, 64, 4, 2, 6, 1},
+     {64, 64, 64, 2, 2, 6, 3}},
+    // FP64 (configurations 0 to 3 only)
+    {{16, 32, 64, 1, 1, 8, 1}, {64, 64, 64, 2, 2, 4, 2}, {32, 32, 64, 2, 1, 6, 1}, {128, 128, 64, 2, 2, 8, 1},
+     {64, 64, 64, 2, 2, 4, 1}, {64, 64, 64, 2, 2, 4, 1}, {64, 64, 64, 2, 2, 4, 1}, {64, 64, 64, 2, 2, 4, 1},
+     {64, 64, 64, 2, 2, 4, 1}},
 };
+// row of kTiles of a precision
+constexpr int tile_table(int precision) {
+    return precision == TWA_PREC_FP64 ? 3 : precision == TWA_PREC_FP32 ? 2 : precision == TWA_PREC_BF16X3 ? 1 : 0;
+}
 inline int n_tile_cfgs() { return kTileCfgs; }
 const TileCfg& tile_cfg(int precision, int id);
 int pick_tile_cfg(int precision, int64_t N, int64_t n_traj);

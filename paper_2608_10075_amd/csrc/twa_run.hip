@@ -47,34 +47,37 @@ static int n_compute_units() {
 // larger tile loads fewer bytes per product but leaves compute units idle
 // where there are few tiles; a round that is the only one costs more (nothing
 // runs beside its epilogue).  Costs measured per step of N x B = 700 x 512 to
-// 10^4 x 1024, e.g. at 1000 x 4096 in FP32 424 us with 64x64 tiles, 333 with
-// 128x64, 340 with 128x128 and 307 with 256x128; at 4096 x 512 in split BF16
-// 377, 312, 289 and (320x256) 1003; at 10^4 x 1024 in BF16 3211 (64x64), 1752
-// (128x128) and 991 (320x256).  FP64 is bound by its MFMA: 64x64 takes 1765 us
-// at 3000 x 1024, 128x128 2607.
-// Where 64x64 tiles are too few to fill the device, 16x32 ones are shorter:
-// FP32 201 x 500 (64 tiles) 29 against 31 us, 700 x 512 (176) 58 against 56;
-// FP64 600 x 400 (130) 89 against 101, 2000 x 512 (512) 531 against 433.
+// 10^4 x 1024, e.g. in FP32 at 1000 x 1024 96 us with 64x64 tiles (two stages
+// of LDS, three blocks a unit), 96 with 128x64, 220 with 256x128; at
+// 2000 x 1024 285, 269 and 376; at 4096 x 1024 1276, 1006 and 826.  Split BF16
+// at 4096 x 512 340 (64x64), 279 (128x64), 266 (128x128) and 982 (320x256);
+// BF16 at 10^4 x 1024 3028 (64x64), 1756 (128x128) and 965 (320x256).
+// Where larger tiles are too few to fill the device, the smallest are shorter:
+// 32x32 up to two to a compute unit (FP32 2000 x 128, 504 of them, 81 against
+// 100 us; 500 x 600, 608, 57 against 40).  FP64, bound by its MFMA, takes
+// 16x32, one wave each, up to one to a SIMD (600 x 400, 950 of them, 70
+// against 96 us; 700 x 512, 1408, 140 against 105), then 32x32 up to four to a
+// unit (700 x 512 94 us; 1000 x 512 138 against 143; 2000 x 512, twice as
+// many, 560 against 420).
 int pick_tile_cfg(int precision, int64_t N, int64_t n_traj) {
     struct Cost {
         int cfg;
         double single, round;
     };
-    static const Cost one[] = {{1, 30, 15}, {3, 42, 36}, {7, 105, 105}};
-    static const Cost two[] = {{1, 45, 26}, {3, 70, 39}, {2, 72, 66}, {7, 250, 250}};
-    static const Cost three[] = {{1, 70, 48}, {3, 100, 75}, {2, 140, 140}, {7, 215, 215}};
-    static const Cost fp64[] = {{1, 149, 105}};
+    static const Cost one[] = {{1, 27, 15}, {3, 42, 36}, {7, 105, 105}};
+    static const Cost two[] = {{1, 45, 26}, {3, 57, 36}, {2, 66, 65}, {7, 250, 250}};
+    static const Cost three[] = {{1, 55, 50}, {4, 58, 40}, {3, 80, 67}, {7, 250, 205}};
     const int np = operand_split(precision);
     const bool f64 = precision == TWA_PREC_FP64;
-    const Cost* c = f64 ? fp64 : np == 1 ? one : np == 2 ? two : three;
-    const int n = f64 ? 1 : np == 1 ? 3 : 4;
+    const Cost* c = np == 1 ? one : np == 2 ? two : three;
+    const int n = np == 1 ? 3 : 4;
     const int64_t ncu = n_compute_units();
     auto tiles = [&](int cfg) {
         const TileCfg& t = tile_cfg(precision, cfg);
         return (round_up(N, t.mt) / t.mt) * (2 * round_up(n_traj, t.nt / 2) / t.nt);
     };
-    if (N <= 48) return 0;
-    if ((f64 && 5 * tiles(1) < 4 * ncu) || (np == 3 && 5 * tiles(1) < 2 * ncu)) return 0;
+    if (N <= 48 || tiles(0) <= (f64 ? 4 : 2) * ncu) return 0;
+    if (f64) return tiles(2) <= 4 * ncu ? 2 : 1;
     int best = 1;
     double tb = 1e300;
     for (int q = 0; q < n; ++q) {
@@ -469,7 +472,8 @@ Geometry make_geometry(int precision, int cfg, int64_t N, int64_t B) {
     g.kt = tc.kbytes / gemm_elt_bytes(precision);
     g.N = N;
     g.B = B;
-    g.P = round_up(N, std::max<int64_t>(tc.mt, g.kt));
+    // whole tiles, K stages and (with one part per unit) ring stages
+    g.P = round_up(N, std::max<int64_t>(tc.mt, g.kt * std::max(1, tc.group / operand_split(precision))));
     g.Bp = round_up(B, tc.nt / 2);
     g.nmt = g.P / tc.mt;
     g.C2 = 2 * g.Bp;

@@ -9,7 +9,7 @@
 
 namespace twa {
 
-const TileCfg& tile_cfg(int precision, int id) { return kTiles[operand_split(precision) - 1][id]; }
+const TileCfg& tile_cfg(int precision, int id) { return kTiles[tile_table(precision)][id]; }
 
 int launch_gemm(const Geometry& g, const EnsembleBuffers& b, const StepConsts& c, int stage, bool tangent,
                 int cur, bool store_y2, bool keep_dlt, hipStream_t st) {

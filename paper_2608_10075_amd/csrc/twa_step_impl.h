@@ -266,7 +266,7 @@ __device__ __forceinline__ void unroll_units(F& f, const int u0, const int n, st
 // contraction + fused Heun stage
 // One output tile (M tile mt of spins, column tile nt, copy cp) of one stage:
 // contraction over K on MFMA followed by the fused epilogue of the kind.
-template <int PREC, int MT, int NT, int KB, int WMW, int WNW, int NST, int STAGE, int KIND>
+template <int PREC, int MT, int NT, int KB, int WMW, int WNW, int NST, int G_, int STAGE, int KIND>
 __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt, const int nt, const int cp) {
     // KIND_Q_SNAPSHOT on the predictor kind: also store the part of the
     // contraction that comes from the second K half (the noise columns), by
@@ -290,17 +290,20 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     static_assert(WM % 16 == 0 && WN % 32 == 0, "wave tile");
     static_assert(KB % 64 == 0, "K stage");
 
-    // NST LDS units (a ring).  A unit holds one part of one K stage of the
-    // operands: rows [0, MT) of A then [MT, MT + NT) of X, KB bytes per row.
+    // NST LDS stages of G_ units (a ring).  A unit holds one part of one K
+    // stage of the operands: rows [0, MT) of A then [MT, MT + NT) of X, KB bytes per row.
     // The split forms load each part once and form all its products from
     // registers and LDS, so NP parts cost NP times the load traffic of one
     // for NP (NP + 1) / 2 times the MFMA work.  Inside every 16-row block the
     // 16-byte piece c of row r is stored at piece position c ^ swz(r), which
     // makes the 16-lane fragment reads of one MFMA operand hit distinct LDS
-    // banks.  The units are distinct LDS objects so that the compiler can tell
+    // banks.  The stages are distinct LDS objects so that the compiler can tell
     // the loads in flight into one from the reads of another.
-    static_assert(NST >= 2 && NST <= 8, "LDS ring depth");
-    constexpr int SB = (MT + NT) * KB;
+    // A small tile's unit is little work between two barriers (64x64: 128
+    // cycles of MFMA against some 300 of barrier and LDS latency), so there a
+    // stage is a whole K stage (G_ = NP) or several.
+    static_assert(NST >= 2 && NST <= 12, "LDS ring depth");
+    constexpr int UB = (MT + NT) * KB, SB = G_ * UB;
     __shared__ __attribute__((aligned(1024))) char L0[SB];
     __shared__ __attribute__((aligned(1024))) char L1[SB];
     __shared__ __attribute__((aligned(1024))) char L2[NST > 2 ? SB : 16];
@@ -309,6 +312,10 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     __shared__ __attribute__((aligned(1024))) char L5[NST > 5 ? SB : 16];
     __shared__ __attribute__((aligned(1024))) char L6[NST > 6 ? SB : 16];
     __shared__ __attribute__((aligned(1024))) char L7[NST > 7 ? SB : 16];
+    __shared__ __attribute__((aligned(1024))) char L8[NST > 8 ? SB : 16];
+    __shared__ __attribute__((aligned(1024))) char L9[NST > 9 ? SB : 16];
+    __shared__ __attribute__((aligned(1024))) char L10[NST > 10 ? SB : 16];
+    __shared__ __attribute__((aligned(1024))) char L11[NST > 11 ? SB : 16];
     __shared__ S sS[NTRJ][2];      // primal collective sums of the trajectories of the tile
     __shared__ S sT[NTRJ][2];      // tangent collective sums
     __shared__ S sG[NTRJ][2];      // collective normals
@@ -346,7 +353,7 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     // columns of X as one of NT KB bytes.
     const char* Ag = reinterpret_cast<const char*>(a.A) + m0 * KB;
     const char* Xg = reinterpret_cast<const char*>(a.X + cp * a.x_copy) + n0 * KB;
-    const int nu = (int)(a.K / KT);                // units
+    const int nu = (int)(a.K / KT) / G_;           // ring stages
     const int64_t a_unit = P * KB, x_unit = 2 * Bp * KB;
     // Direct memory -> LDS loads (buffer_load_dwordx4 ... lds): one wave
     // instruction moves 64 x 16 bytes into 1 KB of LDS, lane i to offset 16 i,
@@ -380,20 +387,22 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
         srcA[j] = q * RPC < MT;
         voff[j] = (uint32_t)((row < MT ? row : row - MT) * KB + pc * 16);
     }
-#define TWA_DMA(U_, BUF_)                                                                               \
-    do {                                                                                                \
-        const Rsrc ra_ = wave_rsrc(Ag + (int64_t)(U_) * a_unit, (int64_t)MT * KB);                      \
-        const Rsrc rx_ = wave_rsrc(Xg + (int64_t)(U_) * x_unit, (int64_t)NT * KB);                      \
+    // stage S_ of the ring: units S_ G_ .. S_ G_ + G_ - 1
+#define TWA_DMA(S_, BUF_)                                                                               \
+    _Pragma("unroll") for (int gu = 0; gu < G_; ++gu) {                                                 \
+        const Rsrc ra_ = wave_rsrc(Ag + ((int64_t)(S_) * G_ + gu) * a_unit, (int64_t)MT * KB);          \
+        const Rsrc rx_ = wave_rsrc(Xg + ((int64_t)(S_) * G_ + gu) * x_unit, (int64_t)NT * KB);          \
         _Pragma("unroll") for (int j = 0; j < CPW; ++j) if (CPW == CPWMIN || wv + j * NWV < NCH)        \
-            buffer_dma16(srcA[j] ? ra_ : rx_, (BUF_) + (wv + j * NWV) * 1024, voff[j]);                  \
-    } while (0)
+            buffer_dma16(srcA[j] ? ra_ : rx_, (BUF_) + gu * UB + (wv + j * NWV) * 1024, voff[j]);        \
+    }
 
     // fragment read offsets of this lane (row within a 16-row block, swizzle)
     const int ra = Prec<PREC>::arow(lane & 15), rx = lane & 15;
     const int offA = (wm0 + ra) * KB, offX = (MT + wn0 + rx) * KB;
     const int swA = swz(ra), swX = swz(rx), grp = lane >> 4;
 #define TWA_BUF(I_) ((I_) == 0 ? L0 : (I_) == 1 ? L1 : (I_) == 2 ? L2 : (I_) == 3 ? L3 : \
-                     (I_) == 4 ? L4 : (I_) == 5 ? L5 : (I_) == 6 ? L6 : L7)
+                     (I_) == 4 ? L4 : (I_) == 5 ? L5 : (I_) == 6 ? L6 : (I_) == 7 ? L7 : \
+                     (I_) == 8 ? L8 : (I_) == 9 ? L9 : (I_) == 10 ? L10 : L11)
     // wait until at most N_ direct loads and no LDS read are pending (expcnt left at its maximum), gfx9 encoding
 #define TWA_WAIT_VM(N_) __builtin_amdgcn_s_waitcnt(((N_) & 15) | (((N_) >> 4) << 14) | (7 << 4) | (0 << 8))
     // fragments of one 64-byte segment of a unit
@@ -403,18 +412,35 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
 #define TWA_FRAG_X(DST_, BUF_, SEG_)                                                                    \
     _Pragma("unroll") for (int j = 0; j < BJ; ++j) DST_[j] = *reinterpret_cast<const uint4*>(           \
         (BUF_) + offX + 16 * j * KB + ((((SEG_) * 4 + grp) ^ swX) << 4))
-#define TWA_MMA(A_, X_)                                                                                 \
+    // LOW_: a product of lower parts
+#define TWA_MMA(A_, X_, LOW_)                                                                                 \
     _Pragma("unroll") for (int i = 0; i < BI; ++i)                                                      \
         _Pragma("unroll") for (int j = 0; j < BJ; ++j) {                                                \
-            if constexpr (LOW && p > 0) Prec<PREC>::mma(accL[i][j], A_[i], X_[j]);                      \
+            if constexpr (LOW && (LOW_)) Prec<PREC>::mma(accL[i][j], A_[i], X_[j]);                     \
             else Prec<PREC>::mma(acc[i][j], A_[i], X_[j]);                                              \
         }
     // Registers allow it: the fragments of the next unit are read while this
     // unit's products run, so no MFMA waits for an LDS read and a unit's LDS is
     // free as soon as its turn comes (LOOK units of the ring are then in
     // registers, not in LDS).
-    constexpr bool AHEAD = KB == 64 && 4 * (BI * BJ * ((QSNAP ? 2 : 1) + (LOW ? 1 : 0)) + NP * (BI + BJ)) + 32 <= 256;
+    constexpr bool AHEAD = G_ > 1 || (KB == 64 && 4 * (BI * BJ * ((QSNAP ? 2 : 1) + (LOW ? 1 : 0)) + NP * (BI + BJ)) +
+                                                          (LOW ? 32 : 48) <= 256);
     constexpr int LOOK = AHEAD ? 1 : 0;
+    static_assert(G_ == 1 || (KB == 64 && (NP == 1 || G_ == NP)), "a stage of several units");
+
+    // prologue: the first stages of the ring in flight; the collective sums
+    // below run while they land
+#pragma unroll
+    for (int u = 0; u < NST - 1 + LOOK; ++u)
+        if (u < nu) {
+            TWA_DMA(u, TWA_BUF(u % NST));
+        }
+    // barrier that orders LDS only (a full one would wait for the loads above)
+    auto lds_sync = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    };
 
     // ---- collective sums of this tile's trajectories: thread group g of
     // trajectory kl adds the partial sums of the M tiles
@@ -444,7 +470,7 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
 #pragma unroll
                 for (int c = 0; c < NCHAN; ++c) red[gq][kl][c] = v[c];
         }
-        __syncthreads();
+        lds_sync();
         for (int t = tid; t < NTRJ; t += NTHR) {
             const int64_t k = k0t + t;
             S v[5];
@@ -494,29 +520,30 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                 sSrc[t][2] = oz;
             }
         }
-        __syncthreads();   // the sums are visible to every wave; red is free again
+        lds_sync();   // the sums are visible to every wave; red is free again
     }
-    // prologue: units 0 .. NST - 2 + LOOK in flight
-    constexpr int UN = NST % NP == 0 ? NST : NST * NP;   // unroll: ring slot and part are compile-time
-    uint4 fa[NP][BI], fx[NP][BJ];
-#pragma unroll
-    for (int u = 0; u < NST - 1 + LOOK; ++u)
-        if (u < nu) TWA_DMA(u, TWA_BUF(u % NST));
+    // unroll: ring slot and (G_ = 1) part are compile-time
+    constexpr int UN = G_ > 1 || NST % NP == 0 ? NST : NST * NP;
+    constexpr int NF = G_ > 1 ? G_ : NP;                 // fragment sets held
+    uint4 fa[NF][BI], fx[NF][BJ];
     if constexpr (AHEAD) {
-        if (nu >= NST) TWA_WAIT_VM((NST - 1) * CPWMIN);
+        if (nu >= NST) TWA_WAIT_VM((NST - 1) * G_ * CPWMIN);
         else TWA_WAIT_VM(0);
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-        TWA_FRAG_A(fa[0], TWA_BUF(0), 0);
-        TWA_FRAG_X(fx[0], TWA_BUF(0), 0);
+#pragma unroll
+        for (int gu = 0; gu < G_; ++gu) {
+            TWA_FRAG_A(fa[gu], TWA_BUF(0) + gu * UB, 0);
+            TWA_FRAG_X(fx[gu], TWA_BUF(0) + gu * UB, 0);
+        }
     }
     // one unit: its part is v % NP, its ring slot v % NST
     auto unit = [&](const int u, auto vc) __attribute__((always_inline)) {
-        constexpr int v = decltype(vc)::value, p = v % NP, pn = (p + 1) % NP;
+        constexpr int v = decltype(vc)::value, p = G_ > 1 ? 0 : v % NP, pn = (p + 1) % NP;
         // unit u (u + 1 with LOOK) has landed once at most the later units are
         // pending (waves that load fewer chunks per unit wait conservatively)
         __builtin_amdgcn_sched_barrier(0);
-        if (nu - 1 - u >= NST - 2 + LOOK) TWA_WAIT_VM((NST - 2) * CPWMIN);
+        if (nu - 1 - u >= NST - 2 + LOOK) TWA_WAIT_VM((NST - 2) * G_ * CPWMIN);
         else TWA_WAIT_VM(0);
         // Barrier without a memory fence: a fence would wait for every load
         // still in flight into the later units.  What it has to order is
@@ -528,7 +555,7 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
         if (u + NST - 1 + LOOK < nu) TWA_DMA(u + NST - 1 + LOOK, TWA_BUF((v + NST - 1 + LOOK) % NST));
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (QSNAP && p == 0) {
-            if (u == a.kq * NP) {
+            if (u * G_ == a.kq * NP) {
 #pragma unroll
                 for (int i = 0; i < BI; ++i)
 #pragma unroll
@@ -538,7 +565,39 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                     }
             }
         }
-        if constexpr (AHEAD) {
+        if constexpr (G_ > 1) {
+            // (after the last stage these reads return stale LDS, never used)
+            uint4 na[G_][BI], nx[G_][BJ];
+#pragma unroll
+            for (int gu = 0; gu < G_; ++gu) {
+                TWA_FRAG_A(na[gu], TWA_BUF((v + 1) % NST) + gu * UB, 0);
+                TWA_FRAG_X(nx[gu], TWA_BUF((v + 1) % NST) + gu * UB, 0);
+            }
+            // with one part every unit's product, else those of the parts pa
+            // and px with pa + px < NP
+#pragma unroll
+            for (int pa = 0; pa < G_; ++pa) {
+                if constexpr (NP == 1) {
+                    TWA_MMA(fa[pa], fx[pa], false);
+                } else {
+#pragma unroll
+                    for (int px = 0; px < G_ - pa; ++px) {
+                        if (pa + px == 0) {
+                            TWA_MMA(fa[pa], fx[px], false);
+                        } else {
+                            TWA_MMA(fa[pa], fx[px], true);
+                        }
+                    }
+                }
+            }
+#pragma unroll
+            for (int gu = 0; gu < G_; ++gu) {
+#pragma unroll
+                for (int i = 0; i < BI; ++i) fa[gu][i] = na[gu][i];
+#pragma unroll
+                for (int j = 0; j < BJ; ++j) fx[gu][j] = nx[gu][j];
+            }
+        } else if constexpr (AHEAD) {
             // (after the last unit these reads return stale LDS, never used)
             uint4 na[BI], nx[BJ];
             TWA_FRAG_A(na, TWA_BUF((v + 1) % NST), 0);
@@ -547,8 +606,8 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
             // (those with pa + px < NP)
 #pragma unroll
             for (int q = 0; q <= p; ++q) {
-                if (p + q < NP) TWA_MMA(fa[p], fx[q]);
-                if (q < p && p + q < NP) TWA_MMA(fa[q], fx[p]);
+                if (p + q < NP) TWA_MMA(fa[p], fx[q], p > 0);
+                if (q < p && p + q < NP) TWA_MMA(fa[q], fx[p], p > 0);
             }
 #pragma unroll
             for (int i = 0; i < BI; ++i) fa[pn][i] = na[i];
@@ -559,18 +618,18 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
             for (int seg = 0; seg < KB / 64; ++seg) {
                 TWA_FRAG_A(fa[0], TWA_BUF(v % NST), seg);
                 TWA_FRAG_X(fx[0], TWA_BUF(v % NST), seg);
-                TWA_MMA(fa[0], fx[0]);
+                TWA_MMA(fa[0], fx[0], false);
             }
         } else {
             static_assert(KB == 64, "one segment per unit in the split forms");
             TWA_FRAG_A(fa[p], TWA_BUF(v % NST), 0);
 #pragma unroll
             for (int q = 0; q < p; ++q)
-                if (p + q < NP) TWA_MMA(fa[p], fx[q]);
+                if (p + q < NP) TWA_MMA(fa[p], fx[q], p > 0);
             TWA_FRAG_X(fx[p], TWA_BUF(v % NST), 0);
 #pragma unroll
             for (int q = 0; q <= p; ++q)
-                if (p + q < NP) TWA_MMA(fa[q], fx[p]);
+                if (p + q < NP) TWA_MMA(fa[q], fx[p], p > 0);
         }
     };
     if constexpr (AHEAD) {
@@ -1105,14 +1164,14 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
 // Each XCD is given a contiguous range of tiles ordered M-tile-major, so the
 // workgroups resident on one XCD share the same rows of A (and walk K
 // together) in that XCD's L2.
-template <int PREC, int MT, int NT, int KB, int WMW, int WNW, int NST, int STAGE, int KIND>
+template <int PREC, int MT, int NT, int KB, int WMW, int WNW, int NST, int G_, int STAGE, int KIND>
 __global__ __launch_bounds__(64 * WMW * WNW) void heun_stage_kernel(GemmArgs<PREC> a) {
     const int nnt = a.nnt;            // column tiles
     const int T = (int)gridDim.x;     // total tiles = nmt * nnt
     const int q = T / 8, r = T % 8;
     const int b = (int)blockIdx.x, x = b % 8, j = b / 8;
     const int L = x * q + (x < r ? x : r) + j;
-    stage_tile<PREC, MT, NT, KB, WMW, WNW, NST, STAGE, KIND>(a, L / nnt, L % nnt, (int)blockIdx.z);
+    stage_tile<PREC, MT, NT, KB, WMW, WNW, NST, G_, STAGE, KIND>(a, L / nnt, L % nnt, (int)blockIdx.z);
     if constexpr ((KIND == KIND_PRIMAL || KIND == KIND_SIB) && STAGE == 2) {
         if (blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0) a.step[0] += 1;
     }
@@ -1122,14 +1181,14 @@ __global__ __launch_bounds__(64 * WMW * WNW) void heun_stage_kernel(GemmArgs<PRE
 // points of a parameter scan), each with its own arguments, over one tile
 // list (point, M tile, column tile, copy) ordered longest-first; workgroup b
 // takes tiles b, b + grid, b + 2 grid, ...
-template <int PREC, int MT, int NT, int KB, int WMW, int WNW, int NST, int STAGE, int KIND>
+template <int PREC, int MT, int NT, int KB, int WMW, int WNW, int NST, int G_, int STAGE, int KIND>
 __global__ __launch_bounds__(64 * WMW * WNW) void heun_stage_grouped(const GemmArgs<PREC>* __restrict__ args,
                                                                      const int4* __restrict__ tiles, int ntiles,
                                                                      int64_t* step) {
     for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
         const int4 tt = tiles[t];
         __syncthreads();   // LDS of the previous tile is free
-        stage_tile<PREC, MT, NT, KB, WMW, WNW, NST, STAGE, KIND>(args[tt.x], tt.y, tt.z, tt.w);
+        stage_tile<PREC, MT, NT, KB, WMW, WNW, NST, G_, STAGE, KIND>(args[tt.x], tt.y, tt.z, tt.w);
     }
     if constexpr ((KIND == KIND_PRIMAL || KIND == KIND_SIB) && STAGE == 2) {
         if (blockIdx.x == 0 && threadIdx.x == 0) step[0] += 1;
@@ -1138,8 +1197,8 @@ __global__ __launch_bounds__(64 * WMW * WNW) void heun_stage_grouped(const GemmA
 
 template <int PREC, int CFG>
 struct CfgT {
-    static constexpr TileCfg C = kTiles[Prec<PREC>::NP - 1][CFG];
-    static constexpr int MT = C.mt, NT = C.nt, KB = C.kbytes, WMW = C.waves_m, WNW = C.waves_n, NST = C.nstage;
+    static constexpr TileCfg C = kTiles[tile_table(PREC)][CFG];
+    static constexpr int MT = C.mt, NT = C.nt, KB = C.kbytes, WMW = C.waves_m, WNW = C.waves_n, NST = C.nstage, G = C.group;
 };
 
 template <int PREC, int CFG, int STAGE, int KIND>
@@ -1149,7 +1208,7 @@ static int launch_kernel(const GemmArgs<PREC>& a, int64_t P, int64_t C2, int nco
     aa.nnt = (int)(C2 / C::NT);
     dim3 grid((unsigned)((P / C::MT) * (C2 / C::NT)), 1u, (unsigned)ncopy);
     dim3 block(64 * C::WMW * C::WNW);
-    hipLaunchKernelGGL((heun_stage_kernel<PREC, C::MT, C::NT, C::KB, C::WMW, C::WNW, C::NST, STAGE, KIND>), grid,
+    hipLaunchKernelGGL((heun_stage_kernel<PREC, C::MT, C::NT, C::KB, C::WMW, C::WNW, C::NST, C::G, STAGE, KIND>), grid,
                        block, 0, st, aa);
     TWA_HIP_CHECK(hipGetLastError());
     return TWA_OK;
@@ -1367,7 +1426,7 @@ template <int PREC, int CFG, int STAGE, int KIND>
 static int grouped_launch_k(const GroupedPlan& pl, int cur, int variant, hipStream_t st) {
     typedef CfgT<PREC, CFG> C;
     const int tl = variant == GV_TANGENT ? 1 : 0;
-    hipLaunchKernelGGL((heun_stage_grouped<PREC, C::MT, C::NT, C::KB, C::WMW, C::WNW, C::NST, STAGE, KIND>),
+    hipLaunchKernelGGL((heun_stage_grouped<PREC, C::MT, C::NT, C::KB, C::WMW, C::WNW, C::NST, C::G, STAGE, KIND>),
                        dim3((unsigned)pl.grid[tl]), dim3(64 * C::WMW * C::WNW), 0, st,
                        static_cast<const GemmArgs<PREC>*>(pl.d_args[variant][STAGE - 1][cur]), pl.d_tiles[tl],
                        pl.ntiles[tl], pl.step);
@@ -1387,7 +1446,7 @@ static int grouped_occupancy() {
     typedef CfgT<PREC, CFG> C;
     int nb = 0;
     hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &nb, heun_stage_grouped<PREC, C::MT, C::NT, C::KB, C::WMW, C::WNW, C::NST, 1, KIND_PRIMAL>,
+        &nb, heun_stage_grouped<PREC, C::MT, C::NT, C::KB, C::WMW, C::WNW, C::NST, C::G, 1, KIND_PRIMAL>,
         64 * C::WMW * C::WNW, 0);
     return nb > 0 ? nb : 1;
 }
