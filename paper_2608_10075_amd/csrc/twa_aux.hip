@@ -186,50 +186,21 @@ int launch_reduce_state(const Geometry& g, const void* s, void* part, hipStream_
 }
 
 // ---------------------------------------------------------------------------
-// per-step noise: zeta^{x,y} of every (trajectory, spin) into the operand,
-// g^{x,y} of every trajectory.  The step index is read from device memory.
+// the noise of one step as a launch of its own (noise_block), into the normals
+// of even steps.  The step index is read from device memory.
 template <int PREC>
-__global__ void noise_kernel(int64_t N, int64_t B, int64_t P, int64_t Bp, uint32_t k0, uint32_t k1,
-                             uint32_t point, const int64_t* step, typename Prec<PREC>::G* Xop,
-                             typename Prec<PREC>::S* g, int64_t kt) {
-    typedef typename Prec<PREC>::S S;
-    // grid: x over Philox slots (pairs of spins), y over trajectories (strided)
-    const int64_t nslot = (N + 1) / 2;
-    const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= nslot) return;
-    const uint32_t n = (uint32_t)step[0];
-    for (int64_t k = blockIdx.y; k < B; k += gridDim.y) {
-        const U4 w = philox4x32_10(U4{(uint32_t)m, (uint32_t)k, n, TAG_PUMP | (point << 8)}, k0, k1);
-        S z0, z1, z2, z3;
-        box_muller(w.x, w.y, z0, z1);
-        box_muller(w.z, w.w, z2, z3);
-        const int64_t i = 2 * m;
-        const int64_t C2 = 2 * Bp, cx = opcol(k, 0), cy = opcol(k, 1);
-        put_x<PREC>(Xop, cx, P + i, C2, kt, z0);
-        put_x<PREC>(Xop, cy, P + i, C2, kt, z1);
-        if (i + 1 < N) {
-            put_x<PREC>(Xop, cx, P + i + 1, C2, kt, z2);
-            put_x<PREC>(Xop, cy, P + i + 1, C2, kt, z3);
-        }
-        if (m == 0) {
-            const U4 v = philox4x32_10(U4{0u, (uint32_t)k, n, TAG_COLLECTIVE | (point << 8)}, k0, k1);
-            S g0, g1;
-            box_muller(v.x, v.y, g0, g1);
-            g[k] = g0;
-            g[Bp + k] = g1;
-        }
-    }
+__global__ __launch_bounds__(256) void noise_kernel(int64_t N, int64_t B, int64_t P, int64_t Bp, uint32_t k0,
+                                                    uint32_t k1, uint32_t point, const int64_t* step,
+                                                    typename Prec<PREC>::G* Xop, typename Prec<PREC>::S* g, int kt) {
+    noise_block<PREC, 256>(blockIdx.x, N, B, P, Bp, kt, k0, k1, point, (uint32_t)step[0], Xop, g);
 }
 
 template <int PREC>
 static int noise_t(const Geometry& g, const EnsembleBuffers& b, const StepConsts& c, hipStream_t st) {
-    const int64_t nslot = (g.N + 1) / 2;
-    hipLaunchKernelGGL(noise_kernel<PREC>, dim3(nblocks(nslot, 256), (unsigned)std::min<int64_t>(g.B, 65535)),
-                       dim3(256), 0, st, g.N, g.B, g.P,
-                       g.Bp, c.key0,
-                       c.key1, (uint32_t)c.point, (const int64_t*)b.step,
+    hipLaunchKernelGGL(noise_kernel<PREC>, dim3((unsigned)noise_blocks<256>(g.N, g.B, g.kt)), dim3(256), 0, st, g.N,
+                       g.B, g.P, g.Bp, c.key0, c.key1, (uint32_t)c.point, (const int64_t*)b.step,
                        static_cast<typename Prec<PREC>::G*>(b.Xop), static_cast<typename Prec<PREC>::S*>(b.g),
-                       g.kt);
+                       (int)g.kt);
     TWA_HIP_CHECK(hipGetLastError());
     return TWA_OK;
 }
@@ -284,15 +255,6 @@ int launch_seed_tangents(const Geometry& g, const EnsembleBuffers& b, int cur, h
 // observation after a step: window moments (Kahan-compensated time sums per
 // trajectory), the two-time origin and lag sums per jackknife block.
 template <typename S>
-__device__ __forceinline__ void kahan_add(S* sum, S* comp, S v) {
-    const S s = *sum, c = *comp;
-    const S y = v - c;
-    const S t = s + y;
-    *comp = (t - s) - y;
-    *sum = t;
-}
-
-template <typename S>
 __global__ __launch_bounds__(256) void observe_kernel(int64_t B, int64_t Bp, int64_t nmt, int J, int64_t burnin,
                                                       int64_t stride, int64_t L, const int64_t* step, const S* part,
                                                       const S* tpart, int64_t tpart_copy, int tangents, S* mom,
@@ -310,13 +272,8 @@ __global__ __launch_bounds__(256) void observe_kernel(int64_t B, int64_t Bp, int
     for (int64_t k = klo + threadIdx.x; k < khi; k += blockDim.x) {
         S sxyz[3];
         tile_sums<S, 3>(part, nmt, Bp, k, 0, sxyz);
-        const S Sx = sxyz[0], Sy = sxyz[1], Sz = sxyz[2];
-        if (in_window) {
-            const S T2 = S(0.25) * (Sx * Sx + Sy * Sy);
-            const S v[5] = {T2, T2 * Sz, T2 * T2, Sz, Sz * Sz};
-#pragma unroll
-            for (int m = 0; m < 5; ++m) kahan_add(mom + (2 * m) * Bp + k, mom + (2 * m + 1) * Bp + k, v[m]);
-        }
+        const S Sx = sxyz[0], Sy = sxyz[1];
+        if (in_window) add_moments(sxyz, mom, Bp, k);
         if (origin) {
             sm0[k] = Sx;
             sm0[Bp + k] = Sy;

@@ -28,7 +28,6 @@ namespace twa {
 
 namespace {
 
-inline unsigned nblk(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
 
 // per-point description used by the grouped noise and observation kernels
 struct PointDesc {
@@ -44,13 +43,12 @@ struct PointDesc {
     double* lag;
 };
 
-// noise of every point for the current step; block b belongs to the point p
+// noise of every point for the step of the counter (the first one: stage 2
+// makes that of the next); block b belongs to the point p
 // with bstart[p] <= b < bstart[p + 1]
 template <int PREC>
 __global__ void noise_grouped_kernel(const PointDesc* __restrict__ pd, const int* __restrict__ bstart, int np,
                                      const int64_t* step) {
-    typedef typename Prec<PREC>::S S;
-    typedef typename Prec<PREC>::G G;
     const int b = blockIdx.x;
     int lo = 0, hi = np - 1;
     while (lo < hi) {
@@ -59,42 +57,9 @@ __global__ void noise_grouped_kernel(const PointDesc* __restrict__ pd, const int
         else hi = mid - 1;
     }
     const PointDesc d = pd[lo];
-    const int64_t nslot = (d.N + 1) / 2;
-    const int64_t t = (int64_t)(b - bstart[lo]) * blockDim.x + threadIdx.x;
-    if (t >= d.B * nslot) return;
-    const int64_t k = t / nslot, m = t % nslot;
-    const uint32_t n = (uint32_t)step[0];
-    const U4 w = philox4x32_10(U4{(uint32_t)m, (uint32_t)k, n, TAG_PUMP | (d.point << 8)}, d.key0, d.key1);
-    S z0, z1, z2, z3;
-    box_muller(w.x, w.y, z0, z1);
-    box_muller(w.z, w.w, z2, z3);
-    const int64_t i = 2 * m;
-    // operand column: [s ; zeta]
-    G* X = static_cast<G*>(d.Xop);
-    const int64_t C2 = 2 * d.Bp, cx = opcol(k, 0), cy = opcol(k, 1);
-    put_x<PREC>(X, cx, d.P + i, C2, d.kt, z0);
-    put_x<PREC>(X, cy, d.P + i, C2, d.kt, z1);
-    if (i + 1 < d.N) {
-        put_x<PREC>(X, cx, d.P + i + 1, C2, d.kt, z2);
-        put_x<PREC>(X, cy, d.P + i + 1, C2, d.kt, z3);
-    }
-    if (m == 0) {
-        const U4 v = philox4x32_10(U4{0u, (uint32_t)k, n, TAG_COLLECTIVE | (d.point << 8)}, d.key0, d.key1);
-        S g0, g1;
-        box_muller(v.x, v.y, g0, g1);
-        S* gg = static_cast<S*>(d.g);
-        gg[k] = g0;
-        gg[d.Bp + k] = g1;
-    }
-}
-
-template <typename S>
-__device__ __forceinline__ void kahan_add2(S* sum, S* comp, S v) {
-    const S s = *sum, c = *comp;
-    const S y = v - c;
-    const S t = s + y;
-    *comp = (t - s) - y;
-    *sum = t;
+    noise_block<PREC, 256>((uint32_t)(b - bstart[lo]), d.N, d.B, d.P, d.Bp, (int)d.kt, d.key0, d.key1, d.point,
+                           (uint32_t)step[0], static_cast<typename Prec<PREC>::G*>(d.Xop),
+                           static_cast<typename Prec<PREC>::S*>(d.g));
 }
 
 // observation after a step, one workgroup per (point, jackknife block j):
@@ -122,13 +87,8 @@ __global__ __launch_bounds__(256) void observe_grouped_kernel(const PointDesc* _
     for (int64_t k = klo + threadIdx.x; k < khi; k += blockDim.x) {
         S sxyz[3];
         tile_sums<S, 3>(part, nmt, Bp, k, 0, sxyz);
-        const S Sx = sxyz[0], Sy = sxyz[1], Sz = sxyz[2];
-        if (in_window) {
-            const S T2 = S(0.25) * (Sx * Sx + Sy * Sy);
-            const S v[5] = {T2, T2 * Sz, T2 * T2, Sz, Sz * Sz};
-#pragma unroll
-            for (int m = 0; m < 5; ++m) kahan_add2(mom + (2 * m) * Bp + k, mom + (2 * m + 1) * Bp + k, v[m]);
-        }
+        const S Sx = sxyz[0], Sy = sxyz[1];
+        if (in_window) add_moments(sxyz, mom, Bp, k);
         if (origin) {
             sm0[k] = Sx;
             sm0[Bp + k] = Sy;
@@ -166,11 +126,13 @@ struct StepKind {
 };
 struct Plan {
     int64_t burnin, L, stride, tan_end;
+    // without lags a state is observed by the stage 1 that starts from it, the
+    // last one by a launch of its own
     StepKind kind(int64_t n) const {
         StepKind k;
         k.tan_active = L > 0 && n >= burnin && n < tan_end;
         k.seed_after = L > 0 && n + 1 == burnin;
-        k.observe = (n + 1 > burnin) || k.seed_after;
+        k.observe = L > 0 && ((n + 1 > burnin) || k.seed_after);
         k.tobs = L > 0 && n + 1 >= burnin && n + 1 <= tan_end;
         return k;
     }
@@ -225,6 +187,39 @@ int launch_observe_grouped(Bucket& bk, bool tobs, hipStream_t st) {
     return TWA_OK;
 }
 
+// the noise of the first step of every point of a bucket
+int launch_first_noise(Bucket& bk, hipStream_t st) {
+    const int np = (int)bk.gs.size();
+    const unsigned nb = (unsigned)bk.nblocks_noise;
+    switch (bk.gs[0].precision) {
+        case TWA_PREC_FP64:
+            hipLaunchKernelGGL(noise_grouped_kernel<TWA_PREC_FP64>, dim3(nb), dim3(256), 0, st, bk.d_pd, bk.d_bstart,
+                               np, (const int64_t*)bk.step);
+            break;
+        case TWA_PREC_FP32:
+            hipLaunchKernelGGL(noise_grouped_kernel<TWA_PREC_FP32>, dim3(nb), dim3(256), 0, st, bk.d_pd, bk.d_bstart,
+                               np, (const int64_t*)bk.step);
+            break;
+        case TWA_PREC_BF16:
+            hipLaunchKernelGGL(noise_grouped_kernel<TWA_PREC_BF16>, dim3(nb), dim3(256), 0, st, bk.d_pd, bk.d_bstart,
+                               np, (const int64_t*)bk.step);
+            break;
+        case TWA_PREC_FP16:
+            hipLaunchKernelGGL(noise_grouped_kernel<TWA_PREC_FP16>, dim3(nb), dim3(256), 0, st, bk.d_pd, bk.d_bstart,
+                               np, (const int64_t*)bk.step);
+            break;
+        case TWA_PREC_BF16X3:
+            hipLaunchKernelGGL(noise_grouped_kernel<TWA_PREC_BF16X3>, dim3(nb), dim3(256), 0, st, bk.d_pd,
+                               bk.d_bstart, np, (const int64_t*)bk.step);
+            break;
+        default:
+            set_error("twa_run_batch: precision must be FP64, FP32, BF16, FP16 or split BF16");
+            return TWA_EINVAL;
+    }
+    TWA_HIP_CHECK(hipGetLastError());
+    return TWA_OK;
+}
+
 int build_bucket(const BatchSpec& sp, const std::vector<int>& idx, int cfg, Bucket& bk, hipStream_t st) {
     int rc;
     const twa_batch_opts* o = sp.o;
@@ -236,7 +231,7 @@ int build_bucket(const BatchSpec& sp, const std::vector<int>& idx, int cfg, Buck
     bk.cs.resize((size_t)np);
     bk.J = (int)std::min<int64_t>(32, o->n_traj);
     const bool tangents = sp.L > 0;
-    if (device_malloc(&bk.step, sizeof(int64_t)) != hipSuccess) {
+    if (device_malloc(&bk.step, 2 * sizeof(int64_t)) != hipSuccess) {
         set_error("twa_run_batch: allocation failed");
         return TWA_ENOMEM;
     }
@@ -254,6 +249,8 @@ int build_bucket(const BatchSpec& sp, const std::vector<int>& idx, int cfg, Buck
         if ((rc = ar.commit(false, st))) return rc;
         b.block = ar.detach();
         b.step = bk.step;   // one step counter for the bucket
+        b.ahead = true;
+        b.fold = sp.L == 0;
         StepConsts& c = bk.cs[(size_t)q];
         c.c1 = 0.5 * o->gamma * pt.dt;
         c.c2 = std::sqrt(o->gamma * pt.dt);
@@ -290,7 +287,7 @@ int build_bucket(const BatchSpec& sp, const std::vector<int>& idx, int cfg, Buck
         d.tpart0 = b.tpart[0];
         d.sm0 = b.sm0;
         d.lag = b.lag;
-        bstart[(size_t)q + 1] = bstart[(size_t)q] + (int)nblk(g.B * ((g.N + 1) / 2), 256);
+        bstart[(size_t)q + 1] = bstart[(size_t)q] + (int)noise_blocks<256>(g.N, g.B, g.kt);
     }
     bk.nblocks_noise = bstart[(size_t)np];
     TWA_HIP_CHECK(hipMalloc(&bk.d_pd, pd.size() * sizeof(PointDesc)));
@@ -299,7 +296,7 @@ int build_bucket(const BatchSpec& sp, const std::vector<int>& idx, int cfg, Buck
     TWA_HIP_CHECK(hipMemcpyAsync(bk.d_bstart, bstart.data(), bstart.size() * sizeof(int), hipMemcpyHostToDevice,
                                  st));
     TWA_HIP_CHECK(hipStreamSynchronize(st));   // the host arrays end with this function
-    TWA_HIP_CHECK(hipMemsetAsync(bk.step, 0, sizeof(int64_t), st));
+    TWA_HIP_CHECK(hipMemsetAsync(bk.step, 0, 2 * sizeof(int64_t), st));
     if ((rc = grouped_prepare(bk.gs, bk.bs, bk.cs, bk.step, tangents, bk.plan, st))) return rc;
     if (sp.L > 0 && sp.burnin == 0) {
         // the origin is the initial state: seed the response copies and observe it
@@ -307,41 +304,14 @@ int build_bucket(const BatchSpec& sp, const std::vector<int>& idx, int cfg, Buck
             if ((rc = launch_seed_tangents(bk.gs[(size_t)q], bk.bs[(size_t)q], 0, st))) return rc;
         if ((rc = launch_observe_grouped(bk, true, st))) return rc;
     }
-    return TWA_OK;
+    return launch_first_noise(bk, st);
 }
 
 // one step of one bucket (the step counter on the device advances in the
-// corrector launch), on stream st
+// corrector launch, which also makes the next step's noise), on stream st
 int bucket_step(Bucket& bk, int cur, const StepKind& k, hipStream_t st) {
     int rc;
     const int np = (int)bk.gs.size();
-    const unsigned nb = (unsigned)bk.nblocks_noise;
-    switch (bk.gs[0].precision) {
-        case TWA_PREC_FP64:
-            hipLaunchKernelGGL(noise_grouped_kernel<TWA_PREC_FP64>, dim3(nb), dim3(256), 0, st, bk.d_pd, bk.d_bstart,
-                               np, (const int64_t*)bk.step);
-            break;
-        case TWA_PREC_FP32:
-            hipLaunchKernelGGL(noise_grouped_kernel<TWA_PREC_FP32>, dim3(nb), dim3(256), 0, st, bk.d_pd, bk.d_bstart,
-                               np, (const int64_t*)bk.step);
-            break;
-        case TWA_PREC_BF16:
-            hipLaunchKernelGGL(noise_grouped_kernel<TWA_PREC_BF16>, dim3(nb), dim3(256), 0, st, bk.d_pd, bk.d_bstart,
-                               np, (const int64_t*)bk.step);
-            break;
-        case TWA_PREC_FP16:
-            hipLaunchKernelGGL(noise_grouped_kernel<TWA_PREC_FP16>, dim3(nb), dim3(256), 0, st, bk.d_pd, bk.d_bstart,
-                               np, (const int64_t*)bk.step);
-            break;
-        case TWA_PREC_BF16X3:
-            hipLaunchKernelGGL(noise_grouped_kernel<TWA_PREC_BF16X3>, dim3(nb), dim3(256), 0, st, bk.d_pd,
-                               bk.d_bstart, np, (const int64_t*)bk.step);
-            break;
-        default:
-            set_error("twa_run_batch: precision must be FP64, FP32, BF16, FP16 or split BF16");
-            return TWA_EINVAL;
-    }
-    TWA_HIP_CHECK(hipGetLastError());
     const int pv = k.tan_active ? GV_PRIMAL_TAN : GV_PRIMAL;
     if ((rc = grouped_launch(bk.plan, 1, cur, pv, st))) return rc;
     if (k.tan_active && (rc = grouped_launch(bk.plan, 1, cur, GV_TANGENT, st))) return rc;
@@ -633,6 +603,9 @@ int run_batch(const twa_point* pts, int np, const twa_batch_opts* o, twa_observa
     hipEventRecord(e0, st);
     if ((rc = run_steps(bks, plan, 0, o->n_steps, cur, o->use_graph != 0, GS, o->progress_every, st, ev, gset)))
         goto cleanup;
+    if (L == 0 && o->n_steps > burnin)
+        for (auto& bk : bks)
+            if ((rc = launch_observe_grouped(bk, false, st))) goto cleanup;
     hipEventRecord(e1, st);
     if (hipStreamSynchronize(st) != hipSuccess) {
         set_error("twa_run_batch: step kernels failed");

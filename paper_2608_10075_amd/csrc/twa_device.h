@@ -233,4 +233,71 @@ __device__ __forceinline__ void put_x(typename Prec<PREC>::G* X, int64_t c, int6
     put_op<PREC>(X + x_index(c, i, C2, kt, Prec<PREC>::NP, 0), C2 * kt, v);
 }
 
+// four elements i .. i + 3 (i % 4 == 0, so they share a K stage) of column c
+// of a column operand, all their parts, one store each (FP64 two)
+template <int PREC>
+__device__ __forceinline__ void put_x4(typename Prec<PREC>::G* X, int64_t c, int64_t i, int64_t C2, int64_t kt,
+                                       const typename Prec<PREC>::S (&v)[4]) {
+    constexpr int NP = Prec<PREC>::NP;
+    typename Prec<PREC>::G* p = X + x_index(c, i, C2, kt, NP, 0);
+    if constexpr (PREC == TWA_PREC_FP64) {
+        reinterpret_cast<double2*>(p)[0] = make_double2(v[0], v[1]);
+        reinterpret_cast<double2*>(p)[1] = make_double2(v[2], v[3]);
+    } else if constexpr (NP > 1) {
+        uint16_t h[4][NP];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) bf16_parts<NP>(v[r], h[r]);
+#pragma unroll
+        for (int q = 0; q < NP; ++q)
+            *reinterpret_cast<ushort4*>(p + q * C2 * kt) = make_ushort4(h[0][q], h[1][q], h[2][q], h[3][q]);
+    } else {
+        uint16_t h[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) h[r] = __builtin_bit_cast(uint16_t, Prec<PREC>::to_g(v[r]));
+        *reinterpret_cast<ushort4*>(p) = make_ushort4(h[0], h[1], h[2], h[3]);
+    }
+}
+
+// The normals of one step: zeta^{x,y} of every (trajectory, spin) into the
+// noise rows of the column operand, g^{x,y} of every trajectory.  A block of
+// NT threads takes one K stage of NT / (kt / 4) neighbouring trajectories, four
+// spins of one trajectory to a thread: its stores fill whole runs of kt
+// elements of neighbouring columns, 8 bytes a lane (one spin a thread stored 2
+// bytes at a time: 4.8 us a launch at N x B = 201 x 500, 16.9 at 1000 x 4096).
+// Rows past N of the last stage stay zero.
+template <int NT>
+__host__ __device__ inline int64_t noise_blocks(int64_t N, int64_t B, int64_t kt) {
+    const int64_t tpb = NT / (kt / 4);
+    return ((N + kt - 1) / kt) * ((B + tpb - 1) / tpb);
+}
+template <int PREC, int NT>
+__device__ __forceinline__ void noise_block(uint32_t blk, int64_t N, int64_t B, int64_t P, int64_t Bp, int kt,
+                                            uint32_t k0, uint32_t k1, uint32_t point, uint32_t n,
+                                            typename Prec<PREC>::G* Xop, typename Prec<PREC>::S* g) {
+    typedef typename Prec<PREC>::S S;
+    const uint32_t nst = (uint32_t)((N + kt - 1) / kt), qs = (uint32_t)kt / 4;
+    const uint32_t stg = blk % nst, tid = threadIdx.x;
+    const int64_t k = (int64_t)(blk / nst) * (NT / qs) + tid / qs, i = (int64_t)stg * kt + 4 * (tid % qs);
+    if (k >= B || i >= N) return;
+    S x[4], y[4];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const U4 w = philox4x32_10(U4{(uint32_t)(i / 2) + h, (uint32_t)k, n, TAG_PUMP | (point << 8)}, k0, k1);
+        box_muller(w.x, w.y, x[2 * h], y[2 * h]);
+        box_muller(w.z, w.w, x[2 * h + 1], y[2 * h + 1]);
+    }
+#pragma unroll
+    for (int r = 1; r < 4; ++r)
+        if (i + r >= N) x[r] = y[r] = S(0);
+    put_x4<PREC>(Xop, opcol(k, 0), P + i, 2 * Bp, kt, x);
+    put_x4<PREC>(Xop, opcol(k, 1), P + i, 2 * Bp, kt, y);
+    if (i == 0) {
+        const U4 v = philox4x32_10(U4{0u, (uint32_t)k, n, TAG_COLLECTIVE | (point << 8)}, k0, k1);
+        S g0, g1;
+        box_muller(v.x, v.y, g0, g1);
+        g[k] = g0;
+        g[Bp + k] = g1;
+    }
+}
+
 }  // namespace twa

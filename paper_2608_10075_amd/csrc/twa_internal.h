@@ -154,7 +154,10 @@ struct EnsembleBuffers {
     void* Sn = nullptr;         // ST [2][Bp] collective sums S^x, S^y of the step's input state
     void* Y = nullptr;          // ST [2][Bp][P] contraction output of stage 1 (and 2)
     void* part[2] = {nullptr, nullptr};// ST [3][nmt][Bp] partial spin sums: [0] current state, [1] predictor
-    void* g = nullptr;          // ST [2][Bp] collective normals of the step
+    void* g = nullptr;          // ST [2][2][Bp] collective normals of the steps of either parity
+    bool ahead = false;         // stage 2 makes the next step's noise (into the other parity's normals),
+                                // stage 1 observes the state it starts from where fold is set
+    bool fold = false;
     void* norm0 = nullptr;      // ST [Bp][P]
     void* mom = nullptr;        // ST [5][2][Bp] Kahan (sum, compensation)
     // response copies (two-time)
@@ -174,7 +177,7 @@ struct EnsembleBuffers {
     void* UZ = nullptr;         // ST [Bp][P] (G o G) s^z
     void* dg = nullptr;         // ST [P] diagonal of G
     double* gmom = nullptr;     // [9][2][Bp] Kahan (sum, compensation) of the estimator quantities
-    int64_t* step = nullptr;    // device step counter
+    int64_t* step = nullptr;    // device step counter; [1]: the next step, written by stage 1 (ahead)
     float* diag = nullptr;      // per-block max norm deviation / nan flags
 };
 
@@ -233,9 +236,11 @@ int launch_gemm_call(const Geometry& g, const GemmCall& c, hipStream_t st);
 enum { GV_PRIMAL = 0, GV_PRIMAL_TAN = 1, GV_TANGENT = 2, GV_COUNT = 3 };
 struct GroupedPlan {
     void* d_args[GV_COUNT][2][2] = {};   // [variant][stage-1][cur] per-ensemble arguments
-    int4* d_tiles[2] = {nullptr, nullptr};   // [0] (point, M tile, column tile, 0); [1] also copy 1
-    int ntiles[2] = {0, 0};
-    int grid[2] = {0, 0};
+    // (point, M tile, column tile, copy): [0] stage 1, with observation blocks
+    // (point, block, -, -1); [1] both response copies; [2] stage 2, with noise blocks
+    int4* d_tiles[3] = {nullptr, nullptr, nullptr};
+    int ntiles[3] = {0, 0, 0};
+    int grid[3] = {0, 0, 0};
     int cfg = 0, precision = 0, integrator = TWA_INT_HEUN;
     bool tangents = false;
     int64_t* step = nullptr;
@@ -327,6 +332,26 @@ __device__ __forceinline__ void tile_sums(const S* part, int64_t nmt, int64_t Bp
     for (; q < nmt; ++q)
 #pragma unroll
         for (int c = 0; c < NC; ++c) out[c] += part[((c0 + c) * nmt + q) * Bp + k];
+}
+
+// v added to a Kahan-compensated sum
+template <typename S>
+__device__ __forceinline__ void kahan_add(S* sum, S* comp, S v) {
+    const S s = *sum, c = *comp;
+    const S y = v - c;
+    const S t = s + y;
+    *comp = (t - s) - y;
+    *sum = t;
+}
+
+// the window moments (T2, T3, T4, Z, ZZ) of one trajectory's spin sums added to
+// its time sums mom [5][2][Bp]
+template <typename S>
+__device__ __forceinline__ void add_moments(const S (&s)[3], S* mom, int64_t Bp, int64_t k) {
+    const S T2 = S(0.25) * (s[0] * s[0] + s[1] * s[1]);
+    const S v[5] = {T2, T2 * s[2], T2 * T2, s[2], s[2] * s[2]};
+#pragma unroll
+    for (int m = 0; m < 5; ++m) kahan_add(mom + (2 * m) * Bp + k, mom + (2 * m + 1) * Bp + k, v[m]);
 }
 
 }  // namespace twa

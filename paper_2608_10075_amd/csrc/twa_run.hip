@@ -420,9 +420,9 @@ void add_buffers(const Geometry& g, bool tangents, int64_t L, int J, bool contra
     const size_t ck = g.coh ? 1 : 0;                              // coherent exchange: one more K block
     // zero at the start: what a run reads before it writes all of (padding of
     // the noise columns, normals of padding trajectories, sums, counters)
-    ar.add(b.g, 2 * Bp * se, true);
+    ar.add(b.g, 4 * Bp * se, true);
     ar.add(b.mom, 10 * Bp * se, true);
-    ar.add(b.step, sizeof(int64_t), true);
+    ar.add(b.step, 2 * sizeof(int64_t), true);
     ar.add(b.diag, 2 * 1024 * sizeof(float), true);
     ar.add(b.sm0, 2 * Bp * se, true);
     if (L > 0) ar.add(b.lag, (size_t)L * J * 6 * sizeof(double), true);

@@ -13,7 +13,7 @@ namespace twa {
 int launch_step_kernels(const Geometry& g, EnsembleBuffers& b, const StepConsts& c, int cur, bool tan_active,
                         GemmTimers* tm, hipStream_t st) {
     int rc;
-    if ((rc = launch_noise(g, b, c, st))) return rc;
+    if (!b.ahead && (rc = launch_noise(g, b, c, st))) return rc;
     if (tm) tm->s1.begin(st);
     // the primal predictor increment is stored only when the response copies
     // of the step read it; otherwise the corrector recomputes it
@@ -36,11 +36,12 @@ struct StepKind {
 
 struct Plan {
     int64_t burnin, L, stride, tan_end;
+    bool each;   // a launch after every step observes (with fold only where decay estimators need it)
     StepKind kind(int64_t n) const {
         StepKind k;
         k.tan_active = L > 0 && n >= burnin && n < tan_end;
         k.seed_after = L > 0 && n + 1 == burnin;
-        k.observe = (n + 1 > burnin) || k.seed_after;
+        k.observe = each && ((n + 1 > burnin) || k.seed_after);
         k.tobs = L > 0 && n + 1 >= burnin && n + 1 <= tan_end;
         return k;
     }
@@ -51,7 +52,7 @@ int one_step(const Geometry& g, EnsembleBuffers& b, const StepConsts& c, int& cu
     int rc;
     if ((rc = launch_step_kernels(g, b, c, cur, k.tan_active, tm, st))) return rc;
     if (k.seed_after && (rc = launch_seed_tangents(g, b, 1 - cur, st))) return rc;
-    if (k.observe && (rc = launch_observe(g, b, c, 1 - cur, k.tobs, st))) return rc;
+    if (k.observe && !b.fold && (rc = launch_observe(g, b, c, 1 - cur, k.tobs, st))) return rc;
     if (decay && k.observe && (rc = launch_decay_observe(g, b, 1 - cur, st))) return rc;
     cur = 1 - cur;
     return TWA_OK;
@@ -180,7 +181,7 @@ int run_single(const twa_params* p, int64_t n_traj, double dt, int64_t n_steps, 
     c.lag_stride = stride;
     c.n_lags = L;
     c.J = J;
-    Plan plan{burnin, L, stride, burnin + (L > 0 ? (L - 1) * stride : 0)};
+    Plan plan{burnin, L, stride, burnin + (L > 0 ? (L - 1) * stride : 0), L > 0 || decay};
     const bool use_graph = p->use_graph && !p->timing;
     const int GS = 16;   // steps per captured graph (even: the state ping-pong returns to its parity)
     int cur = 0;
@@ -246,6 +247,11 @@ int run_single(const twa_params* p, int64_t n_traj, double dt, int64_t n_steps, 
         TWA_TRY(launch_toeplitz_run(g, b, c, toep_tw, toep_spec, n_steps, cur, st));
         n = n_steps;
     }
+    if (n < n_steps) {
+        b.ahead = true;
+        b.fold = L == 0;
+        TWA_TRY(launch_noise(g, b, c, st));   // of the first step
+    }
     while (n < n_steps) {
         const StepKind k = plan.kind(n);
         int64_t run = 1;
@@ -277,6 +283,7 @@ int run_single(const twa_params* p, int64_t n_traj, double dt, int64_t n_steps, 
             n += 1;
         }
     }
+    if (b.fold && n_steps > burnin) TWA_TRY(launch_observe(g, b, c, cur, false, st));
     TWA_HTRY(hipEventRecord(e1, st));
     TWA_TRY(launch_finish(g, b, cur, nblk, st));
     hmom.resize((size_t)10 * g.Bp);

@@ -73,7 +73,7 @@ void grouped_free(GroupedPlan& pl) {
     for (int v = 0; v < GV_COUNT; ++v)
         for (int s = 0; s < 2; ++s)
             for (int c = 0; c < 2; ++c) hipFree(pl.d_args[v][s][c]);
-    for (int t = 0; t < 2; ++t) hipFree(pl.d_tiles[t]);
+    for (int t = 0; t < 3; ++t) hipFree(pl.d_tiles[t]);
     pl = GroupedPlan();
 }
 

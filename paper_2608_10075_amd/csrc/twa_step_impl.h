@@ -72,6 +72,13 @@ struct GemmArgs {
     int64_t t_part_copy;    // element offset between copies of partial sums
     int64_t t_op_copy;      // element offset between copies of operands
     int64_t* step;          // advanced by stage 2 of the primal (block 0)
+    // blocks past the tiles (primal): stage 1 observes the state it starts
+    // from, stage 2 makes the next step's noise
+    int64_t* step_next;     // stage 1 (block 0) writes the next step's index, stage 2's noise reads it
+    S* ob_mom;              // stage 1: window sums (nullptr: no observation)
+    int64_t ob_burnin;
+    S* nz_g;                // stage 2: the next step's collective normals (nullptr: no noise)
+    uint32_t nz_k0, nz_k1, nz_point;
     S* Y2out;               // primal stage 2: where the stage-2 field goes (nullptr: in place into Y)
     // store kind: out = in + sign * acc
     const S* Sin;
@@ -1159,6 +1166,30 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     }
 }
 
+// Blocks past the tiles of a primal stage.  Stage 1: window sums of the state
+// that the step starts from.  Stage 2: the noise of the next step.  As launches
+// of their own they took 6.0 and 4.8 us of 27 per step at N x B = 201 x 500,
+// most of it the launch; here they run beside the tiles.
+template <int PREC, int NTHR, int STAGE>
+__host__ __device__ inline int64_t extra_blocks(const GemmArgs<PREC>& a, int64_t kt) {
+    if (STAGE == 1) return a.ob_mom ? (a.B + NTHR - 1) / NTHR : 0;
+    return a.nz_g ? noise_blocks<NTHR>(a.N, a.B, kt) : 0;
+}
+template <int PREC, int NTHR, int STAGE>
+__device__ __forceinline__ void extra_block(const GemmArgs<PREC>& a, uint32_t blk, int kt) {
+    if constexpr (STAGE == 1) {
+        typedef typename Prec<PREC>::S S;
+        const int64_t k = (int64_t)blk * NTHR + threadIdx.x;
+        if (k >= a.B || a.step[0] <= a.ob_burnin) return;
+        S sums[3];
+        tile_sums<S, 3>(a.part_prim, a.nmt, a.Bp, k, 0, sums);
+        add_moments(sums, a.ob_mom, a.Bp, k);
+    } else {
+        noise_block<PREC, NTHR>(blk, a.N, a.B, a.P, a.Bp, kt, a.nz_k0, a.nz_k1, a.nz_point,
+                                (uint32_t)a.step_next[0], a.Xnext, a.nz_g);
+    }
+}
+
 // One launch = one stage of one ensemble.  XCD-aware tile order: workgroups
 // are dispatched round-robin over the 8 XCDs, so workgroup b runs on XCD b % 8.
 // Each XCD is given a contiguous range of tiles ordered M-tile-major, so the
@@ -1166,32 +1197,52 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
 // together) in that XCD's L2.
 template <int PREC, int MT, int NT, int KB, int WMW, int WNW, int NST, int G_, int STAGE, int KIND>
 __global__ __launch_bounds__(64 * WMW * WNW) void heun_stage_kernel(GemmArgs<PREC> a) {
+    constexpr bool PRIM = KIND == KIND_PRIMAL || KIND == KIND_SIB;
+    constexpr int NTHR = 64 * WMW * WNW, KT = KB / (int)sizeof(typename Prec<PREC>::G);
     const int nnt = a.nnt;            // column tiles
-    const int T = (int)gridDim.x;     // total tiles = nmt * nnt
+    const int T = PRIM ? (int)a.nmt * nnt : (int)gridDim.x;   // total tiles
+    if constexpr (PRIM) {
+        if ((int)blockIdx.x >= T) return extra_block<PREC, NTHR, STAGE>(a, blockIdx.x - T, KT);
+    }
     const int q = T / 8, r = T % 8;
     const int b = (int)blockIdx.x, x = b % 8, j = b / 8;
     const int L = x * q + (x < r ? x : r) + j;
     stage_tile<PREC, MT, NT, KB, WMW, WNW, NST, G_, STAGE, KIND>(a, L / nnt, L % nnt, (int)blockIdx.z);
-    if constexpr ((KIND == KIND_PRIMAL || KIND == KIND_SIB) && STAGE == 2) {
-        if (blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0) a.step[0] += 1;
+    if constexpr (PRIM) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            if constexpr (STAGE == 2) a.step[0] += 1;
+            else if (a.step_next) a.step_next[0] = a.step[0] + 1;
+        }
     }
 }
 
 // Grouped persistent launch: the stage of many independent ensembles (the
 // points of a parameter scan), each with its own arguments, over one tile
 // list (point, M tile, column tile, copy) ordered longest-first; workgroup b
-// takes tiles b, b + grid, b + 2 grid, ...
+// takes tiles b, b + grid, b + 2 grid, ...  The blocks past the tiles of a
+// primal stage (copy -1) come last.
 template <int PREC, int MT, int NT, int KB, int WMW, int WNW, int NST, int G_, int STAGE, int KIND>
 __global__ __launch_bounds__(64 * WMW * WNW) void heun_stage_grouped(const GemmArgs<PREC>* __restrict__ args,
                                                                      const int4* __restrict__ tiles, int ntiles,
                                                                      int64_t* step) {
+    constexpr bool PRIM = KIND == KIND_PRIMAL || KIND == KIND_SIB;
+    constexpr int NTHR = 64 * WMW * WNW, KT = KB / (int)sizeof(typename Prec<PREC>::G);
     for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
         const int4 tt = tiles[t];
+        if constexpr (PRIM) {
+            if (tt.w < 0) {
+                extra_block<PREC, NTHR, STAGE>(args[tt.x], (uint32_t)tt.y, KT);
+                continue;
+            }
+        }
         __syncthreads();   // LDS of the previous tile is free
         stage_tile<PREC, MT, NT, KB, WMW, WNW, NST, G_, STAGE, KIND>(args[tt.x], tt.y, tt.z, tt.w);
     }
-    if constexpr ((KIND == KIND_PRIMAL || KIND == KIND_SIB) && STAGE == 2) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) step[0] += 1;
+    if constexpr (PRIM) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            if constexpr (STAGE == 2) step[0] += 1;
+            else step[1] = step[0] + 1;
+        }
     }
 }
 
@@ -1206,7 +1257,10 @@ static int launch_kernel(const GemmArgs<PREC>& a, int64_t P, int64_t C2, int nco
     typedef CfgT<PREC, CFG> C;
     GemmArgs<PREC> aa = a;
     aa.nnt = (int)(C2 / C::NT);
-    dim3 grid((unsigned)((P / C::MT) * (C2 / C::NT)), 1u, (unsigned)ncopy);
+    constexpr bool PRIM = KIND == KIND_PRIMAL || KIND == KIND_SIB;
+    const int64_t kt = C::KB / (int)sizeof(typename Prec<PREC>::G);
+    const int64_t extra = PRIM ? extra_blocks<PREC, 64 * C::WMW * C::WNW, STAGE>(aa, kt) : 0;
+    dim3 grid((unsigned)((P / C::MT) * (C2 / C::NT) + extra), 1u, (unsigned)ncopy);
     dim3 block(64 * C::WMW * C::WNW);
     hipLaunchKernelGGL((heun_stage_kernel<PREC, C::MT, C::NT, C::KB, C::WMW, C::WNW, C::NST, C::G, STAGE, KIND>), grid,
                        block, 0, st, aa);
@@ -1307,9 +1361,22 @@ static GemmArgs<PREC> make_args(const Geometry& g, const EnsembleBuffers& b, con
     a.Sn = static_cast<S*>(b.Sn);
     a.Y = static_cast<S*>(b.Y);
     a.Dop = static_cast<G*>(b.Dop);
-    a.g = static_cast<const S*>(b.g);
+    a.g = static_cast<const S*>(b.g) + (b.ahead ? cur * 2 * Bp : 0);
     a.store_y2 = store_y2 ? 1 : 0;
     a.step = b.step;
+    if (b.ahead && !tangent) {
+        a.step_next = b.step + 1;
+        if (stage == 1 && b.fold) {
+            a.ob_mom = static_cast<S*>(b.mom);
+            a.ob_burnin = c.burnin;
+        }
+        if (stage == 2) {
+            a.nz_g = static_cast<S*>(b.g) + (1 - cur) * 2 * Bp;
+            a.nz_k0 = c.key0;
+            a.nz_k1 = c.key1;
+            a.nz_point = (uint32_t)c.point;
+        }
+    }
     a.t_state_copy = 3 * Bp * P;
     a.t_y_copy = 2 * Bp * P;
     a.t_part_copy = 3 * g.nmt * Bp;
@@ -1425,7 +1492,7 @@ int launch_call_p(const Geometry& g, const GemmCall& c, hipStream_t st) {
 template <int PREC, int CFG, int STAGE, int KIND>
 static int grouped_launch_k(const GroupedPlan& pl, int cur, int variant, hipStream_t st) {
     typedef CfgT<PREC, CFG> C;
-    const int tl = variant == GV_TANGENT ? 1 : 0;
+    const int tl = variant == GV_TANGENT ? 1 : STAGE == 1 ? 0 : 2;
     hipLaunchKernelGGL((heun_stage_grouped<PREC, C::MT, C::NT, C::KB, C::WMW, C::WNW, C::NST, C::G, STAGE, KIND>),
                        dim3((unsigned)pl.grid[tl]), dim3(64 * C::WMW * C::WNW), 0, st,
                        static_cast<const GemmArgs<PREC>*>(pl.d_args[variant][STAGE - 1][cur]), pl.d_tiles[tl],
@@ -1459,8 +1526,7 @@ static int grouped_dispatch(const GroupedPlan& pl, int stage, int cur, int varia
 
 // XCD-aware order of a tile list: within every full round of `grid` tiles,
 // XCD x (workgroups w with w % 8 == x) gets a contiguous block of the list
-inline void xcd_permute(std::vector<int4>& tiles, int grid) {
-    const int ntl = (int)tiles.size();
+inline void xcd_permute(std::vector<int4>& tiles, int grid, int ntl) {
     if (grid % 8 != 0) return;
     std::vector<int4> perm(tiles);
     const int per = grid / 8;
@@ -1511,18 +1577,32 @@ int grouped_prepare_p(const std::vector<Geometry>& gs, const std::vector<Ensembl
     std::vector<int> order((size_t)np);
     for (int p = 0; p < np; ++p) order[(size_t)p] = p;
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return gs[(size_t)x].P > gs[(size_t)y].P; });
-    for (int tl = 0; tl < (tangents ? 2 : 1); ++tl) {
+    const int64_t nthr = 64 * tc.waves_m * tc.waves_n;
+    for (int tl = 0; tl < 3; ++tl) {
+        if (tl == 1 && !tangents) continue;
         std::vector<int4> tiles;
         for (int p : order) {
             const Geometry& g = gs[(size_t)p];
             const int nnt = (int)(g.C2 / tc.nt);
             for (int mt = 0; mt < (int)g.nmt; ++mt)
                 for (int nt = 0; nt < nnt; ++nt)
-                    for (int cp = 0; cp < (tl ? 2 : 1); ++cp) tiles.push_back(make_int4(p, mt, nt, cp));
+                    for (int cp = 0; cp < (tl == 1 ? 2 : 1); ++cp) tiles.push_back(make_int4(p, mt, nt, cp));
+        }
+        // whole rounds of tiles are permuted, the blocks past them stay last
+        const int ngemm = (int)tiles.size();
+        for (int p : order) {
+            const Geometry& g = gs[(size_t)p];
+            int64_t n = 0;
+            if (tl == 0 && bs[(size_t)p].fold) n = (g.B + nthr - 1) / nthr;
+            if (tl == 2 && bs[(size_t)p].ahead) {
+                const int64_t tpb = nthr / (g.kt / 4);
+                n = ((g.N + g.kt - 1) / g.kt) * ((g.B + tpb - 1) / tpb);
+            }
+            for (int q = 0; q < (int)n; ++q) tiles.push_back(make_int4(p, q, 0, -1));
         }
         const int ntl = (int)tiles.size();
         const int grid = std::max(1, std::min(ncu * occ, ntl));
-        xcd_permute(tiles, grid);
+        xcd_permute(tiles, std::min(grid, ngemm), ngemm);
         TWA_HIP_CHECK(hipMalloc((void**)&pl.d_tiles[tl], tiles.size() * sizeof(int4)));
         TWA_HIP_CHECK(hipMemcpyAsync(pl.d_tiles[tl], tiles.data(), tiles.size() * sizeof(int4), hipMemcpyHostToDevice,
                                      st));
