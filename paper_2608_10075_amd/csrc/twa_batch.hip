@@ -43,8 +43,7 @@ struct PointDesc {
     double* lag;
 };
 
-// noise of every point for the step of the counter (the first one: stage 2
-// makes that of the next); block b belongs to the point p
+// noise of every point for the step of the counter; block b belongs to the point p
 // with bstart[p] <= b < bstart[p + 1]
 template <int PREC>
 __global__ void noise_grouped_kernel(const PointDesc* __restrict__ pd, const int* __restrict__ bstart, int np,
@@ -187,8 +186,8 @@ int launch_observe_grouped(Bucket& bk, bool tobs, hipStream_t st) {
     return TWA_OK;
 }
 
-// the noise of the first step of every point of a bucket
-int launch_first_noise(Bucket& bk, hipStream_t st) {
+// the noise of a step of every point of a bucket
+int launch_noise_grouped(Bucket& bk, hipStream_t st) {
     const int np = (int)bk.gs.size();
     const unsigned nb = (unsigned)bk.nblocks_noise;
     switch (bk.gs[0].precision) {
@@ -249,7 +248,7 @@ int build_bucket(const BatchSpec& sp, const std::vector<int>& idx, int cfg, Buck
         if ((rc = ar.commit(false, st))) return rc;
         b.block = ar.detach();
         b.step = bk.step;   // one step counter for the bucket
-        b.ahead = true;
+        b.ahead = noise_ahead(g);
         b.fold = sp.L == 0;
         StepConsts& c = bk.cs[(size_t)q];
         c.c1 = 0.5 * o->gamma * pt.dt;
@@ -304,14 +303,15 @@ int build_bucket(const BatchSpec& sp, const std::vector<int>& idx, int cfg, Buck
             if ((rc = launch_seed_tangents(bk.gs[(size_t)q], bk.bs[(size_t)q], 0, st))) return rc;
         if ((rc = launch_observe_grouped(bk, true, st))) return rc;
     }
-    return launch_first_noise(bk, st);
+    return bk.bs[0].ahead ? launch_noise_grouped(bk, st) : TWA_OK;
 }
 
 // one step of one bucket (the step counter on the device advances in the
-// corrector launch, which also makes the next step's noise), on stream st
+// corrector launch, which may also make the next step's noise), on stream st
 int bucket_step(Bucket& bk, int cur, const StepKind& k, hipStream_t st) {
     int rc;
     const int np = (int)bk.gs.size();
+    if (!bk.bs[0].ahead && (rc = launch_noise_grouped(bk, st))) return rc;
     const int pv = k.tan_active ? GV_PRIMAL_TAN : GV_PRIMAL;
     if ((rc = grouped_launch(bk.plan, 1, cur, pv, st))) return rc;
     if (k.tan_active && (rc = grouped_launch(bk.plan, 1, cur, GV_TANGENT, st))) return rc;
@@ -409,7 +409,7 @@ int run_steps(std::vector<Bucket>& bks, const Plan& plan, int64_t n0, int64_t n1
 int bucket_of(int64_t N) { return N <= 128 ? 0 : N <= 1024 ? 1 : 2; }
 
 std::vector<int> bucket_candidates(int bucket, int precision) {
-    if (precision == TWA_PREC_FP64) return {0, 1, 2};
+    if (precision == TWA_PREC_FP64) return {0, 1, 3};
     if (bucket == 0) return {0, 1};
     if (bucket == 2 && operand_split(precision) == 2) return {2, 3, 7};
     return {1, 3, 7};

@@ -45,32 +45,44 @@ struct Status {
 // K bytes per LDS stage, waves along M, waves along N).
 // The shapes depend on the parts per operand value (operand_split).  A ring
 // stage holds `group` units, one part of one K stage each: 1, all the parts of
-// a K stage, or with one part several K stages.
+// a K stage, or with one part several K stages.  With split > 1 as many groups
+// of waves share the K stages of a ring stage.
 struct TileCfg {
-    int mt, nt, kbytes, waves_m, waves_n, nstage, group;
+    int mt, nt, kbytes, waves_m, waves_n, nstage, group, split;
 };
 constexpr int kTileCfgs = 9;
 constexpr TileCfg kTiles[4][kTileCfgs] = {
     // one part: BF16, FP16
-    {{32, 32, 64, 2, 1, 6, 2}, {64, 64, 64, 2, 2, 4, 2}, {128, 128, 128, 2, 2, 4, 1}, {128, 128, 64, 2, 2, 8, 1},
-     {64, 64, 64, 2, 2, 4, 4}, {16, 32, 64, 1, 1, 4, 2}, {32, 32, 64, 2, 1, 4, 4}, {320, 256, 128, 4, 2, 2, 1},
-     {320, 256, 64, 4, 2, 4, 1}},
+    {{32, 32, 64, 2, 1, 6, 2, 1}, {64, 64, 64, 2, 2, 4, 2, 1}, {128, 128, 128, 2, 2, 4, 1, 1},
+     {128, 128, 64, 2, 2, 8, 1, 1}, {64, 64, 64, 2, 2, 4, 4, 1}, {32, 32, 64, 1, 1, 4, 4, 2},
+     {64, 64, 64, 2, 2, 4, 4, 2}, {320, 256, 128, 4, 2, 2, 1, 1}, {320, 256, 64, 4, 2, 4, 1, 1}},
     // two parts: split BF16
-    {{32, 32, 64, 2, 1, 6, 2}, {64, 64, 64, 2, 2, 3, 2}, {128, 128, 64, 4, 2, 8, 1}, {128, 64, 64, 2, 2, 3, 2},
-     {64, 64, 64, 2, 2, 6, 2}, {16, 32, 64, 1, 1, 6, 2}, {128, 64, 64, 2, 2, 6, 1}, {320, 256, 64, 4, 2, 4, 1},
-     {256, 128, 64, 4, 2, 6, 1}},
+    {{32, 32, 64, 1, 1, 3, 4, 2}, {64, 64, 64, 2, 2, 3, 2, 1}, {128, 128, 64, 4, 2, 8, 1, 1},
+     {128, 64, 64, 2, 2, 3, 2, 1}, {64, 64, 64, 2, 2, 3, 4, 2}, {32, 32, 64, 2, 1, 6, 2, 1},
+     {32, 32, 64, 2, 1, 3, 4, 2}, {320, 256, 64, 4, 2, 4, 1, 1}, {256, 128, 64, 4, 2, 6, 1, 1}},
     // three parts: FP32
-    {{32, 32, 64, 2, 1, 6, 3}, {64, 64, 64, 2, 2, 3, 3}, {128, 128, 64, 4, 2, 9, 1}, {128, 64, 64, 2, 2, 2, 3},
-     {64, 64, 64, 2, 2, 2, 3}, {16, 32, 64, 1, 1, 4, 3}, {128, 64, 64, 2, 2, 6, 1}, {256, 128, 64, 4, 2, 6, 1},
-     {64, 64, 64, 2, 2, 6, 3}},
-    // FP64 (configurations 0 to 3 only)
-    {{16, 32, 64, 1, 1, 8, 1}, {64, 64, 64, 2, 2, 4, 2}, {32, 32, 64, 2, 1, 6, 1}, {128, 128, 64, 2, 2, 8, 1},
-     {64, 64, 64, 2, 2, 4, 1}, {64, 64, 64, 2, 2, 4, 1}, {64, 64, 64, 2, 2, 4, 1}, {64, 64, 64, 2, 2, 4, 1},
-     {64, 64, 64, 2, 2, 4, 1}},
+    {{32, 32, 64, 2, 1, 3, 6, 2}, {64, 64, 64, 2, 2, 3, 3, 1}, {128, 128, 64, 4, 2, 9, 1, 1},
+     {128, 64, 64, 2, 2, 2, 3, 1}, {64, 64, 64, 2, 2, 2, 3, 1}, {64, 64, 64, 2, 2, 3, 6, 2},
+     {32, 32, 64, 2, 1, 6, 3, 1}, {256, 128, 64, 4, 2, 6, 1, 1}, {16, 32, 64, 1, 1, 4, 3, 1}},
+    // FP64 (configurations 0 to 3 only).  The smallest tiles' rings are as deep
+    // as lets four and three blocks share a compute unit, no more: with five a
+    // unit at times got more than its share while others idled (16x32, stage 1
+    // at 600 x 400 50 us in place of 40).
+    {{16, 32, 64, 1, 1, 10, 1, 1}, {64, 64, 64, 2, 2, 4, 2, 1}, {32, 32, 64, 2, 1, 11, 1, 1},
+     {64, 64, 64, 2, 2, 4, 4, 2}, {64, 64, 64, 2, 2, 4, 1, 1}, {64, 64, 64, 2, 2, 4, 1, 1},
+     {64, 64, 64, 2, 2, 4, 1, 1}, {64, 64, 64, 2, 2, 4, 1, 1}, {64, 64, 64, 2, 2, 4, 1, 1}},
 };
 // row of kTiles of a precision
 constexpr int tile_table(int precision) {
     return precision == TWA_PREC_FP64 ? 3 : precision == TWA_PREC_FP32 ? 2 : precision == TWA_PREC_BF16X3 ? 1 : 0;
+}
+// Whether the corrector's launch may carry the next step's noise.  A noise
+// block takes the LDS of a tile: where only one fits on a compute unit (256x128
+// and 320x256) their short lives follow one another there, and a launch of
+// their own is shorter (FP32 4096 x 1024: 100 us more of stage 2 with them, 17
+// for the launch).
+constexpr bool noise_fits(int mt, int nt, int kbytes, int nstage, int group) {
+    return nstage * group * (mt + nt) * kbytes <= 80 * 1024 || mt * nt <= 64 * 64;
 }
 inline int n_tile_cfgs() { return kTileCfgs; }
 const TileCfg& tile_cfg(int precision, int id);
@@ -273,6 +285,10 @@ int launch_build_A_coh(const Geometry& g, const double* W, const double* F, cons
 int launch_init_state(const Geometry& g, const EnsembleBuffers& b, const StepConsts& c,
                       const double* init_dev, hipStream_t st);
 int launch_reduce_state(const Geometry& g, const void* s, void* part, hipStream_t st);
+inline bool noise_ahead(const Geometry& g) {
+    const TileCfg& t = tile_cfg(g.precision, g.cfg);
+    return noise_fits(t.mt, t.nt, t.kbytes, t.nstage, t.group);
+}
 int launch_noise(const Geometry& g, const EnsembleBuffers& b, const StepConsts& c, hipStream_t st);
 int launch_gemm(const Geometry& g, const EnsembleBuffers& b, const StepConsts& c, int stage,
                 bool tangent, int cur, bool store_y2, bool keep_dlt, hipStream_t st);

@@ -53,12 +53,17 @@ static int n_compute_units() {
 // at 4096 x 512 340 (64x64), 279 (128x64), 266 (128x128) and 982 (320x256);
 // BF16 at 10^4 x 1024 3028 (64x64), 1756 (128x128) and 965 (320x256).
 // Where larger tiles are too few to fill the device, the smallest are shorter:
-// 32x32 up to two to a compute unit (FP32 2000 x 128, 504 of them, 81 against
-// 100 us; 500 x 600, 608, 57 against 40).  FP64, bound by its MFMA, takes
-// 16x32, one wave each, up to one to a SIMD (600 x 400, 950 of them, 70
-// against 96 us; 700 x 512, 1408, 140 against 105), then 32x32 up to four to a
-// unit (700 x 512 94 us; 1000 x 512 138 against 143; 2000 x 512, twice as
-// many, 560 against 420).
+// 32x32 up to two to a compute unit (FP32 2000 x 128, 504 of them, 65 against
+// 87 us with 64x64; 500 x 600, 608, 42 against 33).  FP64, bound by its MFMA,
+// takes 16x32, one wave each, up to one to a SIMD (600 x 400, 950 of them, 65
+// against 89 us; 700 x 512, 1408, 125 against 98), then 32x32 up to three to a
+// unit (700 x 512 86 us, 1500 x 256 164 against 191; 1000 x 512, four, 194
+// against 136).
+// 64x64 tiles that each have a compute unit to themselves share its two waves a
+// SIMD out over K (split, configuration 5 of FP32 and 3 of FP64) where the
+// contraction is long enough to pay for adding the sums: FP32 500 x 600 34
+// against 33 us, 700 x 512 40 against 41, 1200 x 300 54 against 62, 1500 x 256
+// 62 against 72; FP64 500 x 1000 84 against 81, 1000 x 512 130 against 136.
 int pick_tile_cfg(int precision, int64_t N, int64_t n_traj) {
     struct Cost {
         int cfg;
@@ -77,7 +82,8 @@ int pick_tile_cfg(int precision, int64_t N, int64_t n_traj) {
         return (round_up(N, t.mt) / t.mt) * (2 * round_up(n_traj, t.nt / 2) / t.nt);
     };
     if (N <= 48 || tiles(0) <= (f64 ? 4 : 2) * ncu) return 0;
-    if (f64) return tiles(2) <= 4 * ncu ? 2 : 1;
+    const bool split = tiles(1) <= ncu && N >= 600;
+    if (f64) return tiles(2) <= 3 * ncu ? 2 : split ? 3 : 1;
     int best = 1;
     double tb = 1e300;
     for (int q = 0; q < n; ++q) {
@@ -88,7 +94,7 @@ int pick_tile_cfg(int precision, int64_t N, int64_t n_traj) {
             best = c[q].cfg;
         }
     }
-    return best;
+    return best == 1 && np == 3 && split ? 5 : best;
 }
 
 // ---------------------------------------------------------------------------

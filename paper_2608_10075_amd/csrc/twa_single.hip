@@ -248,9 +248,9 @@ int run_single(const twa_params* p, int64_t n_traj, double dt, int64_t n_steps, 
         n = n_steps;
     }
     if (n < n_steps) {
-        b.ahead = true;
+        b.ahead = noise_ahead(g);
         b.fold = L == 0;
-        TWA_TRY(launch_noise(g, b, c, st));   // of the first step
+        if (b.ahead) TWA_TRY(launch_noise(g, b, c, st));   // of the first step
     }
     while (n < n_steps) {
         const StepKind k = plan.kind(n);

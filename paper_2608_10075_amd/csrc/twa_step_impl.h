@@ -273,7 +273,7 @@ __device__ __forceinline__ void unroll_units(F& f, const int u0, const int n, st
 // contraction + fused Heun stage
 // One output tile (M tile mt of spins, column tile nt, copy cp) of one stage:
 // contraction over K on MFMA followed by the fused epilogue of the kind.
-template <int PREC, int MT, int NT, int KB, int WMW, int WNW, int NST, int G_, int STAGE, int KIND>
+template <int PREC, int MT, int NT, int KB, int WMW, int WNW, int NST, int G_, int SK, int STAGE, int KIND>
 __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt, const int nt, const int cp) {
     // KIND_Q_SNAPSHOT on the predictor kind: also store the part of the
     // contraction that comes from the second K half (the noise columns), by
@@ -287,7 +287,7 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     typedef typename Prec<PREC>::G G;
     typedef typename Prec<PREC>::S S;
     typedef typename Prec<PREC>::AV AV;
-    constexpr int NTHR = 64 * WMW * WNW;
+    constexpr int NTHR = 64 * WMW * WNW * SK;
     constexpr int WM = MT / WMW, WN = NT / WNW;
     constexpr int BI = WM / 16, BJ = WN / 16;
     constexpr int PCS = KB / 16;             // 16-byte pieces per row
@@ -296,6 +296,13 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     constexpr int NTRJ = NT / 2;             // trajectories per tile
     static_assert(WM % 16 == 0 && WN % 32 == 0, "wave tile");
     static_assert(KB % 64 == 0, "K stage");
+    // SK > 1: as many groups of waves, each with the products of one of the SK
+    // K stages of a ring stage, so that a tile that has a compute unit to itself
+    // keeps two waves on a SIMD.  Their sums are added through LDS; the epilogue
+    // is split over ES of the groups by 16-row blocks, EBI to a wave.
+    constexpr int GH = G_ / SK;              // units of a ring stage for one group
+    constexpr int ES = BI % SK == 0 ? SK : BI, EBI = BI / ES;
+    static_assert(SK == 1 || (G_ > 1 && G_ % SK == 0 && SK % ES == 0), "groups of waves");
 
     // NST LDS stages of G_ units (a ring).  A unit holds one part of one K
     // stage of the operands: rows [0, MT) of A then [MT, MT + NT) of X, KB bytes per row.
@@ -330,12 +337,13 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     // epilogue, [thread group][trajectory][5 channels] for the collective sums
     constexpr int NG = NTHR / NTRJ;            // thread groups of the collective sums
     static_assert(NG >= 1, "thread groups");
-    __shared__ S red[WMW > NG ? WMW : NG][NTRJ][5];
+    __shared__ S red[WMW * ES > NG ? WMW * ES : NG][NTRJ][5];
     __shared__ S sSrc[NTRJ][3];    // adjoint: observation source of each trajectory
 
     const int64_t m0 = (int64_t)mt * MT, n0 = (int64_t)nt * NT;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave % WMW, wn = wave / WMW;
+    const int gw = SK > 1 ? wave / (WMW * WNW) : 0;      // group of waves
+    const int wm = wave % WMW, wn = SK > 1 ? wave / WMW % WNW : wave / WMW;
     const int wm0 = wm * WM, wn0 = wn * WN;
     const int64_t P = a.P, Bp = a.Bp, nmt = a.nmt;
     const int64_t k0t = n0 / 2;    // first trajectory of the tile
@@ -405,7 +413,7 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
 
     // fragment read offsets of this lane (row within a 16-row block, swizzle)
     const int ra = Prec<PREC>::arow(lane & 15), rx = lane & 15;
-    const int offA = (wm0 + ra) * KB, offX = (MT + wn0 + rx) * KB;
+    const int offA = gw * GH * UB + (wm0 + ra) * KB, offX = gw * GH * UB + (MT + wn0 + rx) * KB;
     const int swA = swz(ra), swX = swz(rx), grp = lane >> 4;
 #define TWA_BUF(I_) ((I_) == 0 ? L0 : (I_) == 1 ? L1 : (I_) == 2 ? L2 : (I_) == 3 ? L3 : \
                      (I_) == 4 ? L4 : (I_) == 5 ? L5 : (I_) == 6 ? L6 : (I_) == 7 ? L7 : \
@@ -426,14 +434,48 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
             if constexpr (LOW && (LOW_)) Prec<PREC>::mma(accL[i][j], A_[i], X_[j]);                     \
             else Prec<PREC>::mma(acc[i][j], A_[i], X_[j]);                                              \
         }
-    // Registers allow it: the fragments of the next unit are read while this
-    // unit's products run, so no MFMA waits for an LDS read and a unit's LDS is
-    // free as soon as its turn comes (LOOK units of the ring are then in
-    // registers, not in LDS).
+    // Where registers allow it, the fragments of the next unit are read while
+    // this unit's products run, so no MFMA waits for an LDS read and a unit's
+    // LDS is free as soon as its turn comes (LOOK units of the ring are then in
+    // registers, not in LDS).  The Heun corrector on 256x128 tiles in FP32 is
+    // left out: it spilled, and each reload drained the loads in flight (stage 2
+    // at 4096 x 1024 450 us, without 333).
     constexpr bool AHEAD = G_ > 1 || (KB == 64 && 4 * (BI * BJ * ((QSNAP ? 2 : 1) + (LOW ? 1 : 0)) + NP * (BI + BJ)) +
-                                                          (LOW ? 32 : 48) <= 256);
+                                                          (LOW ? (KD == KIND_PRIMAL && STAGE == 2 ? 36 : 32) : 48) <=
+                                                      256);
     constexpr int LOOK = AHEAD ? 1 : 0;
-    static_assert(G_ == 1 || (KB == 64 && (NP == 1 || G_ == NP)), "a stage of several units");
+    static_assert(G_ == 1 || (KB == 64 && (NP == 1 || GH == NP)), "a stage of several units");
+
+    // where the epilogue's streams start: the wave's first element of a state
+    // plane, the bytes from there to the plane's end, the lane's byte offset
+    struct WaveAt {
+        int64_t row, kw, base, rem;
+        uint32_t lane;
+    };
+    const int64_t SP = Bp * P;   // plane size
+    auto wave_at = [&](const int wave, const int lane) {
+        const int wvu = __builtin_amdgcn_readfirstlane(wave);
+        WaveAt w;
+        w.row = m0 + (int64_t)(wvu % WMW) * WM + (SK > 1 ? wvu / (WMW * WNW) * EBI * 16 : 0);
+        w.kw = k0t + (int64_t)(SK > 1 ? wvu / WMW % WNW : wvu / WMW) * (WN / 2);
+        w.base = w.kw * P + w.row;
+        w.rem = (SP - w.base) * (int64_t)sizeof(S);
+        w.lane = (uint32_t)(((lane & 15) * P + 4 * (lane >> 4)) * (int64_t)sizeof(S));
+        return w;
+    };
+    constexpr bool PF = KD == KIND_PRIMAL || KD == KIND_SIB;
+    constexpr int NPF = STAGE == 2 ? 5 : 3;
+    S pfn[NPF][4];
+    // In a small tile a wave has a block or two, and the first block's round
+    // trip would come on top of the contraction's: it is made before it, unless
+    // three blocks share a compute unit and hide it anyway.
+    constexpr bool EARLY = PF && G_ > 1 && EBI * BJ <= 4 && NST * SB > 53 * 1024;
+    if constexpr (EARLY) {
+        const WaveAt w = wave_at(wave, lane);
+#pragma unroll
+        for (int c = 0; c < NPF; ++c)
+            bld4(wave_rsrc((c < 3 ? a.s_cur + c * SP : a.Y + (c - 3) * SP) + w.base, w.rem), w.lane, 0, pfn[c]);
+    }
 
     // prologue: the first stages of the ring in flight; the collective sums
     // below run while they land
@@ -456,6 +498,20 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     // Channels: 0, 1 primal x, y; 2, 3 copy x, y; 4 primal z.
     if constexpr (KD != KIND_STORE) {
         constexpr int NCHAN = KD == KIND_ADJ1 ? 5 : TCOPY ? 4 : 2;
+        // what the first NTRJ threads need after the barrier is asked for with
+        // the partial sums, not a memory round trip after them
+        constexpr bool USE_SN = (KD == KIND_PRIMAL || KD == KIND_SIB) && STAGE == 2;
+        const bool use_sn = USE_SN && a.Sn && (a.dlt == nullptr || KD == KIND_SIB);
+        S g0 = 0, g1 = 0, sn0 = 0, sn1 = 0;
+        if (tid < NTRJ) {
+            g0 = a.g[k0t + tid];
+            g1 = a.g[Bp + k0t + tid];
+            if (use_sn) {
+                // sums of the step's input state, for the predictor increment
+                sn0 = a.Sn[k0t + tid];
+                sn1 = a.Sn[Bp + k0t + tid];
+            }
+        }
         {
             const int kl = tid % NTRJ, gq = tid / NTRJ;
             const int64_t k = k0t + kl;
@@ -478,7 +534,8 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                 for (int c = 0; c < NCHAN; ++c) red[gq][kl][c] = v[c];
         }
         lds_sync();
-        for (int t = tid; t < NTRJ; t += NTHR) {
+        if (tid < NTRJ) {
+            const int t = tid;
             const int64_t k = k0t + t;
             S v[5];
 #pragma unroll
@@ -490,21 +547,18 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
             sS[t][0] = sx;
             sS[t][1] = sy;
             if constexpr (KD == KIND_PRIMAL || KD == KIND_SIB) {
-                if (a.Sn) {
-                    if constexpr (STAGE == 1) {
-                        if (mt == 0) {
-                            a.Sn[k] = sx;
-                            a.Sn[Bp + k] = sy;
-                        }
-                    } else if (a.dlt == nullptr || KD == KIND_SIB) {
-                        // sums of the step's input state, for the predictor increment
-                        sT[t][0] = a.Sn[k];
-                        sT[t][1] = a.Sn[Bp + k];
+                if constexpr (STAGE == 1) {
+                    if (a.Sn && mt == 0) {
+                        a.Sn[k] = sx;
+                        a.Sn[Bp + k] = sy;
                     }
+                } else if (use_sn) {
+                    sT[t][0] = sn0;
+                    sT[t][1] = sn1;
                 }
             }
-            sG[t][0] = a.g[k];
-            sG[t][1] = a.g[Bp + k];
+            sG[t][0] = g0;
+            sG[t][1] = g1;
             if constexpr (TCOPY) {
                 sT[t][0] = v[2];
                 sT[t][1] = v[3];
@@ -531,7 +585,7 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     }
     // unroll: ring slot and (G_ = 1) part are compile-time
     constexpr int UN = G_ > 1 || NST % NP == 0 ? NST : NST * NP;
-    constexpr int NF = G_ > 1 ? G_ : NP;                 // fragment sets held
+    constexpr int NF = G_ > 1 ? GH : NP;                 // fragment sets held
     uint4 fa[NF][BI], fx[NF][BJ];
     if constexpr (AHEAD) {
         if (nu >= NST) TWA_WAIT_VM((NST - 1) * G_ * CPWMIN);
@@ -539,7 +593,7 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 #pragma unroll
-        for (int gu = 0; gu < G_; ++gu) {
+        for (int gu = 0; gu < (G_ > 1 ? GH : 1); ++gu) {
             TWA_FRAG_A(fa[gu], TWA_BUF(0) + gu * UB, 0);
             TWA_FRAG_X(fx[gu], TWA_BUF(0) + gu * UB, 0);
         }
@@ -574,21 +628,21 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
         }
         if constexpr (G_ > 1) {
             // (after the last stage these reads return stale LDS, never used)
-            uint4 na[G_][BI], nx[G_][BJ];
+            uint4 na[GH][BI], nx[GH][BJ];
 #pragma unroll
-            for (int gu = 0; gu < G_; ++gu) {
+            for (int gu = 0; gu < GH; ++gu) {
                 TWA_FRAG_A(na[gu], TWA_BUF((v + 1) % NST) + gu * UB, 0);
                 TWA_FRAG_X(nx[gu], TWA_BUF((v + 1) % NST) + gu * UB, 0);
             }
             // with one part every unit's product, else those of the parts pa
             // and px with pa + px < NP
 #pragma unroll
-            for (int pa = 0; pa < G_; ++pa) {
+            for (int pa = 0; pa < GH; ++pa) {
                 if constexpr (NP == 1) {
                     TWA_MMA(fa[pa], fx[pa], false);
                 } else {
 #pragma unroll
-                    for (int px = 0; px < G_ - pa; ++px) {
+                    for (int px = 0; px < GH - pa; ++px) {
                         if (pa + px == 0) {
                             TWA_MMA(fa[pa], fx[px], false);
                         } else {
@@ -598,7 +652,7 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                 }
             }
 #pragma unroll
-            for (int gu = 0; gu < G_; ++gu) {
+            for (int gu = 0; gu < GH; ++gu) {
 #pragma unroll
                 for (int i = 0; i < BI; ++i) fa[gu][i] = na[gu][i];
 #pragma unroll
@@ -654,6 +708,46 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
 #pragma unroll
             for (int j = 0; j < BJ; ++j) acc[i][j] = acc[i][j] + accL[i][j];
     }
+    AV eacc[EBI][BJ], eaccW[QSNAP ? EBI : 1][QSNAP ? BJ : 1];
+    if constexpr (SK == 1) {
+#pragma unroll
+        for (int i = 0; i < BI; ++i)
+#pragma unroll
+            for (int j = 0; j < BJ; ++j) {
+                eacc[i][j] = acc[i][j];
+                if constexpr (QSNAP) eaccW[i][j] = accW[i][j];
+            }
+    } else {
+        // group gw < ES keeps block gw of the tile's rows and adds the others'
+        // sums of it, which they leave in the ring's LDS
+        constexpr int PC = EBI * BJ, WG = WMW * WNW;
+        static_assert(ES * (SK - 1) * WG * PC * 64 * (int)sizeof(AV) <= SB, "room for the sums");
+        AV* lx = reinterpret_cast<AV*>(L0) + (wave % WG) * PC * 64 + lane;
+        auto exchange = [&](AV(&in)[BI][BJ], AV(&out)[EBI][BJ]) {
+            __syncthreads();
+#pragma unroll
+            for (int d = 0; d < ES; ++d)
+#pragma unroll
+                for (int e = 0; e < EBI; ++e)
+#pragma unroll
+                    for (int j = 0; j < BJ; ++j) {
+                        if (gw == d) out[e][j] = in[d * EBI + e][j];
+                        else lx[((d * (SK - 1) + (gw < d ? gw : gw - 1)) * WG * PC + e * BJ + j) * 64] = in[d * EBI + e][j];
+                    }
+            __syncthreads();
+            if (gw < ES) {
+#pragma unroll
+                for (int q = 0; q < SK - 1; ++q)
+#pragma unroll
+                    for (int e = 0; e < EBI; ++e)
+#pragma unroll
+                        for (int j = 0; j < BJ; ++j)
+                            out[e][j] = out[e][j] + lx[((gw * (SK - 1) + q) * WG * PC + e * BJ + j) * 64];
+            }
+        };
+        exchange(acc, eacc);
+        if constexpr (QSNAP) exchange(accW, eaccW);
+    }
 #undef TWA_DMA
 #undef TWA_FRAG_A
 #undef TWA_FRAG_X
@@ -665,9 +759,8 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     // (register r of an accumulator is spin i0 + r with i0 a multiple of 4, so
     // the sign of its row is known at compile time)
     auto sgn = [](const S v, const int r) { return row_flipped<PREC>(r) ? -v : v; };
-    auto av = [&](const int bi, const int c, const int r) { return sgn(acc[bi][c][r], r); };
+    auto av = [&](const int bi, const int c, const int r) { return sgn(eacc[bi][c][r], r); };
     const S c1 = a.c1, c2 = a.c2;
-    const int64_t SP = Bp * P;   // plane size
     // The primal kinds load the state (and, in the corrector, the predictor
     // field) of the next (p, bi) block before the current block is computed
     // and stored, so one block of loads is always in flight behind the stores
@@ -676,22 +769,17 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     // first element, one lane byte offset per layout (state planes [k][P],
     // operand columns of the next contraction) and a uniform byte offset per
     // block (p, bi).
-    constexpr bool PF = KD == KIND_PRIMAL || KD == KIND_SIB;
-    constexpr int NPF = STAGE == 2 ? 5 : 3;
-    constexpr int NBLK = (BJ / 2) * BI;
-    const int wvu = __builtin_amdgcn_readfirstlane(wave);
-    const int64_t wm0u = (int64_t)(wvu % WMW) * WM, kw0 = k0t + (int64_t)(wvu / WMW) * (WN / 2);
-    const int64_t eb_s = kw0 * P + m0 + wm0u;                 // wave base in a state plane
-    const int64_t rem_s = (SP - eb_s) * (int64_t)sizeof(S);
-    const uint32_t lane_s = (uint32_t)(((lane & 15) * P + 4 * (lane >> 4)) * (int64_t)sizeof(S));
+    constexpr int NBLK = (BJ / 2) * EBI;
+    const WaveAt at = wave_at(wave, lane);
+    const int64_t r0 = at.row, kw0 = at.kw, eb_s = at.base, rem_s = at.rem;
+    const uint32_t lane_s = at.lane;
     auto so_s = [&](const int p, const int bi) { return (uint32_t)((16 * p * P + 16 * bi) * (int64_t)sizeof(S)); };
     auto plane = [&](const S* arr, const int c) { return wave_rsrc(arr + c * SP + eb_s, rem_s); };
     // operand columns (stage-blocked): trajectory kw0 + 16 p + (lane & 15) has
     // columns opcol(k, c) = 32 (kw0 / 16 + p) + 16 c + (lane & 15), rows
-    // m0 + wm0u + 16 bi + 4 (lane / 16) + ..; the base is the K stage and the
+    // m0 + 16 bi + 4 (lane / 16) + ..; the base is the K stage and the
     // column block of the wave's first element
     const int64_t C2 = 2 * Bp;
-    const int64_t r0 = m0 + wm0u;
     auto op_rsrc = [&](const G* arr, const int64_t row0, const int64_t rows) {
         const int64_t eb = ((row0 + r0) / KT * (NP * C2) + 32 * (kw0 >> 4)) * KT;
         return wave_rsrc(arr + eb, (rows * NP * C2 - eb) * (int64_t)sizeof(G));
@@ -721,7 +809,6 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
             rperp = op_rsrc(a.Xnext, a.coh * 2 * P, (2 + a.coh) * P);
         }
     }
-    S pfn[NPF][4];
     auto pf_load = [&](const int p, const int bi) {
         const uint32_t so = so_s(p, bi);
         bld4(rs[0], lane_s, so, pfn[0]);
@@ -732,9 +819,9 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
             bld4(ry[1], lane_s, so, pfn[4]);
         }
     };
-    if constexpr (PF) pf_load(0, 0);
+    if constexpr (PF && !EARLY) pf_load(0, 0);
 #pragma unroll
-    for (int p = 0; p < BJ / 2; ++p) {
+    for (int p = 0; p < (ES == SK || gw < ES ? BJ / 2 : 0); ++p) {
         const int kl = wn0 / 2 + 16 * p + (lane & 15);
         const int64_t k = k0t + kl;
         const S Sx = sS[kl][0], Sy = sS[kl][1];
@@ -742,8 +829,8 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
         const S hy0 = c1 * Sy + c2 * sG[kl][1];
         S ps0 = 0, ps1 = 0, ps2 = 0, ps3 = 0;
 #pragma unroll
-        for (int bi = 0; bi < BI; ++bi) {
-            const int64_t i0 = m0 + wm0 + 16 * bi + 4 * (lane >> 4);
+        for (int bi = 0; bi < EBI; ++bi) {
+            const int64_t i0 = r0 + 16 * bi + 4 * (lane >> 4);
             const int64_t off = k * P + i0;
             S x[4], y[4], z[4], fyx[4], fyy[4], fdx[4], fdy[4], fdz[4];
             if constexpr (PF) {
@@ -767,7 +854,7 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                         bld4(plane(a.dlt, 2), lane_s, so_s(p, bi), fdz);
                     }
                 }
-                if (p * BI + bi + 1 < NBLK) pf_load((p * BI + bi + 1) / BI, (p * BI + bi + 1) % BI);
+                if (p * EBI + bi + 1 < NBLK) pf_load((p * EBI + bi + 1) / EBI, (p * EBI + bi + 1) % EBI);
             } else if constexpr (KD != KIND_STORE) {
                 ld4(a.s_cur + off, x);
                 ld4(a.s_cur + SP + off, y);
@@ -803,8 +890,8 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                     S qx[4], qy[4];
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        qx[r] = av(bi, 2 * p, r) - sgn(accW[bi][2 * p][r], r);
-                        qy[r] = av(bi, 2 * p + 1, r) - sgn(accW[bi][2 * p + 1][r], r);
+                        qx[r] = av(bi, 2 * p, r) - sgn(eaccW[bi][2 * p][r], r);
+                        qy[r] = av(bi, 2 * p + 1, r) - sgn(eaccW[bi][2 * p + 1][r], r);
                     }
                     bst4(plane(a.Sout, 0), lane_s + so_s(p, bi), qx);
                     bst4(plane(a.Sout, 1), lane_s + so_s(p, bi), qy);
@@ -1130,10 +1217,10 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
         ps2 += __shfl_xor(ps2, 32);
         ps3 += __shfl_xor(ps3, 32);
         if (lane < 16) {
-            red[wm][kl][0] = ps0;
-            red[wm][kl][1] = ps1;
-            red[wm][kl][2] = ps2;
-            red[wm][kl][3] = ps3;
+            red[wm * ES + gw][kl][0] = ps0;
+            red[wm * ES + gw][kl][1] = ps1;
+            red[wm * ES + gw][kl][2] = ps2;
+            red[wm * ES + gw][kl][3] = ps3;
         }
     }
     if constexpr (KD != KIND_STORE) {
@@ -1146,7 +1233,7 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                 S sum = 0;
                 if (KD != KIND_ADJ2 || c < 2) {
 #pragma unroll
-                    for (int q = 0; q < WMW; ++q) sum += red[q][kl][c];
+                    for (int q = 0; q < WMW * ES; ++q) sum += red[q][kl][c];
                 }
                 po[((int64_t)c * nmt + mt) * Bp + k0t + kl] = sum;
             }
@@ -1158,7 +1245,7 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                 const int c = t / NTRJ, kl = t % NTRJ;
                 S sum = 0;
 #pragma unroll
-                for (int q = 0; q < WMW; ++q) sum += red[q][kl][2 + c];
+                for (int q = 0; q < WMW * ES; ++q) sum += red[q][kl][2 + c];
                 double* gp = a.gacc + (((int64_t)cp * 2 + c) * nmt + mt) * Bp + k0t + kl;
                 *gp += (double)sum;
             }
@@ -1175,7 +1262,7 @@ __host__ __device__ inline int64_t extra_blocks(const GemmArgs<PREC>& a, int64_t
     if (STAGE == 1) return a.ob_mom ? (a.B + NTHR - 1) / NTHR : 0;
     return a.nz_g ? noise_blocks<NTHR>(a.N, a.B, kt) : 0;
 }
-template <int PREC, int NTHR, int STAGE>
+template <int PREC, int NTHR, int STAGE, bool NOISE>
 __device__ __forceinline__ void extra_block(const GemmArgs<PREC>& a, uint32_t blk, int kt) {
     if constexpr (STAGE == 1) {
         typedef typename Prec<PREC>::S S;
@@ -1184,7 +1271,7 @@ __device__ __forceinline__ void extra_block(const GemmArgs<PREC>& a, uint32_t bl
         S sums[3];
         tile_sums<S, 3>(a.part_prim, a.nmt, a.Bp, k, 0, sums);
         add_moments(sums, a.ob_mom, a.Bp, k);
-    } else {
+    } else if constexpr (NOISE) {
         noise_block<PREC, NTHR>(blk, a.N, a.B, a.P, a.Bp, kt, a.nz_k0, a.nz_k1, a.nz_point,
                                 (uint32_t)a.step_next[0], a.Xnext, a.nz_g);
     }
@@ -1195,19 +1282,19 @@ __device__ __forceinline__ void extra_block(const GemmArgs<PREC>& a, uint32_t bl
 // Each XCD is given a contiguous range of tiles ordered M-tile-major, so the
 // workgroups resident on one XCD share the same rows of A (and walk K
 // together) in that XCD's L2.
-template <int PREC, int MT, int NT, int KB, int WMW, int WNW, int NST, int G_, int STAGE, int KIND>
-__global__ __launch_bounds__(64 * WMW * WNW) void heun_stage_kernel(GemmArgs<PREC> a) {
+template <int PREC, int MT, int NT, int KB, int WMW, int WNW, int NST, int G_, int SK, int STAGE, int KIND>
+__global__ __launch_bounds__(64 * WMW * WNW * SK) void heun_stage_kernel(GemmArgs<PREC> a) {
     constexpr bool PRIM = KIND == KIND_PRIMAL || KIND == KIND_SIB;
-    constexpr int NTHR = 64 * WMW * WNW, KT = KB / (int)sizeof(typename Prec<PREC>::G);
+    constexpr int NTHR = 64 * WMW * WNW * SK, KT = KB / (int)sizeof(typename Prec<PREC>::G);
     const int nnt = a.nnt;            // column tiles
     const int T = PRIM ? (int)a.nmt * nnt : (int)gridDim.x;   // total tiles
     if constexpr (PRIM) {
-        if ((int)blockIdx.x >= T) return extra_block<PREC, NTHR, STAGE>(a, blockIdx.x - T, KT);
+        if ((int)blockIdx.x >= T) return extra_block<PREC, NTHR, STAGE, noise_fits(MT, NT, KB, NST, G_)>(a, blockIdx.x - T, KT);
     }
     const int q = T / 8, r = T % 8;
     const int b = (int)blockIdx.x, x = b % 8, j = b / 8;
     const int L = x * q + (x < r ? x : r) + j;
-    stage_tile<PREC, MT, NT, KB, WMW, WNW, NST, G_, STAGE, KIND>(a, L / nnt, L % nnt, (int)blockIdx.z);
+    stage_tile<PREC, MT, NT, KB, WMW, WNW, NST, G_, SK, STAGE, KIND>(a, L / nnt, L % nnt, (int)blockIdx.z);
     if constexpr (PRIM) {
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             if constexpr (STAGE == 2) a.step[0] += 1;
@@ -1221,22 +1308,22 @@ __global__ __launch_bounds__(64 * WMW * WNW) void heun_stage_kernel(GemmArgs<PRE
 // list (point, M tile, column tile, copy) ordered longest-first; workgroup b
 // takes tiles b, b + grid, b + 2 grid, ...  The blocks past the tiles of a
 // primal stage (copy -1) come last.
-template <int PREC, int MT, int NT, int KB, int WMW, int WNW, int NST, int G_, int STAGE, int KIND>
-__global__ __launch_bounds__(64 * WMW * WNW) void heun_stage_grouped(const GemmArgs<PREC>* __restrict__ args,
+template <int PREC, int MT, int NT, int KB, int WMW, int WNW, int NST, int G_, int SK, int STAGE, int KIND>
+__global__ __launch_bounds__(64 * WMW * WNW * SK) void heun_stage_grouped(const GemmArgs<PREC>* __restrict__ args,
                                                                      const int4* __restrict__ tiles, int ntiles,
                                                                      int64_t* step) {
     constexpr bool PRIM = KIND == KIND_PRIMAL || KIND == KIND_SIB;
-    constexpr int NTHR = 64 * WMW * WNW, KT = KB / (int)sizeof(typename Prec<PREC>::G);
+    constexpr int NTHR = 64 * WMW * WNW * SK, KT = KB / (int)sizeof(typename Prec<PREC>::G);
     for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
         const int4 tt = tiles[t];
         if constexpr (PRIM) {
             if (tt.w < 0) {
-                extra_block<PREC, NTHR, STAGE>(args[tt.x], (uint32_t)tt.y, KT);
+                extra_block<PREC, NTHR, STAGE, noise_fits(MT, NT, KB, NST, G_)>(args[tt.x], (uint32_t)tt.y, KT);
                 continue;
             }
         }
         __syncthreads();   // LDS of the previous tile is free
-        stage_tile<PREC, MT, NT, KB, WMW, WNW, NST, G_, STAGE, KIND>(args[tt.x], tt.y, tt.z, tt.w);
+        stage_tile<PREC, MT, NT, KB, WMW, WNW, NST, G_, SK, STAGE, KIND>(args[tt.x], tt.y, tt.z, tt.w);
     }
     if constexpr (PRIM) {
         if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -1249,7 +1336,8 @@ __global__ __launch_bounds__(64 * WMW * WNW) void heun_stage_grouped(const GemmA
 template <int PREC, int CFG>
 struct CfgT {
     static constexpr TileCfg C = kTiles[tile_table(PREC)][CFG];
-    static constexpr int MT = C.mt, NT = C.nt, KB = C.kbytes, WMW = C.waves_m, WNW = C.waves_n, NST = C.nstage, G = C.group;
+    static constexpr int MT = C.mt, NT = C.nt, KB = C.kbytes, WMW = C.waves_m, WNW = C.waves_n, NST = C.nstage, G = C.group,
+                         SK = C.split;
 };
 
 template <int PREC, int CFG, int STAGE, int KIND>
@@ -1259,10 +1347,10 @@ static int launch_kernel(const GemmArgs<PREC>& a, int64_t P, int64_t C2, int nco
     aa.nnt = (int)(C2 / C::NT);
     constexpr bool PRIM = KIND == KIND_PRIMAL || KIND == KIND_SIB;
     const int64_t kt = C::KB / (int)sizeof(typename Prec<PREC>::G);
-    const int64_t extra = PRIM ? extra_blocks<PREC, 64 * C::WMW * C::WNW, STAGE>(aa, kt) : 0;
+    const int64_t extra = PRIM ? extra_blocks<PREC, 64 * C::WMW * C::WNW * C::SK, STAGE>(aa, kt) : 0;
     dim3 grid((unsigned)((P / C::MT) * (C2 / C::NT) + extra), 1u, (unsigned)ncopy);
-    dim3 block(64 * C::WMW * C::WNW);
-    hipLaunchKernelGGL((heun_stage_kernel<PREC, C::MT, C::NT, C::KB, C::WMW, C::WNW, C::NST, C::G, STAGE, KIND>), grid,
+    dim3 block(64 * C::WMW * C::WNW * C::SK);
+    hipLaunchKernelGGL((heun_stage_kernel<PREC, C::MT, C::NT, C::KB, C::WMW, C::WNW, C::NST, C::G, C::SK, STAGE, KIND>), grid,
                        block, 0, st, aa);
     TWA_HIP_CHECK(hipGetLastError());
     return TWA_OK;
@@ -1364,12 +1452,12 @@ static GemmArgs<PREC> make_args(const Geometry& g, const EnsembleBuffers& b, con
     a.g = static_cast<const S*>(b.g) + (b.ahead ? cur * 2 * Bp : 0);
     a.store_y2 = store_y2 ? 1 : 0;
     a.step = b.step;
+    if (b.fold && !tangent && stage == 1) {
+        a.ob_mom = static_cast<S*>(b.mom);
+        a.ob_burnin = c.burnin;
+    }
     if (b.ahead && !tangent) {
         a.step_next = b.step + 1;
-        if (stage == 1 && b.fold) {
-            a.ob_mom = static_cast<S*>(b.mom);
-            a.ob_burnin = c.burnin;
-        }
         if (stage == 2) {
             a.nz_g = static_cast<S*>(b.g) + (1 - cur) * 2 * Bp;
             a.nz_k0 = c.key0;
@@ -1493,8 +1581,8 @@ template <int PREC, int CFG, int STAGE, int KIND>
 static int grouped_launch_k(const GroupedPlan& pl, int cur, int variant, hipStream_t st) {
     typedef CfgT<PREC, CFG> C;
     const int tl = variant == GV_TANGENT ? 1 : STAGE == 1 ? 0 : 2;
-    hipLaunchKernelGGL((heun_stage_grouped<PREC, C::MT, C::NT, C::KB, C::WMW, C::WNW, C::NST, C::G, STAGE, KIND>),
-                       dim3((unsigned)pl.grid[tl]), dim3(64 * C::WMW * C::WNW), 0, st,
+    hipLaunchKernelGGL((heun_stage_grouped<PREC, C::MT, C::NT, C::KB, C::WMW, C::WNW, C::NST, C::G, C::SK, STAGE, KIND>),
+                       dim3((unsigned)pl.grid[tl]), dim3(64 * C::WMW * C::WNW * C::SK), 0, st,
                        static_cast<const GemmArgs<PREC>*>(pl.d_args[variant][STAGE - 1][cur]), pl.d_tiles[tl],
                        pl.ntiles[tl], pl.step);
     TWA_HIP_CHECK(hipGetLastError());
@@ -1513,8 +1601,8 @@ static int grouped_occupancy() {
     typedef CfgT<PREC, CFG> C;
     int nb = 0;
     hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &nb, heun_stage_grouped<PREC, C::MT, C::NT, C::KB, C::WMW, C::WNW, C::NST, C::G, 1, KIND_PRIMAL>,
-        64 * C::WMW * C::WNW, 0);
+        &nb, heun_stage_grouped<PREC, C::MT, C::NT, C::KB, C::WMW, C::WNW, C::NST, C::G, C::SK, 1, KIND_PRIMAL>,
+        64 * C::WMW * C::WNW * C::SK, 0);
     return nb > 0 ? nb : 1;
 }
 
@@ -1577,7 +1665,7 @@ int grouped_prepare_p(const std::vector<Geometry>& gs, const std::vector<Ensembl
     std::vector<int> order((size_t)np);
     for (int p = 0; p < np; ++p) order[(size_t)p] = p;
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return gs[(size_t)x].P > gs[(size_t)y].P; });
-    const int64_t nthr = 64 * tc.waves_m * tc.waves_n;
+    const int64_t nthr = 64 * tc.waves_m * tc.waves_n * tc.split;
     for (int tl = 0; tl < 3; ++tl) {
         if (tl == 1 && !tangents) continue;
         std::vector<int4> tiles;
