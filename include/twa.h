@@ -71,7 +71,11 @@ extern "C" {
 
 /* ---- precisions of the channel-mixing contraction ---------------------- */
 #define TWA_PREC_FP64   0   /* FP64 state, FP64 MFMA contraction               */
-#define TWA_PREC_FP32   1   /* FP32 state, FP32 MFMA contraction               */
+#define TWA_PREC_FP32   1   /* FP32 state; each contraction operand held in all   */
+                            /* its 24 bits as three bf16 parts, the six products  */
+                            /* above 2^-25 of one formed on BF16 MFMA with FP32   */
+                            /* accumulation (errors against FP64 as with the      */
+                            /* FP32 MFMA, which is 16 times slower)               */
 #define TWA_PREC_BF16   2   /* FP32 state, BF16 MFMA inputs, FP32 accumulation */
 #define TWA_PREC_FP16   3   /* FP32 state, FP16 MFMA inputs, FP32 accumulation */
 #define TWA_PREC_BF16X3 4   /* FP32 state; each contraction operand split into   */
@@ -214,8 +218,9 @@ typedef struct twa_params {
     int64_t n_lags;          /* two-time lags L (0 = no two-time correlation)      */
     int64_t lag_stride;      /* steps per lag; <= 0 = max(1, (n_steps-burnin)/L)   */
     int32_t point;           /* Philox point index (counter word 3, bits 8..31)    */
-    int32_t tile_config;     /* < 0: automatic (heuristic; N <= 64 in FP64/FP32    */
-                             /* without two-time runs the fused small-N kernel)    */
+    int32_t tile_config;     /* < 0: automatic (heuristic; N <= 64 in FP64 and     */
+                             /* N <= 128 in FP32 without two-time runs the fused   */
+                             /* small-N kernel; timed runs from N = 65 not)        */
     void* stream;            /* hipStream_t, NULL = null stream                    */
     const double* init_state;/* host, optional [3][n_traj][N] (x, y, z planes):    */
                              /* replaces the discrete sampling when non-NULL       */
@@ -266,7 +271,7 @@ typedef struct twa_observables {
     double stage1_ms;        /* timing = 1: summed device time of the predictor    */
     int64_t stage1_launches; /* contraction launches (HIP events around each) and  */
     double stage2_ms;        /* of the corrector contraction launches              */
-    int64_t stage2_launches;
+    int64_t stage2_launches; /* (small tiles: with the next step's noise)          */
     double gemm_flops;       /* algorithmic flops of all contractions of the run   */
     /* two-time (n_lags > 0): C(l) = Csym(l) + kappa i (chi_xx + chi_yy
        + i chi_yx - i chi_xy) (Eq. (S3) and the Kubo correction after it);
@@ -438,7 +443,7 @@ TWA_API int twa_run_batch(const twa_point* pts, int n_points, const twa_batch_op
  * The observables of the forward run are written to *out.  Requires a pump
  * from twa_build_pump with w > 0 and the Heun integrator; precision FP64,
  * FP32 or split BF16 (TWA_PREC_BF16X3: every contraction, forward and
- * reverse, with its operands in the hi, lo, hi form).  Errors as twa_run.
+ * reverse, with its operands in the hi, lo form).  Errors as twa_run.
  */
 TWA_API int twa_adjoint(const twa_params* p, int64_t n_traj, double dt, int64_t n_steps,
                         uint64_t seed, int32_t ckpt_every, twa_observables* out,
@@ -456,7 +461,7 @@ TWA_API int twa_adjoint(const twa_params* p, int64_t n_traj, double dt, int64_t 
  * forward run in contraction work, no checkpoint store; the cheaper choice
  * for one parameter (the threshold search in w).  Requires a pump from
  * twa_build_pump with w > 0; Heun, no lags, any precision (split BF16
- * included: the tangent's operands in the hi, lo, hi form).  grads: host,
+ * included: the tangent's operands in the hi, lo form).  grads: host,
  * 3 doubles.  Errors as twa_adjoint.
  */
 TWA_API int twa_tangent_w(const twa_params* p, int64_t n_traj, double dt, int64_t n_steps, uint64_t seed,

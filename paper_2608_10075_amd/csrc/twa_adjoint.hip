@@ -281,7 +281,7 @@ int adjoint_impl(const twa_params* p, int64_t n_traj, double dt, int64_t n_steps
     if (mask & 1) obj[nobj++] = 0;
     if (mask & 2) obj[nobj++] = 1;
     const size_t se = sizeof(S), ge = (size_t)gemm_elt_bytes(p->precision);
-    // K extent of one operand block: P, or 3P in the split form (hi, lo, hi)
+    // K extent of one operand block: P for each part of a value
     const int64_t KP = g.P * Prec<PREC>::NP;
     const size_t plane = (size_t)g.Bp * g.P * se;
     const size_t partsz = (size_t)3 * g.nmt * g.Bp * se;
