@@ -23,6 +23,9 @@
  *     caller; pointers documented as "device" are HIP device memory owned by
  *     the caller.  Library-owned objects (twa_pump) are released with their
  *     free function.
+ *   - While a pump handle is alive the library keeps the device buffer of the
+ *     last run, up to 1/64 of the device's memory, for the next one; it is
+ *     freed with the last handle, or when an allocation of the library fails.
  *   - `stream` arguments are hipStream_t passed as void*.  Every compute
  *     entry point is stream-ordered on that stream and returns after its
  *     results are on the host unless stated otherwise; with NULL it runs on a

@@ -298,8 +298,10 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     static_assert(KB % 64 == 0, "K stage");
     // SK > 1: as many groups of waves, each with the products of one of the SK
     // K stages of a ring stage, so that a tile that has a compute unit to itself
-    // keeps two waves on a SIMD.  Their sums are added through LDS; the epilogue
-    // is split over ES of the groups by 16-row blocks, EBI to a wave.
+    // keeps two waves on a SIMD (with one, a K stage of a 64x64 tile in FP32 took
+    // 0.58 us for 0.32 of MFMA; 1500 x 256: 72 us a step, with two groups 62).
+    // Their sums are added through LDS; the epilogue is split over ES of the
+    // groups by 16-row blocks, EBI to a wave.
     constexpr int GH = G_ / SK;              // units of a ring stage for one group
     constexpr int ES = BI % SK == 0 ? SK : BI, EBI = BI / ES;
     static_assert(SK == 1 || (G_ > 1 && G_ % SK == 0 && SK % ES == 0), "groups of waves");
