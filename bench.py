@@ -56,7 +56,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 METRIC = "trajectory-atom-steps/s at N=1e4 + adjoint d(g2)/d(w,alpha) cost vs forward"
-PEAK_TFLOPS = {"bf16": 2500.0, "fp16": 2500.0, "bf16x3": 2500.0, "fp32": 2500.0 / 6, "fp64": 78.6}
+PEAK_TFLOPS = {"bf16": 2500.0, "fp16": 2500.0, "bf16x3": 2500.0, "fp32": 157.3, "fp64": 78.6}
 KERNEL_SOURCES = ["paper_2608_10075_amd/csrc/twa_step_impl.h", "paper_2608_10075_amd/csrc/twa_device.h"]
 STEPS_PER_BENCH_STEP = 1000
 

@@ -74,11 +74,7 @@ extern "C" {
 
 /* ---- precisions of the channel-mixing contraction ---------------------- */
 #define TWA_PREC_FP64   0   /* FP64 state, FP64 MFMA contraction               */
-#define TWA_PREC_FP32   1   /* FP32 state; each contraction operand held in all   */
-                            /* its 24 bits as three bf16 parts, the six products  */
-                            /* above 2^-25 of one formed on BF16 MFMA with FP32   */
-                            /* accumulation (errors against FP64 as with the      */
-                            /* FP32 MFMA, which is 16 times slower)               */
+#define TWA_PREC_FP32   1   /* FP32 state, FP32 MFMA contraction               */
 #define TWA_PREC_BF16   2   /* FP32 state, BF16 MFMA inputs, FP32 accumulation */
 #define TWA_PREC_FP16   3   /* FP32 state, FP16 MFMA inputs, FP32 accumulation */
 #define TWA_PREC_BF16X3 4   /* FP32 state; each contraction operand split into   */

@@ -272,6 +272,10 @@ int adjoint_impl(const twa_params* p, int64_t n_traj, double dt, int64_t n_steps
     const int64_t N = pump->N, B = n_traj;
     const int64_t burnin = p->burnin < 0 ? n_steps / 2 : p->burnin;
     const int cfg = p->tile_config >= 0 ? p->tile_config : pick_tile_cfg(p->precision, N, B);
+    if (p->tile_config >= 0 && !tile_cfg_ok(p->precision, cfg)) {
+        set_error("twa_adjoint: unknown tile configuration");
+        return TWA_EINVAL;
+    }
     const Geometry g = make_geometry(p->precision, cfg, N, B);
     const int J = (int)std::min<int64_t>(32, B);
     const int64_t nseg = (n_steps + K - 1) / K;
@@ -428,7 +432,7 @@ int adjoint_impl(const twa_params* p, int64_t n_traj, double dt, int64_t n_steps
         finalize_moments(traj, B, out);
         out->n_samples = ns;
         out->step_criterion = std::max(p->gamma * (double)N, pump->lam_max) * dt;
-        out->tile_config = cfg;
+        out->tile_config = tile_cfg(p->precision, cfg).base;
         out->max_norm_dev = fwd_norm_dev;
         out->nan_flag = fwd_nan ? 1 : 0;
         if (!std::isfinite(out->SpSm) || !std::isfinite(out->g2)) out->nan_flag = 1;

@@ -409,10 +409,10 @@ int run_steps(std::vector<Bucket>& bks, const Plan& plan, int64_t n0, int64_t n1
 int bucket_of(int64_t N) { return N <= 128 ? 0 : N <= 1024 ? 1 : 2; }
 
 std::vector<int> bucket_candidates(int bucket, int precision) {
-    if (precision == TWA_PREC_FP64) return {0, 1, 3};
-    if (bucket == 0) return {0, 1};
-    if (bucket == 2 && operand_split(precision) == 2) return {2, 3, 7};
-    return {1, 3, 7};
+    if (precision == TWA_PREC_FP64 || bucket == 0) return {0, 1};
+    const int wide = precision == TWA_PREC_BF16 || precision == TWA_PREC_FP16 ? 3 : 2;
+    if (bucket == 1) return {1, 10, wide, 7};
+    return {10, wide, 7};
 }
 
 std::string tune_key(const BatchSpec& sp, const std::vector<int>& idx) {
@@ -676,7 +676,7 @@ int run_batch(const twa_point* pts, int np, const twa_batch_opts* o, twa_observa
             out.max_norm_dev = mx;
             out.step_criterion = std::max(o->gamma * (double)g.N, pumps[(size_t)p]->lam_max) * pts[p].dt;
             out.nan_flag = nan ? 1 : 0;
-            out.tile_config = bk.cfg;
+            out.tile_config = tile_cfg(o->precision, bk.cfg).base;
             out.kernel_ms = loop_ms;   // the whole scan's step loop
             const double nnb = (double)g.N * (double)g.N * (double)g.B;
             out.gemm_flops = 12.0 * nnb * (double)o->n_steps + (L > 0 ? 16.0 * nnb * (double)((L - 1) * stride) : 0.0);

@@ -15,8 +15,8 @@ namespace twa {
 // is then a single contiguous run of MT * kt elements (whole cache lines),
 // where a row-major matrix would give MT runs of kt elements one row pitch
 // apart.  kt = K elements per LDS stage of the tile configuration.
-// In the split forms (Prec::NP parts per value) a stage holds the kt columns
-// of all P rows of part 0, then those of part 1, ...: element (i, j) of part p.
+// In the split form (Prec::NP parts per value) a stage holds the kt columns
+// of all P rows of part 0, then those of part 1: element (i, j) of part p.
 __host__ __device__ __forceinline__ int64_t a_index(int64_t i, int64_t j, int64_t P, int64_t kt, int np = 1,
                                                     int p = 0) {
     return ((j / kt) * np + p) * P * kt + i * kt + (j % kt);
@@ -111,7 +111,8 @@ struct Prec;
 
 template <>
 struct Prec<TWA_PREC_FP64> {
-    static constexpr int NP = 1;      // bf16 parts per operand value (split forms: 2 or 3)
+    static constexpr int NP = 1;      // bf16 parts per operand value
+    static constexpr int NSW = 1;     // sweeps over a K block
     typedef double G;   // contraction operand
     typedef double S;   // state / accumulator
     typedef f64x4 AV;
@@ -128,8 +129,26 @@ struct Prec<TWA_PREC_FP64> {
 };
 
 template <>
+struct Prec<TWA_PREC_FP32> {
+    static constexpr int NP = 1;
+    static constexpr int NSW = 1;
+    // 16x16 MFMA output: register r of lane l holds row 4 (l/16) + r
+    __device__ static __forceinline__ int arow(int m) { return m; }
+    typedef float G;
+    typedef float S;
+    typedef f32x4 AV;
+    __device__ static __forceinline__ G to_g(S v) { return v; }
+    __device__ static __forceinline__ void mma(AV& c, const uint4& a, const uint4& b) {
+        const f32x4 fa = __builtin_bit_cast(f32x4, a), fb = __builtin_bit_cast(f32x4, b);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) c = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[q], fb[q], c, 0, 0, 0);
+    }
+};
+
+template <>
 struct Prec<TWA_PREC_BF16> {
     static constexpr int NP = 1;
+    static constexpr int NSW = 1;
     // 16x16 MFMA output: register r of lane l holds row 4 (l/16) + r
     __device__ static __forceinline__ int arow(int m) { return m; }
     typedef bf16s G;
@@ -145,6 +164,7 @@ struct Prec<TWA_PREC_BF16> {
 template <>
 struct Prec<TWA_PREC_FP16> {
     static constexpr int NP = 1;
+    static constexpr int NSW = 1;
     // 16x16 MFMA output: register r of lane l holds row 4 (l/16) + r
     __device__ static __forceinline__ int arow(int m) { return m; }
     typedef _Float16 G;
@@ -157,40 +177,19 @@ struct Prec<TWA_PREC_FP16> {
     }
 };
 
-// Split forms: every operand value x is stored as NP bf16 parts, each the
-// rounded remainder of the parts before it (hi = bf16(x), then bf16(x - hi),
-// ...; Henry, Tang and Heinecke 2019), each part in a K block of its own, and
-// a contraction sums the products of parts pa and px with pa + px < NP on
-// BF16 MFMA with FP32 accumulation.
-// NP = 2 (TWA_PREC_BF16X3): hi hi + lo hi + hi lo; the dropped lo lo and the
-// rounding of lo are O(2^-17) relative.
+// Split BF16: every operand value x is stored in two bf16 parts, hi = bf16(x)
+// and lo = bf16(x - hi), and one accumulator takes NSW = 3 sweeps over each K
+// block of P values, A.hi X.hi, then A.hi X.lo, then A.lo X.hi; the dropped
+// lo lo and the rounding of lo are O(2^-17) relative.  (All three products of
+// a K stage formed together load each part once, 4 reads in place of 6, and
+// took 266 us a step at 4096 x 512 against 318, but add up in another
+// order; where <S+S-> nearly cancels, g2 and its standard error then differ in
+// the fourth digit, beyond any rounding of the outputs themselves.)
 template <>
 struct Prec<TWA_PREC_BF16X3> : Prec<TWA_PREC_BF16> {
     static constexpr int NP = 2;
+    static constexpr int NSW = 3;
 };
-// NP = 3 (TWA_PREC_FP32): the three parts hold all 24 bits of a binary32
-// value and the six products kept leave out less than 2^-25 of one.  The BF16
-// MFMA is 16 times the FP32 one, so six products take 0.375 of its time.
-// Rounding of the BF16 MFMA, measured on gfx950: unbiased where products are
-// within 2^-8 of C, but smaller ones are added 6 bits below C's last place and
-// cut towards minus infinity there, a bias of -0.0088 of C's last place per
-// MFMA (the FP32 MFMA has none).  The products of lower parts, 5 of the 6, all
-// fall below: in one sum with the first they made the error of N = 201 over
-// 800 steps 2.0e-5 (5.6e-6 with the FP32 MFMA) - one sign on every spin of a
-// trajectory is the uniform field that collective decay amplifies.  So they
-// are summed apart, where C is 2^-8 smaller, and what is left of the bias (far
-// elements of a row) alternates in sign along the chain: the rows of odd spins
-// are stored and contracted with the opposite sign (row_flipped).
-template <>
-struct Prec<TWA_PREC_FP32> : Prec<TWA_PREC_BF16> {
-    static constexpr int NP = 3;
-};
-
-// sign of spin i's row in the constant operands of a precision
-template <int PREC>
-__host__ __device__ constexpr bool row_flipped(int64_t i) {
-    return Prec<PREC>::NP > 1 && (i & 1);
-}
 
 // the bf16 parts of a value
 template <int NP>
@@ -203,7 +202,7 @@ __device__ __forceinline__ void bf16_parts(float v, uint16_t (&h)[NP]) {
     }
 }
 
-// one operand value: p[0], or in the split forms its parts blk elements apart
+// one operand value: p[0], or in the split form its parts blk elements apart
 template <int PREC>
 __device__ __forceinline__ void put_op(typename Prec<PREC>::G* p, int64_t blk, typename Prec<PREC>::S v) {
     constexpr int NP = Prec<PREC>::NP;
@@ -217,13 +216,12 @@ __device__ __forceinline__ void put_op(typename Prec<PREC>::G* p, int64_t blk, t
     }
 }
 
-// element (i, j) of a stage-blocked constant operand, all its parts, with its
-// row's sign
+// element (i, j) of a stage-blocked constant operand, all its parts
 template <int PREC>
 __device__ __forceinline__ void put_a(typename Prec<PREC>::G* A, int64_t i, int64_t j, int64_t P, int64_t kt,
                                       typename Prec<PREC>::S v) {
     constexpr int NP = Prec<PREC>::NP;
-    put_op<PREC>(A + a_index(i, j, P, kt, NP, 0), P * kt, row_flipped<PREC>(i) ? -v : v);
+    put_op<PREC>(A + a_index(i, j, P, kt, NP, 0), P * kt, v);
 }
 
 // element i of column c of a column operand, all its parts
@@ -250,6 +248,8 @@ __device__ __forceinline__ void put_x4(typename Prec<PREC>::G* X, int64_t c, int
 #pragma unroll
         for (int q = 0; q < NP; ++q)
             *reinterpret_cast<ushort4*>(p + q * C2 * kt) = make_ushort4(h[0][q], h[1][q], h[2][q], h[3][q]);
+    } else if constexpr (PREC == TWA_PREC_FP32) {
+        *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
     } else {
         uint16_t h[4];
 #pragma unroll

@@ -42,35 +42,43 @@ struct Status {
 // ---------------------------------------------------------------------------
 // tile configurations of the channel-mixing contraction.  A configuration is
 // (MT rows of spins, NT operand columns = NT/2 trajectories x 2 components,
-// K bytes per LDS stage, waves along M, waves along N).
-// The shapes depend on the parts per operand value (operand_split).  A ring
-// stage holds `group` units, one part of one K stage each: 1, all the parts of
-// a K stage, or with one part several K stages.  With split > 1 as many groups
-// of waves share the K stages of a ring stage.
+// K bytes per LDS stage, waves along M, waves along N, LDS stages, ...).
+// A ring stage holds `group` K stages of one sweep.  With split > 1 as many
+// groups of waves share them.  The order in which the spins of a trajectory
+// are summed follows from mt, waves_m and `sums` (thread groups that add the
+// tiles' partial sums), and nothing else of a configuration shows in a result.
+// Configurations 0 to 8 (FP64: 0 to 3) are those a caller may ask for and keep
+// their shapes (saved tune files name them).  9 and 10 are taken by the
+// automatic choice only: narrower tiles with the row shape of 1 and 2, and so
+// with their results bit for bit (FP64: 32x32, and 64x64 with two groups of
+// waves).  A run reports them as `base`.
 struct TileCfg {
-    int mt, nt, kbytes, waves_m, waves_n, nstage, group, split;
+    int mt, nt, kbytes, waves_m, waves_n, nstage, group, split, sums, base;
 };
-constexpr int kTileCfgs = 9;
+constexpr int kTileCfgs = 11, kPublicTileCfgs = 9;
 constexpr TileCfg kTiles[4][kTileCfgs] = {
-    // one part: BF16, FP16
-    {{32, 32, 64, 2, 1, 6, 2, 1}, {64, 64, 64, 2, 2, 4, 2, 1}, {128, 128, 128, 2, 2, 4, 1, 1},
-     {128, 128, 64, 2, 2, 8, 1, 1}, {64, 64, 64, 2, 2, 4, 4, 1}, {32, 32, 64, 1, 1, 4, 4, 2},
-     {64, 64, 64, 2, 2, 4, 4, 2}, {320, 256, 128, 4, 2, 2, 1, 1}, {320, 256, 64, 4, 2, 4, 1, 1}},
-    // two parts: split BF16
-    {{32, 32, 64, 1, 1, 3, 4, 2}, {64, 64, 64, 2, 2, 3, 2, 1}, {128, 128, 64, 4, 2, 8, 1, 1},
-     {128, 64, 64, 2, 2, 3, 2, 1}, {64, 64, 64, 2, 2, 3, 4, 2}, {32, 32, 64, 2, 1, 6, 2, 1},
-     {32, 32, 64, 2, 1, 3, 4, 2}, {320, 256, 64, 4, 2, 4, 1, 1}, {256, 128, 64, 4, 2, 6, 1, 1}},
-    // three parts: FP32
-    {{32, 32, 64, 2, 1, 3, 6, 2}, {64, 64, 64, 2, 2, 3, 3, 1}, {128, 128, 64, 4, 2, 9, 1, 1},
-     {128, 64, 64, 2, 2, 2, 3, 1}, {64, 64, 64, 2, 2, 2, 3, 1}, {64, 64, 64, 2, 2, 3, 6, 2},
-     {32, 32, 64, 2, 1, 6, 3, 1}, {256, 128, 64, 4, 2, 6, 1, 1}, {16, 32, 64, 1, 1, 4, 3, 1}},
-    // FP64 (configurations 0 to 3 only).  The smallest tiles' rings are as deep
-    // as lets four and three blocks share a compute unit, no more: with five a
-    // unit at times got more than its share while others idled (16x32, stage 1
-    // at 600 x 400 50 us in place of 40).
-    {{16, 32, 64, 1, 1, 10, 1, 1}, {64, 64, 64, 2, 2, 4, 2, 1}, {32, 32, 64, 2, 1, 11, 1, 1},
-     {64, 64, 64, 2, 2, 4, 4, 2}, {64, 64, 64, 2, 2, 4, 1, 1}, {64, 64, 64, 2, 2, 4, 1, 1},
-     {64, 64, 64, 2, 2, 4, 1, 1}, {64, 64, 64, 2, 2, 4, 1, 1}, {64, 64, 64, 2, 2, 4, 1, 1}},
+    // BF16, FP16
+    {{16, 32, 64, 1, 1, 8, 1, 1, 4, 0}, {64, 64, 64, 2, 2, 4, 2, 1, 8, 1}, {128, 128, 128, 2, 2, 4, 1, 1, 4, 2},
+     {128, 128, 64, 2, 2, 8, 1, 1, 4, 3}, {256, 128, 64, 4, 1, 6, 1, 1, 4, 4}, {128, 256, 64, 2, 2, 6, 1, 1, 2, 5},
+     {256, 128, 64, 4, 2, 4, 1, 1, 8, 6}, {320, 256, 128, 4, 2, 2, 1, 1, 4, 7}, {320, 256, 64, 4, 2, 4, 1, 1, 4, 8},
+     {64, 32, 64, 2, 1, 4, 2, 1, 8, 1}, {128, 64, 64, 2, 2, 4, 1, 1, 4, 2}},
+    // split BF16
+    {{16, 32, 64, 1, 1, 8, 1, 1, 4, 0}, {64, 64, 64, 2, 2, 4, 2, 1, 8, 1}, {128, 128, 64, 2, 4, 8, 1, 1, 4, 2},
+     {128, 128, 64, 2, 2, 8, 1, 1, 4, 3}, {256, 128, 64, 4, 1, 6, 1, 1, 4, 4}, {128, 256, 64, 2, 2, 6, 1, 1, 2, 5},
+     {256, 128, 64, 4, 2, 4, 1, 1, 8, 6}, {320, 256, 128, 4, 2, 2, 1, 1, 4, 7}, {320, 256, 64, 4, 2, 4, 1, 1, 4, 8},
+     {64, 32, 64, 2, 1, 4, 2, 1, 8, 1}, {128, 64, 64, 2, 2, 4, 1, 1, 4, 2}},
+    // FP32
+    {{16, 32, 64, 1, 1, 8, 1, 1, 4, 0}, {64, 64, 64, 2, 2, 4, 2, 1, 8, 1}, {128, 128, 64, 2, 4, 8, 1, 1, 4, 2},
+     {128, 128, 64, 2, 2, 8, 1, 1, 4, 3}, {256, 128, 64, 4, 1, 6, 1, 1, 4, 4}, {128, 256, 64, 2, 2, 6, 1, 1, 2, 5},
+     {256, 128, 64, 4, 2, 4, 1, 1, 8, 6}, {320, 256, 128, 4, 2, 2, 1, 1, 4, 7}, {320, 256, 64, 4, 2, 4, 1, 1, 4, 8},
+     {64, 32, 64, 2, 1, 4, 2, 1, 8, 1}, {128, 64, 64, 2, 2, 4, 1, 1, 4, 2}},
+    // FP64 (configurations 0 to 3, 9 and 10 only).  The smallest tiles' rings
+    // are as deep as lets four and three blocks share a compute unit, no more:
+    // with five a unit at times got more than its share while others idled
+    // (16x32, stage 1 at 600 x 400 50 us in place of 40).
+    {{16, 32, 64, 1, 1, 10, 1, 1, 4, 0}, {64, 64, 64, 2, 2, 4, 2, 1, 8, 1}, {128, 128, 128, 2, 2, 4, 1, 1, 4, 2},
+     {128, 128, 64, 2, 2, 8, 1, 1, 4, 3}, {}, {}, {}, {}, {},
+     {32, 32, 64, 2, 1, 11, 1, 1, 8, 0}, {64, 64, 64, 2, 2, 4, 4, 2, 16, 1}},
 };
 // row of kTiles of a precision
 constexpr int tile_table(int precision) {
@@ -84,14 +92,15 @@ constexpr int tile_table(int precision) {
 constexpr bool noise_fits(int mt, int nt, int kbytes, int nstage, int group) {
     return nstage * group * (mt + nt) * kbytes <= 80 * 1024 || mt * nt <= 64 * 64;
 }
-inline int n_tile_cfgs() { return kTileCfgs; }
+// whether a caller may ask for a configuration
+inline bool tile_cfg_ok(int precision, int id) { return id < (precision == TWA_PREC_FP64 ? 4 : kPublicTileCfgs); }
 const TileCfg& tile_cfg(int precision, int id);
 int pick_tile_cfg(int precision, int64_t N, int64_t n_traj);
 
 inline int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
 int gemm_elt_bytes(int precision);
 int state_elt_bytes(int precision);
-int operand_split(int precision);   // bf16 parts per operand value (FP32 3, split BF16 2, else 1)
+int operand_split(int precision);   // bf16 parts per operand value (split BF16 2, else 1)
 
 // ---------------------------------------------------------------------------
 // device buffers and launch geometry of one trajectory ensemble

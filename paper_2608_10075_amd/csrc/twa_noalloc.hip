@@ -191,7 +191,7 @@ int run_noalloc(const twa_params* p, int64_t n_traj, double dt, int64_t n_steps,
         return TWA_EINVAL;
     }
     const int cfg = p->tile_config >= 0 ? p->tile_config : pick_tile_cfg(p->precision, N, B);
-    if (cfg >= n_tile_cfgs() || (p->precision == TWA_PREC_FP64 && cfg > 3)) {
+    if (p->tile_config >= 0 && !tile_cfg_ok(p->precision, cfg)) {
         set_error("twa_run_noalloc: unknown tile configuration");
         return TWA_EINVAL;
     }
@@ -273,7 +273,7 @@ int run_noalloc(const twa_params* p, int64_t n_traj, double dt, int64_t n_steps,
     out->max_norm_dev = hres[J * 5 + 1];
     out->step_criterion = std::max(p->gamma * (double)N, pump->lam_max) * dt;
     out->nan_flag = nan ? 1 : 0;
-    out->tile_config = fused ? TWA_TILE_FUSED : cfg;
+    out->tile_config = fused ? TWA_TILE_FUSED : tile_cfg(p->precision, cfg).base;
     out->kernel_ms = NAN;
     out->gemm_flops = (double)n_steps * 12.0 * (double)N * (double)N * (double)B;
     out->linewidth = out->linewidth_sym = NAN;

@@ -25,11 +25,12 @@ void set_error(const std::string& msg) { g_err = msg; }
 int gemm_elt_bytes(int precision) {
     switch (precision) {
         case TWA_PREC_FP64: return 8;
+        case TWA_PREC_FP32: return 4;
         default: return 2;
     }
 }
 int state_elt_bytes(int precision) { return precision == TWA_PREC_FP64 ? 8 : 4; }
-int operand_split(int precision) { return precision == TWA_PREC_FP32 ? 3 : precision == TWA_PREC_BF16X3 ? 2 : 1; }
+int operand_split(int precision) { return precision == TWA_PREC_BF16X3 ? 2 : 1; }
 
 static int n_compute_units() {
     static int ncu = 0;
@@ -42,59 +43,49 @@ static int n_compute_units() {
     return ncu;
 }
 
-// Tile shape of a contraction: the shortest estimate, in us per step and 1000
-// spins, of rounds of tiles over the compute units x the cost of a round.  A
-// larger tile loads fewer bytes per product but leaves compute units idle
-// where there are few tiles; a round that is the only one costs more (nothing
-// runs beside its epilogue).  Costs measured per step of N x B = 700 x 512 to
-// 10^4 x 1024, e.g. in FP32 at 1000 x 1024 96 us with 64x64 tiles (two stages
-// of LDS, three blocks a unit), 96 with 128x64, 220 with 256x128; at
-// 2000 x 1024 285, 269 and 376; at 4096 x 1024 1276, 1006 and 826.  Split BF16
-// at 4096 x 512 340 (64x64), 279 (128x64), 266 (128x128) and 982 (320x256);
-// BF16 at 10^4 x 1024 3028 (64x64), 1756 (128x128) and 965 (320x256).
-// Where larger tiles are too few to fill the device, the smallest are shorter:
-// 32x32 up to two to a compute unit (FP32 2000 x 128, 504 of them, 65 against
-// 87 us with 64x64; 500 x 600, 608, 42 against 33).  FP64, bound by its MFMA,
-// takes 16x32, one wave each, up to one to a SIMD (600 x 400, 950 of them, 65
-// against 89 us; 700 x 512, 1408, 125 against 98), then 32x32 up to three to a
-// unit (700 x 512 86 us, 1500 x 256 164 against 191; 1000 x 512, four, 194
-// against 136).
-// 64x64 tiles that each have a compute unit to themselves share its two waves a
-// SIMD out over K (split, configuration 5 of FP32 and 3 of FP64) where the
-// contraction is long enough to pay for adding the sums: FP32 500 x 600 34
-// against 33 us, 700 x 512 40 against 41, 1200 x 300 54 against 62, 1500 x 256
-// 62 against 72; FP64 500 x 1000 84 against 81, 1000 x 512 130 against 136.
+// Tile shape of a contraction.  In FP64 the smallest tiles that fill the
+// device: bound by its MFMA, it takes 16x32, one wave each, up to one to a SIMD
+// (600 x 400, 950 of them, 65 against 89 us with 64x64; 700 x 512, 1408, 125
+// against 98), then 32x32 up to three to a unit (700 x 512 86 us, 1500 x 256
+// 164 against 191; 1000 x 512, four, 194 against 136), then 64x64, its waves in
+// two groups over K where each has a compute unit to itself and the
+// contraction is long enough to pay for adding the sums (500 x 1000 84 against
+// 81 us, 1000 x 512 130 against 136).
+// The other precisions: the rows of a tile follow from N (16 to N = 48, 64 to
+// N = 768), above that 128 or 320, whichever gives the shorter estimate of
+// rounds of tiles x work per tile / rate per tile (the 320x256 tile moves 45 %
+// fewer bytes per flop than 128x128, whose bound that is, and runs 1.64 times
+// faster, but needs enough tiles to fill the device).  The rows set the order
+// in which a trajectory's spins are summed, so they follow from this rule
+// alone.  The columns show in no result: narrower tiles where the wide ones are
+// too few to fill the device.  64x32 to one a compute unit (FP32 us a step at
+// 201 x 500 25.6 against 26.4 with 64x64, at 600 x 400 46.4 against 47.5; past
+// that two share a unit's SIMDs unevenly, 400 x 600 54.4 against 36.8).  128x64
+// in FP32 throughout (1000 x 1024 123 against 215 with 128x128, 1000 x 4096 394
+// against 440, 2000 x 2048 751 against 817), in split BF16 to one a unit
+// (2000 x 512 136 against 165; 4096 x 512, two, 334 against 318), in BF16 to two
+// (2000 x 512 54 against 75, 4096 x 512 124 against 132; 4096 x 1024, four, 282
+// against 254).
 int pick_tile_cfg(int precision, int64_t N, int64_t n_traj) {
-    struct Cost {
-        int cfg;
-        double single, round;
-    };
-    static const Cost one[] = {{1, 27, 15}, {3, 42, 36}, {7, 105, 105}};
-    static const Cost two[] = {{1, 45, 26}, {3, 57, 36}, {2, 66, 65}, {7, 250, 250}};
-    static const Cost three[] = {{1, 55, 50}, {4, 58, 40}, {3, 80, 67}, {7, 250, 205}};
-    const int np = operand_split(precision);
-    const bool f64 = precision == TWA_PREC_FP64;
-    const Cost* c = np == 1 ? one : np == 2 ? two : three;
-    const int n = np == 1 ? 3 : 4;
     const int64_t ncu = n_compute_units();
     auto tiles = [&](int cfg) {
         const TileCfg& t = tile_cfg(precision, cfg);
         return (round_up(N, t.mt) / t.mt) * (2 * round_up(n_traj, t.nt / 2) / t.nt);
     };
-    if (N <= 48 || tiles(0) <= (f64 ? 4 : 2) * ncu) return 0;
-    const bool split = tiles(1) <= ncu && N >= 600;
-    if (f64) return tiles(2) <= 3 * ncu ? 2 : split ? 3 : 1;
-    int best = 1;
-    double tb = 1e300;
-    for (int q = 0; q < n; ++q) {
-        const int64_t rounds = (tiles(c[q].cfg) + ncu - 1) / ncu;
-        const double t = rounds == 1 ? c[q].single : (double)rounds * c[q].round;
-        if (t < tb) {
-            tb = t;
-            best = c[q].cfg;
-        }
+    if (precision == TWA_PREC_FP64) {
+        if (N <= 48 || tiles(0) <= 4 * ncu) return 0;
+        return tiles(9) <= 3 * ncu ? 9 : tiles(1) <= ncu && N >= 600 ? 10 : 1;
     }
-    return best == 1 && np == 3 && split ? 5 : best;
+    auto est = [&](int cfg, double rate) {
+        const TileCfg& t = tile_cfg(precision, cfg);
+        return (double)((tiles(cfg) + ncu - 1) / ncu) * (double)(t.mt * t.nt) / rate;
+    };
+    if (N <= 48) return 0;
+    if (N <= 768) return tiles(9) <= ncu ? 9 : 1;
+    if (est(7, 1.64) < est(2, 1.0)) return 7;
+    if (precision == TWA_PREC_FP32) return 10;
+    if (operand_split(precision) > 1) return tiles(10) <= ncu ? 10 : 2;
+    return tiles(10) <= 2 * ncu ? 10 : 3;
 }
 
 // ---------------------------------------------------------------------------
@@ -478,8 +469,8 @@ Geometry make_geometry(int precision, int cfg, int64_t N, int64_t B) {
     g.kt = tc.kbytes / gemm_elt_bytes(precision);
     g.N = N;
     g.B = B;
-    // whole tiles, K stages and (with one part per unit) ring stages
-    g.P = round_up(N, std::max<int64_t>(tc.mt, g.kt * std::max(1, tc.group / operand_split(precision))));
+    // whole tiles and ring stages
+    g.P = round_up(N, std::max<int64_t>(tc.mt, g.kt * tc.group));
     g.Bp = round_up(B, tc.nt / 2);
     g.nmt = g.P / tc.mt;
     g.C2 = 2 * g.Bp;

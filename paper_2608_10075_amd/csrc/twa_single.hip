@@ -129,7 +129,7 @@ int run_single(const twa_params* p, int64_t n_traj, double dt, int64_t n_steps, 
         }
     }
     int cfg = toep ? 0 : p->tile_config >= 0 ? p->tile_config : pick_tile_cfg(p->precision, N, B);
-    if (cfg >= n_tile_cfgs() || (p->precision == TWA_PREC_FP64 && cfg > 3)) {
+    if (p->tile_config >= 0 && !tile_cfg_ok(p->precision, cfg)) {
         set_error("twa_run: unknown tile configuration");
         return TWA_EINVAL;
     }
@@ -336,7 +336,7 @@ int run_single(const twa_params* p, int64_t n_traj, double dt, int64_t n_steps, 
         out->max_norm_dev = mx;
         out->step_criterion = (decay ? pump->lam_max : std::max(p->gamma * (double)N, pump->lam_max)) * dt;
         out->nan_flag = nan ? 1 : 0;
-        out->tile_config = fused ? TWA_TILE_FUSED : toep ? TWA_TILE_TOEPLITZ : cfg;
+        out->tile_config = fused ? TWA_TILE_FUSED : toep ? TWA_TILE_TOEPLITZ : tile_cfg(p->precision, cfg).base;
         out->kernel_ms = loop_ms;
         if (tm) {
             tm->s1.harvest(st);

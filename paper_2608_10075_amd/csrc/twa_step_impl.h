@@ -216,7 +216,7 @@ __device__ __forceinline__ void bstg4(Rsrc r, uint32_t voff, const typename Prec
         bst4(r, voff, g);
     }
 }
-// operand store of a state-like value: one block, or in the split forms its
+// operand store of a state-like value: one block, or in the split form its
 // parts blk bytes apart
 template <int PREC>
 __device__ __forceinline__ void bstg4s(Rsrc r, uint32_t voff, uint32_t blk, const typename Prec<PREC>::S (&v)[4]) {
@@ -273,7 +273,7 @@ __device__ __forceinline__ void unroll_units(F& f, const int u0, const int n, st
 // contraction + fused Heun stage
 // One output tile (M tile mt of spins, column tile nt, copy cp) of one stage:
 // contraction over K on MFMA followed by the fused epilogue of the kind.
-template <int PREC, int MT, int NT, int KB, int WMW, int WNW, int NST, int G_, int SK, int STAGE, int KIND>
+template <int PREC, int MT, int NT, int KB, int WMW, int WNW, int NST, int G_, int SK, int SUMS, int STAGE, int KIND>
 __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt, const int nt, const int cp) {
     // KIND_Q_SNAPSHOT on the predictor kind: also store the part of the
     // contraction that comes from the second K half (the noise columns), by
@@ -292,32 +292,29 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     constexpr int BI = WM / 16, BJ = WN / 16;
     constexpr int PCS = KB / 16;             // 16-byte pieces per row
     constexpr int KT = KB / (int)sizeof(G);
-    constexpr int NP = Prec<PREC>::NP;       // parts per operand value
+    constexpr int NP = Prec<PREC>::NP, NSW = Prec<PREC>::NSW;   // parts per operand value, sweeps over a K block
     constexpr int NTRJ = NT / 2;             // trajectories per tile
     static_assert(WM % 16 == 0 && WN % 32 == 0, "wave tile");
     static_assert(KB % 64 == 0, "K stage");
     // SK > 1: as many groups of waves, each with the products of one of the SK
     // K stages of a ring stage, so that a tile that has a compute unit to itself
-    // keeps two waves on a SIMD (with one, a K stage of a 64x64 tile in FP32 took
-    // 0.58 us for 0.32 of MFMA; 1500 x 256: 72 us a step, with two groups 62).
+    // keeps two waves on a SIMD.
     // Their sums are added through LDS; the epilogue is split over ES of the
     // groups by 16-row blocks, EBI to a wave.
     constexpr int GH = G_ / SK;              // units of a ring stage for one group
     constexpr int ES = BI % SK == 0 ? SK : BI, EBI = BI / ES;
     static_assert(SK == 1 || (G_ > 1 && G_ % SK == 0 && SK % ES == 0), "groups of waves");
 
-    // NST LDS stages of G_ units (a ring).  A unit holds one part of one K
-    // stage of the operands: rows [0, MT) of A then [MT, MT + NT) of X, KB bytes per row.
-    // The split forms load each part once and form all its products from
-    // registers and LDS, so NP parts cost NP times the load traffic of one
-    // for NP (NP + 1) / 2 times the MFMA work.  Inside every 16-row block the
+    // NST LDS stages of G_ units (a ring).  A unit holds one K stage of one
+    // sweep: rows [0, MT) of A then [MT, MT + NT) of X, KB bytes per row.
+    // Inside every 16-row block the
     // 16-byte piece c of row r is stored at piece position c ^ swz(r), which
     // makes the 16-lane fragment reads of one MFMA operand hit distinct LDS
     // banks.  The stages are distinct LDS objects so that the compiler can tell
     // the loads in flight into one from the reads of another.
     // A small tile's unit is little work between two barriers (64x64: 128
     // cycles of MFMA against some 300 of barrier and LDS latency), so there a
-    // stage is a whole K stage (G_ = NP) or several.
+    // stage is several K stages.
     static_assert(NST >= 2 && NST <= 12, "LDS ring depth");
     constexpr int UB = (MT + NT) * KB, SB = G_ * UB;
     __shared__ __attribute__((aligned(1024))) char L0[SB];
@@ -337,8 +334,8 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     __shared__ S sG[NTRJ][2];      // collective normals
     // cross-wave partial sums: [wave row][trajectory][4 channels] in the
     // epilogue, [thread group][trajectory][5 channels] for the collective sums
-    constexpr int NG = NTHR / NTRJ;            // thread groups of the collective sums
-    static_assert(NG >= 1, "thread groups");
+    constexpr int NG = SUMS;                   // thread groups of the collective sums
+    static_assert(NG >= 1 && NG * NTRJ <= NTHR, "thread groups");
     __shared__ S red[WMW * ES > NG ? WMW * ES : NG][NTRJ][5];
     __shared__ S sSrc[NTRJ][3];    // adjoint: observation source of each trajectory
 
@@ -353,25 +350,37 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     // ---- main loop: acc[i][col] = sum_k A[m0+i][k] X[n0+col][k]
     AV acc[BI][BJ];
     AV accW[QSNAP ? BI : 1][QSNAP ? BJ : 1];   // accumulator at K stage kq (snapshot kind)
-    // three parts: the products of lower parts have a sum of their own (see
-    // Prec<TWA_PREC_FP32>)
-    constexpr bool LOW = NP == 3;
-    AV accL[LOW ? BI : 1][LOW ? BJ : 1];
 #pragma unroll
     for (int i = 0; i < BI; ++i)
 #pragma unroll
-        for (int j = 0; j < BJ; ++j) {
-            acc[i][j] = AV{0, 0, 0, 0};
-            if constexpr (LOW) accL[i][j] = AV{0, 0, 0, 0};
-        }
+        for (int j = 0; j < BJ; ++j) acc[i][j] = AV{0, 0, 0, 0};
 
-    // Both operands are stage-blocked: unit u (part u % NP of K stage u / NP)
-    // holds the tile's rows of A as one contiguous run of MT KB bytes and its
-    // columns of X as one of NT KB bytes.
+    // Both operands are stage-blocked: a part of a K stage holds the tile's
+    // rows of A as one contiguous run of MT KB bytes and its columns of X as
+    // one of NT KB bytes.
     const char* Ag = reinterpret_cast<const char*>(a.A) + m0 * KB;
     const char* Xg = reinterpret_cast<const char*>(a.X + cp * a.x_copy) + n0 * KB;
-    const int nu = (int)(a.K / KT) / G_;           // ring stages
+    const int nu = (int)(a.K / KT) / NP * NSW / G_;   // ring stages
     const int64_t a_unit = P * KB, x_unit = 2 * Bp * KB;
+    // Where the ring stage that is loaded next starts (they are loaded in
+    // order).  Split form: after the P / KT K stages of a block comes the next
+    // sweep over it, with the lo part (one unit on) of X, then of A.
+    const int nk = (int)(P / KT);
+    int64_t ao = 0, xo = 0;
+    int q = 0, sweep = 0;
+    auto advance = [&] {
+        ao += G_ * NP * a_unit;
+        xo += G_ * NP * x_unit;
+        if constexpr (NSW > 1) {
+            q += G_;
+            if (q == nk) {
+                q = 0;
+                ao += sweep == 0 ? -(nk * NP) * a_unit : sweep == 1 ? (1 - nk * NP) * a_unit : -a_unit;
+                xo += sweep == 0 ? (1 - nk * NP) * x_unit : sweep == 1 ? -(1 + nk * NP) * x_unit : 0;
+                sweep = sweep == 2 ? 0 : sweep + 1;
+            }
+        }
+    };
     // Direct memory -> LDS loads (buffer_load_dwordx4 ... lds): one wave
     // instruction moves 64 x 16 bytes into 1 KB of LDS, lane i to offset 16 i,
     // so each lane fetches the piece that belongs at its slot.  The buffer
@@ -404,14 +413,16 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
         srcA[j] = q * RPC < MT;
         voff[j] = (uint32_t)((row < MT ? row : row - MT) * KB + pc * 16);
     }
-    // stage S_ of the ring: units S_ G_ .. S_ G_ + G_ - 1
-#define TWA_DMA(S_, BUF_)                                                                               \
-    _Pragma("unroll") for (int gu = 0; gu < G_; ++gu) {                                                 \
-        const Rsrc ra_ = wave_rsrc(Ag + ((int64_t)(S_) * G_ + gu) * a_unit, (int64_t)MT * KB);          \
-        const Rsrc rx_ = wave_rsrc(Xg + ((int64_t)(S_) * G_ + gu) * x_unit, (int64_t)NT * KB);          \
-        _Pragma("unroll") for (int j = 0; j < CPW; ++j) if (CPW == CPWMIN || wv + j * NWV < NCH)        \
-            buffer_dma16(srcA[j] ? ra_ : rx_, (BUF_) + gu * UB + (wv + j * NWV) * 1024, voff[j]);        \
-    }
+#define TWA_DMA(BUF_)                                                                                   \
+    do {                                                                                                \
+        _Pragma("unroll") for (int gu = 0; gu < G_; ++gu) {                                             \
+            const Rsrc ra_ = wave_rsrc(Ag + ao + gu * NP * a_unit, (int64_t)MT * KB);                   \
+            const Rsrc rx_ = wave_rsrc(Xg + xo + gu * NP * x_unit, (int64_t)NT * KB);                   \
+            _Pragma("unroll") for (int j = 0; j < CPW; ++j) if (CPW == CPWMIN || wv + j * NWV < NCH)    \
+                buffer_dma16(srcA[j] ? ra_ : rx_, (BUF_) + gu * UB + (wv + j * NWV) * 1024, voff[j]);    \
+        }                                                                                               \
+        advance();                                                                                      \
+    } while (0)
 
     // fragment read offsets of this lane (row within a 16-row block, swizzle)
     const int ra = Prec<PREC>::arow(lane & 15), rx = lane & 15;
@@ -429,24 +440,16 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
 #define TWA_FRAG_X(DST_, BUF_, SEG_)                                                                    \
     _Pragma("unroll") for (int j = 0; j < BJ; ++j) DST_[j] = *reinterpret_cast<const uint4*>(           \
         (BUF_) + offX + 16 * j * KB + ((((SEG_) * 4 + grp) ^ swX) << 4))
-    // LOW_: a product of lower parts
-#define TWA_MMA(A_, X_, LOW_)                                                                                 \
+#define TWA_MMA(A_, X_)                                                                                 \
     _Pragma("unroll") for (int i = 0; i < BI; ++i)                                                      \
-        _Pragma("unroll") for (int j = 0; j < BJ; ++j) {                                                \
-            if constexpr (LOW && (LOW_)) Prec<PREC>::mma(accL[i][j], A_[i], X_[j]);                     \
-            else Prec<PREC>::mma(acc[i][j], A_[i], X_[j]);                                              \
-        }
+        _Pragma("unroll") for (int j = 0; j < BJ; ++j) Prec<PREC>::mma(acc[i][j], A_[i], X_[j])
     // Where registers allow it, the fragments of the next unit are read while
     // this unit's products run, so no MFMA waits for an LDS read and a unit's
     // LDS is free as soon as its turn comes (LOOK units of the ring are then in
-    // registers, not in LDS).  The Heun corrector on 256x128 tiles in FP32 is
-    // left out: it spilled, and each reload drained the loads in flight (stage 2
-    // at 4096 x 1024 450 us, without 333).
-    constexpr bool AHEAD = G_ > 1 || (KB == 64 && 4 * (BI * BJ * ((QSNAP ? 2 : 1) + (LOW ? 1 : 0)) + NP * (BI + BJ)) +
-                                                          (LOW ? (KD == KIND_PRIMAL && STAGE == 2 ? 36 : 32) : 48) <=
-                                                      256);
+    // registers, not in LDS).
+    constexpr bool AHEAD = G_ > 1 || (KB == 64 && 4 * (BI * BJ * (QSNAP ? 2 : 1) + BI + BJ) + 48 <= 256);
     constexpr int LOOK = AHEAD ? 1 : 0;
-    static_assert(G_ == 1 || (KB == 64 && (NP == 1 || GH == NP)), "a stage of several units");
+    static_assert(G_ == 1 || KB == 64, "a stage of several units");
 
     // where the epilogue's streams start: the wave's first element of a state
     // plane, the bytes from there to the plane's end, the lane's byte offset
@@ -484,7 +487,7 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
 #pragma unroll
     for (int u = 0; u < NST - 1 + LOOK; ++u)
         if (u < nu) {
-            TWA_DMA(u, TWA_BUF(u % NST));
+            TWA_DMA(TWA_BUF(u % NST));
         }
     // barrier that orders LDS only (a full one would wait for the loads above)
     auto lds_sync = [] {
@@ -585,50 +588,45 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
         }
         lds_sync();   // the sums are visible to every wave; red is free again
     }
-    // unroll: ring slot and (G_ = 1) part are compile-time
-    constexpr int UN = G_ > 1 || NST % NP == 0 ? NST : NST * NP;
-    constexpr int NF = G_ > 1 ? GH : NP;                 // fragment sets held
-    uint4 fa[NF][BI], fx[NF][BJ];
+    constexpr int UN = NST;   // unroll: the ring slot is compile-time
+    uint4 fa[GH][BI], fx[GH][BJ];
     if constexpr (AHEAD) {
         if (nu >= NST) TWA_WAIT_VM((NST - 1) * G_ * CPWMIN);
         else TWA_WAIT_VM(0);
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 #pragma unroll
-        for (int gu = 0; gu < (G_ > 1 ? GH : 1); ++gu) {
+        for (int gu = 0; gu < GH; ++gu) {
             TWA_FRAG_A(fa[gu], TWA_BUF(0) + gu * UB, 0);
             TWA_FRAG_X(fx[gu], TWA_BUF(0) + gu * UB, 0);
         }
     }
-    // one unit: its part is v % NP, its ring slot v % NST
+    // one ring stage: its slot is v
     auto unit = [&](const int u, auto vc) __attribute__((always_inline)) {
-        constexpr int v = decltype(vc)::value, p = G_ > 1 ? 0 : v % NP, pn = (p + 1) % NP;
-        // unit u (u + 1 with LOOK) has landed once at most the later units are
-        // pending (waves that load fewer chunks per unit wait conservatively)
+        constexpr int v = decltype(vc)::value;
+        // stage u (u + 1 with LOOK) has landed once at most the later ones are
+        // pending (waves that load fewer chunks per stage wait conservatively)
         __builtin_amdgcn_sched_barrier(0);
         if (nu - 1 - u >= NST - 2 + LOOK) TWA_WAIT_VM((NST - 2) * G_ * CPWMIN);
         else TWA_WAIT_VM(0);
         // Barrier without a memory fence: a fence would wait for every load
-        // still in flight into the later units.  What it has to order is
-        // covered explicitly: this wave's loads into the unit completed (vmcnt
+        // still in flight into the later stages.  What it has to order is
+        // covered explicitly: this wave's loads into the stage completed (vmcnt
         // above), and its reads of the LDS that the next load overwrites are in
         // registers (lgkmcnt above).
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-        if (u + NST - 1 + LOOK < nu) TWA_DMA(u + NST - 1 + LOOK, TWA_BUF((v + NST - 1 + LOOK) % NST));
+        if (u + NST - 1 + LOOK < nu) TWA_DMA(TWA_BUF((v + NST - 1 + LOOK) % NST));
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (QSNAP && p == 0) {
-            if (u * G_ == a.kq * NP) {
+        if constexpr (QSNAP) {
+            if (u * G_ == a.kq * NSW) {
 #pragma unroll
                 for (int i = 0; i < BI; ++i)
 #pragma unroll
-                    for (int j = 0; j < BJ; ++j) {
-                        if constexpr (LOW) accW[i][j] = acc[i][j] + accL[i][j];
-                        else accW[i][j] = acc[i][j];
-                    }
+                    for (int j = 0; j < BJ; ++j) accW[i][j] = acc[i][j];
             }
         }
-        if constexpr (G_ > 1) {
+        if constexpr (AHEAD) {
             // (after the last stage these reads return stale LDS, never used)
             uint4 na[GH][BI], nx[GH][BJ];
 #pragma unroll
@@ -636,23 +634,8 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                 TWA_FRAG_A(na[gu], TWA_BUF((v + 1) % NST) + gu * UB, 0);
                 TWA_FRAG_X(nx[gu], TWA_BUF((v + 1) % NST) + gu * UB, 0);
             }
-            // with one part every unit's product, else those of the parts pa
-            // and px with pa + px < NP
 #pragma unroll
-            for (int pa = 0; pa < GH; ++pa) {
-                if constexpr (NP == 1) {
-                    TWA_MMA(fa[pa], fx[pa], false);
-                } else {
-#pragma unroll
-                    for (int px = 0; px < GH - pa; ++px) {
-                        if (pa + px == 0) {
-                            TWA_MMA(fa[pa], fx[px], false);
-                        } else {
-                            TWA_MMA(fa[pa], fx[px], true);
-                        }
-                    }
-                }
-            }
+            for (int gu = 0; gu < GH; ++gu) TWA_MMA(fa[gu], fx[gu]);
 #pragma unroll
             for (int gu = 0; gu < GH; ++gu) {
 #pragma unroll
@@ -660,39 +643,13 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
 #pragma unroll
                 for (int j = 0; j < BJ; ++j) fx[gu][j] = nx[gu][j];
             }
-        } else if constexpr (AHEAD) {
-            // (after the last unit these reads return stale LDS, never used)
-            uint4 na[BI], nx[BJ];
-            TWA_FRAG_A(na, TWA_BUF((v + 1) % NST), 0);
-            TWA_FRAG_X(nx, TWA_BUF((v + 1) % NST), 0);
-            // the products of part p with the parts up to it that are kept
-            // (those with pa + px < NP)
-#pragma unroll
-            for (int q = 0; q <= p; ++q) {
-                if (p + q < NP) TWA_MMA(fa[p], fx[q], p > 0);
-                if (q < p && p + q < NP) TWA_MMA(fa[q], fx[p], p > 0);
-            }
-#pragma unroll
-            for (int i = 0; i < BI; ++i) fa[pn][i] = na[i];
-#pragma unroll
-            for (int j = 0; j < BJ; ++j) fx[pn][j] = nx[j];
-        } else if constexpr (NP == 1) {
+        } else {
 #pragma unroll
             for (int seg = 0; seg < KB / 64; ++seg) {
-                TWA_FRAG_A(fa[0], TWA_BUF(v % NST), seg);
-                TWA_FRAG_X(fx[0], TWA_BUF(v % NST), seg);
-                TWA_MMA(fa[0], fx[0], false);
+                TWA_FRAG_A(fa[0], TWA_BUF(v), seg);
+                TWA_FRAG_X(fx[0], TWA_BUF(v), seg);
+                TWA_MMA(fa[0], fx[0]);
             }
-        } else {
-            static_assert(KB == 64, "one segment per unit in the split forms");
-            TWA_FRAG_A(fa[p], TWA_BUF(v % NST), 0);
-#pragma unroll
-            for (int q = 0; q < p; ++q)
-                if (p + q < NP) TWA_MMA(fa[p], fx[q], p > 0);
-            TWA_FRAG_X(fx[p], TWA_BUF(v % NST), 0);
-#pragma unroll
-            for (int q = 0; q <= p; ++q)
-                if (p + q < NP) TWA_MMA(fa[q], fx[p], p > 0);
         }
     };
     if constexpr (AHEAD) {
@@ -703,12 +660,6 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
         unroll_units(unit, full, nu, std::make_integer_sequence<int, UN>{});
     } else {
         for (int u0 = 0; u0 < nu; u0 += UN) unroll_units(unit, u0, nu, std::make_integer_sequence<int, UN>{});
-    }
-    if constexpr (LOW) {
-#pragma unroll
-        for (int i = 0; i < BI; ++i)
-#pragma unroll
-            for (int j = 0; j < BJ; ++j) acc[i][j] = acc[i][j] + accL[i][j];
     }
     AV eacc[EBI][BJ], eaccW[QSNAP ? EBI : 1][QSNAP ? BJ : 1];
     if constexpr (SK == 1) {
@@ -758,10 +709,7 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
 #undef TWA_WAIT_VM
 
     // ---- epilogue: fused Heun stage on (spin i, trajectory k)
-    // (register r of an accumulator is spin i0 + r with i0 a multiple of 4, so
-    // the sign of its row is known at compile time)
-    auto sgn = [](const S v, const int r) { return row_flipped<PREC>(r) ? -v : v; };
-    auto av = [&](const int bi, const int c, const int r) { return sgn(eacc[bi][c][r], r); };
+    auto av = [&](const int bi, const int c, const int r) { return eacc[bi][c][r]; };
     const S c1 = a.c1, c2 = a.c2;
     // The primal kinds load the state (and, in the corrector, the predictor
     // field) of the next (p, bi) block before the current block is computed
@@ -892,8 +840,8 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                     S qx[4], qy[4];
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        qx[r] = av(bi, 2 * p, r) - sgn(eaccW[bi][2 * p][r], r);
-                        qy[r] = av(bi, 2 * p + 1, r) - sgn(eaccW[bi][2 * p + 1][r], r);
+                        qx[r] = av(bi, 2 * p, r) - eaccW[bi][2 * p][r];
+                        qy[r] = av(bi, 2 * p + 1, r) - eaccW[bi][2 * p + 1][r];
                     }
                     bst4(plane(a.Sout, 0), lane_s + so_s(p, bi), qx);
                     bst4(plane(a.Sout, 1), lane_s + so_s(p, bi), qy);
@@ -1284,7 +1232,7 @@ __device__ __forceinline__ void extra_block(const GemmArgs<PREC>& a, uint32_t bl
 // Each XCD is given a contiguous range of tiles ordered M-tile-major, so the
 // workgroups resident on one XCD share the same rows of A (and walk K
 // together) in that XCD's L2.
-template <int PREC, int MT, int NT, int KB, int WMW, int WNW, int NST, int G_, int SK, int STAGE, int KIND>
+template <int PREC, int MT, int NT, int KB, int WMW, int WNW, int NST, int G_, int SK, int SUMS, int STAGE, int KIND>
 __global__ __launch_bounds__(64 * WMW * WNW * SK) void heun_stage_kernel(GemmArgs<PREC> a) {
     constexpr bool PRIM = KIND == KIND_PRIMAL || KIND == KIND_SIB;
     constexpr int NTHR = 64 * WMW * WNW * SK, KT = KB / (int)sizeof(typename Prec<PREC>::G);
@@ -1296,7 +1244,7 @@ __global__ __launch_bounds__(64 * WMW * WNW * SK) void heun_stage_kernel(GemmArg
     const int q = T / 8, r = T % 8;
     const int b = (int)blockIdx.x, x = b % 8, j = b / 8;
     const int L = x * q + (x < r ? x : r) + j;
-    stage_tile<PREC, MT, NT, KB, WMW, WNW, NST, G_, SK, STAGE, KIND>(a, L / nnt, L % nnt, (int)blockIdx.z);
+    stage_tile<PREC, MT, NT, KB, WMW, WNW, NST, G_, SK, SUMS, STAGE, KIND>(a, L / nnt, L % nnt, (int)blockIdx.z);
     if constexpr (PRIM) {
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             if constexpr (STAGE == 2) a.step[0] += 1;
@@ -1310,7 +1258,7 @@ __global__ __launch_bounds__(64 * WMW * WNW * SK) void heun_stage_kernel(GemmArg
 // list (point, M tile, column tile, copy) ordered longest-first; workgroup b
 // takes tiles b, b + grid, b + 2 grid, ...  The blocks past the tiles of a
 // primal stage (copy -1) come last.
-template <int PREC, int MT, int NT, int KB, int WMW, int WNW, int NST, int G_, int SK, int STAGE, int KIND>
+template <int PREC, int MT, int NT, int KB, int WMW, int WNW, int NST, int G_, int SK, int SUMS, int STAGE, int KIND>
 __global__ __launch_bounds__(64 * WMW * WNW * SK) void heun_stage_grouped(const GemmArgs<PREC>* __restrict__ args,
                                                                      const int4* __restrict__ tiles, int ntiles,
                                                                      int64_t* step) {
@@ -1325,7 +1273,7 @@ __global__ __launch_bounds__(64 * WMW * WNW * SK) void heun_stage_grouped(const 
             }
         }
         __syncthreads();   // LDS of the previous tile is free
-        stage_tile<PREC, MT, NT, KB, WMW, WNW, NST, G_, SK, STAGE, KIND>(args[tt.x], tt.y, tt.z, tt.w);
+        stage_tile<PREC, MT, NT, KB, WMW, WNW, NST, G_, SK, SUMS, STAGE, KIND>(args[tt.x], tt.y, tt.z, tt.w);
     }
     if constexpr (PRIM) {
         if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -1339,7 +1287,7 @@ template <int PREC, int CFG>
 struct CfgT {
     static constexpr TileCfg C = kTiles[tile_table(PREC)][CFG];
     static constexpr int MT = C.mt, NT = C.nt, KB = C.kbytes, WMW = C.waves_m, WNW = C.waves_n, NST = C.nstage, G = C.group,
-                         SK = C.split;
+                         SK = C.split, SUMS = C.sums;
 };
 
 template <int PREC, int CFG, int STAGE, int KIND>
@@ -1352,7 +1300,7 @@ static int launch_kernel(const GemmArgs<PREC>& a, int64_t P, int64_t C2, int nco
     const int64_t extra = PRIM ? extra_blocks<PREC, 64 * C::WMW * C::WNW * C::SK, STAGE>(aa, kt) : 0;
     dim3 grid((unsigned)((P / C::MT) * (C2 / C::NT) + extra), 1u, (unsigned)ncopy);
     dim3 block(64 * C::WMW * C::WNW * C::SK);
-    hipLaunchKernelGGL((heun_stage_kernel<PREC, C::MT, C::NT, C::KB, C::WMW, C::WNW, C::NST, C::G, C::SK, STAGE, KIND>), grid,
+    hipLaunchKernelGGL((heun_stage_kernel<PREC, C::MT, C::NT, C::KB, C::WMW, C::WNW, C::NST, C::G, C::SK, C::SUMS, STAGE, KIND>), grid,
                        block, 0, st, aa);
     TWA_HIP_CHECK(hipGetLastError());
     return TWA_OK;
@@ -1421,6 +1369,10 @@ static int dispatch_cfg(const GemmArgs<PREC>& a, int cfg, int stage, int kind, i
             case 7: return dispatch_kind<PREC, 7>(a, stage, kind, P, C2, ncopy, st);
             case 8: return dispatch_kind<PREC, 8>(a, stage, kind, P, C2, ncopy, st);
         }
+    }
+    switch (cfg) {
+        case 9: return dispatch_kind<PREC, 9>(a, stage, kind, P, C2, ncopy, st);
+        case 10: return dispatch_kind<PREC, 10>(a, stage, kind, P, C2, ncopy, st);
     }
     set_error("unknown tile configuration");
     return TWA_EINVAL;
@@ -1583,7 +1535,7 @@ template <int PREC, int CFG, int STAGE, int KIND>
 static int grouped_launch_k(const GroupedPlan& pl, int cur, int variant, hipStream_t st) {
     typedef CfgT<PREC, CFG> C;
     const int tl = variant == GV_TANGENT ? 1 : STAGE == 1 ? 0 : 2;
-    hipLaunchKernelGGL((heun_stage_grouped<PREC, C::MT, C::NT, C::KB, C::WMW, C::WNW, C::NST, C::G, C::SK, STAGE, KIND>),
+    hipLaunchKernelGGL((heun_stage_grouped<PREC, C::MT, C::NT, C::KB, C::WMW, C::WNW, C::NST, C::G, C::SK, C::SUMS, STAGE, KIND>),
                        dim3((unsigned)pl.grid[tl]), dim3(64 * C::WMW * C::WNW * C::SK), 0, st,
                        static_cast<const GemmArgs<PREC>*>(pl.d_args[variant][STAGE - 1][cur]), pl.d_tiles[tl],
                        pl.ntiles[tl], pl.step);
@@ -1603,7 +1555,7 @@ static int grouped_occupancy() {
     typedef CfgT<PREC, CFG> C;
     int nb = 0;
     hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &nb, heun_stage_grouped<PREC, C::MT, C::NT, C::KB, C::WMW, C::WNW, C::NST, C::G, C::SK, 1, KIND_PRIMAL>,
+        &nb, heun_stage_grouped<PREC, C::MT, C::NT, C::KB, C::WMW, C::WNW, C::NST, C::G, C::SK, C::SUMS, 1, KIND_PRIMAL>,
         64 * C::WMW * C::WNW * C::SK, 0);
     return nb > 0 ? nb : 1;
 }
@@ -1658,6 +1610,8 @@ int grouped_prepare_p(const std::vector<Geometry>& gs, const std::vector<Ensembl
         case 1: occ = grouped_occupancy<PREC, 1>(); break;
         case 2: occ = grouped_occupancy<PREC, 2>(); break;
         case 3: occ = grouped_occupancy<PREC, 3>(); break;
+        case 9: occ = grouped_occupancy<PREC, 9>(); break;
+        case 10: occ = grouped_occupancy<PREC, 10>(); break;
         case 7:
             if constexpr (PREC != TWA_PREC_FP64) occ = grouped_occupancy<PREC, 7>();
             break;
@@ -1715,11 +1669,13 @@ int grouped_launch_p(const GroupedPlan& pl, int stage, int cur, int variant, hip
         case 1: return grouped_dispatch<PREC, 1>(pl, stage, cur, variant, st);
         case 2: return grouped_dispatch<PREC, 2>(pl, stage, cur, variant, st);
         case 3: return grouped_dispatch<PREC, 3>(pl, stage, cur, variant, st);
+        case 9: return grouped_dispatch<PREC, 9>(pl, stage, cur, variant, st);
+        case 10: return grouped_dispatch<PREC, 10>(pl, stage, cur, variant, st);
         case 7:
             if constexpr (PREC != TWA_PREC_FP64) return grouped_dispatch<PREC, 7>(pl, stage, cur, variant, st);
             break;
     }
-    set_error("grouped launch: tile configuration must be 0..3 or 7 (not 7 in FP64)");
+    set_error("grouped launch: tile configuration must be 0..3, 7 (not in FP64), 9 or 10");
     return TWA_EINVAL;
 }
 

@@ -83,7 +83,7 @@ int run_tangent_w(const twa_params* p, int64_t n_traj, double dt, int64_t n_step
         return TWA_EINVAL;
     }
     const int cfg = p->tile_config >= 0 ? p->tile_config : pick_tile_cfg(p->precision, N, B);
-    if (cfg >= n_tile_cfgs() || (p->precision == TWA_PREC_FP64 && cfg > 3)) {
+    if (p->tile_config >= 0 && !tile_cfg_ok(p->precision, cfg)) {
         set_error("twa_tangent_w: unknown tile configuration");
         return TWA_EINVAL;
     }
@@ -234,7 +234,7 @@ int run_tangent_w(const twa_params* p, int64_t n_traj, double dt, int64_t n_step
         out->max_norm_dev = mx;
         out->step_criterion = std::max(p->gamma * (double)N, pump->lam_max) * dt;
         out->nan_flag = nan ? 1 : 0;
-        out->tile_config = cfg;
+        out->tile_config = tile_cfg(p->precision, cfg).base;
         out->kernel_ms = ms;
         out->gemm_flops = 20.0 * (double)N * (double)N * (double)B * (double)n_steps;
         out->linewidth = out->linewidth_sym = NAN;
