@@ -6,21 +6,9 @@
 #include <stdint.h>
 
 #include "../../include/twa.h"
+#include "twa_index.h"
 
 namespace twa {
-
-// The constant operand A of a contraction (P rows, K columns) is stored
-// stage-blocked: the kt columns of K stage q of all P rows are contiguous,
-// row after row, and the stages follow one another.  One LDS stage of MT rows
-// is then a single contiguous run of MT * kt elements (whole cache lines),
-// where a row-major matrix would give MT runs of kt elements one row pitch
-// apart.  kt = K elements per LDS stage of the tile configuration.
-// In the split form (Prec::NP parts per value) a stage holds the kt columns
-// of all P rows of part 0, then those of part 1: element (i, j) of part p.
-__host__ __device__ __forceinline__ int64_t a_index(int64_t i, int64_t j, int64_t P, int64_t kt, int np = 1,
-                                                    int p = 0) {
-    return ((j / kt) * np + p) * P * kt + i * kt + (j % kt);
-}
 
 // ---------------------------------------------------------------------------
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11): ten rounds of two 32x32
@@ -68,24 +56,6 @@ __device__ __forceinline__ void box_muller(uint32_t a, uint32_t b, double& z0, d
     sincospi(2.0 * u2, &s, &c);
     z0 = r * c;
     z1 = r * s;
-}
-
-// Operand column of component a (0 = x, 1 = y) of trajectory k: x and y of
-// 16 consecutive trajectories sit in two adjacent 16-column blocks, so one
-// lane of an MFMA output pair holds both components of one (spin, trajectory).
-__device__ __forceinline__ int64_t opcol(int64_t k, int a) {
-    return 32 * (k >> 4) + 16 * a + (k & 15);
-}
-
-// The column operand X of a contraction (C2 columns) is stage-blocked the same
-// way: element i of column c, part p, with the kt elements of one K stage of
-// all columns contiguous.  A stage's columns of a tile are then one contiguous
-// run (a row-major operand gave runs of one stage's 64 or 128 bytes, half a
-// cache line at 64), and 16 neighbouring columns written by one epilogue block
-// share cache lines.
-__host__ __device__ __forceinline__ int64_t x_index(int64_t c, int64_t i, int64_t C2, int64_t kt, int np = 1,
-                                                    int p = 0) {
-    return ((i / kt) * np + p) * C2 * kt + c * kt + i % kt;
 }
 
 // ---------------------------------------------------------------------------

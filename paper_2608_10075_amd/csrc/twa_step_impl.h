@@ -199,53 +199,28 @@ __device__ __forceinline__ void bst4(Rsrc r, uint32_t voff, const S (&v)[4]) {
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, t1), r, voff + 16, 0, 0);
     }
 }
-// four operand values (contraction type) from state values
-template <int PREC>
-__device__ __forceinline__ void bstg4(Rsrc r, uint32_t voff, const typename Prec<PREC>::S (&v)[4]) {
+// four operand values of a column from state values, all their parts: at(q) is
+// the descriptor of part q (of the lane's block), voff the lane's byte offset
+template <int PREC, typename At>
+__device__ __forceinline__ void bstg4(At&& at, uint32_t voff, const typename Prec<PREC>::S (&v)[4]) {
     typedef typename Prec<PREC>::G G;
-    if constexpr (sizeof(G) == 2) {
-        uint16_t h[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) h[q] = __builtin_bit_cast(uint16_t, Prec<PREC>::to_g(v[q]));
-        const u32x2 t = {(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16)};
-        __builtin_amdgcn_raw_buffer_store_b64(t, r, voff, 0, 0);
-    } else {
-        typename Prec<PREC>::S g[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) g[q] = Prec<PREC>::to_g(v[q]);
-        bst4(r, voff, g);
-    }
-}
-// operand store of a state-like value: one block, or in the split form its
-// parts blk bytes apart
-template <int PREC>
-__device__ __forceinline__ void bstg4s(Rsrc r, uint32_t voff, uint32_t blk, const typename Prec<PREC>::S (&v)[4]) {
     constexpr int NP = Prec<PREC>::NP;
-    if constexpr (NP > 1) {
+    if constexpr (sizeof(G) == 2) {
         uint16_t h[4][NP];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) bf16_parts<NP>(v[q], h[q]);
+        for (int r = 0; r < 4; ++r) {
+            if constexpr (NP > 1) bf16_parts<NP>(v[r], h[r]);
+            else h[r][0] = __builtin_bit_cast(uint16_t, Prec<PREC>::to_g(v[r]));
+        }
 #pragma unroll
-        for (int p = 0; p < NP; ++p) {
-            const u32x2 t = {(uint32_t)h[0][p] | ((uint32_t)h[1][p] << 16),
-                             (uint32_t)h[2][p] | ((uint32_t)h[3][p] << 16)};
-            __builtin_amdgcn_raw_buffer_store_b64(t, r, voff + p * blk, 0, 0);
+        for (int q = 0; q < NP; ++q) {
+            const u32x2 t = {(uint32_t)h[0][q] | ((uint32_t)h[1][q] << 16),
+                             (uint32_t)h[2][q] | ((uint32_t)h[3][q] << 16)};
+            __builtin_amdgcn_raw_buffer_store_b64(t, at(q), voff, 0, 0);
         }
     } else {
-        bstg4<PREC>(r, voff, v);
+        bst4(at(0), voff, v);
     }
-}
-// coherent exchange: (v^y, -v^x) into the perpendicular blocks of the x and y
-// columns (byte offsets vx_off, vy_off)
-template <int PREC>
-__device__ __forceinline__ void bstg4perp(Rsrc r, uint32_t vx_off, uint32_t vy_off, uint32_t blk,
-                                          const typename Prec<PREC>::S (&vx)[4],
-                                          const typename Prec<PREC>::S (&vy)[4]) {
-    typename Prec<PREC>::S m[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) m[q] = -vx[q];
-    bstg4s<PREC>(r, vx_off, blk, vy);
-    bstg4s<PREC>(r, vy_off, blk, m);
 }
 
 // operand store of four consecutive spins of a column (they share a K stage)
@@ -725,39 +700,38 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
     const uint32_t lane_s = at.lane;
     auto so_s = [&](const int p, const int bi) { return (uint32_t)((16 * p * P + 16 * bi) * (int64_t)sizeof(S)); };
     auto plane = [&](const S* arr, const int c) { return wave_rsrc(arr + c * SP + eb_s, rem_s); };
-    // operand columns (stage-blocked): trajectory kw0 + 16 p + (lane & 15) has
-    // columns opcol(k, c) = 32 (kw0 / 16 + p) + 16 c + (lane & 15), rows
-    // m0 + 16 bi + 4 (lane / 16) + ..; the base is the K stage and the
-    // column block of the wave's first element
+    // operand columns (stage-blocked, see op_block)
     const int64_t C2 = 2 * Bp;
-    auto op_rsrc = [&](const G* arr, const int64_t row0, const int64_t rows) {
-        const int64_t eb = ((row0 + r0) / KT * (NP * C2) + 32 * (kw0 >> 4)) * KT;
-        return wave_rsrc(arr + eb, (rows * NP * C2 - eb) * (int64_t)sizeof(G));
+    // v into block (p, bi) of component c of the operand whose rows start at row0
+    auto st_op = [&](G* arr, const int64_t row0, const int p, const int c, const int bi, const S(&v)[4]) {
+        const int64_t row = row0 + r0 + 16 * bi, col = 32 * ((kw0 >> 4) + p);
+        auto store = [&](const int64_t rw) {
+            auto at = [&](const int q) {
+                return wave_rsrc(arr + op_block(rw, col, C2, KT, NP, q), op_block_span(KT) * (int)sizeof(G));
+            };
+            bstg4<PREC>(at, op_lane(lane, c, row, KT) * (uint32_t)sizeof(G), v);
+        };
+        if constexpr (KT >= 16) {
+            store(row);
+        } else {
+            if (lane < 32) store(row);
+            else store(row + 8);
+        }
     };
-    const int r4 = 4 * (lane >> 4);
-    const uint32_t op_lane = KT >= 16 ? (uint32_t)(((lane & 15) * KT + r4) * sizeof(G))
-                                      : (uint32_t)(((int64_t)(r4 / KT) * C2 * KT + (lane & 15) * KT + r4 % KT) *
-                                                   (int64_t)sizeof(G));
-    const int rin = (int)(r0 % KT);
-    auto so_op = [&](const int p, const int c, const int bi) {
-        const int rr = rin + 16 * bi;
-        return (uint32_t)(((int64_t)(rr / KT) * NP * C2 + 32 * p + 16 * c) * (KT * (int64_t)sizeof(G)) +
-                          (rr % KT) * (int64_t)sizeof(G));
+    // coherent exchange: (v^y, -v^x) into the perpendicular blocks
+    auto st_perp = [&](G* arr, const int64_t row0, const int p, const int bi, const S(&vx)[4], const S(&vy)[4]) {
+        S m[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) m[r] = -vx[r];
+        st_op(arr, row0, p, 0, bi, vy);
+        st_op(arr, row0, p, 1, bi, m);
     };
-    const uint32_t blk_b = (uint32_t)(C2 * (KT * (int64_t)sizeof(G)));   // stride of the parts
-    Rsrc rs[3], ry[2], rop, rperp;
+    Rsrc rs[3], ry[2];
     if constexpr (PF) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) rs[c] = plane(a.s_cur, c);
 #pragma unroll
         for (int c = 0; c < 2; ++c) ry[c] = plane(a.Y, c);
-        if constexpr (STAGE == 1) {
-            rop = op_rsrc(a.Dop, 0, (1 + a.coh) * P);
-            rperp = op_rsrc(a.Dop, a.coh * P, (1 + a.coh) * P);
-        } else {
-            rop = op_rsrc(a.Xnext, 0, (2 + a.coh) * P);
-            rperp = op_rsrc(a.Xnext, a.coh * 2 * P, (2 + a.coh) * P);
-        }
     }
     auto pf_load = [&](const int p, const int bi) {
         const uint32_t so = so_s(p, bi);
@@ -832,10 +806,9 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                 }
                 bst4(ry[0], lane_s + so_s(p, bi), yx);
                 bst4(ry[1], lane_s + so_s(p, bi), yy);
-                bstg4s<PREC>(rop, op_lane + so_op(p, 0, bi), blk_b, dx);
-                bstg4s<PREC>(rop, op_lane + so_op(p, 1, bi), blk_b, dy);
-                if (a.coh)
-                    bstg4perp<PREC>(rperp, op_lane + so_op(p, 0, bi), op_lane + so_op(p, 1, bi), blk_b, dx, dy);
+                st_op(a.Dop, 0, p, 0, bi, dx);
+                st_op(a.Dop, 0, p, 1, bi, dy);
+                if (a.coh) st_perp(a.Dop, P, p, bi, dx, dy);
                 if constexpr (QSNAP) {
                     S qx[4], qy[4];
 #pragma unroll
@@ -863,10 +836,9 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                 }
                 bst4(ry[0], lane_s + so_s(p, bi), yx);
                 bst4(ry[1], lane_s + so_s(p, bi), yy);
-                bstg4s<PREC>(rop, op_lane + so_op(p, 0, bi), blk_b, dx);
-                bstg4s<PREC>(rop, op_lane + so_op(p, 1, bi), blk_b, dy);
-                if (a.coh)
-                    bstg4perp<PREC>(rperp, op_lane + so_op(p, 0, bi), op_lane + so_op(p, 1, bi), blk_b, dx, dy);
+                st_op(a.Dop, 0, p, 0, bi, dx);
+                st_op(a.Dop, 0, p, 1, bi, dy);
+                if (a.coh) st_perp(a.Dop, P, p, bi, dx, dy);
             } else if constexpr (KD == KIND_SIB && STAGE == 2) {
                 // corrector: the midpoint rule from s_n with the field at the
                 // midpoint m = s_n + D/2: contraction Y1 + A_left D / 2, sums (S_n + S~)/2
@@ -887,10 +859,9 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                 bst4(plane(a.s_next, 0), lane_s + so_s(p, bi), nx);
                 bst4(plane(a.s_next, 1), lane_s + so_s(p, bi), ny);
                 bst4(plane(a.s_next, 2), lane_s + so_s(p, bi), nz);
-                bstg4s<PREC>(rop, op_lane + so_op(p, 0, bi), blk_b, nx);
-                bstg4s<PREC>(rop, op_lane + so_op(p, 1, bi), blk_b, ny);
-                if (a.coh)
-                    bstg4perp<PREC>(rperp, op_lane + so_op(p, 0, bi), op_lane + so_op(p, 1, bi), blk_b, nx, ny);
+                st_op(a.Xnext, 0, p, 0, bi, nx);
+                st_op(a.Xnext, 0, p, 1, bi, ny);
+                if (a.coh) st_perp(a.Xnext, 2 * P, p, bi, nx, ny);
             } else if constexpr (KD == KIND_PRIMAL && STAGE == 2) {
                 S dx[4], dy[4], dz[4], yx[4], yy[4], nx[4], ny[4], nz[4];
 #pragma unroll
@@ -941,10 +912,9 @@ __device__ __forceinline__ void stage_tile(const GemmArgs<PREC>& a, const int mt
                     bst4(plane(yo, 0), lane_s + so_s(p, bi), yx);
                     bst4(plane(yo, 1), lane_s + so_s(p, bi), yy);
                 }
-                bstg4s<PREC>(rop, op_lane + so_op(p, 0, bi), blk_b, nx);
-                bstg4s<PREC>(rop, op_lane + so_op(p, 1, bi), blk_b, ny);
-                if (a.coh)
-                    bstg4perp<PREC>(rperp, op_lane + so_op(p, 0, bi), op_lane + so_op(p, 1, bi), blk_b, nx, ny);
+                st_op(a.Xnext, 0, p, 0, bi, nx);
+                st_op(a.Xnext, 0, p, 1, bi, ny);
+                if (a.coh) st_perp(a.Xnext, 2 * P, p, bi, nx, ny);
             } else if constexpr (KD == KIND_TANGENT && STAGE == 1) {
                 const S tSx = sT[kl][0], tSy = sT[kl][1];
                 const S* tc = a.t_cur + cp * a.t_state_copy;
