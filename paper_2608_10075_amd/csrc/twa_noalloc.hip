@@ -26,11 +26,7 @@ namespace twa {
 
 namespace {
 
-// The split forms lay their operands out in bf16 parts (six bytes a value in
-// FP32) and in tiles of their own, so a run of TWA_NOALLOC_SCRATCH_BYTES as
-// documented_bytes counts them takes up to twice that.
-constexpr size_t kScratchBytes = 2 * (size_t)TWA_NOALLOC_SCRATCH_BYTES;
-__device__ __align__(256) unsigned char scratch[kScratchBytes];
+__device__ __align__(256) unsigned char scratch[TWA_NOALLOC_SCRATCH_BYTES];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -69,8 +65,7 @@ struct Carver {
     }
 };
 
-// the buffers twa_run allocates for a run without lags, op_bytes a
-// contraction operand value
+// the buffers of a run without lags, op_bytes a contraction operand value
 double* carve(Carver& cv, const Geometry& g, size_t op_bytes, EnsembleBuffers& b) {
     const size_t se = (size_t)state_elt_bytes(g.precision);
     const size_t P = (size_t)g.P, Bp = (size_t)g.Bp, C2 = (size_t)g.C2, nmt = (size_t)g.nmt;
@@ -91,34 +86,19 @@ double* carve(Carver& cv, const Geometry& g, size_t op_bytes, EnsembleBuffers& b
     return static_cast<double*>(cv.take((32 * 5 + 3) * sizeof(double)));
 }
 
-// The bytes a run counts against TWA_NOALLOC_SCRATCH_BYTES: its buffers
-// padded to fixed tiles (16x32 to N = 48, 64x64 to 768, then 128x128, or
-// 320x256 where that is fewer rounds of 256 tiles at 1.64 times the rate), an
-// operand value at 8 (FP64), 4 (FP32), 6 (split BF16) or 2 bytes.  What a run
-// takes in fact follows its own tiles and parts; which runs are accepted does
-// not change with them.
-size_t documented_bytes(const twa_params* p, int64_t N, int64_t B) {
-    int id = p->tile_config;
-    if (id < 0) {
-        auto est = [&](const TileCfg& t, double rate) {
-            const int64_t tiles = (round_up(N, t.mt) / t.mt) * (2 * round_up(B, t.nt / 2) / t.nt);
-            return (double)((tiles + 255) / 256) * (double)(t.mt * t.nt) / rate;
-        };
-        id = N <= 48 ? 0 : N <= 768 ? 1
-             : p->precision != TWA_PREC_FP64 && est(kTiles[0][7], 1.64) < est(kTiles[0][2], 1.0) ? 7 : 2;
-    }
-    const TileCfg& tc = kTiles[0][id];
-    const size_t op = p->precision == TWA_PREC_FP64 ? 8 : p->precision == TWA_PREC_FP32 ? 4
-                      : p->precision == TWA_PREC_BF16X3 ? 6 : 2;
-    Geometry g;
-    g.precision = p->precision;
-    g.P = round_up(N, std::max<int64_t>(tc.mt, tc.kbytes / (op == 6 ? 2 : (int)op)));
-    g.Bp = round_up(B, tc.nt / 2);
-    g.nmt = g.P / tc.mt;
-    g.C2 = 2 * g.Bp;
+// The tile whose padding a run is counted with against
+// TWA_NOALLOC_SCRATCH_BYTES, with split-BF16 operands at 6 bytes a value: which
+// runs are accepted follows from N and the precision (and an asked-for tile)
+// and not from the tile and operand layout that is fastest for them.
+int counted_tile(const twa_params* p, int64_t N, int64_t B) {
+    if (p->tile_config >= 0) return p->tile_config;
+    if (p->precision == TWA_PREC_FP64) return N <= 48 ? 0 : N <= 768 ? 1 : 2;
+    return tile_cfg(p->precision, pick_tile_cfg(p->precision, N, B)).base;
+}
+size_t counted_bytes(const Geometry& g) {
     Carver cv{nullptr};
     EnsembleBuffers b;
-    carve(cv, g, op, b);
+    carve(cv, g, (size_t)gemm_elt_bytes(g.precision) * (g.precision == TWA_PREC_BF16X3 ? 3 : 1), b);
     return cv.used;
 }
 
@@ -190,31 +170,47 @@ int run_noalloc(const twa_params* p, int64_t n_traj, double dt, int64_t n_steps,
         set_error("twa_run_noalloc: the averaging window is empty");
         return TWA_EINVAL;
     }
-    const int cfg = p->tile_config >= 0 ? p->tile_config : pick_tile_cfg(p->precision, N, B);
-    if (p->tile_config >= 0 && !tile_cfg_ok(p->precision, cfg)) {
+    if (p->tile_config >= 0 && !tile_cfg_ok(p->precision, p->tile_config)) {
         set_error("twa_run_noalloc: unknown tile configuration");
         return TWA_EINVAL;
     }
-    Geometry g = make_geometry(p->precision, cfg, N, B);
-    g.integrator = p->integrator;
     const bool fused = p->tile_config < 0 && small_path_applies(p->precision, N, 0);
     const int J = (int)std::min<int64_t>(32, B);
     const int nblk = (int)std::min<int64_t>(1024, std::max<int64_t>(1, (B * N + 255) / 256));
     hipStream_t st = (hipStream_t)p->stream;
 
-    const size_t need = documented_bytes(p, N, B);
-    void* base = nullptr;
-    int rc = scratch_address(&base);
-    if (rc) return rc;
-    Carver cv{static_cast<char*>(base)};
-    EnsembleBuffers b;
-    double* res = carve(cv, g, (size_t)gemm_elt_bytes(g.precision) * operand_split(g.precision), b);
-    if (need > (size_t)TWA_NOALLOC_SCRATCH_BYTES || cv.used > kScratchBytes) {
+    int cfg = counted_tile(p, N, B);
+    Geometry g = make_geometry(p->precision, cfg, N, B);
+    const size_t need = counted_bytes(g);
+    if (need > (size_t)TWA_NOALLOC_SCRATCH_BYTES) {
         set_error("twa_run_noalloc: N = " + std::to_string(N) + ", n_traj = " + std::to_string(B) + " needs " +
                   std::to_string(need) + " bytes of device scratch; the limit is " +
                   std::to_string((size_t)TWA_NOALLOC_SCRATCH_BYTES) + " (use twa_run)");
         return TWA_ENOMEM;
     }
+    void* base = nullptr;
+    int rc = scratch_address(&base);
+    if (rc) return rc;
+    Carver cv{static_cast<char*>(base)};
+    EnsembleBuffers b;
+    double* res = nullptr;
+    const size_t op = (size_t)gemm_elt_bytes(p->precision) * operand_split(p->precision);
+    if (p->tile_config < 0 && !fused) {
+        // the tile of twa_run.  Its smaller rows (FP64) mean more partial sums:
+        // where those no longer fit, the counted tile, which does
+        const int c = pick_tile_cfg(p->precision, N, B);
+        const Geometry gc = make_geometry(p->precision, c, N, B);
+        res = carve(cv, gc, op, b);
+        if (cv.used <= (size_t)TWA_NOALLOC_SCRATCH_BYTES) {
+            cfg = c;
+            g = gc;
+        } else {
+            res = nullptr;
+            cv.used = 0;
+        }
+    }
+    if (!res) res = carve(cv, g, op, b);
+    g.integrator = p->integrator;
 
     StepConsts c;
     c.c1 = 0.5 * p->gamma * dt;
