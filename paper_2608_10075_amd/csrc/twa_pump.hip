@@ -37,8 +37,10 @@ __global__ void scale_columns_kernel(int64_t N, const double* V, const double* r
 // launches of its column-by-column reduction, so half the columns take half of
 // it (N = 1024: 22.8 ms with one solve of size N, 13.4 with two halves; N = 200
 // 4.9 and 2.4; N = 4096 66 with halves).  An odd chain's second block
-// is short of one row: it gets a decoupled one with the eigenvalue pad, above
-// all others, which is left out again.
+// is short of one row: it gets a decoupled one with the eigenvalue pad, which is
+// left out again as the largest: twice a bound of the others, so that no
+// round-off can sort it among them (a chain of short range has its whole
+// spectrum within round-off of the bound itself).
 __global__ void split_kernel(int64_t N, const double* W, double pad, double* U) {
     const int64_t n1 = (N + 1) / 2, t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= n1 * n1) return;
@@ -103,7 +105,8 @@ static int factorise(twa_pump* p, bool chain, hipStream_t st) {
     rocblas_int* info = nullptr;
     int* order = nullptr;
     const int64_t n1 = (N + 1) / 2;
-    const bool halves = chain && N >= 16;   // (a smaller one is a single launch's work either way)
+    // (a smaller one is a single launch's work either way; the sums of two elements stay finite)
+    const bool halves = chain && N >= 16 && p->w < 1e300;
     rocblas_handle h = nullptr;
     int rc = TWA_OK;
     auto fail = [&](int code, const std::string& m) {
@@ -126,10 +129,10 @@ static int factorise(twa_pump* p, bool chain, hipStream_t st) {
     }
     if (halves) {
         // the blocks lie in Vs: 2 n1^2 <= N^2
-        double pad = 1.0;   // above the largest row sum
-        for (int64_t d = 1; d < N; ++d) pad += 2.0 * std::pow((double)d + 1.0, -p->alpha);
+        double rows = 1.0;   // bound of the row sums at w = 1
+        for (int64_t d = 1; d < N; ++d) rows += 2.0 * std::pow((double)d + 1.0, -p->alpha);
         hipLaunchKernelGGL(split_kernel, dim3((unsigned)((n1 * n1 + 255) / 256)), dim3(256), 0, st, N, p->W,
-                           p->w > 0 ? p->w * pad : 1.0, Vs);
+                           p->w > 0 ? 2.0 * p->w * rows : 1.0, Vs);
         if (rocsolver_dsyevd_strided_batched(h, rocblas_evect_original, rocblas_fill_upper, (rocblas_int)n1, Vs,
                                              (rocblas_int)n1, n1 * n1, D, n1, E, n1, info, 2) !=
             rocblas_status_success) {
