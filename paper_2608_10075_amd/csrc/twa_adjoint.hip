@@ -195,8 +195,8 @@ int dfactor_dalpha(const twa_pump* p, double* Wa, double* Fa, hipStream_t st) {
     for (int64_t j = 0; j < N; ++j) rr[(size_t)j] = p->lam[j] > tol ? std::sqrt(p->lam[j]) : 0.0;
     const double one = 1.0, zero = 0.0;
     const rocblas_int n = (rocblas_int)N;
-    if (hipMalloc(&T, bytes) != hipSuccess || hipMalloc(&U, bytes) != hipSuccess ||
-        hipMalloc(&r, N * sizeof(double)) != hipSuccess) {
+    if (device_malloc(&T, bytes) != hipSuccess || device_malloc(&U, bytes) != hipSuccess ||
+        device_malloc(&r, N * sizeof(double)) != hipSuccess) {
         set_error("twa_adjoint: device allocation for dF/dalpha failed");
         rc = TWA_ENOMEM;
         goto done;

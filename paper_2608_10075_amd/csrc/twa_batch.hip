@@ -289,9 +289,9 @@ int build_bucket(const BatchSpec& sp, const std::vector<int>& idx, int cfg, Buck
         bstart[(size_t)q + 1] = bstart[(size_t)q] + (int)noise_blocks<256>(g.N, g.B, g.kt);
     }
     bk.nblocks_noise = bstart[(size_t)np];
-    TWA_HIP_CHECK(hipMalloc(&bk.d_pd, pd.size() * sizeof(PointDesc)));
+    TWA_HIP_CHECK(device_malloc(&bk.d_pd, pd.size() * sizeof(PointDesc)));
     TWA_HIP_CHECK(hipMemcpyAsync(bk.d_pd, pd.data(), pd.size() * sizeof(PointDesc), hipMemcpyHostToDevice, st));
-    TWA_HIP_CHECK(hipMalloc(&bk.d_bstart, bstart.size() * sizeof(int)));
+    TWA_HIP_CHECK(device_malloc(&bk.d_bstart, bstart.size() * sizeof(int)));
     TWA_HIP_CHECK(hipMemcpyAsync(bk.d_bstart, bstart.data(), bstart.size() * sizeof(int), hipMemcpyHostToDevice,
                                  st));
     TWA_HIP_CHECK(hipStreamSynchronize(st));   // the host arrays end with this function
@@ -633,7 +633,7 @@ int run_batch(const twa_point* pts, int np, const twa_batch_opts* o, twa_observa
                      hipSuccess;
             double* export_dev = nullptr;
             if (ok && po && po->final_state) {
-                ok = hipMalloc(&export_dev, (size_t)3 * g.B * g.N * sizeof(double)) == hipSuccess &&
+                ok = device_malloc(&export_dev, (size_t)3 * g.B * g.N * sizeof(double)) == hipSuccess &&
                      launch_export_state(g, b.s[cur], export_dev, st) == TWA_OK &&
                      hipMemcpyAsync(po->final_state, export_dev, (size_t)3 * g.B * g.N * sizeof(double),
                                     hipMemcpyDeviceToHost, st) == hipSuccess;

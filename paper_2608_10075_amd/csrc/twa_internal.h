@@ -135,7 +135,7 @@ class Arena {
     // calls that wait for their stream before they release).
     int commit(bool keep, hipStream_t st);
     void release();
-    // the block without its owner: freed by free_buffers
+    // the block without its owner, whose caller frees it
     void* detach();
 
   private:

@@ -113,6 +113,16 @@ static int factorise(twa_pump* p, bool chain, hipStream_t st) {
         set_error(m);
         rc = code;
     };
+    // a library call that finds no memory for its workspace is made again
+    // without the block kept between runs
+    auto solve = [&](auto call) {
+        rocblas_status s = call();
+        if (s == rocblas_status_memory_error && kept_block_bytes() > 0) {
+            kept_block_free();
+            s = call();
+        }
+        return s == rocblas_status_success;
+    };
     std::vector<double> lam((size_t)N + 1), rr((size_t)N);
     std::vector<int> ord((size_t)N);
     if (device_malloc(&p->V, bytes) != hipSuccess || device_malloc(&D, (N + 1) * sizeof(double)) != hipSuccess ||
@@ -133,9 +143,10 @@ static int factorise(twa_pump* p, bool chain, hipStream_t st) {
         for (int64_t d = 1; d < N; ++d) rows += 2.0 * std::pow((double)d + 1.0, -p->alpha);
         hipLaunchKernelGGL(split_kernel, dim3((unsigned)((n1 * n1 + 255) / 256)), dim3(256), 0, st, N, p->W,
                            p->w > 0 ? 2.0 * p->w * rows : 1.0, Vs);
-        if (rocsolver_dsyevd_strided_batched(h, rocblas_evect_original, rocblas_fill_upper, (rocblas_int)n1, Vs,
-                                             (rocblas_int)n1, n1 * n1, D, n1, E, n1, info, 2) !=
-            rocblas_status_success) {
+        if (!solve([&] {
+                return rocsolver_dsyevd_strided_batched(h, rocblas_evect_original, rocblas_fill_upper, (rocblas_int)n1,
+                                                        Vs, (rocblas_int)n1, n1 * n1, D, n1, E, n1, info, 2);
+            })) {
             fail(TWA_EHIP, "rocsolver_dsyevd_strided_batched failed");
             goto done;
         }
@@ -145,8 +156,10 @@ static int factorise(twa_pump* p, bool chain, hipStream_t st) {
             goto done;
         }
         // symmetric matrix: row- and column-major storage coincide
-        if (rocsolver_dsyevd(h, rocblas_evect_original, rocblas_fill_upper, (rocblas_int)N, p->V, (rocblas_int)N, D,
-                             E, info) != rocblas_status_success) {
+        if (!solve([&] {
+                return rocsolver_dsyevd(h, rocblas_evect_original, rocblas_fill_upper, (rocblas_int)N, p->V,
+                                        (rocblas_int)N, D, E, info);
+            })) {
             fail(TWA_EHIP, "rocsolver_dsyevd failed");
             goto done;
         }

@@ -1566,7 +1566,7 @@ int grouped_prepare_p(const std::vector<Geometry>& gs, const std::vector<Ensembl
                                                    win && stage == 2, win || tan);
                     h[(size_t)p].nnt = (int)(gs[(size_t)p].C2 / tc.nt);
                 }
-                TWA_HIP_CHECK(hipMalloc(&pl.d_args[v][stage - 1][cur], h.size() * sizeof(GemmArgs<PREC>)));
+                TWA_HIP_CHECK(device_malloc(&pl.d_args[v][stage - 1][cur], h.size() * sizeof(GemmArgs<PREC>)));
                 TWA_HIP_CHECK(hipMemcpyAsync(pl.d_args[v][stage - 1][cur], h.data(), h.size() * sizeof(GemmArgs<PREC>),
                                              hipMemcpyHostToDevice, st));
                 TWA_HIP_CHECK(hipStreamSynchronize(st));   // h ends with this iteration
@@ -1617,7 +1617,7 @@ int grouped_prepare_p(const std::vector<Geometry>& gs, const std::vector<Ensembl
         const int ntl = (int)tiles.size();
         const int grid = std::max(1, std::min(ncu * occ, ntl));
         xcd_permute(tiles, std::min(grid, ngemm), ngemm);
-        TWA_HIP_CHECK(hipMalloc((void**)&pl.d_tiles[tl], tiles.size() * sizeof(int4)));
+        TWA_HIP_CHECK(device_malloc(&pl.d_tiles[tl], tiles.size() * sizeof(int4)));
         TWA_HIP_CHECK(hipMemcpyAsync(pl.d_tiles[tl], tiles.data(), tiles.size() * sizeof(int4), hipMemcpyHostToDevice,
                                      st));
         TWA_HIP_CHECK(hipStreamSynchronize(st));   // the host list ends with this iteration
