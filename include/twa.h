@@ -25,7 +25,8 @@
  *     free function.
  *   - While a pump handle is alive the library keeps the device buffer of the
  *     last run, up to 1/64 of the device's memory, for the next one; it is
- *     freed with the last handle, or when an allocation of the library fails.
+ *     freed with the last handle, when an allocation of the library fails, and
+ *     when a run needs less than an eighth of it (above 16 MiB).
  *   - `stream` arguments are hipStream_t passed as void*.  Every compute
  *     entry point is stream-ordered on that stream and returns after its
  *     results are on the host unless stated otherwise; with NULL it runs on a

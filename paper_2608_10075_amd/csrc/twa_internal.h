@@ -156,7 +156,8 @@ hipError_t device_malloc(T** p, size_t bytes) {
     return device_malloc(reinterpret_cast<void**>(p), bytes);
 }
 // The kept block lives as long as any pump handle does, holds at most a 64th
-// of the device's memory and is only touched under the API lock.
+// of the device's memory and is only touched under the API lock.  A call that
+// needs less than an eighth of a large one gives it back and keeps its own.
 void kept_block_free();
 size_t kept_block_bytes();
 void pump_born();

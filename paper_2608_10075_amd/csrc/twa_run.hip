@@ -355,7 +355,8 @@ int Arena::commit(bool keep, hipStream_t st) {
     }
     int dev = 0;
     TWA_HIP_CHECK(hipGetDevice(&dev));
-    if (keep && g_kept.p && !g_kept.lent && g_kept.device == dev && g_kept.bytes >= total) {
+    const bool fits = g_kept.bytes >= total && g_kept.bytes <= std::max<size_t>(8 * total, 16u << 20);
+    if (keep && g_kept.p && !g_kept.lent && g_kept.device == dev && fits) {
         block_ = g_kept.p;
         bytes_ = g_kept.bytes;
         g_kept.lent = true;

@@ -1,7 +1,13 @@
-"""The device buffer kept between runs: every allocation of the library can
+"""The device buffer kept between runs: a small run after a large one does not
+keep the large one's, the last handle gives back what is left, results do not
+depend on what a kept buffer held, and every allocation of the library can
 give it back when memory is short."""
+import gc
 import os
 import re
+
+import numpy as np
+import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -12,3 +18,37 @@ def test_every_allocation_can_give_the_kept_buffer_back():
            if re.search(r"\bhipMalloc\w*\(", line) and not line.lstrip().startswith("//")]
     # device_malloc's own two calls
     assert [f for f, _ in raw] == ["twa_run.hip", "twa_run.hip"], raw
+
+
+@pytest.fixture(scope="module")
+def twa():
+    import torch
+    assert torch.cuda.is_available()
+    import paper_2608_10075_amd as m
+    return m
+
+
+@pytest.mark.gpu
+def test_small_run_does_not_keep_a_large_buffer(twa):
+    import torch
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    gc.collect()
+    small, large = twa.build_pump(100, 1.0, 1.0), twa.build_pump(1500, 1.0, 1.0)
+    kw = dict(seed=2, precision="fp32", tile_config=1, norm_tol=-1, want_traj=True)
+    first = twa.run(small, 64, 1e-4, 20, **kw)
+    before = free()
+    big = twa.run(large, 4096, 1e-5, 4, **kw)
+    held = before - free()
+    assert held > 400e6   # state, fields and operands of 4096 x 1536
+    again = twa.run(large, 4096, 1e-5, 4, **kw)
+    assert np.array_equal(big.traj_moments, again.traj_moments)
+    second = twa.run(small, 64, 1e-4, 20, **kw)
+    assert np.array_equal(first.traj_moments, second.traj_moments)
+    assert before - free() < 64e6
+    # a run of a like size takes the kept buffer over
+    third = twa.run(small, 48, 1e-4, 20, **kw)
+    assert np.array_equal(third.traj_moments, first.traj_moments[:48])
