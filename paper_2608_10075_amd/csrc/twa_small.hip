@@ -4,14 +4,17 @@
 // by its launches.  One launch integrates every step: a workgroup owns T = 8 CB
 // trajectories for the whole run, with
 //   * NB = ceil(N / 16) compute waves, wave w holding the 16 rows of spins
-//     16 w .. 16 w + 15 of A' = -dt/2 W + Gamma dt/2 (the collective term of
-//     Eq. (S1) is a constant added to the matrix) and of -sqrt(dt) F in
-//     registers and the spins themselves in the MFMA output layout; the spin
-//     vectors are exchanged through LDS;
+//     16 w .. 16 w + 15 of -dt/2 W and of -sqrt(dt) F in registers and the
+//     spins themselves in the MFMA output layout; the spin vectors are
+//     exchanged through LDS, and every wave sums them for the collective term
+//     of Eq. (S1) from the operands it reads anyway;
 //   * four producer waves that draw the next steps' noise into LDS and form
 //     the window moments of the steps before, off the compute waves' path.
 // Bound by the per-step chain exchange -> MFMA -> update -> exchange ->
 // MFMA -> update of the compute waves (MFMA issue from N of about 50 on).
+// From N = 17 on every sum is formed in the order of the stage kernels on the
+// tiles they take for that N (16 rows to N = 48, then 64), so in FP32 a run
+// gives the same bits on either path (to N = 16 the noise field is added first).
 // Heun and the semi-implicit midpoint scheme; FP64 or FP32 state, operands and
 // MFMA.  Noise from the same Philox counters as the multi-kernel path.
 #include <algorithm>
@@ -69,6 +72,56 @@ __device__ __forceinline__ double ror8(double v) {
                                                 __builtin_amdgcn_mov_dpp(h.y, 0x128, 0xf, 0xf, true)));
 }
 
+// v plus the value of the lane 16 (32) lanes away: rows of 16 lanes pairwise, then halves
+__device__ __forceinline__ float across16(float v) {
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+__device__ __forceinline__ float across32(float v) {
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+__device__ __forceinline__ double across16(double v) {
+    const uint2 h = __builtin_bit_cast(uint2, v);
+    const auto x = __builtin_amdgcn_permlane16_swap(h.x, h.x, false, false);
+    const auto y = __builtin_amdgcn_permlane16_swap(h.y, h.y, false, false);
+    return __builtin_bit_cast(double, make_uint2(x[0], y[0])) + __builtin_bit_cast(double, make_uint2(x[1], y[1]));
+}
+__device__ __forceinline__ double across32(double v) {
+    const uint2 h = __builtin_bit_cast(uint2, v);
+    const auto x = __builtin_amdgcn_permlane32_swap(h.x, h.x, false, false);
+    const auto y = __builtin_amdgcn_permlane32_swap(h.y, h.y, false, false);
+    return __builtin_bit_cast(double, make_uint2(x[0], y[0])) + __builtin_bit_cast(double, make_uint2(x[1], y[1]));
+}
+
+// Sum over the spins of a column in the order of the stage kernels: lane group
+// g adds its rows 4 g .. 4 g + 3 of the 16-row blocks of a wave of theirs (one
+// block to N = 48, two beyond), the four groups are added, then the waves of a
+// tile (one, two) and the tiles.  add() takes the blocks in order; total() is
+// the same in all lanes of a column.
+template <typename S, int NB>
+struct ColumnSum {
+    static constexpr int RB = NB > 3 ? 2 : 1, NW = (NB + RB - 1) / RB;
+    S ps[NW];
+    template <typename V>
+    __device__ __forceinline__ void add(const int q, const V& v) {
+        S p = q % RB ? ps[q / RB] : S(0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) p += v[r];
+        ps[q / RB] = p;
+    }
+    __device__ __forceinline__ S total() const {
+        S s = 0;
+#pragma unroll
+        for (int w = 0; w < NW; w += RB) {
+            S t = S(0) + across32(across16(ps[w]));
+            if (RB == 2 && w + 1 < NW) t += across32(across16(ps[w + 1]));
+            s += t;
+        }
+        return s;
+    }
+};
+
 // orders a wave's own LDS accesses (which the hardware executes in order) for
 // the compiler
 __device__ __forceinline__ void wave_lds_fence() {
@@ -81,8 +134,8 @@ struct SmallArgs {
     int n;                    // atoms
     int64_t B, P, Bp;
     const double *W, *F;
-    double cw, cf, c1;        // -dt/2, -sqrt(dt), Gamma dt / 2
-    S c2;                     // sqrt(Gamma dt)
+    double cw, cf;            // -dt/2, -sqrt(dt)
+    S c1, c2;                 // Gamma dt / 2, sqrt(Gamma dt)
     uint32_t k0, k1, point;
     int64_t n_steps, burnin;
     int sib;
@@ -103,10 +156,12 @@ __global__ __launch_bounds__(64 * (NB + PRODUCERS)) void small_run_kernel(SmallA
     constexpr int ZB = NB == 1 ? PRODUCERS : 2;
     __shared__ __attribute__((aligned(16))) S Xs[COLS][XP];     // state, x and y columns
     __shared__ __attribute__((aligned(16))) S Xd[COLS][XP];     // predictor increment
+    __shared__ __attribute__((aligned(16))) S Xp[NB == 1 ? 1 : COLS][XP];   // predictor (NB > 1)
+    __shared__ __attribute__((aligned(16))) S Xz[NB == 1 ? 1 : T][XP];      // state, z (NB > 1, for the window moments)
     __shared__ __attribute__((aligned(16))) S Z[ZB][COLS][XP];  // pump normals (NB = 1: one per producer)
     __shared__ S Gn[NB == 1 ? PRODUCERS : 2][T][2];             // collective normals
     __shared__ __attribute__((aligned(16))) S Q[NB == 1 ? 2 * U : 1][NB == 1 ? COLS : 1][XP];   // noise fields (NB = 1)
-    __shared__ S R[2][U][NB][4][3][T];                          // partial spin sums of the steps of a batch
+    __shared__ S R[2][U][NB == 1 ? 4 : 1][3][T];                // partial spin sums of the steps of a batch (NB = 1)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, g = lane >> 4, n = a.n;
     const int64_t kb = (int64_t)blockIdx.x * T;      // first trajectory
@@ -127,27 +182,33 @@ __global__ __launch_bounds__(64 * (NB + PRODUCERS)) void small_run_kernel(SmallA
             for (int s = 0; s < 4; ++s) {
                 const int j = 16 * q + 4 * g + s;
                 const bool in = i < n && j < n;
-                aw[q][s] = compute && in ? (S)(a.cw * a.W[i * n + j] + a.c1) : S(0);
+                aw[q][s] = compute && in ? (S)(a.cw * a.W[i * n + j]) : S(0);
                 af[q][s] = has_f && in ? (S)(a.cf * a.F[i * n + j]) : S(0);
             }
     }
-    auto contract = [&](const V (&m)[NB], const S (&X)[COLS][XP], V (&acc)[CB]) {
+    auto frag = [&](const S (*X)[XP], const int q, const int b) {
+        return *reinterpret_cast<const V*>(&X[16 * b + c][16 * q + 4 * g]);
+    };
+    // each(q, b, v): block q of column block b as it is read
+    auto contract = [&](const V (&m)[NB], const S (*X)[XP], V (&acc)[CB], auto&& each) {
 #pragma unroll
         for (int q = 0; q < NB; ++q)
 #pragma unroll
             for (int b = 0; b < CB; ++b) {
-                const V v = *reinterpret_cast<const V*>(&X[16 * b + c][16 * q + 4 * g]);
+                const V v = frag(X, q, b);
 #pragma unroll
                 for (int s = 0; s < 4; ++s) acc[b] = K::mfma(m[q][s], v[s], acc[b]);
+                each(q, b, v);
             }
     };
+    auto nothing = [](int, int, const V&) {};
 
     // ---- compute waves: spins of rows i0 .. i0 + 3 of trajectory tl
     const int tl = CB == 1 ? (c & 7) : c, i0 = 16 * w + 4 * g;
     const bool isy = CB == 1 && c >= 8;
     const int64_t k = kb + tl;
     S x[4] = {0, 0, 0, 0}, y[4] = {0, 0, 0, 0}, z[4] = {0, 0, 0, 0};
-    auto put = [&](S (&X)[COLS][XP], const S (&vx)[4], const S (&vy)[4]) {
+    auto put = [&](S (*X)[XP], const S (&vx)[4], const S (&vy)[4]) {
         if constexpr (CB == 2) {
             *reinterpret_cast<V*>(&X[c][i0]) = V{vx[0], vx[1], vx[2], vx[3]};
             *reinterpret_cast<V*>(&X[16 + c][i0]) = V{vy[0], vy[1], vy[2], vy[3]};
@@ -171,40 +232,83 @@ __global__ __launch_bounds__(64 * (NB + PRODUCERS)) void small_run_kernel(SmallA
             }
         }
     };
-    S hx[4], hy[4], dx[4], dy[4], dz[4];
-    // predictor: the fields at s_n (their noise part in acc already), its increment
-    auto predictor = [&](V (&acc)[CB], const S gx, const S gy) {
-        contract(aw, Xs, acc);
+    // the x and y totals of the lane's trajectory
+    auto totals = [&](const ColumnSum<S, NB> (&cs)[CB], S& tx, S& ty) {
+        const S v = cs[0].total();
+        if constexpr (CB == 2) {
+            tx = v;
+            ty = cs[1].total();
+        } else {
+            const S o = ror8(v);
+            tx = isy ? o : v;
+            ty = isy ? v : o;
+        }
+    };
+    // NB = 1: the wave holds all spins of its trajectories, and sums them while
+    // they go through LDS
+    auto own_total = [&](const S (&v)[4]) {
+        return across32(across16(((v[0] + v[1]) + v[2]) + v[3]));
+    };
+    S hx[4], hy[4], dx[4], dy[4], dz[4], px[4], py[4], Sx = 0, Sy = 0, gx = 0, gy = 0;
+    // predictor: the fields at s_n and its increment.  acc: what the noise
+    // gives already (NB = 1, else zero), then the pump and the noise; g0, g1:
+    // the collective noise field where acc does not hold it
+    auto predictor = [&](V (&acc)[CB], const S (*zb)[XP], const S g0, const S g1) {
+        if constexpr (NB == 1) {
+            contract(aw, Xs, acc, nothing);
+            Sx = own_total(x);
+            Sy = own_total(y);
+        } else {
+            ColumnSum<S, NB> cs[CB];
+            contract(aw, Xs, acc, [&](const int q, const int b, const V& v) { cs[b].add(q, v); });
+            contract(af, zb, acc, nothing);
+            totals(cs, Sx, Sy);
+        }
+        gx = g0;
+        gy = g1;
+        const S cx0 = a.c1 * Sx + gx, cy0 = a.c1 * Sy + gy;
         fields(acc, hx, hy);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            hx[r] += gx;
-            hy[r] += gy;
+            const S Hx = hx[r] + cx0, Hy = hy[r] + cy0;
             if (a.sib) {
-                const S bx = S(0.5) * hy[r], by = S(-0.5) * hx[r];
+                const S bx = S(0.5) * Hy, by = S(-0.5) * Hx;
                 const S cx = by * z[r], cy = -(bx * z[r]), cz = bx * y[r] - by * x[r];
                 const S f = S(-2) / (S(1) + bx * bx + by * by);
                 dx[r] = f * (cx - by * cz);
                 dy[r] = f * (cy + bx * cz);
                 dz[r] = f * (cz - (bx * cy - by * cx));
             } else {
-                dx[r] = z[r] * hx[r];
-                dy[r] = z[r] * hy[r];
-                dz[r] = -(x[r] * hx[r] + y[r] * hy[r]);
+                dx[r] = z[r] * Hx;
+                dy[r] = z[r] * Hy;
+                dz[r] = -(x[r] * Hx + y[r] * Hy);
             }
+            px[r] = x[r] + dx[r];
+            py[r] = y[r] + dy[r];
         }
         put(Xd, dx, dy);
+        if constexpr (NB > 1) put(Xp, px, py);
     };
-    // corrector: the field moves by A' D (Heun) or A' D / 2 (midpoint)
+    // corrector: the pump field moves by that of D (Heun) or D / 2 (midpoint),
+    // the collective one is that of the predictor's sums (or the mean of both)
     auto corrector = [&](S* red) {
         V acc[CB] = {};
-        contract(aw, Xd, acc);
-        S fx[4], fy[4], sx = 0, sy = 0, sz = 0;
+        S fx[4], fy[4], sx = 0, sy = 0, sz = 0, Px, Py;
+        if constexpr (NB == 1) {
+            contract(aw, Xd, acc, nothing);
+            Px = own_total(px);
+            Py = own_total(py);
+        } else {
+            ColumnSum<S, NB> cs[CB];
+            contract(aw, Xd, acc, [&](const int q, const int b, const V&) { cs[b].add(q, frag(Xp, q, b)); });
+            totals(cs, Px, Py);
+        }
+        const S cx0 = a.c1 * (a.sib ? S(0.5) * (Sx + Px) : Px) + gx, cy0 = a.c1 * (a.sib ? S(0.5) * (Sy + Py) : Py) + gy;
         fields(acc, fx, fy);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             if (a.sib) {
-                const S Hx = hx[r] + S(0.5) * fx[r], Hy = hy[r] + S(0.5) * fy[r];
+                const S Hx = (hx[r] + S(0.5) * fx[r]) + cx0, Hy = (hy[r] + S(0.5) * fy[r]) + cy0;
                 const S bx = S(0.5) * Hy, by = S(-0.5) * Hx;
                 const S ax = x[r] - by * z[r], ay = y[r] + bx * z[r], az = z[r] - (bx * y[r] - by * x[r]);
                 const S bd = bx * ax + by * ay;
@@ -213,7 +317,7 @@ __global__ __launch_bounds__(64 * (NB + PRODUCERS)) void small_run_kernel(SmallA
                 y[r] = (ay + bx * az + by * bd) * inv;
                 z[r] = (az - (bx * ay - by * ax)) * inv;
             } else {
-                const S Hx = hx[r] + fx[r], Hy = hy[r] + fy[r];
+                const S Hx = (hx[r] + fx[r]) + cx0, Hy = (hy[r] + fy[r]) + cy0;
                 const S px = x[r] + dx[r], py = y[r] + dy[r], pz = z[r] + dz[r];
                 const S ex = pz * Hx, ey = pz * Hy, ez = -(px * Hx + py * Hy);
                 x[r] = x[r] + S(0.5) * (dx[r] + ex);
@@ -225,7 +329,9 @@ __global__ __launch_bounds__(64 * (NB + PRODUCERS)) void small_run_kernel(SmallA
             sz += z[r];
         }
         put(Xs, x, y);
-        if (!isy) {   // red: [4 (g)][3][T]
+        if constexpr (NB > 1) {
+            if (!isy) *reinterpret_cast<V*>(&Xz[tl][i0]) = V{z[0], z[1], z[2], z[3]};
+        } else if (!isy) {   // red: [4 (g)][3][T]
             red[(g * 3 + 0) * T + tl] = sx;
             red[(g * 3 + 1) * T + tl] = sy;
             red[(g * 3 + 2) * T + tl] = sz;
@@ -265,25 +371,38 @@ __global__ __launch_bounds__(64 * (NB + PRODUCERS)) void small_run_kernel(SmallA
         gb[t][0] = g0;
         gb[t][1] = g1;
     };
-    // window moments of the steps st .. st + nst - 1 of a batch (first
-    // producer wave): lane l < 3 T adds the partial sums of component l / T of
-    // trajectory l % T, lanes t < T keep the Kahan sums of trajectory t
+    // window moments (first producer wave): lanes t < T keep the Kahan sums of
+    // trajectory t
     S msum[5] = {0, 0, 0, 0, 0}, mcmp[5] = {0, 0, 0, 0, 0};
-    auto observe = [&](const int64_t st, const int nst, const S (&rb)[U][NB][4][3][T]) {
+    auto moments = [&](const S Tx, const S Ty, const S Tz) {
+        const S T2 = S(0.25) * (Tx * Tx + Ty * Ty);
+        const S mv[5] = {T2, T2 * Tz, T2 * T2, Tz, Tz * Tz};
+#pragma unroll
+        for (int m = 0; m < 5; ++m) kahan(msum[m], mcmp[m], mv[m]);
+    };
+    // NB = 1, the steps st .. st + nst - 1 of a batch: lane l < 3 T adds the
+    // partial sums of component l / T of trajectory l % T
+    auto observe = [&](const int64_t st, const int nst, const S (&rb)[U][NB == 1 ? 4 : 1][3][T]) {
         for (int u = 0; u < nst; ++u) {
             if (st + u + 1 <= a.burnin) continue;
             const int l = lane < 3 * T ? lane : 0, cc = l / T, t = l % T;
-            S v = 0;
-#pragma unroll
-            for (int q = 0; q < NB; ++q)
-#pragma unroll
-                for (int gg = 0; gg < 4; ++gg) v += rb[u][q][gg][cc][t];
-            const S Sx = v, Sy = __shfl(v, T + (lane % T)), Sz = __shfl(v, 2 * T + (lane % T));
-            const S T2 = S(0.25) * (Sx * Sx + Sy * Sy);
-            const S mv[5] = {T2, T2 * Sz, T2 * T2, Sz, Sz * Sz};
-#pragma unroll
-            for (int m = 0; m < 5; ++m) kahan(msum[m], mcmp[m], mv[m]);
+            const S v = (rb[u][0][cc][t] + rb[u][1][cc][t]) + (rb[u][2][cc][t] + rb[u][3][cc][t]);
+            moments(v, __shfl(v, T + (lane % T)), __shfl(v, 2 * T + (lane % T)));
         }
+    };
+    // NB > 1: the state after step st, from the columns
+    auto observe_columns = [&](const int64_t st) {
+        if (st + 1 <= a.burnin) return;
+        ColumnSum<S, NB> cs[CB], cz;
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+#pragma unroll
+            for (int b = 0; b < CB; ++b) cs[b].add(q, frag(Xs, q, b));
+            cz.add(q, *reinterpret_cast<const V*>(&Xz[tl][16 * q + 4 * g]));
+        }
+        S Tx, Ty;
+        totals(cs, Tx, Ty);
+        moments(Tx, Ty, cz.total());
     };
 
     if (compute) {
@@ -308,14 +427,14 @@ __global__ __launch_bounds__(64 * (NB + PRODUCERS)) void small_run_kernel(SmallA
                 if (lane < T) collective_item(lane, st + u, Gn[pw]);
                 wave_lds_fence();
                 V acc[CB] = {};
-                contract(af, Z[pw], acc);
+                contract(af, Z[pw], acc, nothing);
                 S fx[4], fy[4];
                 fields(acc, fx, fy);
-                const S gx = c2 * Gn[pw][tl][0], gy = c2 * Gn[pw][tl][1];
+                const S qx = c2 * Gn[pw][tl][0], qy = c2 * Gn[pw][tl][1];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    fx[r] += gx;
-                    fy[r] += gy;
+                    fx[r] += qx;
+                    fy[r] += qy;
                 }
                 if constexpr (CB == 2) {
                     *reinterpret_cast<V*>(&Q[buf * U + u][c][4 * g]) = V{fx[0], fx[1], fx[2], fx[3]};
@@ -341,9 +460,9 @@ __global__ __launch_bounds__(64 * (NB + PRODUCERS)) void small_run_kernel(SmallA
 #pragma unroll
                     for (int b = 0; b < CB; ++b)
                         acc[b] = *reinterpret_cast<const V*>(&Q[buf * U + u][16 * b + c][4 * g]);
-                    predictor(acc, S(0), S(0));
+                    predictor(acc, nullptr, S(0), S(0));
                     wave_lds_fence();
-                    corrector(&R[buf][u][0][0][0][0]);
+                    corrector(&R[buf][u][0][0][0]);
                     wave_lds_fence();
                 }
             } else {
@@ -372,18 +491,17 @@ __global__ __launch_bounds__(64 * (NB + PRODUCERS)) void small_run_kernel(SmallA
         for (int64_t st = 0; st < a.n_steps; ++st, buf ^= 1) {
             if (compute) {
                 V acc[CB] = {};
-                contract(af, Z[buf], acc);
-                predictor(acc, c2 * Gn[buf][tl][0], c2 * Gn[buf][tl][1]);
+                predictor(acc, Z[buf], c2 * Gn[buf][tl][0], c2 * Gn[buf][tl][1]);
             } else {
-                if (pw == 0 && st > 0) observe(st - 1, 1, R[buf ^ 1]);
+                if (pw == 0 && st > 0) observe_columns(st - 1);
                 if (st + 1 < a.n_steps) produce(0, min(cut, all), st + 1, buf ^ 1);
             }
             __syncthreads();
-            if (compute) corrector(&R[buf][0][w][0][0][0]);
+            if (compute) corrector(nullptr);
             else if (st + 1 < a.n_steps) produce(min(cut, all), all, st + 1, buf ^ 1);
             __syncthreads();
         }
-        if (!compute && pw == 0 && a.n_steps > 0) observe(a.n_steps - 1, 1, R[buf ^ 1]);
+        if (!compute && pw == 0 && a.n_steps > 0) observe_columns(a.n_steps - 1);
     }
 
     if (compute) {
@@ -436,7 +554,7 @@ int launch_small_s(const Geometry& g, const EnsembleBuffers& b, const StepConsts
     a.F = pump->F;
     a.cw = -0.5 * dt;
     a.cf = -std::sqrt(dt);
-    a.c1 = c.c1;
+    a.c1 = (S)c.c1;
     a.c2 = (S)c.c2;
     a.k0 = c.key0;
     a.k1 = c.key1;

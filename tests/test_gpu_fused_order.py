@@ -1,0 +1,46 @@
+"""The fused small-N kernel sums in the order of the stage kernels: in FP32 a
+run of 17 to 128 atoms gives the same bits on either path, so timing a run
+(which keeps the stage launches from N = 65 on) or scanning it in a batch does
+not change its result, and the collective term of Eq. (S1) is added apart from
+the pump's.  FP64 differs by the order of K only (bound: that of the FP64
+parity tests)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+FUSED = 99
+
+
+@pytest.fixture(scope="module")
+def twa():
+    import torch
+    assert torch.cuda.is_available()
+    import paper_2608_10075_amd as m
+    return m
+
+
+def _run(twa, prec, N, B, integ, **kw):
+    p = twa.build_pump(N, 2.0, 0.8)
+    return twa.run(p, B, 0.02 / N, 41, seed=7, burnin=13, precision=prec, integrator=integ, want_final_state=True,
+                   want_traj=True, norm_tol=-1, **kw)
+
+
+@pytest.mark.parametrize("N", [17, 32, 33, 48, 49, 64, 65, 80, 96, 97, 113, 128])
+@pytest.mark.parametrize("B", [9, 2051])
+def test_fused_run_has_the_bits_of_the_stage_kernels(twa, N, B):
+    for prec in ("fp32", "fp64") if N <= 64 else ("fp32",):
+        for integ in ("heun", "sib"):
+            a = _run(twa, prec, N, B, integ)
+            b = _run(twa, prec, N, B, integ, tile_config=0 if N <= 48 else 1)
+            assert a.obs["tile_config"] == FUSED and b.obs["tile_config"] != FUSED
+            if prec == "fp64":
+                assert np.max(np.abs(a.final_state - b.final_state)) < 1e-11
+            else:
+                assert np.array_equal(a.final_state, b.final_state)
+                assert np.array_equal(a.traj_moments, b.traj_moments)
+
+
+@pytest.mark.parametrize("N", [65, 100, 128])
+def test_timing_does_not_change_a_result(twa, N):
+    a, b = _run(twa, "fp32", N, 40, "heun"), _run(twa, "fp32", N, 40, "heun", timing=True)
+    assert np.array_equal(a.final_state, b.final_state) and np.array_equal(a.traj_moments, b.traj_moments)
