@@ -423,14 +423,16 @@ std::string tune_key(const BatchSpec& sp, const std::vector<int>& idx) {
     return s.str();
 }
 
-int cached_cfg(const char* path, const std::string& key) {
+// the last entry of a key that names a tile grouped launches have (files of
+// earlier versions hold ones that are no candidates any more)
+int cached_cfg(const char* path, const std::string& key, int precision) {
     if (!path) return -1;
     std::ifstream f(path);
     std::string k;
-    int c;
+    int c, found = -1;
     while (f >> k >> c)
-        if (k == key) return c;
-    return -1;
+        if (k == key && ((c >= 0 && c <= 3) || c == 10 || (c == 7 && precision != TWA_PREC_FP64))) found = c;
+    return found;
 }
 
 void store_cfg(const char* path, const std::string& key, int cfg) {
@@ -563,9 +565,8 @@ int run_batch(const twa_point* pts, int np, const twa_batch_opts* o, twa_observa
             int cfg = o->tile_config;
             if (cfg < 0) {
                 const std::string key = tune_key(sp, groups[(size_t)b]);
-                cfg = cached_cfg(o->tune_cache, key);
-                const std::vector<int> cand = bucket_candidates(b, o->precision);
-                if (std::find(cand.begin(), cand.end(), cfg) == cand.end()) {
+                cfg = cached_cfg(o->tune_cache, key, o->precision);
+                if (cfg < 0) {
                     if ((rc = autotune_bucket(sp, groups[(size_t)b], b, st, &cfg))) goto cleanup;
                     store_cfg(o->tune_cache, key, cfg);
                 }
