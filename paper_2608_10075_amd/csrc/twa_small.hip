@@ -17,6 +17,7 @@
 // gives the same bits on either path (to N = 16 the noise field is added first).
 // Heun and the semi-implicit midpoint scheme; FP64 or FP32 state, operands and
 // MFMA.  Noise from the same Philox counters as the multi-kernel path.
+// The shortest chains have a kernel of their own, lanes_run_kernel.
 #include <algorithm>
 #include <cmath>
 
@@ -28,6 +29,7 @@ namespace twa {
 namespace {
 
 constexpr int PRODUCERS = 4;   // producer waves per workgroup
+constexpr int LANES_THREADS = 256;
 
 template <typename S>
 struct Small;
@@ -522,6 +524,156 @@ __global__ __launch_bounds__(64 * (NB + PRODUCERS)) void small_run_kernel(SmallA
     }
 }
 
+// midpoint rotation of the semi-implicit scheme (same closed form as the step kernels)
+template <typename S>
+__device__ __forceinline__ void rotate(S x, S y, S z, S Hx, S Hy, S& ox, S& oy, S& oz) {
+    const S bx = S(0.5) * Hy, by = S(-0.5) * Hx;
+    const S ax = x - by * z, ay = y + bx * z, az = z - (bx * y - by * x);
+    const S bd = bx * ax + by * ay;
+    const S inv = S(1) / (S(1) + bx * bx + by * by);
+    ox = (ax - by * az + bx * bd) * inv;
+    oy = (ay + bx * az + by * bd) * inv;
+    oz = (az - (bx * ay - by * ax)) * inv;
+}
+
+// The shortest chains, a spin to a lane: a trajectory occupies NL = 2^k >= N
+// lanes of one wave and forms its products from rows of the operands and the
+// spin vectors in LDS.  No lane works on padding, where the matrix kernel above
+// pads to 16 spins, so it is the faster one for few spins and many trajectories
+// (see lanes_apply).  Bound by the LDS reads of its products.
+template <typename S, int NL>
+__global__ __launch_bounds__(LANES_THREADS) void lanes_run_kernel(SmallArgs<S> a) {
+    constexpr int TPB = LANES_THREADS / NL;            // trajectories per block
+    __shared__ S Aw[NL * NL];                          // -dt/2 W, row-major N x N
+    __shared__ S Af[NL * NL];                          // -sqrt(dt) F
+    __shared__ S vx[TPB][NL], vy[TPB][NL], ux[TPB][NL], uy[TPB][NL];
+    const int n = a.n;
+    const int64_t B = a.B, P = a.P, Bp = a.Bp;
+    const uint32_t k0 = a.k0, k1 = a.k1, point = a.point;
+    const S c1 = a.c1, c2 = a.c2;
+    for (int t = threadIdx.x; t < n * n; t += LANES_THREADS) {
+        Aw[t] = (S)(a.cw * a.W[t]);
+        Af[t] = (S)(a.cf * a.F[t]);
+    }
+    const int tl = threadIdx.x / NL, i = threadIdx.x % NL;   // trajectory in block, spin
+    const int64_t k = (int64_t)blockIdx.x * TPB + tl;
+    const bool live = k < B && i < n;
+    const int64_t SP = Bp * P;
+    S x = 0, y = 0, z = 0;
+    if (live) {
+        x = a.s_in[k * P + i];
+        y = a.s_in[SP + k * P + i];
+        z = a.s_in[2 * SP + k * P + i];
+    }
+    S msum[5] = {0, 0, 0, 0, 0}, mcmp[5] = {0, 0, 0, 0, 0};
+    const S* aw = Aw + i * n;
+    const S* af = Af + i * n;
+    __syncthreads();
+
+    for (int64_t st = 0; st < a.n_steps; ++st) {
+        // noise of the step (counters of the multi-kernel path)
+        S zx = 0, zy = 0, g0 = 0, g1 = 0;
+        {
+            const uint32_t ks = (uint32_t)k, ns = (uint32_t)st;
+            const U4 w = philox4x32_10(U4{(uint32_t)(i >> 1), ks, ns, TAG_PUMP | (point << 8)}, k0, k1);
+            S a0, a1, a2, a3;
+            box_muller(w.x, w.y, a0, a1);
+            box_muller(w.z, w.w, a2, a3);
+            if (live) {
+                zx = (i & 1) ? a2 : a0;
+                zy = (i & 1) ? a3 : a1;
+            }
+            const U4 v = philox4x32_10(U4{0u, ks, ns, TAG_COLLECTIVE | (point << 8)}, k0, k1);
+            box_muller(v.x, v.y, g0, g1);
+        }
+        // stage 1: fields at s_n
+        vx[tl][i] = x;
+        vy[tl][i] = y;
+        ux[tl][i] = zx;
+        uy[tl][i] = zy;
+        __syncthreads();
+        S Yx = 0, Yy = 0, Qx = 0, Qy = 0, Sx = 0, Sy = 0;
+        for (int j = 0; j < n; ++j) {
+            Yx += aw[j] * vx[tl][j];
+            Yy += aw[j] * vy[tl][j];
+            Qx += af[j] * ux[tl][j];
+            Qy += af[j] * uy[tl][j];
+            Sx += vx[tl][j];
+            Sy += vy[tl][j];
+        }
+        const S Hx = (Yx + Qx) + (c1 * Sx + c2 * g0), Hy = (Yy + Qy) + (c1 * Sy + c2 * g1);
+        S px, py, pz, dx = 0, dy = 0, dz = 0;
+        if (a.sib) {
+            rotate(x, y, z, Hx, Hy, px, py, pz);
+        } else {
+            dx = z * Hx;
+            dy = z * Hy;
+            dz = -(x * Hx + y * Hy);
+            px = x + dx;
+            py = y + dy;
+            pz = z + dz;
+        }
+        if (!live) px = py = pz = 0;
+        // stage 2: fields at the predictor (Heun) or the midpoint (semi-implicit)
+        const S mx = a.sib ? S(0.5) * (x + px) : px, my = a.sib ? S(0.5) * (y + py) : py;
+        __syncthreads();   // stage-1 reads done
+        vx[tl][i] = mx;
+        vy[tl][i] = my;
+        __syncthreads();
+        S Y2x = 0, Y2y = 0, S2x = 0, S2y = 0;
+        for (int j = 0; j < n; ++j) {
+            Y2x += aw[j] * vx[tl][j];
+            Y2y += aw[j] * vy[tl][j];
+            S2x += vx[tl][j];
+            S2y += vy[tl][j];
+        }
+        const S H2x = (Y2x + Qx) + (c1 * S2x + c2 * g0), H2y = (Y2y + Qy) + (c1 * S2y + c2 * g1);
+        if (a.sib) {
+            rotate(x, y, z, H2x, H2y, x, y, z);
+        } else {
+            const S ex = pz * H2x, ey = pz * H2y, ez = -(px * H2x + py * H2y);
+            x = x + S(0.5) * (dx + ex);
+            y = y + S(0.5) * (dy + ey);
+            z = z + S(0.5) * (dz + ez);
+        }
+        if (!live) x = y = z = 0;
+        // window moments of the new state
+        if (st + 1 > a.burnin) {
+            __syncthreads();   // stage-2 reads done
+            vx[tl][i] = x;
+            vy[tl][i] = y;
+            ux[tl][i] = z;
+            __syncthreads();
+            if (i == 0) {
+                S Tx = 0, Ty = 0, Tz = 0;
+                for (int j = 0; j < n; ++j) {
+                    Tx += vx[tl][j];
+                    Ty += vy[tl][j];
+                    Tz += ux[tl][j];
+                }
+                const S T2 = S(0.25) * (Tx * Tx + Ty * Ty);
+                const S v[5] = {T2, T2 * Tz, T2 * T2, Tz, Tz * Tz};
+#pragma unroll
+                for (int m = 0; m < 5; ++m) kahan(msum[m], mcmp[m], v[m]);
+            }
+        }
+        __syncthreads();   // all reads of this step done before the next step's writes
+    }
+    if (k < B) {
+        if (i < n) {
+            a.s_out[k * P + i] = x;
+            a.s_out[SP + k * P + i] = y;
+            a.s_out[2 * SP + k * P + i] = z;
+        }
+        if (i == 0)
+#pragma unroll
+            for (int m = 0; m < 5; ++m) {
+                a.mom[(2 * m) * Bp + k] = msum[m];
+                a.mom[(2 * m + 1) * Bp + k] = mcmp[m];
+            }
+    }
+}
+
 template <typename S, int NB, int CB>
 int launch_small_t(const SmallArgs<S>& a, hipStream_t st) {
     constexpr int T = 8 * CB;
@@ -540,6 +692,28 @@ int launch_small_nb(const SmallArgs<S>& a, int nb, int cb, hipStream_t st) {
         if (nb > NB) return launch_small_nb<S, NB + 1>(a, nb, cb, st);
         return cb == 1 ? launch_small_t<S, NB, 1>(a, st) : launch_small_t<S, NB, 2>(a, st);
     }
+}
+
+template <typename S, int NL>
+int launch_lanes_t(const SmallArgs<S>& a, hipStream_t st) {
+    constexpr int TPB = LANES_THREADS / NL;
+    hipLaunchKernelGGL((lanes_run_kernel<S, NL>), dim3((unsigned)((a.B + TPB - 1) / TPB)), dim3(LANES_THREADS), 0, st, a);
+    TWA_HIP_CHECK(hipGetLastError());
+    return TWA_OK;
+}
+
+// Where a spin to a lane is faster, in us a step against the matrix kernel.
+// FP32: to N = 4 everywhere (N = 2 1.3 against 1.5 at 4096 trajectories, 8.5
+// against 48 at 131072), and past the 4096 trajectories that the matrix kernel
+// takes in one round, to N = 15 (8192: N = 8 1.6 against 3.0, N = 15 2.7 against
+// 3.1; N = 16, its rows on the same LDS banks, 4.0 against 3.1) and to N = 27
+// where N is no multiple of 4 (32768: N = 17 14.6 against 18.7, N = 27 19.0
+// against 18.9, N = 20 21.8 against 18.9).  FP64: past 4096 to N = 8 (8192: 3.5
+// against 4.0, N = 9 5.0 against 4.1).
+template <typename S>
+bool lanes_apply(int n, int64_t B) {
+    if (sizeof(S) == 8) return n <= 8 && B > 4096;
+    return n <= 4 || (B > 4096 && (n <= 15 || (n <= 27 && n % 4 != 0)));
 }
 
 template <typename S>
@@ -565,8 +739,12 @@ int launch_small_s(const Geometry& g, const EnsembleBuffers& b, const StepConsts
     a.s_in = static_cast<const S*>(b.s[0]);
     a.s_out = static_cast<S*>(b.s[out_cur]);
     a.mom = static_cast<S*>(b.mom);
-    // 8 trajectories per workgroup up to one workgroup per compute unit (FP64 N = 50 x 512: 3.7 us per step
-    // against 6.1 with 16; FP32 N = 100 x 2000: 4.1 against 6.4), then 16 (FP32 N = 128 x 4096: 8.1 against 9.3)
+    if (lanes_apply<S>(a.n, a.B)) {
+        if (a.n <= 8) return launch_lanes_t<S, 8>(a, st);
+        if constexpr (sizeof(S) == 4) return a.n <= 16 ? launch_lanes_t<S, 16>(a, st) : launch_lanes_t<S, 32>(a, st);
+    }
+    // 8 trajectories per workgroup up to one workgroup per compute unit (us a step: FP64 N = 50 x 512 4.5 against
+    // 7.0 with 16, FP32 N = 100 x 2000 5.2 against 7.9), then 16 (FP32 N = 128 x 4096 9.1 against 11.1)
     const int cb = g.B <= 8 * 256 ? 1 : 2;
     return launch_small_nb<S, 1>(a, (int)((g.N + 15) / 16), cb, st);
 }

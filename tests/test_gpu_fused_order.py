@@ -1,6 +1,6 @@
 """The fused small-N kernel sums in the order of the stage kernels: in FP32 a
-run of 17 to 128 atoms gives the same bits on either path, so timing a run
-(which keeps the stage launches from N = 65 on) or scanning it in a batch does
+run of 17 to 128 atoms and up to 4096 trajectories gives the same bits on
+either path, so timing a run (which keeps the stage launches from N = 65 on) or scanning it in a batch does
 not change its result, and the collective term of Eq. (S1) is added apart from
 the pump's.  FP64 differs by the order of K only (bound: that of the FP64
 parity tests)."""
