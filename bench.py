@@ -57,7 +57,7 @@ sys.path.insert(0, ROOT)
 
 METRIC = "trajectory-atom-steps/s at N=1e4 + adjoint d(g2)/d(w,alpha) cost vs forward"
 PEAK_TFLOPS = {"bf16": 2500.0, "fp16": 2500.0, "bf16x3": 2500.0, "fp32": 157.3, "fp64": 78.6}
-KERNEL_SOURCES = ["paper_2608_10075_amd/csrc/twa_step_impl.h", "paper_2608_10075_amd/csrc/twa_device.h"]
+KERNEL_SOURCES = ["paper_2608_10075_amd/csrc/" + f for f in ("twa_step_impl.h", "twa_device.h", "twa_index.h")]
 STEPS_PER_BENCH_STEP = 1000
 
 

@@ -254,7 +254,12 @@ typedef struct twa_observables {
        T4 = <S+S+S-S->_TWA, Z = <S^z>_TWA, ZZ = <S^z S^z>_TWA                */
     double T2, T3, T4, Z, ZZ;
     /* normal-ordered observables: Sz = <S^z>; SpSm = T2 + Z/2 (SM step 6);
-       g2 = (T4 + 2 T3 - Z/3 + ZZ/2 - 4 T2/3) / SpSm^2 (Eq. (S2), main text) */
+       g2 = (T4 + 2 T3 - Z/3 + ZZ/2 - 4 T2/3) / SpSm^2 (Eq. (S2), main text).
+       Below threshold SpSm is the small difference of two numbers of the size
+       of the chain (of either sign in a small ensemble); g2, g2_se and the
+       gradients of g2, which divide by its square and cube, have no digits
+       where it comes out near zero, in any precision: use T2, Z or more
+       trajectories there                                                    */
     double Sz, SpSm, g2;
     /* delete-one-block jackknife standard errors (32 contiguous blocks of
        trajectories, fewer if n_traj < 32), same order as above              */
@@ -265,8 +270,11 @@ typedef struct twa_observables {
     double max_norm_dev;     /* max over spins of | |s|^2(end) - |s|^2(start) |    */
     double step_criterion;   /* max(Gamma N, lam_max) dt; the paper asks < 0.05    */
     int32_t nan_flag;        /* 1 if a NaN/Inf was seen                            */
-    int32_t tile_config;     /* tile configuration used (TWA_TILE_FUSED: the fused */
-                             /* small-N kernel, every step in one launch)          */
+    int32_t tile_config;     /* tile configuration used (TWA_TILE_FUSED: a fused   */
+                             /* small-N kernel, every step in one launch).  The    */
+                             /* automatic choice may take a narrower tile of the   */
+                             /* one reported; in FP64 alone that can change the    */
+                             /* last bits of a result                              */
     double kernel_ms;        /* device time of the step loop (HIP events)          */
     double stage1_ms;        /* timing = 1: summed device time of the predictor    */
     int64_t stage1_launches; /* contraction launches (HIP events around each) and  */
@@ -352,7 +360,8 @@ TWA_API int twa_run(const twa_params* p, int64_t n_traj, double dt, int64_t n_st
  * is carved from a file-scope device array of TWA_NOALLOC_SCRATCH_BYTES that
  * each device holds until the process ends (its address taken once per
  * device), and the jackknife block sums are formed on the device.  Same
- * kernels and results as twa_run (bit for bit) for: a pump from
+ * kernels and results as twa_run (bit for bit; FP64 runs close to the size
+ * limit may differ in the last bits) for: a pump from
  * twa_build_pump or twa_build_pump_dense, Heun or the semi-implicit scheme,
  * any precision, n_lags = 0, no init_state; no hipGraph replay and no timing
  * (kernel_ms is NaN).  The caller passes the stream (NULL = null stream).

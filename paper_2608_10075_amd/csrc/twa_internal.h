@@ -91,8 +91,8 @@ constexpr int tile_table(int precision) {
 // Whether the corrector's launch may carry the next step's noise.  A noise
 // block takes the LDS of a tile: where only one fits on a compute unit (256x128
 // and 320x256) their short lives follow one another there, and a launch of
-// their own is shorter (FP32 4096 x 1024: 100 us more of stage 2 with them, 17
-// for the launch).
+// their own is shorter (4096 x 1024 on 256x128 tiles: 100 us more of stage 2
+// with them, 17 for the launch).
 constexpr bool noise_fits(int mt, int nt, int kbytes, int nstage, int group) {
     return nstage * group * (mt + nt) * kbytes <= 80 * 1024 || mt * nt <= 64 * 64;
 }
