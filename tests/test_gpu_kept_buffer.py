@@ -52,3 +52,50 @@ def test_small_run_does_not_keep_a_large_buffer(twa):
     # a run of a like size takes the kept buffer over
     third = twa.run(small, 48, 1e-4, 20, **kw)
     assert np.array_equal(third.traj_moments, first.traj_moments[:48])
+
+
+PATHS = ["fused", "lanes", "stage", "sib", "lags", "decay", "exchange", "toeplitz", "adjoint", "tangent"]
+
+
+def _result(twa, path, prec):
+    N, B, dt, T = (12 if path == "fused" else 3 if path == "lanes" else 131), 33, 1e-5, 24
+    kw = dict(precision=prec, norm_tol=-1)
+    if path in ("adjoint", "tangent"):
+        p = twa.build_pump(N, 1.0, 1.0)
+        obs, g = (twa.adjoint(p, B, dt, T, 5, ckpt_every=4, **kw) if path == "adjoint"
+                  else twa.tangent_w(p, B, dt, T, 5, **kw))
+        return [np.array([obs["T4"], obs["ZZ"], obs["g2_se"]]), np.array(list(g.values()))], p
+    if path == "toeplitz":
+        p = twa.build_pump_toeplitz(N, 1.0, 1.0)
+        kw["pump_path"] = "toeplitz"
+    elif path in ("decay", "exchange"):
+        i = np.arange(N)
+        d = np.abs(i[:, None] - i[None, :])
+        p = twa.build_model(1.0 / (1.0 + d), 0.5 ** d, 0.1 * (d == 1.0) if path == "exchange" else None)
+    else:
+        p = twa.build_pump(N, 1.0, 1.0)
+    if path == "lags":
+        kw.update(n_lags=4, lag_stride=2, burnin=15, want_lags=True)
+    r = twa.run(p, B, dt, T, 5, integrator="sib" if path == "sib" else "heun", want_traj=True, want_final_state=True,
+                **kw)
+    out = [r.traj_moments, r.final_state]
+    if path == "lags":
+        out += [r.corr_blocks, r.chi_blocks]
+    if path in ("decay", "exchange"):
+        out.append(r.traj_gen)
+    return out, p
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("prec,path", [(q, p) for q in ("fp64", "fp32", "bf16") for p in PATHS
+                                       if q != "bf16" or p not in ("fused", "lanes", "toeplitz", "adjoint")])
+def test_what_a_kept_buffer_holds_shows_in_no_result(twa, prec, path):
+    gc.collect()
+    want, p = _result(twa, path, prec)
+    # runs that leave a buffer of infinities and NaN, of a size that the next run takes over
+    bad = twa.build_pump(131, 1.0, 1.0)
+    for B in (64, 512, 2048):
+        twa.run(bad, B, 1e4, 8, 5, precision="fp64", tile_config=1, norm_tol=-1, allow_unstable=True)
+        got, _ = _result(twa, path, prec)
+        for a, b in zip(want, got):
+            assert np.array_equal(a, b), (path, prec, B)
